@@ -2,7 +2,7 @@
 // the fp32 MFMA core (gemm.h), and the dense layers on the same core.
 #include <algorithm>
 
-#include "gemm_bf16.h"
+#include "gemm_split.h"
 #include "kernels.h"
 
 namespace ax {
@@ -306,6 +306,94 @@ static int launch_slab_finish(const float* ws, int ns, int groups, long M, int N
   return ALEXNET_OK;
 }
 
+// ----------------------------------------- fp32 products on the bf16 matrix cores ---
+// (gemm_split.h)  Dense operands, 16-byte loads.
+typedef Tile<128, 128, kBKs, 2, 2> S128;
+typedef Tile<128, 96, kBKs, 4, 1> S96;
+typedef Tile<128, 192, kBKs, 2, 2> S192;
+typedef Tile<128, 64, kBKs, 2, 2> S64;
+// rate of a tile on a long reduction over the fp32 matrix rate of a compute unit, measured at 4096 x 4608 x 2048
+// (160, 153, 159 and 133 TFLOP/s; the fp32 kernels reach 101 there)
+static const TileOption kTileOptionsSplit[] = {
+    {128, 128, kBKs, 1.02}, {128, 96, kBKs, 0.97}, {128, 192, kBKs, 1.01}, {128, 64, kBKs, 0.84}};
+// Cheapest (tile, slices) for a launch of the split kernel, as plan_gemm(), with one difference: these kernels fetch
+// one k-tile ahead only, and a workgroup that has its compute unit to itself waits for memory about half the time (a
+// weight gradient of 192 x 128 x 2048 x 72: 105 us in 216 workgroups, see fill), so slices are worth having until two
+// or three workgroups share every unit.
+static GemmPlan plan_split(int M, int N, int K, int groups, double out_bytes, int max_s, double* t_out = nullptr) {
+  GemmPlan best{128, 128, 1, ceil_div(K, kBKs) * kBKs};
+  double best_t = 1e30;
+  const int ktiles = ceil_div(K, kBKs);
+  for (const TileOption& to : kTileOptionsSplit) {
+    const long tiles = (long)ceil_div(M, to.bm) * ceil_div(N, to.bn) * groups;
+    const double t_tile = 2.0 * to.bm * to.bn * (double)ktiles * kBKs / (0.614e12 * to.eff);
+    for (int s = 1; s <= max_s && s <= ktiles; ++s) {
+      const int per = ceil_div(ktiles, s);
+      if (ceil_div(ktiles, per) != s) continue;
+      if (s > 1 && per * kBKs < 96) break;
+      const int c = ceil_div(tiles * s, 256), most = to.bn > 128 ? 2 : 3;  // workgroups per unit: of the launch, at once
+      const double fill = c >= most ? 1.0 : c == 2 ? 0.85 : 0.5;
+      double t = c * t_tile * per / ktiles / fill + 4e-6;
+      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + 6e-6;
+      if (t < best_t * 0.98) {
+        best_t = t;
+        best = GemmPlan{to.bm, to.bn, s, per * kBKs};
+      }
+    }
+  }
+  if (t_out) *t_out = best_t;
+  return best;
+}
+template <class T, class AL, class BL, class Epi>
+static int launch_tile_split(const typename AL::Params& ap, const typename BL::Params& bp, const Epi& ep, int M, int N,
+                             int K, int kchunk, int nsplit, int groups, hipStream_t st) {
+  if (M <= 0 || N <= 0) return ALEXNET_OK;
+  const int gx = ceil_div(M, T::BM), gy = ceil_div(N, T::BN), gz = groups * nsplit;
+  const long total = (long)gx * gy * gz;
+  if (total > 0x7fffffffL) {
+    set_error("GEMM grid too large (%d,%d,%d)", gx, gy, gz);
+    return ALEXNET_ESHAPE;
+  }
+  const SplitGrid grid{make_fastdiv((uint32_t)gx), make_fastdiv((uint32_t)gy), make_fastdiv((uint32_t)nsplit)};
+  KernelScope ks("gemm", g_algo_flops > 0 ? g_algo_flops : 2.0 * M * N * (double)K * groups,
+                 gemm_bytes(M, N, K, groups), st);
+  hipLaunchKernelGGL((gemm_split_kernel<T, AL, BL, Epi>), dim3((unsigned)total), dim3(kThreads), 0, st, ap, bp, ep, M,
+                     N, K, kchunk, grid);
+  AX_LAUNCH_CHECK();
+  return ALEXNET_OK;
+}
+// ALT / BLT: loaders by number of rows
+template <template <int> class ALT, template <int> class BLT, class Epi>
+static int by_tile_split(const GemmPlan& p, const DenseParams& a, const DenseParams& b, const Epi& e, int M, int N, int K,
+                         int groups, hipStream_t st) {
+#define AX_SPLIT(T) \
+  return launch_tile_split<T, ALT<T::BM>, BLT<T::BN>, Epi>(a, b, e, M, N, K, p.kchunk, p.ns, groups, st)
+  if (p.bn == 192) AX_SPLIT(S192);
+  if (p.bn == 96) AX_SPLIT(S96);
+  if (p.bn == 64) AX_SPLIT(S64);
+  AX_SPLIT(S128);
+#undef AX_SPLIT
+}
+// A pointwise convolution (the products of a transformed layer among them) is a dense product per group.
+static inline bool pointwise(const ConvGeom& c) { return c.k == 1 && c.stride == 1 && c.pad == 0; }
+static inline DenseParams pointwise_A(const ConvGeom& c, const float* x) {
+  return DenseParams{x, c.Cin, c.cg(), (int)c.P(), (uint32_t)(c.in_elems() * 4)};
+}
+static inline bool split_fwd_ok(const ConvGeom& c) { return pointwise(c) && c.cg() % 4 == 0 && c.og() % 4 == 0; }
+static GemmPlan split_fwd_plan(const ConvGeom& c) {
+  const GemmDims d = fwd_dims(c);
+  return plan_split(d.M, d.N, d.K, d.groups, (double)c.out_elems() * 4, 8);
+}
+// weight gradient: the operands may change places, whichever way the tiles cover the result with less padding
+static GemmPlan split_bwdw_plan(const ConvGeom& c, bool* swapped) {
+  const GemmDims d = bwdw_dims(c);
+  double t[2];
+  const GemmPlan p = plan_split(d.M, d.N, d.K, d.groups, (double)c.w_elems() * 4, 256, &t[0]);
+  const GemmPlan q = plan_split(d.N, d.M, d.K, d.groups, (double)c.w_elems() * 4, 256, &t[1]);
+  *swapped = t[1] < 0.98 * t[0];
+  return *swapped ? q : p;
+}
+
 // ------------------------------------------------------------- convolution ---
 template <class F, class Epi>
 static int by_tile_tap(const GemmPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e,
@@ -340,6 +428,7 @@ size_t conv_fwd_ws_floats(const ConvGeom& c) {
   ns = std::max(ns, fwd_plan(c, false, false, true).ns);
   ns = std::max(ns, fwd_plan(c, false, true, false, true).ns);
   if (run16_mode(c)) ns = std::max(ns, run16_fwd_plan(c).ns);
+  if (split_fwd_ok(c)) ns = std::max(ns, split_fwd_plan(c).ns);
   return ns > 1 ? (size_t)ns * c.out_elems() : 0;
 }
 size_t conv_bwd_data_ws_floats(const ConvGeom& c) {
@@ -355,6 +444,11 @@ size_t conv_bwd_weight_ws_floats(const ConvGeom& c) {
       if (p.ns > 1) n = std::max(n, (size_t)p.ns * c.w_elems());
       if (run_mode(c)) n = std::max(n, (size_t)bwdw_plan(c, true, bf, table).ns * run_w_elems(c));
     }
+  if (split_fwd_ok(c)) {
+    bool swapped;
+    const int ns = split_bwdw_plan(c, &swapped).ns;
+    if (ns > 1) n = std::max(n, (size_t)ns * c.w_elems());
+  }
   return n;
 }
 
@@ -422,6 +516,18 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
       AX_TRY((by_tile_16<ConvGatherTap16<IM2COL_FWD>>(p, a, b, ep, d, st)));
     else
       AX_TRY((by_tile_16<ConvGather16<IM2COL_FWD>>(p, a, b, ep, d, st)));
+    return finish(launch_slab_finish(ws, p.ns, d.groups, d.M, d.N, bias, relu, nullptr, y, st));
+  }
+  if (!g_bf16 && split_fwd_ok(c) && fwd_A_vec(c, x) && fwd_B_vec(c, wf)) {
+    const GemmPlan p = split_fwd_plan(c);
+    const DenseParams a = pointwise_A(c, x), b = fwd_B(c, wf);
+    copy.pending = y16 != nullptr;
+    if (p.ns == 1) {
+      EpiBiasAct ep{y, c.Cout, bias, relu, c.og(), 0, 0, nullptr};
+      return finish(by_tile_split<SplitKInner, SplitRowInner>(p, a, b, ep, d.M, d.N, d.K, d.groups, st));
+    }
+    EpiSlab ep{ws, (long)d.M * d.N, d.N, nullptr};
+    AX_TRY((by_tile_split<SplitKInner, SplitRowInner>(p, a, b, ep, d.M, d.N, d.K, d.groups, st)));
     return finish(launch_slab_finish(ws, p.ns, d.groups, d.M, d.N, bias, relu, nullptr, y, st));
   }
   if (run) d.K = run_k(c);
@@ -598,6 +704,23 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
   GemmDims d = bwdw_dims(c);
   if (run) d.M = run_k(c);
   const bool av = run || bwdw_A_vec(c, x), bv = bwdw_B_vec(c, dy);
+  if (!g_bf16 && !run && split_fwd_ok(c) && av && bv) {
+    bool swapped;
+    const GemmPlan p = split_bwdw_plan(c, &swapped);
+    const long slab = (long)d.M * d.N;
+    DenseParams a = pointwise_A(c, x);
+    a.R = c.cg();
+    float* out = p.ns > 1 ? ws : dwf;
+    if (swapped) {
+      EpiSlabSwapped ep{out, slab, d.N, nullptr};
+      AX_TRY((by_tile_split<SplitRowInner, SplitRowInner>(p, bwdw_B(c, dy), a, ep, d.N, d.M, d.K, d.groups, st)));
+    } else {
+      EpiSlab ep{out, slab, d.N, nullptr};
+      AX_TRY((by_tile_split<SplitRowInner, SplitRowInner>(p, a, bwdw_B(c, dy), ep, d.M, d.N, d.K, d.groups, st)));
+    }
+    if (defer_ns) *defer_ns = p.ns;
+    return defer_ns || p.ns == 1 ? ALEXNET_OK : launch_reduce_slabs(ws, p.ns, slab, d.groups, dwf, st);
+  }
   const bool bf = g_bf16 && av && bv;
   const Im2colParams a = run ? run_A(c, x) : bwdw_A(c, x);
   bool table = av && bv && table_ok(a, d) && (!bf || d.K % kBKbf == 0);
@@ -660,6 +783,7 @@ static int fc_split(int B, int N, int K, int* kchunk, bool bf) {
   *kchunk = best_per * bk;
   return best;
 }
+static GemmPlan fc_plan(int B, int N, int K) { return plan_split(B, N, K, 1, (double)B * N * 4, 64); }
 size_t fc_ws_floats(int B, int in, int out) {
   int kc;
   size_t n = 0;
@@ -667,6 +791,8 @@ size_t fc_ws_floats(int B, int in, int out) {
     n = std::max(n, (size_t)fc_split(B, out, in, &kc, bf) * B * out);
     n = std::max(n, (size_t)fc_split(B, in, out, &kc, bf) * B * in);
   }
+  n = std::max(n, (size_t)fc_plan(B, out, in).ns * B * out);
+  n = std::max(n, (size_t)fc_plan(B, in, out).ns * B * in);
   return n;
 }
 
@@ -700,12 +826,13 @@ __global__ void fc_bwd_finish_kernel(const float* __restrict__ ws, int nsplit, s
 
 static inline bool vec_ok(const float* p, long ld) { return aligned16(p) && ld % 4 == 0; }
 
-template <template <int, int, bool> class ALT, template <int, int, bool> class BLT>
-static int launch_dense(bool vec, const DenseParams& a, const DenseParams& b, const EpiSlab& ep, int M, int N, int K,
-                        int kchunk, int ns, hipStream_t st) {
-  if (vec)
-    return launch_tile<T128, ALT<128, kBK, true>, BLT<128, kBK, true>, EpiSlab>(a, b, ep, M, N, K, kchunk, ns, 1, st);
-  return launch_tile<T128, ALT<128, kBK, false>, BLT<128, kBK, false>, EpiSlab>(a, b, ep, M, N, K, kchunk, ns, 1, st);
+// 16-byte loads: on the bf16 matrix cores, tile and slices by `p`; else on the fp32 ones
+template <template <int> class SA, template <int> class SB, template <int, int, bool> class ALT,
+          template <int, int, bool> class BLT>
+static int launch_dense(bool vec, const GemmPlan& p, const DenseParams& a, const DenseParams& b, const EpiSlab& ep, int M,
+                        int N, int K, hipStream_t st) {
+  if (vec) return by_tile_split<SA, SB>(p, a, b, ep, M, N, K, 1, st);
+  return launch_tile<T128, ALT<128, kBK, false>, BLT<128, kBK, false>, EpiSlab>(a, b, ep, M, N, K, p.kchunk, p.ns, 1, st);
 }
 
 typedef BfRowMajor<DenseKInner<128, kBKbf, true>, 128, kBKbf> BfDenseK;
@@ -722,8 +849,10 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
                   hipStream_t st, const uint16_t* x16, const uint16_t* w16, uint16_t* y16) {
   const bool vec = vec_ok(x, in) && vec_ok(w, in), bf = g_bf16 && vec;
   const bool s16 = bf && x16 && w16 && fc_bf16_stored_ok(in, out) && aligned16(x16) && aligned16(w16);
-  int kchunk;
-  const int ns = fc_split(B, out, in, &kchunk, bf);
+  GemmPlan p{128, 128, 0, 0};
+  if (vec && !bf) p = fc_plan(B, out, in);
+  else p.ns = fc_split(B, out, in, &p.kchunk, bf);
+  const int ns = p.ns, kchunk = p.kchunk;
   DenseParams a{x, in, 0, B, (uint32_t)((size_t)B * in * 4)};
   DenseParams b{w, in, 0, out, (uint32_t)((size_t)out * in * 4)};
   EpiSlab ep{ws, (long)B * out, out, nullptr};
@@ -735,7 +864,7 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
   else if (bf)
     AX_TRY((launch_tile_bf<B128, BfDenseK, BfDenseK, EpiSlab>(a, b, ep, B, out, in, kchunk, ns, 1, st)));
   else
-    AX_TRY((launch_dense<DenseKInner, DenseKInner>(vec, a, b, ep, B, out, in, kchunk, ns, st)));
+    AX_TRY((launch_dense<SplitKInner, SplitKInner, DenseKInner, DenseKInner>(vec, p, a, b, ep, B, out, in, st)));
   const size_t total = (size_t)B * out;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1), st);
   hipLaunchKernelGGL(fc_fwd_finish_kernel, dim3(ceil_div(total, 256)), dim3(256), 0, st, ws, ns, B, out, act, y, y16);
@@ -747,8 +876,10 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
                        float* ws, hipStream_t st, const uint16_t* dy16, const uint16_t* w16, uint16_t* dx16) {
   const bool vec = vec_ok(dy, out) && vec_ok(w, in), bf = g_bf16 && vec;
   const bool s16 = bf && dy16 && w16 && fc_bf16_stored_ok(in, out) && aligned16(dy16) && aligned16(w16);
-  int kchunk;
-  const int ns = fc_split(B, in, out, &kchunk, bf);
+  GemmPlan p{128, 128, 0, 0};
+  if (vec && !bf) p = fc_plan(B, in, out);
+  else p.ns = fc_split(B, in, out, &p.kchunk, bf);
+  const int ns = p.ns, kchunk = p.kchunk;
   DenseParams a{dy, out, 0, B, (uint32_t)((size_t)B * out * 4)};
   DenseParams b{w, in, 0, in, (uint32_t)((size_t)out * in * 4)};
   EpiSlab ep{ws, (long)B * in, in, nullptr};
@@ -760,7 +891,7 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
   else if (bf)
     AX_TRY((launch_tile_bf<B128, BfDenseK, BfDenseR, EpiSlab>(a, b, ep, B, in, out, kchunk, ns, 1, st)));
   else
-    AX_TRY((launch_dense<DenseKInner, DenseRowInner>(vec, a, b, ep, B, in, out, kchunk, ns, st)));
+    AX_TRY((launch_dense<SplitKInner, SplitRowInner, DenseKInner, DenseRowInner>(vec, p, a, b, ep, B, in, out, st)));
   const size_t total = (size_t)B * in;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1 + (gate ? 1 : 0)), st);
   hipLaunchKernelGGL(fc_bwd_finish_kernel, dim3(ceil_div(total, 256)), dim3(256), 0, st, ws, ns, total, gate, dx,
@@ -781,7 +912,8 @@ int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy
                                                              round_up(B, kBKbf), 1, 1, st);
   if (g_bf16 && vec)
     return launch_tile_bf<B128, BfDenseR, BfDenseR, EpiSlab>(a, b, ep, out, in, B, round_up(B, kBKbf), 1, 1, st);
-  return launch_dense<DenseRowInner, DenseRowInner>(vec, a, b, ep, out, in, B, round_up(B, kBK), 1, st);
+  const GemmPlan p = vec ? plan_split(out, in, B, 1, 0, 1) : GemmPlan{128, 128, 1, round_up(B, kBK)};
+  return launch_dense<SplitRowInner, SplitRowInner, DenseRowInner, DenseRowInner>(vec, p, a, b, ep, out, in, B, st);
 }
 
 }  // namespace ax

@@ -1,0 +1,382 @@
+// fp32 products on the bf16 matrix cores: every fp32 operand value is split into three bf16 terms,
+//
+//   x = h + m + l,   h = bf16(x), m = bf16(x - h), l = x - h - m     (all three exact: 8 + 8 + 8 significand bits)
+//
+// and a product a*b is the sum of the six term products that matter,
+//
+//   hh + hm + mh + mm + hl + lh,
+//
+// each exact in the matrix core, accumulated in fp32.  What is dropped (ml, lm, ll) is below 2^-25 of |a*b|, less
+// than the rounding of one fp32 addition, and an accumulator is rounded once per 16-deep step and term pair (six times
+// per 16 products) instead of once per two products (eight times), so the result is no further from the exact sum than
+// the fp32 MFMA's.  An infinite operand gives NaN (its remainder is inf - inf), as inf * 0 does.
+//
+// Why: v_mfma_f32_32x32x16_bf16 does 1024 flop per SIMD and clock, v_mfma_f32_32x32x2_f32 does 64; six of the
+// former are 16/6 = 2.7 times as fast as the latter for the same contraction.
+//
+// Measured inside a batch-128 training step against the fp32 MFMA kernels: products of the transformed layers,
+// forward, 216 -> 170 (second layer), 128 -> 93 (third), 97 -> 78 us (fourth); their weight gradients 239 -> 149,
+// 154 -> 104, 131 -> 104, 87 -> 51 us; dense layers, forward, 116 -> 97 us.  4096 x 4608 x 2048 alone: 101 -> 160 TFLOP/s
+// at half the matrix cores' issue rate; the clock falls from 2.2 to 1.7 GHz in such a run, so power bounds it as much as
+// the splitting (88 vector instructions per 24 MFMAs and wave) does.  The products of the transformed layers are
+// short (K = 128 .. 256) and move 3 - 3.8 TB/s as well.  Relative error of those products against 64 bits, fp32 MFMA
+// -> here: 2.4e-7 -> 2.2e-7 at K = 192, 8.3e-7 -> 7.1e-7 at K = 2048.
+//
+// Addressing, zero fill, split-k and epilogues are those of gemm.h; operands are fetched as fp32 and split once per
+// workgroup, on their way into LDS.
+//
+// LDS layout, in 16-byte units of eight consecutive k of one row: unit (plane, k octet, position of the row).
+//   k-contiguous operands    position = row; a load of four k is one 8-byte store per plane, and an octet's rows
+//                            are padded so that the two octets of a 16-deep step lie half the banks apart
+//   row-contiguous operands  a thread fetches k and k+1 of four rows and stores one word per row and plane; row
+//                            4q + j sits at position j*(ROWS/4 + 4) + q, so that the lanes of a store are 16 bytes apart
+// A fragment is one 16-byte read per plane in both, without bank conflicts.
+#pragma once
+
+#include "gemm_bf16.h"
+
+namespace ax {
+
+constexpr int kPlanes = 3;
+constexpr int kBKs = 16;  // depth of a k-tile: one MFMA step
+
+AX_HD float bf_lo(uint32_t w) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __uint_as_float(w << 16);
+#else
+  const uint32_t u = w << 16;
+  float f;
+  memcpy(&f, &u, 4);
+  return f;
+#endif
+}
+AX_HD float bf_hi(uint32_t w) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __uint_as_float(w & 0xffff0000u);
+#else
+  const uint32_t u = w & 0xffff0000u;
+  float f;
+  memcpy(&f, &u, 4);
+  return f;
+#endif
+}
+// the three terms of x (low halves) and y (high halves)
+struct SplitPair {
+  uint32_t t[kPlanes];
+};
+// two values rounded to bf16 (nearest even) by one instruction: through pack_bf16() the compiler, which sees that the
+// halves are widened again, converts every value a second time on its own
+AX_HD uint32_t split_pack(float lo, float hi) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  uint32_t w;
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(w) : "v"(lo), "v"(hi));
+  return w;
+#else
+  return pack_bf16(lo, hi);
+#endif
+}
+AX_HD SplitPair split_pair(float x, float y) {
+  SplitPair s;
+  s.t[0] = split_pack(x, y);
+  const float rx = x - bf_lo(s.t[0]), ry = y - bf_hi(s.t[0]);
+  s.t[1] = split_pack(rx, ry);
+  s.t[2] = split_pack(rx - bf_lo(s.t[1]), ry - bf_hi(s.t[1]));
+  return s;
+}
+
+// four consecutive k (quad kq of the tile) of one row of a k-contiguous operand
+template <int RP>
+AX_HD void split_store_quad(uint32_t* lds, int row, int kq, const float4& v) {
+  uint32_t* d = lds + ((kq >> 1) * RP + row) * 4 + 2 * (kq & 1);
+  const SplitPair a = split_pair(v.x, v.y), b = split_pair(v.z, v.w);
+#pragma unroll
+  for (int p = 0; p < kPlanes; ++p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    v2u w;
+    w[0] = a.t[p];
+    w[1] = b.t[p];
+    *reinterpret_cast<v2u*>(d + p * 2 * RP * 4) = w;
+#else
+    d[p * 2 * RP * 4] = a.t[p];
+    d[p * 2 * RP * 4 + 1] = b.t[p];
+#endif
+  }
+}
+// a unit of a row-contiguous operand: rows 4*rq .. 4*rq+3 at k = 2*kp (a) and 2*kp + 1 (b), two rows at a time
+template <int ROWS>
+struct SplitRowStore {
+  static constexpr int SP = ROWS / 4 + 4, RP = 4 * SP;
+  static AX_HD int pos(int row) { return (row & 3) * SP + (row >> 2); }
+  // unit idx of the tile: its row quad and pair of k.  Four lanes take the four pairs of an octet, so that the words
+  // a wave stores at once lie side by side.
+  static AX_HD int quad(int idx) { return (idx >> 2) % (ROWS / 4); }
+  static AX_HD int pair(int idx) { return (idx & 3) + 4 * (idx / ROWS); }
+  static AX_HD void store_half(uint32_t* lds, int rq, int kp, int half, const float4& a, const float4& b) {
+    uint32_t* d = lds + ((kp >> 2) * RP + 2 * half * SP + rq) * 4 + (kp & 3);
+    const SplitPair s0 = half ? split_pair(a.z, b.z) : split_pair(a.x, b.x);
+    const SplitPair s1 = half ? split_pair(a.w, b.w) : split_pair(a.y, b.y);
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p) {
+      d[p * 2 * RP * 4] = s0.t[p];
+      d[(p * 2 * RP + SP) * 4] = s1.t[p];
+    }
+  }
+};
+
+// ---- loaders --------------------------------------------------------------------
+//   fetch(r, kleft)        issue the loads of the next k-tile, of which kleft k are left, and step on; a k-tile past
+//                          the end (kleft <= 0) reads nothing and returns zeros
+//   store_step(s, lds, r)  split and store part s of what fetch() brought
+// Byte offsets run along with k; rows outside the operand start at kOob and stay outside: a reduction spans less
+// than 2 GiB.
+
+// elem(row, k) = p[row*ld + k]; ld and K multiples of four, 16-byte aligned
+template <int ROWS>
+struct SplitKInner {
+  static constexpr int QK = kBKs / 4, NQ = ROWS * QK, NL = (NQ + kThreads - 1) / kThreads, NS = NL;
+  static constexpr bool kWhole = NQ % kThreads == 0;  // else some threads own no quad in the last round
+  static constexpr int RP = ROWS + 8, UNITS = kPlanes * 2 * RP;
+  static AX_HD int pos(int row) { return row; }
+  static constexpr int block_units(int t) { return 32 * t; }  // pos(row + 32 t) - pos(row)
+  typedef DenseParams Params;
+  BufView v;
+  int tid, kq;
+  uint32_t off[NL];
+  AX_HD SplitKInner(const Params& a, int g, int tid_, int row0, int kbeg)
+      : v(make_view(a.p + (long)g * a.gstride, a.bytes - (uint32_t)(g * a.gstride * 4))), tid(tid_) {
+    kq = tid % QK;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int idx = tid + i * kThreads, row = row0 + idx / QK;
+      off[i] = (kWhole || idx < NQ) && row < a.R ? ((uint32_t)row * (uint32_t)a.ld + (uint32_t)(kbeg + 4 * kq)) * 4u : kOob;
+    }
+  }
+  AX_HD void fetch(float4* r, int kleft) {
+    const bool in = 4 * kq < kleft;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      r[i] = buf_ld4(v, in ? off[i] : kOob);
+      off[i] += kBKs * 4;
+    }
+  }
+  AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
+    const int idx = tid + s * kThreads;
+    if (kWhole || idx < NQ) split_store_quad<RP>(lds, idx / QK, kq, r[s]);
+  }
+};
+
+// elem(row, k) = p[k*ld + row]; rows and ld multiples of four, 16-byte aligned
+template <int ROWS>
+struct SplitRowInner {
+  typedef SplitRowStore<ROWS> St;
+  static constexpr int QR = ROWS / 4, NU = QR * (kBKs / 2), NUT = (NU + kThreads - 1) / kThreads, NL = 2 * NUT,
+                       NS = 2 * NUT;
+  static constexpr bool kWhole = NU % kThreads == 0;  // else some threads own no unit in the last round
+  static constexpr int RP = St::RP, UNITS = kPlanes * 2 * RP;
+  static AX_HD int pos(int row) { return St::pos(row); }
+  static constexpr int block_units(int t) { return 8 * t; }
+  typedef DenseParams Params;
+  BufView v;
+  int tid;
+  uint32_t ld4, off[NUT];  // ld4: bytes between consecutive k
+  AX_HD SplitRowInner(const Params& a, int g, int tid_, int row0, int kbeg)
+      : v(make_view(a.p + (long)g * a.gstride, a.bytes - (uint32_t)(g * a.gstride * 4))), tid(tid_) {
+    ld4 = (uint32_t)a.ld * 4u;
+#pragma unroll
+    for (int u = 0; u < NUT; ++u) {
+      const int idx = tid + u * kThreads, row = row0 + 4 * St::quad(idx), kp = St::pair(idx);
+      off[u] = (kWhole || idx < NU) && row < a.R ? (uint32_t)(kbeg + 2 * kp) * ld4 + (uint32_t)row * 4u : kOob;
+    }
+  }
+  AX_HD void fetch(float4* r, int kleft) {
+#pragma unroll
+    for (int u = 0; u < NUT; ++u) {
+      const int k = 2 * St::pair(tid + u * kThreads);
+      r[2 * u] = buf_ld4(v, k < kleft ? off[u] : kOob);
+      r[2 * u + 1] = buf_ld4(v, k + 1 < kleft ? off[u] + ld4 : kOob);
+      off[u] += kBKs * ld4;
+    }
+  }
+  AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
+    const int u = s >> 1, idx = tid + u * kThreads;
+    if (kWhole || idx < NU) St::store_half(lds, St::quad(idx), St::pair(idx), s & 1, r[2 * u], r[2 * u + 1]);
+  }
+};
+
+template <class L>
+AX_HD void split_store_all(const L& l, uint32_t* lds, const float4* r) {
+#pragma unroll
+  for (int s = 0; s < L::NS; ++s) l.store_step(s, lds, r);
+}
+// 16-byte unit that holds k octet kh of `row` in plane p
+template <class L>
+AX_HD int split_unit(int p, int kh, int row) {
+  return (p * 2 + kh) * L::RP + L::pos(row);
+}
+// the six term products, largest first: planes of A and B
+AX_HD int split_plane_a(int q) { return q == 2 || q == 3 ? 1 : q == 5 ? 2 : 0; }
+AX_HD int split_plane_b(int q) { return q == 1 || q == 3 ? 1 : q == 4 ? 2 : 0; }
+constexpr int kSplitProducts = 6;
+
+// A weight gradient with its operands exchanged (rows of the product = columns of the result): ws[z][n][m] = v.  The
+// lanes of a store run along m, the result's contiguous direction.
+struct EpiSlabSwapped {
+  static constexpr bool kTransposed = true;
+  float* ws;
+  long slab;  // M*N
+  long ldc;   // M
+  float* base;
+  AX_HD void set_group(int /*g*/, int z) { base = ws + (long)z * slab; }
+  AX_HD void apply(int m, int n, float v) const { base[(long)n * ldc + m] = v; }
+  AX_HD void apply4(int m, int n, float4 v) const {
+    apply(m, n, v.x); apply(m, n + 1, v.y); apply(m, n + 2, v.z); apply(m, n + 3, v.w);
+  }
+};
+
+// ================================= kernel ====================================
+#ifndef AX_HOST_EMU
+template <class L, int TT>
+struct SplitFrags {
+  v8bf f[kPlanes][TT];
+  template <int P>
+  __device__ __forceinline__ void read(const uint32_t* lane_base) {  // lane_base: the lane's unit in plane 0, block 0
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+      f[P][t] = __builtin_bit_cast(v8bf, *reinterpret_cast<const v4u*>(lane_base + (P * 2 * L::RP + L::block_units(t)) * 4));
+  }
+};
+
+// Side work of one k-tile, dealt over the first four of its six groups of MFMAs: split and store tile t+1.  Its
+// registers are then free for the loads of tile t+2, which have the rest of this tile and the next barrier to arrive.
+template <class AL, class BL, int SLOT, int W = 0>
+__device__ __forceinline__ void split_side_slot(AL& al, BL& bl, uint32_t* as_next, uint32_t* bs_next, float4* ra,
+                                                float4* rb, int kleft) {
+  constexpr int TOTAL = AL::NS + BL::NS, SLOTS = 4, PER = (TOTAL + SLOTS - 1) / SLOTS, IDX = SLOT * PER + W;
+  if constexpr (SLOT < SLOTS && W < PER) {
+    if constexpr (IDX < AL::NS)
+      al.store_step(IDX, as_next, ra);
+    else if constexpr (IDX < TOTAL)
+      bl.store_step(IDX - AL::NS, bs_next, rb);
+    if constexpr (IDX == AL::NS - 1) al.fetch(ra, kleft);
+    if constexpr (IDX == TOTAL - 1) bl.fetch(rb, kleft);
+    split_side_slot<AL, BL, SLOT, W + 1>(al, bl, as_next, bs_next, ra, rb, kleft);
+  }
+}
+template <class T, class AL, class BL, bool TR, int Q = 0>
+__device__ __forceinline__ void split_groups(const uint32_t* as, const uint32_t* bs, SplitFrags<AL, T::TM>& fa,
+                                             SplitFrags<BL, T::TN>& fb, v16f (&acc)[T::TM][T::TN], AL& al, BL& bl,
+                                             uint32_t* as_next, uint32_t* bs_next, float4* ra, float4* rb, int kleft) {
+  if constexpr (Q < kSplitProducts) {
+    // the terms of a plane are read shortly before their first use, so that two planes are live at a time
+    if constexpr (Q == 0) {
+      fa.template read<0>(as);
+      fb.template read<0>(bs);
+      fb.template read<1>(bs);
+    }
+    if constexpr (Q == 1) fa.template read<1>(as);
+    if constexpr (Q == 3) {
+      fb.template read<2>(bs);
+      fa.template read<2>(as);
+    }
+#pragma unroll
+    for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TN; ++j) {
+        const v8bf a = fa.f[split_plane_a(Q)][i], b = fb.f[split_plane_b(Q)][j];
+        acc[i][j] = TR ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[i][j], 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[i][j], 0, 0, 0);
+      }
+    split_side_slot<AL, BL, Q>(al, bl, as_next, bs_next, ra, rb, kleft);
+    __builtin_amdgcn_sched_barrier(0);
+    split_groups<T, AL, BL, TR, Q + 1>(as, bs, fa, fb, acc, al, bl, as_next, bs_next, ra, rb, kleft);
+  }
+}
+
+template <class T>
+struct SplitMinBlocks {
+  static constexpr int value = T::BM * T::BN <= 128 * 128 ? 3 : 2;
+};
+
+// The one-dimensional grid of gx * gy * (groups * nsplit) workgroups (see xcd_tile).  The divisors are constants of the
+// launch, so that a workgroup's place is worked out on the scalar unit and the buffer descriptors that depend on it
+// stay in scalar registers.
+struct SplitGrid {
+  FastDiv gx, gy, nsplit;
+};
+template <class T, class AL, class BL, class Epi>
+__global__ void __launch_bounds__(kThreads, (SplitMinBlocks<T>::value))
+gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int N, int K, int kchunk,
+                  SplitGrid grid) {
+  static_assert(T::BK == kBKs && T::RB == 32, "16-deep k-tiles of 32 x 32 blocks");
+  __shared__ __attribute__((aligned(16))) uint32_t As[2][AL::UNITS * 4];
+  __shared__ __attribute__((aligned(16))) uint32_t Bs[2][BL::UNITS * 4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave % T::WAVES_M, wn = wave / T::WAVES_M;
+  const uint32_t total = gridDim.x, L = blockIdx.x, q8 = total >> 3, r8 = total & 7, xcd = L & 7;
+  const uint32_t tile = xcd * q8 + min(xcd, r8) + (L >> 3);  // as in xcd_tile
+  const uint32_t rest = fdiv(tile, grid.gy), z = fdiv(rest, grid.gx), g = fdiv(z, grid.nsplit);
+  const int split = (int)(z - g * grid.nsplit.d);
+  const int m0 = (int)(rest - z * grid.gx.d) * T::BM, n0 = (int)(tile - rest * grid.gy.d) * T::BN;
+  const int kbeg = split * kchunk;
+  const int kend = min(K, kbeg + kchunk);
+  const int nt = kend > kbeg ? (kend - kbeg + T::BK - 1) / T::BK : 0;
+
+  AL al(ap, (int)g, tid, m0, kbeg);
+  BL bl(bp, (int)g, tid, n0, kbeg);
+  ep.set_group((int)g, (int)z);
+
+  v16f acc[T::TM][T::TN];
+#pragma unroll
+  for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  if (nt > 0) {
+    const int kh = lane >> 5;
+    const int a_off = split_unit<AL>(0, kh, wm * (T::TM * 32) + (lane & 31)) * 4;
+    const int b_off = split_unit<BL>(0, kh, wn * (T::TN * 32) + (lane & 31)) * 4;
+    // tile t is multiplied from LDS buffer t&1 while tile t+1 goes from registers to the other buffer and tile t+2
+    // is fetched
+    float4 ra[AL::NL], rb[BL::NL];
+    al.fetch(ra, kend - kbeg);
+    bl.fetch(rb, kend - kbeg);
+    split_store_all(al, As[0], ra);
+    split_store_all(bl, Bs[0], rb);
+    al.fetch(ra, kend - kbeg - T::BK);
+    bl.fetch(rb, kend - kbeg - T::BK);
+    __syncthreads();
+    for (int t = 0; t < nt; ++t) {
+      const int p = t & 1;
+      SplitFrags<AL, T::TM> fa;
+      SplitFrags<BL, T::TN> fb;
+      split_groups<T, AL, BL, Epi::kTransposed>(As[p] + a_off, Bs[p] + b_off, fa, fb, acc, al, bl, As[p ^ 1], Bs[p ^ 1],
+                                                ra, rb, kend - kbeg - (t + 2) * T::BK);
+      __syncthreads();
+    }
+  }
+
+#pragma unroll
+  for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < T::TN; ++j) {
+      if constexpr (Epi::kTransposed) {
+        store_block<T>(ep, acc[i][j], m0 + wm * (T::TM * 32) + i * 32 + (lane & 31), n0 + wn * (T::TN * 32) + j * 32,
+                       lane, M, N);
+      } else {
+        const int n = n0 + wn * (T::TN * 32) + j * 32 + (lane & 31);
+        if (n >= N) continue;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = m0 + wm * (T::TM * 32) + i * 32 + acc_row(lane, r);
+          if (m < M) ep.apply(m, n, acc[i][j][r]);
+        }
+      }
+    }
+}
+#endif  // AX_HOST_EMU
+
+}  // namespace ax

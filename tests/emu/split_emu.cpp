@@ -1,0 +1,183 @@
+// CPU emulation of the workgroup program in csrc/gemm_split.h: the real loaders, three-way splits, LDS stores and
+// fragment index maps run thread by thread with the MFMA replaced by its definition, and the products are compared
+// with plain double-precision loops.  Built with -fsanitize=address,undefined, so an access outside an operand or an
+// LDS tile aborts here.  Also checks that the split is exact.
+#include <math.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <algorithm>
+#include <vector>
+
+struct float4 {
+  float x, y, z, w;
+};
+#define AX_HOST_EMU 1
+#include "../../paper_1412_2302_amd/csrc/conv_plan.h"
+namespace ax {
+inline void emu_fail(const char* what) {
+  fprintf(stderr, "EMULATION FAULT: %s\n", what);
+  abort();
+}
+}  // namespace ax
+
+#include "../../paper_1412_2302_amd/csrc/gemm_split.h"
+
+using namespace ax;
+
+static int failures = 0;
+static float frand() { return (float)rand() / RAND_MAX * 2.f - 1.f; }
+
+template <class T, class AL, class BL, class Epi>
+static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int N, int K, int kchunk,
+                      int nsplit, int groups) {
+  const int gx = (M + T::BM - 1) / T::BM, gy = (N + T::BN - 1) / T::BN, gz = groups * nsplit;
+  std::vector<uint32_t> As(AL::UNITS * 4), Bs(BL::UNITS * 4);
+  std::vector<float> acc((size_t)T::BM * T::BN);
+  for (int bz = 0; bz < gz; ++bz)
+    for (int by = 0; by < gy; ++by)
+      for (int bx = 0; bx < gx; ++bx) {
+        const int g = bz / nsplit, split = bz - g * nsplit;
+        const int m0 = bx * T::BM, n0 = by * T::BN;
+        const int kbeg = split * kchunk, kend = std::min(K, kbeg + kchunk);
+        const int nt = kend > kbeg ? (kend - kbeg + T::BK - 1) / T::BK : 0;
+        std::fill(acc.begin(), acc.end(), 0.f);
+        Epi e = ep;
+        e.set_group(g, bz);
+        for (int t = 0; t < nt; ++t) {
+          std::fill(As.begin(), As.end(), 0x7fc07fc0u);  // two bf16 NaNs: an unwritten slot shows up
+          std::fill(Bs.begin(), Bs.end(), 0x7fc07fc0u);
+          for (int tid = 0; tid < kThreads; ++tid) {
+            AL al(ap, g, tid, m0, kbeg);
+            BL bl(bp, g, tid, n0, kbeg);
+            float4 ra[AL::NL], rb[BL::NL];
+            for (int u = 0; u <= t; ++u) {  // offsets run along with k
+              al.fetch(ra, kend - kbeg - u * T::BK);
+              bl.fetch(rb, kend - kbeg - u * T::BK);
+            }
+            split_store_all(al, As.data(), ra);
+            split_store_all(bl, Bs.data(), rb);
+          }
+          // fragments as the kernel addresses them: the unit of the wave's first block, block t further on
+          auto val = [](const std::vector<uint32_t>& lds, int unit, int e) {
+            const uint32_t w = lds.at((size_t)unit * 4 + e / 2);
+            return (e & 1) ? bf_hi(w) : bf_lo(w);
+          };
+          for (int i = 0; i < T::BM; ++i)
+            for (int j = 0; j < T::BN; ++j) {
+              const int wa = i / (T::TM * 32), ta = i / 32 % T::TM, wb = j / (T::TN * 32), tb = j / 32 % T::TN;
+              float& c = acc[(size_t)i * T::BN + j];
+              for (int q = 0; q < kSplitProducts; ++q) {
+                float s = 0.f;
+                for (int kh = 0; kh < 2; ++kh) {
+                  const int ua = split_unit<AL>(0, kh, wa * (T::TM * 32) + i % 32) + split_plane_a(q) * 2 * AL::RP + AL::block_units(ta);
+                  const int ub = split_unit<BL>(0, kh, wb * (T::TN * 32) + j % 32) + split_plane_b(q) * 2 * BL::RP + BL::block_units(tb);
+                  for (int x = 0; x < 8; ++x) s += val(As, ua, x) * val(Bs, ub, x);
+                }
+                c += s;
+              }
+            }
+        }
+        for (int i = 0; i < T::BM && m0 + i < M; ++i)
+          for (int j = 0; j < T::BN && n0 + j < N; ++j) e.apply(m0 + i, n0 + j, acc[(size_t)i * T::BN + j]);
+      }
+}
+
+static void check(const char* what, int M, int N, int K, const std::vector<float>& got, const std::vector<double>& want) {
+  double num = 0, den = 0;
+  bool nan = false;
+  for (size_t i = 0; i < want.size(); ++i) {
+    if (!(got[i] == got[i])) nan = true;
+    num += (got[i] - want[i]) * (got[i] - want[i]);
+    den += want[i] * want[i];
+  }
+  const double rel = sqrt(num / (den > 0 ? den : 1));
+  const bool ok = !nan && rel < 5e-7;  // fp32 accumulation; a lost or doubled term pair is at least 2^-17
+  printf("%-10s %4d x %4d x %4d rel_l2=%.3e %s\n", what, M, N, K, rel, ok ? "ok" : "FAIL");
+  if (!ok) ++failures;
+}
+
+static void split_is_exact() {
+  long bad = 0;
+  for (int i = 0; i < 2000000; ++i) {
+    uint32_t u = ((uint32_t)rand() << 16) ^ (uint32_t)rand() ^ ((uint32_t)rand() << 31);
+    const int e = (u >> 23) & 255;
+    if (e < 30 || e > 253) continue;  // the last term stays a normal number, the first one finite
+    float x;
+    memcpy(&x, &u, 4);
+    const SplitPair s = split_pair(x, -x);
+    if ((double)bf_lo(s.t[0]) + bf_lo(s.t[1]) + bf_lo(s.t[2]) != (double)x) ++bad;
+    if ((double)bf_hi(s.t[0]) + bf_hi(s.t[1]) + bf_hi(s.t[2]) != -(double)x) ++bad;
+  }
+  const SplitPair z = split_pair(0.f, -0.f);
+  for (int p = 0; p < kPlanes; ++p)
+    if (bf_lo(z.t[p]) != 0.f || bf_hi(z.t[p]) != 0.f) ++bad;
+  printf("exact split %s\n", bad ? "FAIL" : "ok");
+  if (bad) ++failures;
+}
+
+// M x N x K with the operands of the four kinds of product: A and B contiguous along k or along their rows;
+// ns slices of the reduction, ng groups side by side in memory (the layout of the transformed convolutions)
+template <class T>
+static void dense_case(int M, int N, int K, int ns, int ng) {
+  typedef SplitKInner<T::BM> AK;
+  typedef SplitRowInner<T::BM> AR;
+  typedef SplitRowInner<T::BN> BR;
+  // exact-size heap buffers: the sanitizer flags any access past either end
+  float *a = new float[(size_t)M * K * ng], *b = new float[(size_t)K * N * ng];
+  for (size_t i = 0; i < (size_t)M * K * ng; ++i) a[i] = frand();
+  for (size_t i = 0; i < (size_t)K * N * ng; ++i) b[i] = frand();
+  const int ktiles = (K + 15) / 16, kc = (ktiles + ns - 1) / ns * 16;
+  const long slab = (long)M * N;
+  auto run = [&](const char* what, bool a_k, bool b_k) {
+    std::vector<double> ref(slab * ng, 0.0);
+    // groups side by side along k (a_k: a[m][g*K + k]) or along rows (a[k][g*M + m]); b_k: b[g][n][k], else b[g][k][n]
+    auto A = [&](int g, int m, int k) { return (double)(a_k ? a[(size_t)m * K * ng + g * K + k] : a[((size_t)k * ng + g) * M + m]); };
+    auto Bv = [&](int g, int k, int n) { return (double)(b_k ? b[((size_t)g * N + n) * K + k] : b[((size_t)g * K + k) * N + n]); };
+    for (int g = 0; g < ng; ++g)
+      for (int m = 0; m < M; ++m)
+        for (int n = 0; n < N; ++n)
+          for (int k = 0; k < K; ++k) ref[(g * (size_t)M + m) * N + n] += A(g, m, k) * Bv(g, k, n);
+    std::vector<float> ws((size_t)slab * ns * ng, NAN), c(slab * ng, 0.f);
+    DenseParams pa{a, a_k ? (long)K * ng : (long)M * ng, a_k ? K : M, M, (uint32_t)((size_t)M * K * ng * 4)};
+    DenseParams pb{b, b_k ? K : N, (long)K * N, N, (uint32_t)((size_t)K * N * ng * 4)};
+    EpiSlab e{ws.data(), slab, N, nullptr};
+    if (a_k && b_k) {
+      emu_split<T, AK, SplitKInner<T::BN>, EpiSlab>(pa, pb, e, M, N, K, kc, ns, ng);
+    } else if (a_k) {
+      emu_split<T, AK, BR, EpiSlab>(pa, pb, e, M, N, K, kc, ns, ng);
+    } else {
+      emu_split<T, AR, BR, EpiSlab>(pa, pb, e, M, N, K, kc, ns, ng);
+    }
+    for (int g = 0; g < ng; ++g)
+      for (int s = 0; s < ns; ++s)
+        for (long i = 0; i < slab; ++i) c[g * slab + i] += ws[((size_t)g * ns + s) * slab + i];
+    check(what, M, N, K, c, ref);
+  };
+  run("k,k", true, true);
+  run("k,rows", true, false);
+  run("rows,rows", false, false);
+  delete[] a;
+  delete[] b;
+}
+
+int main() {
+  srand(4321);
+  split_is_exact();
+  typedef Tile<128, 128, 16, 2, 2> S128;
+  typedef Tile<128, 192, 16, 2, 2> S192;
+  typedef Tile<128, 96, 16, 4, 1> S96;
+  typedef Tile<128, 64, 16, 2, 2> S64;
+  // one tile with room to spare, whole tiles, one row and one quad past a tile; k below, at and past a k-tile
+  dense_case<S128>(4, 4, 4, 1, 1);
+  dense_case<S128>(128, 128, 32, 1, 2);
+  dense_case<S128>(132, 260, 52, 2, 2);
+  dense_case<S192>(132, 196, 20, 1, 2);
+  dense_case<S192>(64, 192, 48, 3, 3);
+  dense_case<S96>(132, 100, 36, 2, 2);
+  dense_case<S96>(128, 96, 16, 1, 3);
+  dense_case<S64>(60, 68, 36, 2, 2);
+  printf(failures ? "FAILED %d\n" : "ALL OK\n", failures);
+  return failures ? 1 : 0;
+}
