@@ -374,6 +374,27 @@ static int by_tile_split(const GemmPlan& p, const DenseParams& a, const DensePar
   AX_SPLIT(S128);
 #undef AX_SPLIT
 }
+// The first layer in run mode: a k-tile passes at most one run's end and one row's end of the loaders SplitRun and
+// SplitRunT.
+static inline bool split_run_ok(const ConvGeom& c) { return run_mode(c) && run_len(c) >= kBKs && c.Wo >= kBKs && c.Cout % 4 == 0; }
+static GemmPlan split_run_fwd_plan(const ConvGeom& c) {
+  return plan_split((int)c.P(), c.Cout, run_k(c), 1, (double)c.out_elems() * 4, 8);
+}
+static GemmPlan split_run_bwdw_plan(const ConvGeom& c) {
+  return plan_split(run_k(c), c.Cout, (int)c.P(), 1, (double)run_w_elems(c) * 4, 256);
+}
+// A of either product by tile, B = packed weights or output gradient
+template <template <int> class ALT, class Epi>
+static int by_tile_run(const GemmPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e, int M, int N, int K,
+                       hipStream_t st) {
+#define AX_SPLIT(T) \
+  return launch_tile_split<T, ALT<T::BM>, SplitRowInner<T::BN>, Epi>(a, b, e, M, N, K, p.kchunk, p.ns, 1, st)
+  if (p.bn == 192) AX_SPLIT(S192);
+  if (p.bn == 96) AX_SPLIT(S96);
+  if (p.bn == 64) AX_SPLIT(S64);
+  AX_SPLIT(S128);
+#undef AX_SPLIT
+}
 // A pointwise convolution (the products of a transformed layer among them) is a dense product per group.
 static inline bool pointwise(const ConvGeom& c) { return c.k == 1 && c.stride == 1 && c.pad == 0; }
 static inline DenseParams pointwise_A(const ConvGeom& c, const float* x) {
@@ -429,6 +450,7 @@ size_t conv_fwd_ws_floats(const ConvGeom& c) {
   ns = std::max(ns, fwd_plan(c, false, true, false, true).ns);
   if (run16_mode(c)) ns = std::max(ns, run16_fwd_plan(c).ns);
   if (split_fwd_ok(c)) ns = std::max(ns, split_fwd_plan(c).ns);
+  if (split_run_ok(c)) ns = std::max(ns, split_run_fwd_plan(c).ns);
   return ns > 1 ? (size_t)ns * c.out_elems() : 0;
 }
 size_t conv_bwd_data_ws_floats(const ConvGeom& c) {
@@ -449,6 +471,7 @@ size_t conv_bwd_weight_ws_floats(const ConvGeom& c) {
     const int ns = split_bwdw_plan(c, &swapped).ns;
     if (ns > 1) n = std::max(n, (size_t)ns * c.w_elems());
   }
+  if (split_run_ok(c)) n = std::max(n, (size_t)split_run_bwdw_plan(c).ns * run_w_elems(c));
   return n;
 }
 
@@ -531,6 +554,17 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
     return finish(launch_slab_finish(ws, p.ns, d.groups, d.M, d.N, bias, relu, nullptr, y, st));
   }
   if (run) d.K = run_k(c);
+  if (!g_bf16 && run && split_run_ok(c) && aligned16(wrun)) {
+    const GemmPlan p = split_run_fwd_plan(c);
+    copy.pending = y16 != nullptr;
+    if (p.ns == 1) {
+      EpiBiasAct ep{y, c.Cout, bias, relu, c.og(), 0, 0, nullptr};
+      return finish(by_tile_run<SplitRun>(p, run_A(c, x), run_B(c, wrun), ep, d.M, d.N, d.K, st));
+    }
+    EpiSlab ep{ws, (long)d.M * d.N, d.N, nullptr};
+    AX_TRY((by_tile_run<SplitRun>(p, run_A(c, x), run_B(c, wrun), ep, d.M, d.N, d.K, st)));
+    return finish(launch_slab_finish(ws, p.ns, 1, d.M, d.N, bias, relu, nullptr, y, st));
+  }
   const bool av = run || fwd_A_vec(c, x), bv = run || fwd_B_vec(c, wf);
   const bool bf = g_bf16 && av && bv;
   const Im2colParams a = run ? run_A(c, x) : fwd_A(c, x);
@@ -723,8 +757,9 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
   }
   const bool bf = g_bf16 && av && bv;
   const Im2colParams a = run ? run_A(c, x) : bwdw_A(c, x);
-  bool table = av && bv && table_ok(a, d) && (!bf || d.K % kBKbf == 0);
-  GemmPlan p = bwdw_plan(c, run, bf, table);
+  const bool split = !g_bf16 && run && split_run_ok(c);
+  bool table = !split && av && bv && table_ok(a, d) && (!bf || d.K % kBKbf == 0);
+  GemmPlan p = split ? split_run_bwdw_plan(c) : bwdw_plan(c, run, bf, table);
   if (table && p.kchunk > kMaxTableK) {  // no split count within reach keeps the k range inside the table
     table = false;
     p = bwdw_plan(c, run, bf, false);
@@ -733,7 +768,9 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
   float* out = run ? dwrun : dwf;
   EpiSlab ep{p.ns > 1 ? ws : out, slab, d.N, nullptr};
   const bool s16 = bf && table && !run && x16 && dy16 && conv_bf16_stored_ok(c) && aligned16(x16) && aligned16(dy16);
-  if (s16)
+  if (split)
+    AX_TRY((by_tile_run<SplitRunT>(p, a, bwdw_B(c, dy), ep, d.M, d.N, d.K, st)));
+  else if (s16)
     AX_TRY((by_tile_bf<ConvWeightGradTable16>(p, im2col16(a, x16), dense16(bwdw_B(c, dy), dy16), ep, d, st)));
   else if (bf && table)
     AX_TRY((by_tile_bf<ConvWeightGradTableBf>(p, a, bwdw_B(c, dy), ep, d, st)));

@@ -204,6 +204,98 @@ struct SplitRowInner {
   }
 };
 
+// The implicit im2col operand of run mode (Im2colParams): row = output pixel, k = (kernel row, position in its run).
+// Runs of at least one k-tile (run_len() >= 16), so that a step of one k-tile passes at most one run's end.
+template <int ROWS>
+struct SplitRun {
+  static constexpr int QK = kBKs / 4, NQ = ROWS * QK, NL = NQ / kThreads, NS = NL;
+  static_assert(NQ % kThreads == 0, "tile must be a whole number of loads per thread");
+  static constexpr int RP = ROWS + 8, UNITS = kPlanes * 2 * RP;
+  static AX_HD int pos(int row) { return row; }
+  static constexpr int block_units(int t) { return 32 * t; }
+  typedef Im2colParams Params;
+  BufView v;
+  int tid, kq, run, j;   // j: position in the run of the thread's quad
+  uint32_t skip;         // bytes from a run's end to the next kernel row's run
+  uint32_t off[NL];
+  AX_HD SplitRun(const Params& a, int /*g*/, int tid_, int row0, int kbeg) : v(make_view(a.x, a.bytes)), tid(tid_) {
+    kq = tid % QK;
+    run = a.Cg;
+    skip = (uint32_t)(a.W - run) * 4u;
+    const int k = kbeg + 4 * kq, r = (int)fdiv((uint32_t)k, a.d_cg);
+    j = k - r * run;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int p = row0 + (tid + i * kThreads) / QK;
+      const PixCoord c = decode_pixel(p < a.P ? p : 0, a);
+      const uint32_t base = row_base<IM2COL_FWD>(a, c.n, c.y * a.stride + r, c.x * a.stride_x + j, 0);
+      off[i] = p < a.P ? base : kOob;
+    }
+  }
+  AX_HD void fetch(float4* r, int kleft) {
+    const bool in = 4 * kq < kleft;
+    j += kBKs;
+    const bool over = j >= run;
+    const uint32_t step = kBKs * 4u + (over ? skip : 0u);
+    if (over) j -= run;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      r[i] = buf_ld4(v, in ? off[i] : kOob);
+      off[i] += step;
+    }
+  }
+  AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
+    split_store_quad<RP>(lds, (tid + s * kThreads) / QK, kq, r[s]);
+  }
+};
+// Its transpose (weight gradient): row = (kernel row, position in its run), k = output pixel.  A thread owns one row
+// quad and a pair of pixels that moves on by one k-tile at a time; rows of at least one k-tile of pixels (OW >= 16), so
+// that a step passes at most one row's end.
+template <int ROWS>
+struct SplitRunT {
+  typedef SplitRowStore<ROWS> St;
+  static constexpr int QR = ROWS / 4, NU = QR * (kBKs / 2), NL = 2, NS = 2;
+  static_assert(NU == kThreads, "one unit per thread");
+  static constexpr int RP = St::RP, UNITS = kPlanes * 2 * RP;
+  static AX_HD int pos(int row) { return St::pos(row); }
+  static constexpr int block_units(int t) { return 8 * t; }
+  typedef Im2colParams Params;
+  BufView v;
+  int tid, OW, OH, x, y;                 // (y, x): the first pixel of the pair
+  uint32_t off, outside, pix, row, img;  // byte steps: to the next pixel, past a row's end, past a picture's end
+  AX_HD SplitRunT(const Params& a, int /*g*/, int tid_, int row0, int kbeg)
+      : v(make_view(a.x, a.bytes)), tid(tid_), OW(a.OW), OH(a.OH) {
+    const int m = row0 + 4 * St::quad(tid);
+    const int r = (int)fdiv((uint32_t)m, a.d_cg), j = m - r * a.Cg;
+    outside = r < a.kh ? 0u : kOob;
+    const PixCoord c = decode_pixel(kbeg + 2 * St::pair(tid), a);
+    y = c.y;
+    x = c.x;
+    off = row_base<IM2COL_FWD>(a, c.n, c.y * a.stride + r, c.x * a.stride_x + j, 0);
+    pix = (uint32_t)a.stride_x * 4u;
+    row = (uint32_t)(a.stride * a.W - a.OW * a.stride_x) * 4u;
+    img = (uint32_t)((a.H - a.OH * a.stride) * a.W) * 4u;
+  }
+  // off of a pixel px of row py that may lie past the row's end
+  AX_HD uint32_t wrap(uint32_t o, int px, int py) const {
+    return px < OW ? o : o + row + (py + 1 < OH ? 0u : img);
+  }
+  AX_HD void fetch(float4* r, int kleft) {
+    const int k = 2 * St::pair(tid);
+    r[0] = buf_ld4(v, k < kleft ? off | outside : kOob);
+    r[1] = buf_ld4(v, k + 1 < kleft ? wrap(off + pix, x + 1, y) | outside : kOob);
+    off = wrap(off + kBKs * pix, x + kBKs, y);
+    x += kBKs;
+    if (x >= OW) {
+      x -= OW;
+      y = y + 1 < OH ? y + 1 : 0;
+    }
+  }
+  AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
+    St::store_half(lds, St::quad(tid), St::pair(tid), s & 1, r[0], r[1]);
+  }
+};
+
 template <class L>
 AX_HD void split_store_all(const L& l, uint32_t* lds, const float4* r) {
 #pragma unroll

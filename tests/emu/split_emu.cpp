@@ -162,6 +162,56 @@ static void dense_case(int M, int N, int K, int ns, int ng) {
   delete[] b;
 }
 
+// first-layer shapes in run mode: forward and weight gradient of an unpadded convolution over three-channel pictures
+template <class T>
+static void run_case(int B, int H, int W, int Cout, int k, int st, int ns) {
+  ConvGeom c;
+  c.B = B; c.H = H; c.W = W; c.Cin = 3; c.Cout = Cout; c.k = k; c.stride = st; c.pad = 0; c.groups = 1;
+  c.Ho = (H - k) / st + 1;
+  c.Wo = (W - k) / st + 1;
+  const int run = run_len(c), kc = k * 3, K = run_k(c), P = (int)c.P();
+  if (!run_mode(c) || run < 16 || c.Wo < 16) emu_fail("not a case of the run loaders");
+  float *x = new float[c.in_elems()], *w = new float[run_w_elems(c)], *dy = new float[c.out_elems()];
+  for (long i = 0; i < c.in_elems(); ++i) x[i] = frand();
+  for (long i = 0; i < c.out_elems(); ++i) dy[i] = frand();
+  for (int r = 0; r < k; ++r)
+    for (int j = 0; j < run; ++j)
+      for (int o = 0; o < Cout; ++o) w[((long)r * run + j) * Cout + o] = j < kc ? frand() : 0.f;
+  std::vector<double> y_ref(c.out_elems(), 0.0), dw_ref(run_w_elems(c), 0.0);
+  for (int p = 0; p < P; ++p) {
+    const int n = p / (c.Ho * c.Wo), oy = p / c.Wo % c.Ho, ox = p % c.Wo;
+    for (int r = 0; r < k; ++r)
+      for (int j = 0; j < kc; ++j) {
+        const double v = x[(((long)n * H + oy * st + r) * W + ox * st) * 3 + j];
+        for (int o = 0; o < Cout; ++o) {
+          y_ref[(long)p * Cout + o] += v * w[((long)r * run + j) * Cout + o];
+          dw_ref[((long)r * run + j) * Cout + o] += v * dy[(long)p * Cout + o];
+        }
+      }
+  }
+  auto chunk = [&](int len) { return ((len + 15) / 16 + ns - 1) / ns * 16; };
+  {
+    std::vector<float> ws((size_t)ns * c.out_elems(), NAN), y(c.out_elems(), 0.f);
+    EpiSlab e{ws.data(), (long)P * Cout, Cout, nullptr};
+    emu_split<T, SplitRun<T::BM>, SplitRowInner<T::BN>, EpiSlab>(run_A(c, x), run_B(c, w), e, P, Cout, K, chunk(K), ns, 1);
+    for (int s = 0; s < ns; ++s)
+      for (long i = 0; i < c.out_elems(); ++i) y[i] += ws[s * c.out_elems() + i];
+    check("run fwd", P, Cout, K, y, y_ref);
+  }
+  {
+    std::vector<float> ws((size_t)ns * run_w_elems(c), NAN), dw(run_w_elems(c), 0.f);
+    EpiSlab e{ws.data(), run_w_elems(c), Cout, nullptr};
+    emu_split<T, SplitRunT<T::BM>, SplitRowInner<T::BN>, EpiSlab>(run_A(c, x), bwdw_B(c, dy), e, K, Cout, P, chunk(P), ns, 1);
+    for (int s = 0; s < ns; ++s)
+      for (long i = 0; i < run_w_elems(c); ++i) dw[i] += ws[s * run_w_elems(c) + i];
+    for (int r = 0; r < k; ++r)  // the padding of a run reads the pixels behind it; nobody uses its gradient
+      for (int j = kc; j < run; ++j)
+        for (int o = 0; o < Cout; ++o) dw[((long)r * run + j) * Cout + o] = 0.f;
+    check("run bwd_w", K, Cout, P, dw, dw_ref);
+  }
+  delete[] x; delete[] w; delete[] dy;
+}
+
 int main() {
   srand(4321);
   split_is_exact();
@@ -178,6 +228,9 @@ int main() {
   dense_case<S96>(132, 100, 36, 2, 2);
   dense_case<S96>(128, 96, 16, 1, 3);
   dense_case<S64>(60, 68, 36, 2, 2);
+  run_case<S96>(2, 75, 76, 96, 11, 4, 1);   // 17 pixels a row: a k-tile crosses a row's end, and a picture's
+  run_case<S96>(3, 41, 45, 20, 7, 2, 3);    // runs of 24, slices that start inside a run and inside a row
+  run_case<S128>(1, 22, 36, 132, 5, 1, 2);  // runs of 16, 32 pixels a row
   printf(failures ? "FAILED %d\n" : "ALL OK\n", failures);
   return failures ? 1 : 0;
 }
