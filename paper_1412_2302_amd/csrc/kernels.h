@@ -112,6 +112,8 @@ size_t fc_ws_floats(int B, int in, int out);
 // x16 / w16 / dy16: bf16 copies of the operands (same layouts); when those of a product are given, the handle's
 // GEMMs are bf16 and fc_bf16_stored_ok(), the product reads them.  y16 / dx16: where to leave a bf16 copy of the result.
 bool fc_bf16_stored_ok(int in, int out);
+// the forward product of so few rows reads the fp32 weights directly, also in bf16 handles
+bool fc_rows_ok(int B, int in);
 int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const FcAct& act, float* y, float* ws,
                   hipStream_t st, const uint16_t* x16 = nullptr, const uint16_t* w16 = nullptr, uint16_t* y16 = nullptr);
 int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, const float* gate, float* dx,
@@ -136,7 +138,9 @@ int launch_crop_params(uint64_t key, int B, int range_x, int range_y, int32_t* o
 int launch_preprocess(const uint8_t* raw, const float* mean, const int32_t* ox, const int32_t* oy,
                       const int32_t* flip, int B, int C, int RH, int RW, int CH, int CW, float* out, hipStream_t st,
                       uint16_t* out4 = nullptr);  // out4: also the pictures as bf16, four channels per pixel (C <= 4)
-int launch_nchw_to_nhwc(const float* src, float* dst, int N, int C, int H, int W, hipStream_t st);
+// d4 (may be null, C < 4): also the pixels as bf16 with four channels each (launch_pad4_bf16)
+int launch_nchw_to_nhwc(const float* src, float* dst, int N, int C, int H, int W, hipStream_t st,
+                        uint16_t* d4 = nullptr);
 int launch_nhwc_to_nchw(const float* src, float* dst, int N, int C, int H, int W, hipStream_t st);
 int launch_lrn_fwd(const float* a, float* b, long pixels, int C, int n, float k, float alpha, float beta,
                    hipStream_t st);
