@@ -861,6 +861,105 @@ __global__ void fc_bwd_finish_kernel(const float* __restrict__ ws, int nsplit, s
   if (dx16) store_bf16(dx16 + i, s);
 }
 
+// y = act(x w^T + b) for at most kFcRows rows of x: the weights are read once, and that is all the time there is -- a
+// matrix tile would be 1/16 full at best and needs slices of the reduction, and a second kernel to add them, to reach
+// every compute unit.  A wave owns two outputs and runs along k, 1024 values at a time, with eight 16-byte loads of
+// weights in flight per lane; the rows of x pass through LDS, shared by the workgroup's four waves.  The sums stay in
+// fp32: one chain of in/64 products per lane, then a tree over the lanes.  BF: both operands rounded to bf16 first, as
+// the bf16 products have them (a handle's bf16 copy of the weights, twice the traffic of reading them, is not needed).
+// 4096 x 9216, one row: 55 + 5 us (slices, finish) -> see the dispatch rule in launch_fc_fwd.
+constexpr int kFcRows = 8;
+template <int BB, bool BF>
+__global__ void __launch_bounds__(256)
+fc_rows_kernel(const float* __restrict__ x, const float* __restrict__ w, int B, int in, int out, FcAct act,
+               float* __restrict__ y, uint16_t* __restrict__ y16) {
+  constexpr int R = 2, CH = 1024, Q = CH / 256;  // outputs per wave; k per chunk; 16-byte loads per lane and chunk
+  __shared__ float4 xs[BB][CH / 4];
+  const int tid = threadIdx.x, lane = tid & 63, row0 = (blockIdx.x * 4 + (tid >> 6)) * R, in4 = in / 4;
+  auto prep = [](float4 v) {
+    if (BF) {
+      const uint32_t a = pack_bf16(v.x, v.y), b = pack_bf16(v.z, v.w);
+      v = make_float4(bf_lo(a), bf_hi(a), bf_lo(b), bf_hi(b));
+    }
+    return v;
+  };
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  float acc[R][BB];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int b = 0; b < BB; ++b) acc[r][b] = 0.f;
+  for (int c0 = 0; c0 < in4; c0 += CH / 4) {
+    float4 wv[R][Q];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float4* wr = reinterpret_cast<const float4*>(w) + (size_t)min(row0 + r, out - 1) * in4;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int k = c0 + q * 64 + lane;
+        wv[r][q] = zero;
+        if (k < in4) wv[r][q] = wr[k];
+      }
+    }
+    __syncthreads();  // the waves are done with the last chunk of x
+    for (int i = tid; i < BB * (CH / 4); i += 256) {
+      const int b = i / (CH / 4), k = c0 + i % (CH / 4);
+      float4 v = zero;
+      if (b < B && k < in4) v = reinterpret_cast<const float4*>(x)[(size_t)b * in4 + k];
+      xs[b][i % (CH / 4)] = prep(v);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      float4 wq[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) wq[r] = prep(wv[r][q]);
+#pragma unroll
+      for (int b = 0; b < BB; ++b) {
+        const float4 xv = xs[b][q * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          acc[r][b] = fmaf(wq[r].x, xv.x, acc[r][b]);
+          acc[r][b] = fmaf(wq[r].y, xv.y, acc[r][b]);
+          acc[r][b] = fmaf(wq[r].z, xv.z, acc[r][b]);
+          acc[r][b] = fmaf(wq[r].w, xv.w, acc[r][b]);
+        }
+      }
+    }
+  }
+  float mine = 0.f;  // lane r*BB + b keeps the sum of output row0 + r, row b
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int b = 0; b < BB; ++b) {
+      float s = acc[r][b];
+#pragma unroll
+      for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d);
+      if (lane == r * BB + b) mine = s;
+    }
+  const int b = lane % BB, o = row0 + lane / BB;
+  if (lane >= R * BB || b >= B || o >= out) return;
+  const size_t i = (size_t)b * out + o;
+  if (act.bias) mine += act.bias[o];
+  if (act.relu) mine = mine > 0.f ? mine : 0.f;
+  if (act.dropout && !dropout_keep(act.key, act.tag, i, act.thresh24)) mine = 0.f;
+  y[i] = mine * act.scale;
+  if (y16) store_bf16(y16 + i, mine * act.scale);
+}
+bool fc_rows_ok(int B, int in) { return B <= kFcRows && in % 4 == 0; }
+template <bool BF>
+static int launch_fc_rows(int B, int in, int out, const float* x, const float* w, const FcAct& act, float* y,
+                          uint16_t* y16, hipStream_t st) {
+  KernelScope ks("fc_rows", 2.0 * B * in * (double)out, 4.0 * ((double)in * out + (double)B * (in + out)), st);
+  const dim3 grid(ceil_div(out, 8)), block(256);
+  if (B <= 1) hipLaunchKernelGGL((fc_rows_kernel<1, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
+  else if (B <= 2) hipLaunchKernelGGL((fc_rows_kernel<2, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
+  else if (B <= 4) hipLaunchKernelGGL((fc_rows_kernel<4, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
+  else hipLaunchKernelGGL((fc_rows_kernel<8, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
+  AX_LAUNCH_CHECK();
+  return ALEXNET_OK;
+}
+
 static inline bool vec_ok(const float* p, long ld) { return aligned16(p) && ld % 4 == 0; }
 
 // 16-byte loads: on the bf16 matrix cores, tile and slices by `p`; else on the fp32 ones
@@ -885,6 +984,8 @@ static inline DenseParams dense16_of(const uint16_t* p, long ld, int rows, size_
 int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const FcAct& act, float* y, float* ws,
                   hipStream_t st, const uint16_t* x16, const uint16_t* w16, uint16_t* y16) {
   const bool vec = vec_ok(x, in) && vec_ok(w, in), bf = g_bf16 && vec;
+  if (vec && fc_rows_ok(B, in))
+    return bf ? launch_fc_rows<true>(B, in, out, x, w, act, y, y16, st) : launch_fc_rows<false>(B, in, out, x, w, act, y, y16, st);
   const bool s16 = bf && x16 && w16 && fc_bf16_stored_ok(in, out) && aligned16(x16) && aligned16(w16);
   GemmPlan p{128, 128, 0, 0};
   if (vec && !bf) p = fc_plan(B, out, in);
