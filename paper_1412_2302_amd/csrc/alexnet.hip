@@ -460,11 +460,15 @@ static int stage_bwd_data(alexnet* n, Stage& s, const float* dy, const float* wf
 static int fcw16_refresh(alexnet* n, hipStream_t st) {
   return launch_to_bf16(n->params + n->fc[0].w_off, n->fcw16, n->n_weights - n->fc[0].w_off, st);
 }
+// the dense layers multiply with the bf16 copy of their weights; a forward pass of a few rows alone does not
+static bool fcw16_needed(const alexnet* n, bool train) {
+  return n->fc16 && (train || !fc_rows_ok(n->cfg.batch, n->flat));
+}
 static int run_forward(alexnet* n, const float* in, bool train, uint64_t step, hipStream_t st,
                        hipEvent_t taps_ready = nullptr, uint16_t* in16 = nullptr, hipEvent_t fcw_ready = nullptr) {
   const alexnet_config_t& c = n->cfg;
   set_gemm_precision(c.precision);
-  if (n->fc16 && !fcw_ready) AX_TRY(fcw16_refresh(n, st));
+  if (!fcw_ready && fcw16_needed(n, train)) AX_TRY(fcw16_refresh(n, st));
   const float* h = in;
   bool waited = false;
   bool x16_ready = false;  // the kernel that made h also left its bf16 copy in the next stage's x16
@@ -658,6 +662,41 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
   }
   ProfContext pcb("bias_grads");
   return launch_colsum_batch(bias_sums, st);
+}
+
+// Everything a forward pass derives from the weights -- transformed taps, bf16 copies -- is made on the side stream,
+// under the first layer (which needs its own bf16 weights only); ev_u_done and ev_fcw_done tell when.
+static int fork_forward_weights(alexnet* n, bool train, hipStream_t st) {
+  AX_HIP(hipEventRecord(n->ev_step_begin, st));
+  AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_step_begin, 0));
+  for (int i = 0; i < kStages; ++i) {  // the convolutions' first: they are needed soonest
+    Stage& s = n->st[i];
+    ProfContext pc(s.lab[1]);
+    if (s.wino) AX_TRY(launch_wino_filter(s.g, n->params + s.w_off, s.wino_u, n->upd_stream));
+    if (s.b16)
+      AX_TRY(launch_to_bf16_transposed(n->params + s.w_off, s.wf16, s.g.groups, s.g.kf(), s.g.og(), n->upd_stream));
+    if (s.r16)
+      AX_TRY(launch_run16_pack(n->params + s.w_off, s.wf16, s.g.k, s.g.Cin,
+                               (int)(conv_run16_w_elems(s.g) / ((size_t)s.g.k * s.g.Cout)), s.g.Cout, n->upd_stream));
+  }
+  AX_HIP(hipEventRecord(n->ev_u_done, n->upd_stream));
+  if (fcw16_needed(n, train)) {
+    ProfContext pc("fc.weights16");
+    AX_TRY(fcw16_refresh(n, n->upd_stream));
+    AX_HIP(hipEventRecord(n->ev_fcw_done, n->upd_stream));
+  }
+  return ALEXNET_OK;
+}
+
+// An inference pass: the weights' forms on the side stream where there are any (a fork that nothing joins would break a
+// caller's graph capture).  Before, they were made in front of each layer: 29 of 604 us at batch 50, 25 of 230 at batch
+// 1, and 62 + 20 of 1250 us for the bf16 copies at batch 256.
+static int run_inference(alexnet* n, const float* in, uint16_t* in16, hipStream_t st) {
+  bool convs = false;
+  for (int i = 0; i < kStages; ++i) convs = convs || n->st[i].wino || n->st[i].b16 || n->st[i].r16;
+  const bool fc = fcw16_needed(n, false);
+  if (convs || fc) AX_TRY(fork_forward_weights(n, false, st));
+  return run_forward(n, in, false, 0, st, convs ? n->ev_u_done : nullptr, in16, fc ? n->ev_fcw_done : nullptr);
 }
 
 static int fwd_bwd(alexnet* n, int32_t slot, const int32_t* d_labels, uint64_t step, float* d_loss, hipStream_t st,
@@ -860,10 +899,8 @@ int alexnet_set_input(alexnet_t* n, const float* d_input_nchw, int32_t slot, voi
   REQUIRE(n && d_input_nchw, ALEXNET_EINVAL, "alexnet_set_input: null argument");
   REQUIRE(slot == 0 || slot == 1, ALEXNET_EINVAL, "alexnet_set_input: slot must be 0 or 1");
   const alexnet_config_t& c = n->cfg;
-  AX_TRY(launch_nchw_to_nhwc(d_input_nchw, n->input[slot], c.batch, c.in_c, c.crop_h, c.crop_w, S(stream)));
-  if (n->input16[slot])
-    AX_TRY(launch_pad4_bf16(n->input[slot], n->input16[slot], (size_t)c.batch * c.crop_h * c.crop_w, c.in_c, S(stream)));
-  return ALEXNET_OK;
+  return launch_nchw_to_nhwc(d_input_nchw, n->input[slot], c.batch, c.in_c, c.crop_h, c.crop_w, S(stream),
+                             n->input16[slot]);
 }
 
 int alexnet_forward_backward(alexnet_t* n, int32_t slot, const int32_t* d_labels, uint64_t step, float* d_loss,
@@ -889,24 +926,7 @@ int alexnet_train_step(alexnet_t* n, int32_t slot, const int32_t* d_labels, uint
   if (early) {
     // the backward-data packing of the convolution weights depends on the weights only: it runs on the side
     // stream under the forward pass
-    AX_HIP(hipEventRecord(n->ev_step_begin, S(stream)));
-    AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_step_begin, 0));
-    for (int i = 0; i < kStages; ++i) {  // transformed taps of the forward pass first: it needs them soonest
-      Stage& s = n->st[i];
-      ProfContext pc(s.lab[1]);
-      if (s.wino) AX_TRY(launch_wino_filter(s.g, n->params + s.w_off, s.wino_u, n->upd_stream));
-      if (s.b16)
-        AX_TRY(launch_to_bf16_transposed(n->params + s.w_off, s.wf16, s.g.groups, s.g.kf(), s.g.og(), n->upd_stream));
-      if (s.r16)
-        AX_TRY(launch_run16_pack(n->params + s.w_off, s.wf16, s.g.k, s.g.Cin,
-                                 (int)(conv_run16_w_elems(s.g) / ((size_t)s.g.k * s.g.Cout)), s.g.Cout, n->upd_stream));
-    }
-    AX_HIP(hipEventRecord(n->ev_u_done, n->upd_stream));
-    if (n->fc16) {  // needed next, by the dense layers' forward products
-      ProfContext pc("fc.weights16");
-      AX_TRY(fcw16_refresh(n, n->upd_stream));
-      AX_HIP(hipEventRecord(n->ev_fcw_done, n->upd_stream));
-    }
+    AX_TRY(fork_forward_weights(n, true, S(stream)));
     for (int i = 1; i < kStages; ++i) {
       Stage& s = n->st[i];
       ProfContext pc(s.lab[3]);
@@ -928,8 +948,8 @@ int alexnet_train_step(alexnet_t* n, int32_t slot, const int32_t* d_labels, uint
 int alexnet_forward(alexnet_t* n, const float* d_input_nchw, float* d_probs, void* stream) {
   REQUIRE(n && d_input_nchw && d_probs, ALEXNET_EINVAL, "alexnet_forward: null argument");
   const alexnet_config_t& c = n->cfg;
-  AX_TRY(launch_nchw_to_nhwc(d_input_nchw, n->input[2], c.batch, c.in_c, c.crop_h, c.crop_w, S(stream)));
-  AX_TRY(run_forward(n, n->input[2], false, 0, S(stream)));  // the first layer pads its own bf16 copy
+  AX_TRY(launch_nchw_to_nhwc(d_input_nchw, n->input[2], c.batch, c.in_c, c.crop_h, c.crop_w, S(stream), n->input16[2]));
+  AX_TRY(run_inference(n, n->input[2], n->input16[2], S(stream)));
   Dense& last = n->fc[kFc - 1];
   return launch_softmax_xent(last.act, nullptr, c.batch, last.out, 1, d_probs, n->row_loss, n->err_flag, S(stream));
 }
@@ -940,7 +960,7 @@ int alexnet_validate(alexnet_t* n, int32_t slot, const int32_t* d_labels, const 
   REQUIRE(slot == 0 || slot == 1, ALEXNET_EINVAL, "alexnet_validate: slot must be 0 or 1");
   REQUIRE(nk >= 1 && nk <= 8, ALEXNET_EINVAL, "alexnet_validate: between 1 and 8 values of k");
   for (int j = 0; j < nk; ++j) REQUIRE(ks[j] >= 1, ALEXNET_EINVAL, "alexnet_validate: k must be positive");
-  AX_TRY(run_forward(n, n->input[slot], false, 0, S(stream), nullptr, n->input16[slot]));
+  AX_TRY(run_inference(n, n->input[slot], n->input16[slot], S(stream)));
   Dense& last = n->fc[kFc - 1];
   // the order of the scores is the order of the probabilities, so the logits are counted directly
   return launch_topk_count(last.act, d_labels, n->cfg.batch, last.out, ks, nk, d_counts, n->err_flag, S(stream));
