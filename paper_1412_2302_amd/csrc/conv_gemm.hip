@@ -312,19 +312,23 @@ typedef Tile<128, 128, kBKs, 2, 2> S128;
 typedef Tile<128, 96, kBKs, 4, 1> S96;
 typedef Tile<128, 192, kBKs, 2, 2> S192;
 typedef Tile<128, 64, kBKs, 2, 2> S64;
+typedef Tile<64, 128, kBKs, 2, 2> S64m;
 // rate of a tile on a long reduction over the fp32 matrix rate of a compute unit, measured at 4096 x 4608 x 2048
 // (160, 153, 159 and 133 TFLOP/s; the fp32 kernels reach 101 there)
 static const TileOption kTileOptionsSplit[] = {
-    {128, 128, kBKs, 1.02}, {128, 96, kBKs, 0.97}, {128, 192, kBKs, 1.01}, {128, 64, kBKs, 0.84}};
+    {128, 128, kBKs, 1.02}, {128, 96, kBKs, 0.97}, {128, 192, kBKs, 1.01}, {128, 64, kBKs, 0.84},
+    {64, 128, kBKs, 0.84}};  // the last one for dense layers on at most 64 rows, where a 128-row tile is half empty
 // Cheapest (tile, slices) for a launch of the split kernel, as plan_gemm(), with one difference: these kernels fetch
 // one k-tile ahead only, and a workgroup that has its compute unit to itself waits for memory about half the time (a
 // weight gradient of 192 x 128 x 2048 x 72: 105 us in 216 workgroups, see fill), so slices are worth having until two
 // or three workgroups share every unit.
-static GemmPlan plan_split(int M, int N, int K, int groups, double out_bytes, int max_s, double* t_out = nullptr) {
+static GemmPlan plan_split(int M, int N, int K, int groups, double out_bytes, int max_s, double* t_out = nullptr,
+                           bool allow64 = false) {
   GemmPlan best{128, 128, 1, ceil_div(K, kBKs) * kBKs};
   double best_t = 1e30;
   const int ktiles = ceil_div(K, kBKs);
   for (const TileOption& to : kTileOptionsSplit) {
+    if (to.bm == 64 && !allow64) continue;
     const long tiles = (long)ceil_div(M, to.bm) * ceil_div(N, to.bn) * groups;
     const double t_tile = 2.0 * to.bm * to.bn * (double)ktiles * kBKs / (0.614e12 * to.eff);
     for (int s = 1; s <= max_s && s <= ktiles; ++s) {
@@ -368,6 +372,7 @@ static int by_tile_split(const GemmPlan& p, const DenseParams& a, const DensePar
                          int groups, hipStream_t st) {
 #define AX_SPLIT(T) \
   return launch_tile_split<T, ALT<T::BM>, BLT<T::BN>, Epi>(a, b, e, M, N, K, p.kchunk, p.ns, groups, st)
+  if (p.bm == 64) AX_SPLIT(S64m);
   if (p.bn == 192) AX_SPLIT(S192);
   if (p.bn == 96) AX_SPLIT(S96);
   if (p.bn == 64) AX_SPLIT(S64);
@@ -820,7 +825,7 @@ static int fc_split(int B, int N, int K, int* kchunk, bool bf) {
   *kchunk = best_per * bk;
   return best;
 }
-static GemmPlan fc_plan(int B, int N, int K) { return plan_split(B, N, K, 1, (double)B * N * 4, 64); }
+static GemmPlan fc_plan(int B, int N, int K) { return plan_split(B, N, K, 1, (double)B * N * 4, 64, nullptr, B <= 64); }
 size_t fc_ws_floats(int B, int in, int out) {
   int kc;
   size_t n = 0;
@@ -960,15 +965,36 @@ static int launch_fc_rows(int B, int in, int out, const float* x, const float* w
   return ALEXNET_OK;
 }
 
+// An unsliced dense product finishes itself: y = act(v + bias), as fc_fwd_finish_kernel does behind slices.
+struct EpiFcAct {
+  static constexpr bool kTransposed = true;
+  float* y;
+  long ldc;
+  FcAct act;
+  uint16_t* y16;  // may be null
+  AX_HD void set_group(int /*g*/, int /*z*/) {}
+  __device__ void apply(int m, int n, float v) const {
+    const size_t i = (size_t)m * ldc + n;
+    if (act.bias) v += act.bias[n];
+    if (act.relu) v = v > 0.f ? v : 0.f;
+    if (act.dropout && !dropout_keep(act.key, act.tag, i, act.thresh24)) v = 0.f;
+    y[i] = v * act.scale;
+    if (y16) store_bf16(y16 + i, v * act.scale);
+  }
+  __device__ void apply4(int m, int n, float4 v) const {
+    apply(m, n, v.x); apply(m, n + 1, v.y); apply(m, n + 2, v.z); apply(m, n + 3, v.w);
+  }
+};
+
 static inline bool vec_ok(const float* p, long ld) { return aligned16(p) && ld % 4 == 0; }
 
 // 16-byte loads: on the bf16 matrix cores, tile and slices by `p`; else on the fp32 ones
 template <template <int> class SA, template <int> class SB, template <int, int, bool> class ALT,
-          template <int, int, bool> class BLT>
-static int launch_dense(bool vec, const GemmPlan& p, const DenseParams& a, const DenseParams& b, const EpiSlab& ep, int M,
+          template <int, int, bool> class BLT, class Epi>
+static int launch_dense(bool vec, const GemmPlan& p, const DenseParams& a, const DenseParams& b, const Epi& ep, int M,
                         int N, int K, hipStream_t st) {
   if (vec) return by_tile_split<SA, SB>(p, a, b, ep, M, N, K, 1, st);
-  return launch_tile<T128, ALT<128, kBK, false>, BLT<128, kBK, false>, EpiSlab>(a, b, ep, M, N, K, p.kchunk, p.ns, 1, st);
+  return launch_tile<T128, ALT<128, kBK, false>, BLT<128, kBK, false>, Epi>(a, b, ep, M, N, K, p.kchunk, p.ns, 1, st);
 }
 
 typedef BfRowMajor<DenseKInner<128, kBKbf, true>, 128, kBKbf> BfDenseK;
@@ -993,16 +1019,20 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
   const int ns = p.ns, kchunk = p.kchunk;
   DenseParams a{x, in, 0, B, (uint32_t)((size_t)B * in * 4)};
   DenseParams b{w, in, 0, out, (uint32_t)((size_t)out * in * 4)};
-  EpiSlab ep{ws, (long)B * out, out, nullptr};
   // both operands run along k = in
-  if (s16)
-    AX_TRY((launch_tile_bf<B128, Dense16K, Dense16K, EpiSlab>(dense16_of(x16, in, B, (size_t)B * in),
-                                                                dense16_of(w16, in, out, (size_t)out * in), ep, B, out,
-                                                                in, kchunk, ns, 1, st)));
-  else if (bf)
-    AX_TRY((launch_tile_bf<B128, BfDenseK, BfDenseK, EpiSlab>(a, b, ep, B, out, in, kchunk, ns, 1, st)));
-  else
-    AX_TRY((launch_dense<SplitKInner, SplitKInner, DenseKInner, DenseKInner>(vec, p, a, b, ep, B, out, in, st)));
+  auto product = [&](const auto& ep) -> int {
+    typedef std::decay_t<decltype(ep)> Epi;
+    if (s16)
+      return launch_tile_bf<B128, Dense16K, Dense16K, Epi>(dense16_of(x16, in, B, (size_t)B * in),
+                                                           dense16_of(w16, in, out, (size_t)out * in), ep, B, out, in,
+                                                           kchunk, ns, 1, st);
+    if (bf) return launch_tile_bf<B128, BfDenseK, BfDenseK, Epi>(a, b, ep, B, out, in, kchunk, ns, 1, st);
+    return launch_dense<SplitKInner, SplitKInner, DenseKInner, DenseKInner>(vec, p, a, b, ep, B, out, in, st);
+  };
+  // (the mask's hash, 64 values per lane one after the other, costs a full tile more than the second launch: 128 rows
+  // 256 wide 456 against 434 us per small training step)
+  if (ns == 1 && (!act.dropout || B <= 32)) return product(EpiFcAct{y, out, act, y16});
+  AX_TRY(product(EpiSlab{ws, (long)B * out, out, nullptr}));
   const size_t total = (size_t)B * out;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1), st);
   hipLaunchKernelGGL(fc_fwd_finish_kernel, dim3(ceil_div(total, 256)), dim3(256), 0, st, ws, ns, B, out, act, y, y16);
@@ -1020,16 +1050,18 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
   const int ns = p.ns, kchunk = p.kchunk;
   DenseParams a{dy, out, 0, B, (uint32_t)((size_t)B * out * 4)};
   DenseParams b{w, in, 0, in, (uint32_t)((size_t)out * in * 4)};
-  EpiSlab ep{ws, (long)B * in, in, nullptr};
   // A runs along k = out, B along its rows = in
-  if (s16)
-    AX_TRY((launch_tile_bf<B128, Dense16K, Dense16R, EpiSlab>(dense16_of(dy16, out, B, (size_t)B * out),
-                                                                dense16_of(w16, in, in, (size_t)out * in), ep, B, in,
-                                                                out, kchunk, ns, 1, st)));
-  else if (bf)
-    AX_TRY((launch_tile_bf<B128, BfDenseK, BfDenseR, EpiSlab>(a, b, ep, B, in, out, kchunk, ns, 1, st)));
-  else
-    AX_TRY((launch_dense<SplitKInner, SplitRowInner, DenseKInner, DenseRowInner>(vec, p, a, b, ep, B, in, out, st)));
+  auto product = [&](const auto& ep) -> int {
+    typedef std::decay_t<decltype(ep)> Epi;
+    if (s16)
+      return launch_tile_bf<B128, Dense16K, Dense16R, Epi>(dense16_of(dy16, out, B, (size_t)B * out),
+                                                           dense16_of(w16, in, in, (size_t)out * in), ep, B, in, out,
+                                                           kchunk, ns, 1, st);
+    if (bf) return launch_tile_bf<B128, BfDenseK, BfDenseR, Epi>(a, b, ep, B, in, out, kchunk, ns, 1, st);
+    return launch_dense<SplitKInner, SplitRowInner, DenseKInner, DenseRowInner>(vec, p, a, b, ep, B, in, out, st);
+  };
+  if (ns == 1) return product(EpiGate{dx, in, gate, in, 0, 0, dx16});
+  AX_TRY(product(EpiSlab{ws, (long)B * in, in, nullptr}));
   const size_t total = (size_t)B * in;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1 + (gate ? 1 : 0)), st);
   hipLaunchKernelGGL(fc_bwd_finish_kernel, dim3(ceil_div(total, 256)), dim3(256), 0, st, ws, ns, total, gate, dx,

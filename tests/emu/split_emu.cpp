@@ -228,6 +228,7 @@ int main() {
   dense_case<S96>(132, 100, 36, 2, 2);
   dense_case<S96>(128, 96, 16, 1, 3);
   dense_case<S64>(60, 68, 36, 2, 2);
+  dense_case<Tile<64, 128, 16, 2, 2>>(50, 132, 40, 2, 1);
   run_case<S96>(2, 75, 76, 96, 11, 4, 1);   // 17 pixels a row: a k-tile crosses a row's end, and a picture's
   run_case<S96>(3, 41, 45, 20, 7, 2, 3);    // runs of 24, slices that start inside a run and inside a row
   run_case<S128>(1, 22, 36, 132, 5, 1, 2);  // runs of 16, 32 pixels a row
