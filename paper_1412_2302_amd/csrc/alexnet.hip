@@ -88,6 +88,7 @@ struct Stage {
   bool wino;     // forward and weight gradient
   bool wino_bx;  // data gradient too
   float *wino_v, *wino_u, *wino_ub;
+  bool wino_pass;  // in training and inference passes too (see winograd_in_pass)
   float *wrun, *dwrun;  // run-mode copies of the weights and their gradient (null when not used)
   // bf16 handles: copies in bf16 (nearest even) of the stage's GEMM operands -- input, output gradient, and the
   // forward and backward-data weights with the reduction contiguous, wf16[g][o][(r,s,c)], wb16[g][c][(r,s,o)] --
@@ -166,6 +167,13 @@ struct alexnet {
 // ALEXNET_FLAG_DIRECT_CONV in the configuration keeps every stage on the direct implicit GEMM.
 static bool use_winograd(const alexnet_config_t& c, const ConvGeom& g) {
   if (c.precision != ALEXNET_PRECISION_FP32 || !wino_ok(g)) return false;
+// In a training or inference pass the layer also has to be large enough for the multiplies to matter: the transformed
+// form takes two or three launches more, each as long as a small direct product.  Whole passes on the full net, all
+// layers transformed | those direct that the line leaves so: one picture 232 | 147 us, 4 pictures (0.6 to 1.8 GFLOP a
+// layer) 263 | 205, 8 (1.2 to 3.6) 310 | 300; with the line at 4 GFLOP 16 pictures (2.4 to 7.2) 351 | 372 and training
+// on 24 (3.6 to 11) 1391 | 1420.  Training the small nets of the tests, batch 256: 682 | 603 and 590 | 513.
+constexpr double kWinoMinFlops = 2e9;
+static bool winograd_in_pass(const ConvGeom& g) { return 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k >= kWinoMinFlops; }
   if (c.flags & ALEXNET_FLAG_DIRECT_CONV) return false;
   return wino_gain(g) >= 1.5;
 }
@@ -287,6 +295,7 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     s.x16 = s.b16 ? a.take<uint16_t>(s.g.in_elems()) : s.r16 ? a.take<uint16_t>(conv_run16_x_elems(s.g)) : nullptr;
     s.x16_own = s.x16;
     s.dy16 = s.b16 ? a.take<uint16_t>(ae) : nullptr;
+    s.wino_pass = s.wino && winograd_in_pass(s.g);
     s.wf16 = s.b16 ? a.take<uint16_t>(s.g.w_elems()) : s.r16 ? a.take<uint16_t>(conv_run16_w_elems(s.g)) : nullptr;
     s.wb16 = s.b16 ? a.take<uint16_t>(s.g.w_elems()) : nullptr;
     s.wino = use_winograd(c, s.g) && s.w_off % 4 == 0 && s.b_off % 4 == 0;
@@ -384,8 +393,10 @@ static inline bool aligned256(const void* p) { return ((uintptr_t)p & 255) == 0;
 static uint32_t drop_thresh(float p) { return (uint32_t)floor((double)p * (double)(1 << 24)); }
 
 // ---- one convolution stage, by the F(4x4, 3x3) path when the stage has one and the tensors allow 16-byte access ----
-static bool wino_usable(const Stage& s, const void* a, const void* b, const void* c, const void* d = nullptr) {
-  return s.wino && aligned16(a) && aligned16(b) && aligned16(c) && aligned16(d);
+// in_pass: the call is part of a training or inference pass, not an operator of its own
+static bool wino_usable(const Stage& s, bool in_pass, const void* a, const void* b, const void* c,
+                        const void* d = nullptr) {
+  return (in_pass ? s.wino_pass : s.wino) && aligned16(a) && aligned16(b) && aligned16(c) && aligned16(d);
 }
 // bf16 handles, stages whose operands have bf16 copies: true when this call can use them
 static bool b16_usable(const Stage& s, const void* a, const void* b) { return s.b16 && aligned16(a) && aligned16(b); }
@@ -395,8 +406,9 @@ static bool b16_usable(const Stage& s, const void* a, const void* b) { return s.
 // x16_ready: s.x16 already holds the bf16 copy of x (the kernel that made x wrote it);
 // y16 (may be null): where to leave a bf16 copy of y for the stage that reads y next
 static int stage_fwd(alexnet* n, Stage& s, const float* x, const float* wf, const float* bias, int relu, float* y,
-                     bool taps_ready, hipStream_t st, bool x16_ready = false, uint16_t* y16 = nullptr) {
-  if (wino_usable(s, x, wf, y, bias)) {
+                     bool taps_ready, hipStream_t st, bool in_pass = false, bool x16_ready = false,
+                     uint16_t* y16 = nullptr) {
+  if (wino_usable(s, in_pass, x, wf, y, bias)) {
     if (!taps_ready) AX_TRY(launch_wino_filter(s.g, wf, s.wino_u, st));
     AX_TRY(launch_wino_fwd(s.g, x, s.wino_u, bias, relu, y, s.wino_v, n->wino_m, n->gemm_ws, st));
     return y16 ? launch_to_bf16(y, y16, (size_t)s.g.out_elems(), st) : ALEXNET_OK;
@@ -419,8 +431,8 @@ static int stage_fwd(alexnet* n, Stage& s, const float* x, const float* wf, cons
 // tail: put the end of a transformed stage's weight gradient off to launch_wgrad_tail() (see WgradTail)
 // dy16_ready: s.dy16 already holds the bf16 copy of dy (the kernel that made dy wrote it)
 static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* dy, float* dwf, bool have_v,
-                            hipStream_t st, WgradTail* tail = nullptr, bool dy16_ready = false) {
-  if (wino_usable(s, x, dy, dwf)) {
+                            hipStream_t st, bool in_pass = false, WgradTail* tail = nullptr, bool dy16_ready = false) {
+  if (wino_usable(s, in_pass, x, dy, dwf)) {
     if (!have_v) AX_TRY(launch_wino_input(s.g, x, s.wino_v, st));
     if (tail) return launch_wino_bwd_weight(s.g, s.wino_v, dy, dwf, n->wino_a, s.wino_du, s.wino_slices, st, tail);
     return launch_wino_bwd_weight(s.g, s.wino_v, dy, dwf, n->wino_a, n->wino_du, n->gemm_ws, st);
@@ -437,8 +449,8 @@ static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* d
 // dx16 (may be null): where to leave a bf16 copy of dx for the stage below
 static int stage_bwd_data(alexnet* n, Stage& s, const float* dy, const float* wf, const float* wb, float* wphase,
                           const float* gate, float* dx, bool taps_ready, bool yt_ready, hipStream_t st,
-                          uint16_t* dx16 = nullptr) {
-  if (s.wino_bx && wino_usable(s, dy, wb, dx, gate)) {
+                          bool in_pass = false, uint16_t* dx16 = nullptr) {
+  if (s.wino_bx && wino_usable(s, in_pass, dy, wb, dx, gate)) {
     if (!taps_ready) AX_TRY(launch_wino_filter_bwd(s.g, wb, s.wino_ub, st));
     if (!yt_ready) AX_TRY(launch_wino_output_grad(s.g, dy, n->wino_a, st));
     AX_TRY(launch_wino_bwd_data(s.g, n->wino_a, s.wino_ub, gate, dx, n->wino_m, n->gemm_ws, st));
@@ -483,12 +495,12 @@ static int run_forward(alexnet* n, const float* in, bool train, uint64_t step, h
     uint16_t* next16 = i + 1 == kStages ? n->flat16 : n->st[i + 1].b16 ? n->st[i + 1].x16 : nullptr;
     {
       ProfContext pc(s.lab[1]);
-      if ((s.wino || s.b16 || s.r16) && taps_ready && !waited) {
+      if ((s.wino_pass || s.b16 || s.r16) && taps_ready && !waited) {
         AX_HIP(hipStreamWaitEvent(st, taps_ready, 0));
         waited = true;
       }
       AX_TRY(stage_fwd(n, s, h, n->params + s.w_off, n->params + s.b_off, 1, s.act, taps_ready != nullptr, st,
-                       x16_ready, s.plain() ? next16 : nullptr));
+                       true, x16_ready, s.plain() ? next16 : nullptr));
     }
     x16_ready = s.plain() && next16 != nullptr;
     ProfContext pc(s.lab[0]);
@@ -630,7 +642,7 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     const float* x = i == 0 ? in : n->st[i - 1].out();
     {
       ProfContext pc(s.lab[2]);
-      AX_TRY(stage_bwd_weight(n, s, x, s.dact, n->grads + s.w_off, true, st, &wgrad_tail, dy16_ready));
+      AX_TRY(stage_bwd_weight(n, s, x, s.dact, n->grads + s.w_off, true, st, true, &wgrad_tail, dy16_ready));
       if (!bias_done)
         AX_TRY(colsum_batch_add(bias_sums, s.dact, s.g.P(), s.g.Cout, n->grads + s.b_off, n->colsum_ws, &bias_ws_used));
     }
@@ -646,7 +658,7 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       // a stage below without LRN or pool takes this data gradient as its output gradient as it is
       uint16_t* below16 = (prev.plain() && prev.b16) ? prev.dy16 : nullptr;
       AX_TRY(stage_bwd_data(n, s, s.dact, n->params + s.w_off, s.wb, s.wphase, prev.plain() ? prev.act : nullptr,
-                            prev.d_out, early_update, true, st, below16));
+                            prev.d_out, early_update, true, st, true, below16));
       dy16_ready = below16 != nullptr;
     } else {
       dy16_ready = false;
@@ -672,7 +684,7 @@ static int fork_forward_weights(alexnet* n, bool train, hipStream_t st) {
   for (int i = 0; i < kStages; ++i) {  // the convolutions' first: they are needed soonest
     Stage& s = n->st[i];
     ProfContext pc(s.lab[1]);
-    if (s.wino) AX_TRY(launch_wino_filter(s.g, n->params + s.w_off, s.wino_u, n->upd_stream));
+    if (s.wino_pass) AX_TRY(launch_wino_filter(s.g, n->params + s.w_off, s.wino_u, n->upd_stream));
     if (s.b16)
       AX_TRY(launch_to_bf16_transposed(n->params + s.w_off, s.wf16, s.g.groups, s.g.kf(), s.g.og(), n->upd_stream));
     if (s.r16)
@@ -693,7 +705,7 @@ static int fork_forward_weights(alexnet* n, bool train, hipStream_t st) {
 // 1, and 62 + 20 of 1250 us for the bf16 copies at batch 256.
 static int run_inference(alexnet* n, const float* in, uint16_t* in16, hipStream_t st) {
   bool convs = false;
-  for (int i = 0; i < kStages; ++i) convs = convs || n->st[i].wino || n->st[i].b16 || n->st[i].r16;
+  for (int i = 0; i < kStages; ++i) convs = convs || n->st[i].wino_pass || n->st[i].b16 || n->st[i].r16;
   const bool fc = fcw16_needed(n, false);
   if (convs || fc) AX_TRY(fork_forward_weights(n, false, st));
   return run_forward(n, in, false, 0, st, convs ? n->ev_u_done : nullptr, in16, fc ? n->ev_fcw_done : nullptr);
@@ -931,7 +943,7 @@ int alexnet_train_step(alexnet_t* n, int32_t slot, const int32_t* d_labels, uint
       Stage& s = n->st[i];
       ProfContext pc(s.lab[3]);
       AX_TRY(launch_conv_weight_wb(n->params + s.w_off, s.wb, s.g.Cout, s.g.cg(), s.g.k, s.g.groups, n->upd_stream));
-      if (s.wino_bx) AX_TRY(launch_wino_filter_bwd(s.g, s.wb, s.wino_ub, n->upd_stream));
+      if (s.wino_bx && s.wino_pass) AX_TRY(launch_wino_filter_bwd(s.g, s.wb, s.wino_ub, n->upd_stream));
       if (s.b16) AX_TRY(launch_to_bf16_transposed(s.wb, s.wb16, s.g.groups, s.g.kb(), s.g.cg(), n->upd_stream));
     }
     AX_HIP(hipEventRecord(n->ev_wb_done, n->upd_stream));
