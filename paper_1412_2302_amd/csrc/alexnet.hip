@@ -71,6 +71,7 @@ struct Profiler : ProfSink {
 static thread_local Profiler* g_profiler = nullptr;
 
 static const int kStages = 5, kFc = 3, kSlots = 3;  // slot 2 is the inference input
+static const int kUpdateForkStage = 3;  // stage of the backward pass beside which the dense-layer update starts
 static_assert(kMaxColsumJobs >= kStages + kFc, "one bias-gradient job per layer");
 static_assert(kMaxWgradJobs >= kStages, "one weight-gradient tail per stage");
 
@@ -87,8 +88,8 @@ struct Stage {
   // (kept for the weight gradient) and the transformed taps of the forward and backward-data passes
   bool wino;     // forward and weight gradient
   bool wino_bx;  // data gradient too
-  float *wino_v, *wino_u, *wino_ub;
   bool wino_pass;  // in training and inference passes too (see winograd_in_pass)
+  float *wino_v, *wino_u, *wino_ub;
   float *wrun, *dwrun;  // run-mode copies of the weights and their gradient (null when not used)
   // bf16 handles: copies in bf16 (nearest even) of the stage's GEMM operands -- input, output gradient, and the
   // forward and backward-data weights with the reduction contiguous, wf16[g][o][(r,s,c)], wb16[g][c][(r,s,o)] --
@@ -152,10 +153,6 @@ struct alexnet {
   int32_t* err_flag;
   size_t gemm_ws_floats, colsum_ws_floats_;
   int flat;  // flatten size feeding fc6
-  // the dense-layer update starts on the side stream in this stage of the backward pass, just before its
-  // weight gradient (behind its pooling adjoint) or just before its data gradient
-  int upd_fork_stage;
-  bool upd_fork_before_bx;
   // The dense layers hold 96 % of the parameters and finish their backward pass first: their update, which is
   // bound by memory bandwidth, runs on this stream under the convolution backward pass, which is not.
   hipStream_t upd_stream;
@@ -167,6 +164,9 @@ struct alexnet {
 // ALEXNET_FLAG_DIRECT_CONV in the configuration keeps every stage on the direct implicit GEMM.
 static bool use_winograd(const alexnet_config_t& c, const ConvGeom& g) {
   if (c.precision != ALEXNET_PRECISION_FP32 || !wino_ok(g)) return false;
+  if (c.flags & ALEXNET_FLAG_DIRECT_CONV) return false;
+  return wino_gain(g) >= 1.5;
+}
 // In a training or inference pass the layer also has to be large enough for the multiplies to matter: the transformed
 // form takes two or three launches more, each as long as a small direct product.  Whole passes on the full net, all
 // layers transformed | those direct that the line leaves so: one picture 232 | 147 us, 4 pictures (0.6 to 1.8 GFLOP a
@@ -174,9 +174,6 @@ static bool use_winograd(const alexnet_config_t& c, const ConvGeom& g) {
 // on 24 (3.6 to 11) 1391 | 1420.  Training the small nets of the tests, batch 256: 682 | 603 and 590 | 513.
 constexpr double kWinoMinFlops = 2e9;
 static bool winograd_in_pass(const ConvGeom& g) { return 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k >= kWinoMinFlops; }
-  if (c.flags & ALEXNET_FLAG_DIRECT_CONV) return false;
-  return wino_gain(g) >= 1.5;
-}
 
 static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
   const alexnet_config_t& c = *cfg;
@@ -240,7 +237,6 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
   }
   n->flat = C * H * W;
   int in = n->flat;
-  n->upd_fork_stage = kStages - 1;
   for (int j = 0; j < kFc; ++j) {
     if (c.fc[j] <= 0) {
       set_error("fc width must be positive");
@@ -295,11 +291,11 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     s.x16 = s.b16 ? a.take<uint16_t>(s.g.in_elems()) : s.r16 ? a.take<uint16_t>(conv_run16_x_elems(s.g)) : nullptr;
     s.x16_own = s.x16;
     s.dy16 = s.b16 ? a.take<uint16_t>(ae) : nullptr;
-    s.wino_pass = s.wino && winograd_in_pass(s.g);
     s.wf16 = s.b16 ? a.take<uint16_t>(s.g.w_elems()) : s.r16 ? a.take<uint16_t>(conv_run16_w_elems(s.g)) : nullptr;
     s.wb16 = s.b16 ? a.take<uint16_t>(s.g.w_elems()) : nullptr;
     s.wino = use_winograd(c, s.g) && s.w_off % 4 == 0 && s.b_off % 4 == 0;
     s.wino_bx = s.wino && wino_bwd_data_ok(s.g);
+    s.wino_pass = s.wino && winograd_in_pass(s.g);
     s.wino_v = s.wino ? a.take<float>(wino_v_floats(s.g)) : nullptr;
     s.wino_u = s.wino ? a.take<float>(wino_u_floats(s.g)) : nullptr;
     s.wino_ub = s.wino_bx ? a.take<float>(wino_u_floats(s.g)) : nullptr;
@@ -322,27 +318,6 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     if (s.lrn && s.pool) {
       cws = std::max(cws, lrn_part_floats(s.g.Cout));
       cws_batch += lrn_part_floats(s.g.Cout);
-    }
-  }
-  {
-    // The dense-layer update shares the chip best with a direct fp32 convolution GEMM of the backward pass, the
-    // largest one: the transformed layers move several times their activations and compete with it for
-    // bandwidth, and so do the bf16 products (those keep the fork behind the last stage, the earliest possible).
-    double best = -1;
-    n->upd_fork_before_bx = false;
-    for (int i = 0; i < kStages && c.precision == ALEXNET_PRECISION_FP32; ++i) {
-      const Stage& s = n->st[i];
-      const double fl = (double)s.g.P() * s.g.Cout * s.g.cg() * s.g.k * s.g.k;
-      if (!s.wino && fl > best) {
-        best = fl;
-        n->upd_fork_stage = i;
-        n->upd_fork_before_bx = false;
-      }
-      if (i > 0 && !s.wino_bx && fl > best) {
-        best = fl;
-        n->upd_fork_stage = i;
-        n->upd_fork_before_bx = s.wino;  // behind a transformed weight gradient, else before both GEMMs
-      }
     }
   }
   n->fc16 = c.precision == ALEXNET_PRECISION_BF16 && n->fc[0].w_off % 4 == 0;
@@ -553,10 +528,8 @@ static int update_range(alexnet* n, size_t begin, size_t end, hipStream_t st) {
   const alexnet_config_t& c = n->cfg;
   if (end <= begin) return ALEXNET_OK;
   const size_t decayed = n->n_weights > begin ? std::min(n->n_weights, end) - begin : 0;
-  // Beside the bf16 products, which lean on the memory system themselves, the update is held to one workgroup
-  // per CU: it still ends well inside the convolution backward pass, and the step is about 1.5 % shorter.
   return launch_sgd_update(n->params + begin, n->mom + begin, n->grads + begin, end - begin, decayed, c.lr, c.momentum,
-                           c.weight_decay, st, c.precision == ALEXNET_PRECISION_BF16 ? 256u : 0u);
+                           c.weight_decay, st, 256u);
 }
 
 // early_update: also start the update of the dense-layer weights on the side stream as soon as the dense
@@ -628,8 +601,13 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
                             c.lrn_alpha, c.lrn_beta, 1, st));
       dy16_ready = false;
     }
-    // Fork of the dense-layer update (see upd_fork_stage), never in front of this stage's pooling adjoint: that
-    // kernel is bound by bandwidth like the update and would be starved by it.
+    // Fork of the dense-layer update, behind this stage's pooling adjoint: that kernel is bound by bandwidth like the
+    // update and would be starved by it.  Early (the update is as long as the rest of a small batch's backward pass)
+    // and held to one workgroup per CU, it costs the products beside it about what it moves.  Step with the fork in
+    // front of conv5 / conv4 / conv3 / conv2's weight gradient: batch 37 1488 / 1493 / 1504 / 1532 us, batch 128 3297 /
+    // 3253 / 3256 / 3282, batch 256 5819 / 5771 / 5779 / 5823, bf16 batch 64 1503 / 1499 / 1490 / 1556, batch 256 within
+    // 1 %; at 1024 workgroups in front of conv1's weight gradient (the products bound it when they were fp32 MFMAs)
+    // 1591, 3278 us.
     auto fork_update = [&]() -> int {
       AX_HIP(hipEventRecord(n->ev_fc_done, st));
       AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_fc_done, 0));
@@ -637,8 +615,7 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       AX_HIP(hipEventRecord(n->ev_upd_done, n->upd_stream));
       return ALEXNET_OK;
     };
-    const bool fork_here = early_update && i == n->upd_fork_stage;
-    if (fork_here && !n->upd_fork_before_bx) AX_TRY(fork_update());
+    if (early_update && i == kUpdateForkStage) AX_TRY(fork_update());
     const float* x = i == 0 ? in : n->st[i - 1].out();
     {
       ProfContext pc(s.lab[2]);
@@ -646,7 +623,6 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       if (!bias_done)
         AX_TRY(colsum_batch_add(bias_sums, s.dact, s.g.P(), s.g.Cout, n->grads + s.b_off, n->colsum_ws, &bias_ws_used));
     }
-    if (fork_here && n->upd_fork_before_bx) AX_TRY(fork_update());
     if (i > 0) {
       ProfContext pc(s.lab[3]);
       Stage& prev = n->st[i - 1];
