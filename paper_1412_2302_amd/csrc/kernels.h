@@ -125,7 +125,7 @@ int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy
 // ---- bandwidth-bound kernels (ops.hip) --------------------------------------
 int launch_fill(float* p, size_t n, float v, hipStream_t st);
 // dst[i] = bf16(src[i]), round to nearest even
-int launch_to_bf16(const float* src, uint16_t* dst, size_t n, hipStream_t st);
+int launch_to_bf16(const float* src, uint16_t* dst, size_t n, hipStream_t st, unsigned max_blocks = 4096);
 // dst[g][n][k] = bf16(src[g][k][n]) for G matrices of K x N
 int launch_to_bf16_transposed(const float* src, uint16_t* dst, int G, int K, int N, hipStream_t st);
 // pictures with C < 4 channels as bf16 with four channels per pixel (the rest zero); the first layer's packed
