@@ -2,7 +2,7 @@
 // the fp32 MFMA core (gemm.h), and the dense layers on the same core.
 #include <algorithm>
 
-#include "gemm_split.h"
+#include "gemm16.h"
 #include "kernels.h"
 
 namespace ax {
@@ -246,6 +246,25 @@ struct ConvWeightGradTable16 {
         a, b, e, d.M, d.N, d.K, kchunk, ns, d.groups, st, (size_t)std::min(kchunk, d.K) * sizeof(PixelEntry));
   }
 };
+// 192 columns per group and enough 128 x 192 tiles for two workgroups per CU (at batch 64, 172 tiles, the 128 x 64 tile of
+// gemm_bf16.h is the faster one, 33 against 38 us; at batch 256, 676 tiles, 83 against 107)
+typedef Tile<128, 192, kBKbf, 2, 2> B192;
+static bool tile192_ok(const GemmDims& d) {
+  return d.N % 192 == 0 && d.N % 128 != 0 && (long)ceil_div(d.M, 128) * (d.N / 192) * d.groups >= 512;
+}
+template <int MODE, class Epi>
+static int launch_tile192(const Im2colParams& a, const DenseParams& b, const Epi& e, const GemmDims& d, hipStream_t st) {
+  typedef Unit16<Im2colKTap16<128, kBKbf, MODE>, 128, kBKbf> AL;
+  typedef Unit16<DenseKInner16<192, kBKbf>, 192, kBKbf> BL;
+  const int gx = ceil_div(d.M, 128), gy = d.N / 192;
+  const SplitGrid grid{make_fastdiv((uint32_t)gx), make_fastdiv((uint32_t)gy), make_fastdiv(1u)};
+  KernelScope ks("gemm_bf16", g_algo_flops > 0 ? g_algo_flops : 2.0 * d.M * d.N * (double)d.K * d.groups,
+                 gemm_bytes(d.M, d.N, d.K, d.groups), st);
+  hipLaunchKernelGGL((gemm16_kernel<B192, AL, BL, Epi>), dim3((unsigned)(gx * gy * d.groups)), dim3(kThreads), 0, st, a, b,
+                     e, d.M, d.N, d.K, d.K, grid);
+  AX_LAUNCH_CHECK();
+  return ALEXNET_OK;
+}
 template <class F, class Epi>
 static int by_tile_16(const GemmPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e, const GemmDims& d,
                       hipStream_t st) {
@@ -533,6 +552,8 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
     const DenseParams b = fwd_B16k(c, wf16);
     const GemmPlan p = fwd_plan(c, false, true, false, d.N % 128 == 0);  // 256-row tiles only without padded columns
     const bool tap = tap_ok(a, d, kBKbf);
+    if (tap && tile192_ok(d))
+      return launch_tile192<IM2COL_FWD>(a, b, EpiBiasAct{y, c.Cout, bias, relu, c.og(), 0, 0, y16}, d, st);
     if (p.ns == 1) {
       EpiBiasAct ep{y, c.Cout, bias, relu, c.og(), 0, 0, y16};
       if (tap) return by_tile_16<ConvGatherTap16<IM2COL_FWD>>(p, a, b, ep, d, st);
@@ -690,6 +711,8 @@ int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, co
     const DenseParams b = bwdd_B16k(c, wb16);
     const GemmPlan p = bwdd_plan(c, true, false, d.N % 128 == 0);
     const bool tap = tap_ok(a, d, kBKbf);
+    if (tap && tile192_ok(d))
+      return launch_tile192<IM2COL_T1>(a, b, EpiGate{dx, c.Cin, gate, c.cg(), 0, 0, dx16}, d, st);
     if (p.ns == 1) {
       EpiGate ep{dx, c.Cin, gate, c.cg(), 0, 0, dx16};
       if (tap) return by_tile_16<ConvGatherTap16<IM2COL_T1>>(p, a, b, ep, d, st);

@@ -22,7 +22,7 @@ inline void emu_fail(const char* what) {
 }
 }  // namespace ax
 
-#include "../../paper_1412_2302_amd/csrc/gemm_split.h"
+#include "../../paper_1412_2302_amd/csrc/gemm16.h"
 
 using namespace ax;
 
@@ -212,6 +212,75 @@ static void run_case(int B, int H, int W, int Cout, int k, int st, int ns) {
   delete[] x; delete[] w; delete[] dy;
 }
 
+// gemm16.h: a 3x3 layer over bf16 tensors, one tap per k-tile, LDS units of eight k
+template <class T, int MODE>
+static void conv16_case(int B, int H, int Cin, int Cout, int groups) {
+  ConvGeom c;
+  c.B = B; c.H = H; c.W = H + 1; c.Cin = Cin; c.Cout = Cout; c.k = 3; c.stride = 1; c.pad = 1; c.groups = groups;
+  c.Ho = c.H;
+  c.Wo = c.W;
+  typedef Unit16<Im2colKTap16<T::BM, T::BK, MODE>, T::BM, T::BK> AL;
+  typedef Unit16<DenseKInner16<T::BN, T::BK>, T::BN, T::BK> BL;
+  const bool fwd = MODE == IM2COL_FWD;
+  const GemmDims d = fwd ? fwd_dims(c) : bwdd_dims(c);
+  const long nx = fwd ? c.in_elems() : c.out_elems();
+  uint16_t *x = new uint16_t[nx], *w = new uint16_t[c.w_elems()];  // w: [g][column][(tap, channel)]
+  for (long i = 0; i < nx; ++i) x[i] = (uint16_t)bf16_bits(frand());
+  for (long i = 0; i < c.w_elems(); ++i) w[i] = (uint16_t)bf16_bits(frand());
+  const Im2colParams ap = im2col16(fwd ? fwd_A(c, nullptr) : bwdd_A(c, nullptr), x);
+  const DenseParams bp = fwd ? fwd_B16k(c, w) : bwdd_B16k(c, w);
+  const int Ctot = fwd ? Cin : Cout, Cg = Ctot / groups, ncol = fwd ? Cout : Cin;
+  std::vector<double> ref((size_t)d.M * ncol, 0.0);
+  std::vector<float> y((size_t)d.M * ncol, NAN);
+  for (int m = 0; m < d.M; ++m)
+    for (int g = 0; g < groups; ++g)
+      for (int n = 0; n < d.N; ++n)
+        for (int r = 0; r < 3; ++r)
+          for (int s = 0; s < 3; ++s) {
+            const int py = m / c.W % c.H, px = m % c.W, iy = fwd ? py - 1 + r : py + 1 - r, ix = fwd ? px - 1 + s : px + 1 - s;
+            if (iy < 0 || iy >= c.H || ix < 0 || ix >= c.W) continue;
+            for (int k = 0; k < Cg; ++k)
+              ref[(size_t)m * ncol + g * d.N + n] +=
+                  (double)bf_lo(x[(((long)(m / (c.H * c.W)) * c.H + iy) * c.W + ix) * Ctot + g * Cg + k]) *
+                  bf_lo(w[((long)g * d.N + n) * d.K + (r * 3 + s) * Cg + k]);
+          }
+  EpiGate e{y.data(), ncol, nullptr, d.N, 0, 0, nullptr};
+  std::vector<uint32_t> As(AL::UNITS * 4), Bs(BL::UNITS * 4);
+  for (int g = 0; g < groups; ++g)
+    for (int m0 = 0; m0 < d.M; m0 += T::BM)
+      for (int n0 = 0; n0 < d.N; n0 += T::BN) {
+        std::vector<float> acc((size_t)T::BM * T::BN, 0.f);
+        e.set_group(g, g);
+        for (int k0 = 0; k0 < d.K; k0 += T::BK) {
+          std::fill(As.begin(), As.end(), 0x7fc07fc0u);
+          std::fill(Bs.begin(), Bs.end(), 0x7fc07fc0u);
+          for (int tid = 0; tid < kThreads; ++tid) {
+            AL al(ap, g, tid, m0);
+            BL bl(bp, g, tid, n0);
+            float4 ra[AL::NL], rb[BL::NL];
+            plan_all(al, k0, d.K);
+            plan_all(bl, k0, d.K);
+            al.fetch(ra);
+            bl.fetch(rb);
+            split_store_all(al, As.data(), ra);
+            split_store_all(bl, Bs.data(), rb);
+          }
+          for (int i = 0; i < T::BM; ++i)
+            for (int j = 0; j < T::BN; ++j)
+              for (int o = 0; o < T::BK / 8; ++o)
+                for (int q = 0; q < 4; ++q) {
+                  const uint32_t a = As.at((o * AL::RP + i) * 4 + q), b = Bs.at((o * BL::RP + j) * 4 + q);
+                  acc[(size_t)i * T::BN + j] += bf_lo(a) * bf_lo(b) + bf_hi(a) * bf_hi(b);
+                }
+        }
+        for (int i = 0; i < T::BM && m0 + i < d.M; ++i)
+          for (int j = 0; j < T::BN && n0 + j < d.N; ++j) e.apply(m0 + i, n0 + j, acc[(size_t)i * T::BN + j]);
+      }
+  check(fwd ? "conv16" : "conv16 T", d.M, d.N, d.K, y, ref);
+  delete[] x;
+  delete[] w;
+}
+
 int main() {
   srand(4321);
   split_is_exact();
@@ -229,6 +298,8 @@ int main() {
   dense_case<S96>(128, 96, 16, 1, 3);
   dense_case<S64>(60, 68, 36, 2, 2);
   dense_case<Tile<64, 128, 16, 2, 2>>(50, 132, 40, 2, 1);
+  conv16_case<Tile<128, 192, 32, 2, 2>, IM2COL_FWD>(3, 7, 64, 384, 2);
+  conv16_case<Tile<128, 192, 32, 2, 2>, IM2COL_T1>(3, 7, 384, 128, 2);
   run_case<S96>(2, 75, 76, 96, 11, 4, 1);   // 17 pixels a row: a k-tile crosses a row's end, and a picture's
   run_case<S96>(3, 41, 45, 20, 7, 2, 3);    // runs of 24, slices that start inside a run and inside a row
   run_case<S128>(1, 22, 36, 132, 5, 1, 2);  // runs of 16, 32 pixels a row

@@ -46,3 +46,22 @@ def test_wide_range_of_magnitudes(lib):
     scale = sx * sw.T  # every output on its own scale
     assert rel_l2(y / scale, (x.astype(np.float64) @ w.T.astype(np.float64)) / scale) <= _bar(n)
     net.close()
+
+
+def test_bf16_products_with_192_columns(lib):
+    """The 128 x 192 bf16 tile (csrc/gemm16.h): 545 row tiles, the last one ragged, padding on every side, forward and
+    data gradient, against the fp32 products of the same bf16 values (fp32 sums on both sides)."""
+    wl = dict(S.MINI, name="wide", crop=33, raw=33,
+              conv=[(192, 1, 1, 0, 1, 0, 0), (192, 3, 1, 1, 1, 0, 0)] + [(8, 1, 1, 0, 1, 0, 0)] * 3, fc=[8, 8, 4])
+    batch = 64
+    bf, ref = lib.AlexNet(wl, batch, precision=1), lib.AlexNet(wl, batch, flags=lib.FLAG_DIRECT_CONV)
+
+    def values(shape, seed):  # bf16 holds these exactly
+        v = S.make_normal(shape, seed)
+        return (v.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)
+    x, w = values((batch, 192, 33, 33), 1), values((192, 192, 3, 3), 2)
+    dy, b = values((batch, 192, 33, 33), 3), np.zeros(192, np.float32)
+    for op in (lambda n: n.conv_forward(2, x, w, b), lambda n: n.conv_backward_data(2, dy, w, x.shape)):
+        assert rel_l2(op(bf).cpu().numpy(), op(ref).cpu().numpy()) <= _bar(9 * 192)
+    bf.close()
+    ref.close()
