@@ -405,11 +405,11 @@ static GemmPlan split_run_fwd_plan(const ConvGeom& c) {
   return plan_split((int)c.P(), c.Cout, run_k(c), 1, (double)c.out_elems() * 4, 8);
 }
 static GemmPlan split_run_bwdw_plan(const ConvGeom& c) {
-  return plan_split(run_k(c), c.Cout, (int)c.P(), 1, (double)run_w_elems(c) * 4, 256);
+  return plan_split(c.k * c.k * c.Cin, c.Cout, (int)c.P(), 1, (double)c.w_elems() * 4, 256);
 }
 // A of either product by tile, B = packed weights or output gradient
-template <template <int> class ALT, class Epi>
-static int by_tile_run(const GemmPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e, int M, int N, int K,
+template <template <int> class ALT, class AP, class Epi>
+static int by_tile_run(const GemmPlan& p, const AP& a, const DenseParams& b, const Epi& e, int M, int N, int K,
                        hipStream_t st) {
 #define AX_SPLIT(T) \
   return launch_tile_split<T, ALT<T::BM>, SplitRowInner<T::BN>, Epi>(a, b, e, M, N, K, p.kchunk, p.ns, 1, st)
@@ -495,7 +495,7 @@ size_t conv_bwd_weight_ws_floats(const ConvGeom& c) {
     const int ns = split_bwdw_plan(c, &swapped).ns;
     if (ns > 1) n = std::max(n, (size_t)ns * c.w_elems());
   }
-  if (split_run_ok(c)) n = std::max(n, (size_t)split_run_bwdw_plan(c).ns * run_w_elems(c));
+  if (split_run_ok(c)) n = std::max(n, (size_t)split_run_bwdw_plan(c).ns * c.w_elems());
   return n;
 }
 
@@ -785,9 +785,17 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
   }
   const bool bf = g_bf16 && av && bv;
   const Im2colParams a = run ? run_A(c, x) : bwdw_A(c, x);
-  const bool split = !g_bf16 && run && split_run_ok(c);
-  bool table = !split && av && bv && table_ok(a, d) && (!bf || d.K % kBKbf == 0);
-  GemmPlan p = split ? split_run_bwdw_plan(c) : bwdw_plan(c, run, bf, table);
+  if (!g_bf16 && run && split_run_ok(c)) {  // compact rows, see SplitRunT
+    const GemmPlan p = split_run_bwdw_plan(c);
+    const int kc = c.k * c.Cin;
+    const long slab = (long)c.k * kc * c.Cout;
+    EpiSlab ep{p.ns > 1 ? ws : dwrun, slab, c.Cout, nullptr};
+    AX_TRY((by_tile_run<SplitRunT>(p, run_t_params(a, kc), bwdw_B(c, dy), ep, c.k * kc, c.Cout, d.K, st)));
+    if (defer_ns) *defer_ns = 1;
+    return launch_reduce_slabs_unpack(p.ns > 1 ? ws : dwrun, p.ns, slab, c.k, kc / 4 * 4, kc, c.Cout, dwf, st);
+  }
+  bool table = av && bv && table_ok(a, d) && (!bf || d.K % kBKbf == 0);
+  GemmPlan p = bwdw_plan(c, run, bf, table);
   if (table && p.kchunk > kMaxTableK) {  // no split count within reach keeps the k range inside the table
     table = false;
     p = bwdw_plan(c, run, bf, false);
@@ -796,9 +804,7 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
   float* out = run ? dwrun : dwf;
   EpiSlab ep{p.ns > 1 ? ws : out, slab, d.N, nullptr};
   const bool s16 = bf && table && !run && x16 && dy16 && conv_bf16_stored_ok(c) && aligned16(x16) && aligned16(dy16);
-  if (split)
-    AX_TRY((by_tile_run<SplitRunT>(p, a, bwdw_B(c, dy), ep, d.M, d.N, d.K, st)));
-  else if (s16)
+  if (s16)
     AX_TRY((by_tile_bf<ConvWeightGradTable16>(p, im2col16(a, x16), dense16(bwdw_B(c, dy), dy16), ep, d, st)));
   else if (bf && table)
     AX_TRY((by_tile_bf<ConvWeightGradTableBf>(p, a, bwdw_B(c, dy), ep, d, st)));
@@ -814,7 +820,7 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
   }
   if (defer_ns) *defer_ns = 1;
   if (run && p.ns > 1)  // slices of the padded layout straight to the packed one
-    return launch_reduce_slabs_unpack(ws, p.ns, slab, run_len(c), c.k * c.Cin, c.Cout, dwf, st);
+    return launch_reduce_slabs_unpack(ws, p.ns, slab, c.k, run_len(c), c.k * c.Cin, c.Cout, dwf, st);
   if (p.ns > 1) AX_TRY(launch_reduce_slabs(ws, p.ns, slab, d.groups, out, st));
   if (run) AX_TRY(launch_conv_run_unpack(c, dwrun, dwf, st));
   return ALEXNET_OK;
@@ -1052,9 +1058,10 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
     if (bf) return launch_tile_bf<B128, BfDenseK, BfDenseK, Epi>(a, b, ep, B, out, in, kchunk, ns, 1, st);
     return launch_dense<SplitKInner, SplitKInner, DenseKInner, DenseKInner>(vec, p, a, b, ep, B, out, in, st);
   };
-  // (the mask's hash, 64 values per lane one after the other, costs a full tile more than the second launch: 128 rows
-  // 256 wide 456 against 434 us per small training step)
-  if (ns == 1 && (!act.dropout || B <= 32)) return product(EpiFcAct{y, out, act, y16});
+  // A full tile that finishes itself works through 32 to 64 values per lane, one after the other: the mask's hash costs
+  // more there than a second launch (128 rows 256 wide: 456 against 434 us per small training step), and so does the
+  // gate in the bf16 kernels, whose blocks are not transposed (438 against 434).
+  if (ns == 1 && (B <= 32 || (!bf && !act.dropout))) return product(EpiFcAct{y, out, act, y16});
   AX_TRY(product(EpiSlab{ws, (long)B * out, out, nullptr}));
   const size_t total = (size_t)B * out;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1), st);
@@ -1083,7 +1090,7 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
     if (bf) return launch_tile_bf<B128, BfDenseK, BfDenseR, Epi>(a, b, ep, B, in, out, kchunk, ns, 1, st);
     return launch_dense<SplitKInner, SplitRowInner, DenseKInner, DenseRowInner>(vec, p, a, b, ep, B, in, out, st);
   };
-  if (ns == 1) return product(EpiGate{dx, in, gate, in, 0, 0, dx16});
+  if (ns == 1 && (B <= 32 || !bf)) return product(EpiGate{dx, in, gate, in, 0, 0, dx16});  // see launch_fc_fwd
   AX_TRY(product(EpiSlab{ws, (long)B * in, in, nullptr}));
   const size_t total = (size_t)B * in;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1 + (gate ? 1 : 0)), st);

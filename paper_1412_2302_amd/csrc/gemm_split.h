@@ -248,42 +248,77 @@ struct SplitRun {
     split_store_quad<RP>(lds, (tid + s * kThreads) / QK, kq, r[s]);
   }
 };
-// Its transpose (weight gradient): row = (kernel row, position in its run), k = output pixel.  A thread owns one row
-// quad and a pair of pixels that moves on by one k-tile at a time; rows of at least one k-tile of pixels (OW >= 16), so
-// that a step passes at most one row's end.
+// Its transpose (weight gradient): k = output pixel, row = one of the k*C floats of a kernel row.  The whole quads of
+// every kernel row come first and the floats left over at the runs' ends behind them, (3 mod 4 channels of the last
+// tap), as quads gathered one float at a time: 11 rows of 33 floats are 363 rows, three tiles of 128, where runs padded
+// to 36 are 396 and need a fourth tile for 12 of them.
+struct RunTParams {
+  Im2colParams g;     // run mode
+  int quads, left;    // whole quads and floats left over per kernel row
+  FastDiv d_quads, d_left;
+};
+inline RunTParams run_t_params(const Im2colParams& g, int floats) {
+  return RunTParams{g, floats / 4, floats % 4, make_fastdiv((uint32_t)(floats / 4)), make_fastdiv((uint32_t)(floats % 4))};
+}
+// A thread owns one row quad and a pair of pixels that moves on by one k-tile at a time; rows of at least one k-tile of
+// pixels (OW >= 16), so that a step passes at most one row's end.
 template <int ROWS>
 struct SplitRunT {
   typedef SplitRowStore<ROWS> St;
   static constexpr int QR = ROWS / 4, NU = QR * (kBKs / 2), NL = 2, NS = 2;
-  static_assert(NU == kThreads, "one unit per thread");
+  static_assert(NU <= kThreads, "at most one unit per thread");
   static constexpr int RP = St::RP, UNITS = kPlanes * 2 * RP;
   static AX_HD int pos(int row) { return St::pos(row); }
   static constexpr int block_units(int t) { return 8 * t; }
-  typedef Im2colParams Params;
+  typedef RunTParams Params;
   BufView v;
   int tid, OW, OH, x, y;                 // (y, x): the first pixel of the pair
-  uint32_t off, outside, pix, row, img;  // byte steps: to the next pixel, past a row's end, past a picture's end
+  uint32_t off, pix, row, img;           // byte offset of its origin; steps to the next pixel, past a row's, a picture's end
+  uint32_t tap[4];                       // of the quad's rows from a pixel's origin, kOob for a row past the end
+  bool gather;                           // rows that do not lie side by side
   AX_HD SplitRunT(const Params& a, int /*g*/, int tid_, int row0, int kbeg)
-      : v(make_view(a.x, a.bytes)), tid(tid_), OW(a.OW), OH(a.OH) {
-    const int m = row0 + 4 * St::quad(tid);
-    const int r = (int)fdiv((uint32_t)m, a.d_cg), j = m - r * a.Cg;
-    outside = r < a.kh ? 0u : kOob;
-    const PixCoord c = decode_pixel(kbeg + 2 * St::pair(tid), a);
+      : v(make_view(a.g.x, a.g.bytes)), tid(tid_), OW(a.g.OW), OH(a.g.OH) {
+    const Im2colParams& g = a.g;
+    const int q = row0 / 4 + St::quad(tid), rest = 4 * (q - g.kh * a.quads);
+    gather = rest >= 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      int r, j;
+      if (gather) {
+        r = a.left ? (int)fdiv((uint32_t)(rest + e), a.d_left) : g.kh;
+        j = 4 * a.quads + (rest + e - r * a.left);
+      } else {
+        r = (int)fdiv((uint32_t)q, a.d_quads);
+        j = 4 * (q - r * a.quads) + e;
+      }
+      tap[e] = r < g.kh ? (uint32_t)(r * g.W + j) * 4u : kOob;
+    }
+    const PixCoord c = decode_pixel(kbeg + 2 * St::pair(tid), g);
     y = c.y;
     x = c.x;
-    off = row_base<IM2COL_FWD>(a, c.n, c.y * a.stride + r, c.x * a.stride_x + j, 0);
-    pix = (uint32_t)a.stride_x * 4u;
-    row = (uint32_t)(a.stride * a.W - a.OW * a.stride_x) * 4u;
-    img = (uint32_t)((a.H - a.OH * a.stride) * a.W) * 4u;
+    off = row_base<IM2COL_FWD>(g, c.n, c.y * g.stride, c.x * g.stride_x, 0);
+    pix = (uint32_t)g.stride_x * 4u;
+    row = (uint32_t)(g.stride * g.W - g.OW * g.stride_x) * 4u;
+    img = (uint32_t)((g.H - g.OH * g.stride) * g.W) * 4u;
   }
   // off of a pixel px of row py that may lie past the row's end
   AX_HD uint32_t wrap(uint32_t o, int px, int py) const {
     return px < OW ? o : o + row + (py + 1 < OH ? 0u : img);
   }
+  AX_HD void load(float4& r, uint32_t o, bool in) const {
+    if (gather) {  // o + kOob stays outside
+      r.x = buf_ld1(v, in ? o + tap[0] : kOob);
+      r.y = buf_ld1(v, in ? o + tap[1] : kOob);
+      r.z = buf_ld1(v, in ? o + tap[2] : kOob);
+      r.w = buf_ld1(v, in ? o + tap[3] : kOob);
+    } else {
+      r = buf_ld4(v, in ? o + tap[0] : kOob);
+    }
+  }
   AX_HD void fetch(float4* r, int kleft) {
     const int k = 2 * St::pair(tid);
-    r[0] = buf_ld4(v, k < kleft ? off | outside : kOob);
-    r[1] = buf_ld4(v, k + 1 < kleft ? wrap(off + pix, x + 1, y) | outside : kOob);
+    load(r[0], off, k < kleft);
+    load(r[1], wrap(off + pix, x + 1, y), k + 1 < kleft);
     off = wrap(off + kBKs * pix, x + kBKs, y);
     x += kBKs;
     if (x >= OW) {
@@ -292,7 +327,7 @@ struct SplitRunT {
     }
   }
   AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
-    St::store_half(lds, St::quad(tid), St::pair(tid), s & 1, r[0], r[1]);
+    if (NU == kThreads || tid < NU) St::store_half(lds, St::quad(tid), St::pair(tid), s & 1, r[0], r[1]);
   }
 };
 

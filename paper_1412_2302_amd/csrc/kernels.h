@@ -193,8 +193,9 @@ int colsum_batch_add(ColsumBatch& b, const float* m, long rows, int cols, float*
 size_t colsum_batch_ws_floats(long rows, int cols);
 int launch_colsum_batch(const ColsumBatch& b, hipStream_t st);
 int launch_reduce_slabs(const float* ws, int nsplit, long slab, int groups, float* out, hipStream_t st);
-// one result of k*run rows by cout columns, rows (r, j >= kc) dropped and the rest packed to r*kc + j
-int launch_reduce_slabs_unpack(const float* ws, int nsplit, long slab, int run, int kc, int cout, float* out,
+// one result by cout columns: the first k*head rows are (r, j < head), the rest (r, j = head .. kc - 1); packed to rows
+// r*kc + j, rows with j >= kc (padded runs: head > kc) dropped
+int launch_reduce_slabs_unpack(const float* ws, int nsplit, long slab, int k, int head, int kc, int cout, float* out,
                                hipStream_t st);
 // max_blocks: upper limit of the grid (0: the default, four workgroups per CU)
 int launch_sgd_update(float* w, float* v, const float* g, size_t n, size_t n_decay, float lr, float mu, float wd,

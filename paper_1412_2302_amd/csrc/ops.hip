@@ -1319,7 +1319,7 @@ reduce_slabs_kernel(const float* __restrict__ ws, int nsplit, size_t slab, int g
 // The same for one result whose rows are runs padded to `run` entries (run mode of the first layer's weight
 // gradient): row (r, j) goes to row r*kc + j of the packed layout, the padding rows j >= kc nowhere.
 __global__ void __launch_bounds__(256)
-reduce_slabs_unpack_kernel(const float* __restrict__ ws, int nsplit, size_t slab, int run, int kc, int cout,
+reduce_slabs_unpack_kernel(const float* __restrict__ ws, int nsplit, size_t slab, int k, int head, int kc, int cout,
                            float* __restrict__ out) {
   __shared__ float sh[4][64];
   const int el = threadIdx.x & 63, part = threadIdx.x >> 6;
@@ -1334,16 +1334,22 @@ reduce_slabs_unpack_kernel(const float* __restrict__ ws, int nsplit, size_t slab
   __syncthreads();
   if (part == 0 && i < slab) {
     const size_t row = i / cout;
-    const int o = (int)(i - row * cout), r = (int)(row / run), j = (int)(row - (size_t)r * run);
+    const int o = (int)(i - row * cout), left = kc - head, m = (int)row;
+    int r = m / head, j = m - r * head;
+    if (r >= k) {  // the floats behind the heads
+      const int e = m - k * head;
+      r = e / left;
+      j = head + e - r * left;
+    }
     if (j < kc) out[((size_t)r * kc + j) * cout + o] = (sh[0][el] + sh[1][el]) + (sh[2][el] + sh[3][el]);
   }
 }
-int launch_reduce_slabs_unpack(const float* ws, int nsplit, long slab, int run, int kc, int cout, float* out,
+int launch_reduce_slabs_unpack(const float* ws, int nsplit, long slab, int k, int head, int kc, int cout, float* out,
                                hipStream_t st) {
   if (!slab) return ALEXNET_OK;
   KernelScope ks("reduce_slabs", 0, (double)slab * 4.0 * (nsplit + 1), st);
   hipLaunchKernelGGL(reduce_slabs_unpack_kernel, dim3(grid_for((size_t)slab, 64)), dim3(256), 0, st, ws, nsplit,
-                     (size_t)slab, run, kc, cout, out);
+                     (size_t)slab, k, head, kc, cout, out);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }

@@ -198,16 +198,17 @@ static void run_case(int B, int H, int W, int Cout, int k, int st, int ns) {
       for (long i = 0; i < c.out_elems(); ++i) y[i] += ws[s * c.out_elems() + i];
     check("run fwd", P, Cout, K, y, y_ref);
   }
-  {
-    std::vector<float> ws((size_t)ns * run_w_elems(c), NAN), dw(run_w_elems(c), 0.f);
-    EpiSlab e{ws.data(), run_w_elems(c), Cout, nullptr};
-    emu_split<T, SplitRunT<T::BM>, SplitRowInner<T::BN>, EpiSlab>(run_A(c, x), bwdw_B(c, dy), e, K, Cout, P, chunk(P), ns, 1);
-    for (int s = 0; s < ns; ++s)
-      for (long i = 0; i < run_w_elems(c); ++i) dw[i] += ws[s * run_w_elems(c) + i];
-    for (int r = 0; r < k; ++r)  // the padding of a run reads the pixels behind it; nobody uses its gradient
-      for (int j = kc; j < run; ++j)
-        for (int o = 0; o < Cout; ++o) dw[((long)r * run + j) * Cout + o] = 0.f;
-    check("run bwd_w", K, Cout, P, dw, dw_ref);
+  {  // rows of the weight gradient: whole quads of every kernel row, then the floats left over
+    const int M = k * kc, head = kc / 4 * 4, left = kc - head;
+    std::vector<float> ws((size_t)ns * M * Cout, NAN), dw(run_w_elems(c), 0.f);
+    EpiSlab e{ws.data(), (long)M * Cout, Cout, nullptr};
+    emu_split<T, SplitRunT<T::BM>, SplitRowInner<T::BN>, EpiSlab>(run_t_params(run_A(c, x), kc), bwdw_B(c, dy), e, M, Cout, P, chunk(P), ns, 1);
+    for (int m = 0; m < M; ++m) {
+      const int r = m < k * head ? m / head : (m - k * head) / left, j = m < k * head ? m % head : head + (m - k * head) % left;
+      for (int s = 0; s < ns; ++s)
+        for (int o = 0; o < Cout; ++o) dw[((long)r * run + j) * Cout + o] += ws[((long)s * M + m) * Cout + o];
+    }
+    check("run bwd_w", M, Cout, P, dw, dw_ref);
   }
   delete[] x; delete[] w; delete[] dy;
 }
