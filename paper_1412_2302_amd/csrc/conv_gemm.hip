@@ -69,7 +69,9 @@ static GemmPlan plan_gemm(int M, int N, int K, int groups, double out_bytes, int
       if (max_chunk && per * bk > max_chunk) continue;  // the workgroup's k range must fit its pixel table
       const double rounds = (double)ceil_div(tiles * s, 256);
       double t = rounds * t_tile * per / ktiles + 4e-6;
-      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + 6e-6;
+      // a second launch of a few microseconds (6 here: the small nets' 15 us products stay whole, 357 against 346 us a
+      // step)
+      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + 4e-6;
       if (t < best_t * 0.98) {  // prefer earlier (larger, unsplit) candidates unless clearly better
         best_t = t;
         best = GemmPlan{to.bm, to.bn, s, per * bk};
@@ -355,6 +357,7 @@ static GemmPlan plan_split(int M, int N, int K, int groups, double out_bytes, in
       if (ceil_div(ktiles, per) != s) continue;
       if (s > 1 && per * kBKs < 96) break;
       const int c = ceil_div(tiles * s, 256), most = to.bn > 128 ? 2 : 3;  // workgroups per unit: of the launch, at once
+      if (s > 1 && c > 4 * most) break;  // more slices only add traffic
       const double fill = c >= most ? 1.0 : c == 2 ? 0.85 : 0.5;
       double t = c * t_tile * per / ktiles / fill + 4e-6;
       if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + 6e-6;
@@ -1059,9 +1062,9 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
     return launch_dense<SplitKInner, SplitKInner, DenseKInner, DenseKInner>(vec, p, a, b, ep, B, out, in, st);
   };
   // A full tile that finishes itself works through 32 to 64 values per lane, one after the other: the mask's hash costs
-  // more there than a second launch (128 rows 256 wide: 456 against 434 us per small training step), and so does the
-  // gate in the bf16 kernels, whose blocks are not transposed (438 against 434).
-  if (ns == 1 && (B <= 32 || (!bf && !act.dropout))) return product(EpiFcAct{y, out, act, y16});
+  // more there than a second launch (128 rows 256 wide: 456 against 434 us per small training step), and so do mask and
+  // gate in the bf16 kernels, whose blocks are not transposed (438 against 434; 30 rows 200 wide 363 against 357).
+  if (ns == 1 && !bf && (B <= 32 || !act.dropout)) return product(EpiFcAct{y, out, act, y16});
   AX_TRY(product(EpiSlab{ws, (long)B * out, out, nullptr}));
   const size_t total = (size_t)B * out;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1), st);
@@ -1090,7 +1093,7 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
     if (bf) return launch_tile_bf<B128, BfDenseK, BfDenseR, Epi>(a, b, ep, B, in, out, kchunk, ns, 1, st);
     return launch_dense<SplitKInner, SplitRowInner, DenseKInner, DenseRowInner>(vec, p, a, b, ep, B, in, out, st);
   };
-  if (ns == 1 && (B <= 32 || !bf)) return product(EpiGate{dx, in, gate, in, 0, 0, dx16});  // see launch_fc_fwd
+  if (ns == 1 && !bf) return product(EpiGate{dx, in, gate, in, 0, 0, dx16});  // see launch_fc_fwd
   AX_TRY(product(EpiSlab{ws, (long)B * in, in, nullptr}));
   const size_t total = (size_t)B * in;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1 + (gate ? 1 : 0)), st);
