@@ -71,7 +71,6 @@ struct Profiler : ProfSink {
 static thread_local Profiler* g_profiler = nullptr;
 
 static const int kStages = 5, kFc = 3, kSlots = 3;  // slot 2 is the inference input
-static const int kUpdateForkStage = 3;  // stage of the backward pass beside which the dense-layer update starts
 static_assert(kMaxColsumJobs >= kStages + kFc, "one bias-gradient job per layer");
 static_assert(kMaxWgradJobs >= kStages, "one weight-gradient tail per stage");
 
@@ -153,6 +152,8 @@ struct alexnet {
   int32_t* err_flag;
   size_t gemm_ws_floats, colsum_ws_floats_;
   int flat;  // flatten size feeding fc6
+  int upd_fork_stage;   // stage of the backward pass beside which the dense-layer update starts on the side stream
+  bool fork_inference;  // inference passes make the weights' forms on the side stream
   // The dense layers hold 96 % of the parameters and finish their backward pass first: their update, which is
   // bound by memory bandwidth, runs on this stream under the convolution backward pass, which is not.
   hipStream_t upd_stream;
@@ -173,6 +174,11 @@ static bool use_winograd(const alexnet_config_t& c, const ConvGeom& g) {
 // layer) 263 | 205, 8 (1.2 to 3.6) 310 | 300; with the line at 4 GFLOP 16 pictures (2.4 to 7.2) 351 | 372 and training
 // on 24 (3.6 to 11) 1391 | 1420.  Training the small nets of the tests, batch 256: 682 | 603 and 590 | 513.
 constexpr double kWinoMinFlops = 2e9;
+// Forward flops of the convolutions from which (fp32) the dense-layer update starts a stage later -- batch 37 of the full
+// net, 49 GFLOP, either way alike, 128, 170 GFLOP, 0.8 % faster -- and (bf16) an inference pass makes its weight copies on
+// the side stream: its first layer needs one of them, and with little to hide them under the two streams' meeting costs
+// more (batch 16 341 against 320 us, the small nets 147 and 166 against 109 and 134; batch 100, 133 GFLOP, 694 against 713).
+constexpr double kForkFlops = 100e9;
 static bool winograd_in_pass(const ConvGeom& g) { return 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k >= kWinoMinFlops; }
 
 static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
@@ -320,6 +326,14 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
       cws_batch += lrn_part_floats(s.g.Cout);
     }
   }
+  double conv_flops = 0;
+  for (int i = 0; i < kStages; ++i) {
+    const ConvGeom& g = n->st[i].g;
+    conv_flops += 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k;
+  }
+  const bool fp32 = c.precision == ALEXNET_PRECISION_FP32, large = conv_flops >= kForkFlops;
+  n->upd_fork_stage = fp32 && large ? kStages - 2 : kStages - 1;
+  n->fork_inference = fp32 || large;
   n->fc16 = c.precision == ALEXNET_PRECISION_BF16 && n->fc[0].w_off % 4 == 0;
   for (int j = 0; j < kFc; ++j) n->fc16 = n->fc16 && fc_bf16_stored_ok(n->fc[j].in, n->fc[j].out);
   n->fcw16 = n->fc16 ? a.take<uint16_t>(n->n_weights - n->fc[0].w_off) : nullptr;
@@ -610,7 +624,8 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     // front of conv5 / conv4 / conv3 / conv2's weight gradient: batch 37 1488 / 1493 / 1504 / 1532 us, batch 128 3297 /
     // 3253 / 3256 / 3282, batch 256 5819 / 5771 / 5779 / 5823, bf16 batch 64 1503 / 1499 / 1490 / 1556, batch 256 within
     // 1 %; at 1024 workgroups in front of conv1's weight gradient (the products bound it when they were fp32 MFMAs)
-    // 1591, 3278 us.
+    // 1591, 3278 us.  So behind the last stage where the rest of the pass is short (bf16; see kForkFlops), one stage
+    // later otherwise.
     auto fork_update = [&]() -> int {
       AX_HIP(hipEventRecord(n->ev_fc_done, st));
       AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_fc_done, 0));
@@ -618,7 +633,7 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       AX_HIP(hipEventRecord(n->ev_upd_done, n->upd_stream));
       return ALEXNET_OK;
     };
-    if (early_update && i == kUpdateForkStage) AX_TRY(fork_update());
+    if (early_update && i == n->upd_fork_stage) AX_TRY(fork_update());
     const float* x = i == 0 ? in : n->st[i - 1].out();
     {
       ProfContext pc(s.lab[2]);
@@ -683,6 +698,7 @@ static int fork_forward_weights(alexnet* n, bool train, hipStream_t st) {
 // caller's graph capture).  Before, they were made in front of each layer: 29 of 604 us at batch 50, 25 of 230 at batch
 // 1, and 62 + 20 of 1250 us for the bf16 copies at batch 256.
 static int run_inference(alexnet* n, const float* in, uint16_t* in16, hipStream_t st) {
+  if (!n->fork_inference) return run_forward(n, in, false, 0, st, nullptr, in16);
   bool convs = false;
   for (int i = 0; i < kStages; ++i) convs = convs || n->st[i].wino_pass || n->st[i].b16 || n->st[i].r16;
   const bool fc = fcw16_needed(n, false);
