@@ -98,7 +98,9 @@ typedef struct {
  * channel counts per group that are multiples of 4 (conv2-5 of Section 2's
  * network) are computed through F(4x4, 3x3) tile transforms (a 5x5 kernel as
  * four 3x3 sub-kernels): the same result up to rounding order with 2.6x fewer
- * multiplications, at the price of more workspace.  ALEXNET_FLAG_DIRECT_CONV
+ * multiplications, at the price of more workspace.  (Training and inference
+ * passes run layers under 2 GFLOP directly all the same: extra launches cost
+ * more there.)  ALEXNET_FLAG_DIRECT_CONV
  * in cfg->flags keeps those stages on the direct implicit GEMM; the flag is
  * part of the configuration, so alexnet_query and alexnet_create size and lay
  * out the workspace for the same choice. */
