@@ -904,8 +904,10 @@ __global__ void fc_bwd_finish_kernel(const float* __restrict__ ws, int nsplit, s
 // weights in flight per lane; the rows of x pass through LDS, shared by the workgroup's four waves.  The sums stay in
 // fp32: one chain of in/64 products per lane, then a tree over the lanes.  BF: both operands rounded to bf16 first, as
 // the bf16 products have them (a handle's bf16 copy of the weights, twice the traffic of reading them, is not needed).
-// 4096 x 9216, one row: 55 + 5 us (slices, finish) -> see the dispatch rule in launch_fc_fwd.
-constexpr int kFcRows = 8;
+// fc6 + fc7 of one picture: 111 + 9 us (products in slices, finish) -> 37, 5.9 TB/s.  The line is at four rows: with
+// more the multiplies bound it.  One-pass inference, tiles | here: 1 row 163 | 143 us, 2 178 | 165, 4 209 | 206, 6 252 |
+// 267, 8 279 | 298; bf16 handles, which need no copy of the weights here, 4 241 | 229, 8 264 | 289.
+constexpr int kFcRows = 4;
 template <int BB, bool BF>
 __global__ void __launch_bounds__(256)
 fc_rows_kernel(const float* __restrict__ x, const float* __restrict__ w, int B, int in, int out, FcAct act,
@@ -991,8 +993,7 @@ static int launch_fc_rows(int B, int in, int out, const float* x, const float* w
   const dim3 grid(ceil_div(out, 8)), block(256);
   if (B <= 1) hipLaunchKernelGGL((fc_rows_kernel<1, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
   else if (B <= 2) hipLaunchKernelGGL((fc_rows_kernel<2, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
-  else if (B <= 4) hipLaunchKernelGGL((fc_rows_kernel<4, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
-  else hipLaunchKernelGGL((fc_rows_kernel<8, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
+  else hipLaunchKernelGGL((fc_rows_kernel<kFcRows, BF>), grid, block, 0, st, x, w, B, in, out, act, y, y16);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }

@@ -14,13 +14,13 @@
 // Why: v_mfma_f32_32x32x16_bf16 does 1024 flop per SIMD and clock, v_mfma_f32_32x32x2_f32 does 64; six of the
 // former are 16/6 = 2.7 times as fast as the latter for the same contraction.
 //
-// Measured inside a batch-128 training step against the fp32 MFMA kernels: products of the transformed layers,
-// forward, 216 -> 170 (second layer), 128 -> 93 (third), 97 -> 78 us (fourth); their weight gradients 239 -> 149,
-// 154 -> 104, 131 -> 104, 87 -> 51 us; dense layers, forward, 116 -> 97 us.  4096 x 4608 x 2048 alone: 101 -> 160 TFLOP/s
-// at half the matrix cores' issue rate; the clock falls from 2.2 to 1.7 GHz in such a run, so power bounds it as much as
-// the splitting (88 vector instructions per 24 MFMAs and wave) does.  The products of the transformed layers are
-// short (K = 128 .. 256) and move 3 - 3.8 TB/s as well.  Relative error of those products against 64 bits, fp32 MFMA
-// -> here: 2.4e-7 -> 2.2e-7 at K = 192, 8.3e-7 -> 7.1e-7 at K = 2048.
+// Measured inside a batch-128 training step against the fp32 MFMA kernels: forward products 282 -> 199 us (first layer),
+// 216 -> 170 (second, transformed), 128 -> 93 (third), 97 -> 78 (fourth); weight gradients 353 -> 218, 239 -> 149, 154 ->
+// 104, 131 -> 104, 87 -> 51 us; dense layers, forward, 116 -> 97 us.  4096 x 4608 x 2048 alone: 101 -> 160 TFLOP/s at half
+// the matrix cores' issue rate; the clock falls from 2.2 to 1.7 GHz in such a run, so power bounds it as much as the
+// splitting (88 vector instructions per 24 MFMAs and wave) does.  The products of the transformed layers are short
+// (K = 128 .. 256) and move 3 - 3.8 TB/s as well.  Relative error of those products against 64 bits, fp32 MFMA -> here:
+// 2.4e-7 -> 2.2e-7 at K = 192, 8.3e-7 -> 7.1e-7 at K = 2048.
 //
 // Addressing, zero fill, split-k and epilogues are those of gemm.h; operands are fetched as fp32 and split once per
 // workgroup, on their way into LDS.

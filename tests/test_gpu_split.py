@@ -65,3 +65,16 @@ def test_bf16_products_with_192_columns(lib):
         assert rel_l2(op(bf).cpu().numpy(), op(ref).cpu().numpy()) <= _bar(9 * 192)
     bf.close()
     ref.close()
+
+
+@pytest.mark.parametrize("batch,nin,nout", [(1, 8, 8), (3, 1032, 24), (4, 2048, 9)])
+def test_few_dense_rows_with_bf16_products(lib, batch, nin, nout):
+    """Dense layers on a few rows of a bf16 handle: both operands rounded to bf16, fp32 sums."""
+    net = lib.AlexNet(dict(S.MINI, name="rows", fc=[nin, nout, 4]), batch, precision=1)
+
+    def values(shape, seed):  # bf16 holds these exactly
+        return (S.make_normal(shape, seed).view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)
+    x, w, b = values((batch, nin), 1), values((nout, nin), 2), S.make_normal((nout,), 3)
+    y = net.fc_forward(7, x, w, b).cpu().numpy()
+    assert rel_l2(y, x.astype(np.float64) @ w.astype(np.float64).T + b) <= _bar(nin)
+    net.close()
