@@ -331,14 +331,13 @@ static int launch_slab_finish(const float* ws, int ns, int groups, long M, int N
 // (gemm_split.h)  Dense operands, 16-byte loads.
 typedef Tile<128, 128, kBKs, 2, 2> S128;
 typedef Tile<128, 96, kBKs, 4, 1> S96;
-typedef Tile<128, 192, kBKs, 2, 2> S192;
 typedef Tile<128, 64, kBKs, 2, 2> S64;
 typedef Tile<64, 128, kBKs, 2, 2> S64m;
 // rate of a tile on a long reduction over the fp32 matrix rate of a compute unit, measured at 4096 x 4608 x 2048
-// (160, 153, 159 and 133 TFLOP/s; the fp32 kernels reach 101 there)
+// (147, 140, 125 and 127 TFLOP/s; the fp32 kernels reach 101 there)
 static const TileOption kTileOptionsSplit[] = {
-    {128, 128, kBKs, 1.02}, {128, 96, kBKs, 0.97}, {128, 192, kBKs, 1.01}, {128, 64, kBKs, 0.84},
-    {64, 128, kBKs, 0.84}};  // the last one for dense layers on at most 64 rows, where a 128-row tile is half empty
+    {128, 128, kBKs, 0.94}, {128, 96, kBKs, 0.89}, {128, 64, kBKs, 0.80},
+    {64, 128, kBKs, 0.81}};  // the last one for dense layers on at most 64 rows, where a 128-row tile is half empty
 // Cheapest (tile, slices) for a launch of the split kernel, as plan_gemm(), with one difference: these kernels fetch
 // one k-tile ahead only, and a workgroup that has its compute unit to itself waits for memory about half the time (a
 // weight gradient of 192 x 128 x 2048 x 72: 105 us in 216 workgroups, see fill), so slices are worth having until two
@@ -356,7 +355,8 @@ static GemmPlan plan_split(int M, int N, int K, int groups, double out_bytes, in
       const int per = ceil_div(ktiles, s);
       if (ceil_div(ktiles, per) != s) continue;
       if (s > 1 && per * kBKs < 96) break;
-      const int c = ceil_div(tiles * s, 256), most = to.bn > 128 ? 2 : 3;  // workgroups per unit: of the launch, at once
+      // workgroups per unit: of the launch, at once (see SplitMinBlocks)
+      const int c = ceil_div(tiles * s, 256), most = to.bm * to.bn < 128 * 128 ? 3 : 2;
       if (s > 1 && c > 4 * most) break;  // more slices only add traffic
       const double fill = c >= most ? 1.0 : c == 2 ? 0.85 : 0.5;
       double t = c * t_tile * per / ktiles / fill + 4e-6;
@@ -395,7 +395,6 @@ static int by_tile_split(const GemmPlan& p, const DenseParams& a, const DensePar
 #define AX_SPLIT(T) \
   return launch_tile_split<T, ALT<T::BM>, BLT<T::BN>, Epi>(a, b, e, M, N, K, p.kchunk, p.ns, groups, st)
   if (p.bm == 64) AX_SPLIT(S64m);
-  if (p.bn == 192) AX_SPLIT(S192);
   if (p.bn == 96) AX_SPLIT(S96);
   if (p.bn == 64) AX_SPLIT(S64);
   AX_SPLIT(S128);
@@ -416,7 +415,6 @@ static int by_tile_run(const GemmPlan& p, const AP& a, const DenseParams& b, con
                        hipStream_t st) {
 #define AX_SPLIT(T) \
   return launch_tile_split<T, ALT<T::BM>, SplitRowInner<T::BN>, Epi>(a, b, e, M, N, K, p.kchunk, p.ns, 1, st)
-  if (p.bn == 192) AX_SPLIT(S192);
   if (p.bn == 96) AX_SPLIT(S96);
   if (p.bn == 64) AX_SPLIT(S64);
   AX_SPLIT(S128);

@@ -6,10 +6,14 @@
 //
 //   hh + hm + mh + mm + hl + lh,
 //
-// each exact in the matrix core, accumulated in fp32.  What is dropped (ml, lm, ll) is below 2^-25 of |a*b|, less
-// than the rounding of one fp32 addition, and an accumulator is rounded once per 16-deep step and term pair (six times
-// per 16 products) instead of once per two products (eight times), so the result is no further from the exact sum than
-// the fp32 MFMA's.  An infinite operand gives NaN (its remainder is inf - inf), as inf * 0 does.
+// each exact in the matrix core, accumulated in fp32: hh in one set of accumulators, the other five, 2^-8 of it and
+// less, in a second one, and the two are added at the end.  What is dropped (ml, lm, ll) is below 2^-24 of |a*b| and of
+// either sign.  An accumulator is rounded once per MFMA, and only hh's roundings count: one per 16 products, where the
+// fp32 MFMA rounds its sum once per two.  (All six terms in one set of accumulators round six times per 16: 2.2e-7 of
+// the result at K = 192 and 7.1e-7 at 2048 against 7.7e-8 and 2.8e-7 so, 2.5e-7 and 8.3e-7 for the fp32 MFMA -- but
+// where half the products are zero, as behind a ReLU, the fp32 MFMA rounds less often and a single set was less exact
+// than it at every length, 1.28 times its error at K = 64, 1.14 at 9216.)  An infinite operand gives NaN (its remainder
+// is inf - inf), as inf * 0 does.
 //
 // Why: v_mfma_f32_32x32x16_bf16 does 1024 flop per SIMD and clock, v_mfma_f32_32x32x2_f32 does 64; six of the
 // former are 16/6 = 2.7 times as fast as the latter for the same contraction.
@@ -19,8 +23,13 @@
 // 104, 131 -> 104, 87 -> 51 us; dense layers, forward, 116 -> 97 us.  4096 x 4608 x 2048 alone: 101 -> 160 TFLOP/s at half
 // the matrix cores' issue rate; the clock falls from 2.2 to 1.7 GHz in such a run, so power bounds it as much as the
 // splitting (88 vector instructions per 24 MFMAs and wave) does.  The products of the transformed layers are short
-// (K = 128 .. 256) and move 3 - 3.8 TB/s as well.  Relative error of those products against 64 bits, fp32 MFMA -> here:
-// 2.4e-7 -> 2.2e-7 at K = 192, 8.3e-7 -> 7.1e-7 at K = 2048.
+// (K = 128 .. 256) and move 3 - 3.8 TB/s as well.
+//
+// The second set of accumulators costs registers: the 128 x 128 tile fits a compute unit twice instead of three times
+// (its LDS with two row-contiguous operands, 55,296 bytes, allows no more anyway), 128 x 96 and 128 x 64 three times.
+// Alone, one set -> two: 128 x 128 151 -> 147 TFLOP/s on 4096 x 4608 x 2048, 176 -> 182 us on 72 products of 6272 x 128 x
+// 192; 128 x 96 and 128 x 64 within 2 %.  A 128 x 192 tile no longer fits (72 products of 6272 x 192 x 128 took 202 us with
+// it, 233 with 128 x 96).
 //
 // Addressing, zero fill, split-k and epilogues are those of gemm.h; operands are fetched as fp32 and split once per
 // workgroup, on their way into LDS.
@@ -393,8 +402,8 @@ __device__ __forceinline__ void split_side_slot(AL& al, BL& bl, uint32_t* as_nex
 }
 template <class T, class AL, class BL, bool TR, int Q = 0>
 __device__ __forceinline__ void split_groups(const uint32_t* as, const uint32_t* bs, SplitFrags<AL, T::TM>& fa,
-                                             SplitFrags<BL, T::TN>& fb, v16f (&acc)[T::TM][T::TN], AL& al, BL& bl,
-                                             uint32_t* as_next, uint32_t* bs_next, float4* ra, float4* rb, int kleft) {
+                                             SplitFrags<BL, T::TN>& fb, v16f (&hi)[T::TM][T::TN],
+                                             v16f (&lo)[T::TM][T::TN], AL& al, BL& bl, uint32_t* as_next, uint32_t* bs_next, float4* ra, float4* rb, int kleft) {
   if constexpr (Q < kSplitProducts) {
     // the terms of a plane are read shortly before their first use, so that two planes are live at a time
     if constexpr (Q == 0) {
@@ -412,18 +421,21 @@ __device__ __forceinline__ void split_groups(const uint32_t* as, const uint32_t*
 #pragma unroll
       for (int j = 0; j < T::TN; ++j) {
         const v8bf a = fa.f[split_plane_a(Q)][i], b = fb.f[split_plane_b(Q)][j];
-        acc[i][j] = TR ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[i][j], 0, 0, 0)
-                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[i][j], 0, 0, 0);
+        v16f& c = Q == 0 ? hi[i][j] : lo[i][j];
+        c = TR ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0)
+               : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
       }
     split_side_slot<AL, BL, Q>(al, bl, as_next, bs_next, ra, rb, kleft);
     __builtin_amdgcn_sched_barrier(0);
-    split_groups<T, AL, BL, TR, Q + 1>(as, bs, fa, fb, acc, al, bl, as_next, bs_next, ra, rb, kleft);
+    split_groups<T, AL, BL, TR, Q + 1>(as, bs, fa, fb, hi, lo, al, bl, as_next, bs_next, ra, rb, kleft);
   }
 }
 
+// Workgroups per compute unit: 128 x 128 has 128 accumulators a lane, which with everything else is 212 registers; 96 or
+// 64 leave room for three.
 template <class T>
 struct SplitMinBlocks {
-  static constexpr int value = T::BM * T::BN <= 128 * 128 ? 3 : 2;
+  static constexpr int value = T::BM * T::BN < 128 * 128 ? 3 : 2;
 };
 
 // The one-dimensional grid of gx * gy * (groups * nsplit) workgroups (see xcd_tile).  The divisors are constants of the
@@ -454,13 +466,13 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
   BL bl(bp, (int)g, tid, n0, kbeg);
   ep.set_group((int)g, (int)z);
 
-  v16f acc[T::TM][T::TN];
+  v16f acc[T::TM][T::TN], lo[T::TM][T::TN];  // hh; the other term products
 #pragma unroll
   for (int i = 0; i < T::TM; ++i)
 #pragma unroll
     for (int j = 0; j < T::TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = lo[i][j][r] = 0.f;
 
   if (nt > 0) {
     const int kh = lane >> 5;
@@ -480,10 +492,16 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
       const int p = t & 1;
       SplitFrags<AL, T::TM> fa;
       SplitFrags<BL, T::TN> fb;
-      split_groups<T, AL, BL, Epi::kTransposed>(As[p] + a_off, Bs[p] + b_off, fa, fb, acc, al, bl, As[p ^ 1], Bs[p ^ 1],
+      split_groups<T, AL, BL, Epi::kTransposed>(As[p] + a_off, Bs[p] + b_off, fa, fb, acc, lo, al, bl, As[p ^ 1], Bs[p ^ 1],
                                                 ra, rb, kend - kbeg - (t + 2) * T::BK);
       __syncthreads();
     }
+#pragma unroll
+    for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += lo[i][j][r];
   }
 
 #pragma unroll

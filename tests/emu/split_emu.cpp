@@ -34,7 +34,7 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
                       int nsplit, int groups) {
   const int gx = (M + T::BM - 1) / T::BM, gy = (N + T::BN - 1) / T::BN, gz = groups * nsplit;
   std::vector<uint32_t> As(AL::UNITS * 4), Bs(BL::UNITS * 4);
-  std::vector<float> acc((size_t)T::BM * T::BN);
+  std::vector<float> acc((size_t)T::BM * T::BN), lo(acc.size());
   for (int bz = 0; bz < gz; ++bz)
     for (int by = 0; by < gy; ++by)
       for (int bx = 0; bx < gx; ++bx) {
@@ -43,6 +43,7 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
         const int kbeg = split * kchunk, kend = std::min(K, kbeg + kchunk);
         const int nt = kend > kbeg ? (kend - kbeg + T::BK - 1) / T::BK : 0;
         std::fill(acc.begin(), acc.end(), 0.f);
+        std::fill(lo.begin(), lo.end(), 0.f);
         Epi e = ep;
         e.set_group(g, bz);
         for (int t = 0; t < nt; ++t) {
@@ -67,8 +68,8 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
           for (int i = 0; i < T::BM; ++i)
             for (int j = 0; j < T::BN; ++j) {
               const int wa = i / (T::TM * 32), ta = i / 32 % T::TM, wb = j / (T::TN * 32), tb = j / 32 % T::TN;
-              float& c = acc[(size_t)i * T::BN + j];
               for (int q = 0; q < kSplitProducts; ++q) {
+                float& c = (q == 0 ? acc : lo)[(size_t)i * T::BN + j];
                 float s = 0.f;
                 for (int kh = 0; kh < 2; ++kh) {
                   const int ua = split_unit<AL>(0, kh, wa * (T::TM * 32) + i % 32) + split_plane_a(q) * 2 * AL::RP + AL::block_units(ta);
@@ -80,7 +81,7 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
             }
         }
         for (int i = 0; i < T::BM && m0 + i < M; ++i)
-          for (int j = 0; j < T::BN && n0 + j < N; ++j) e.apply(m0 + i, n0 + j, acc[(size_t)i * T::BN + j]);
+          for (int j = 0; j < T::BN && n0 + j < N; ++j) e.apply(m0 + i, n0 + j, acc[(size_t)i * T::BN + j] + lo[(size_t)i * T::BN + j]);
       }
 }
 

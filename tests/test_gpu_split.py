@@ -78,3 +78,30 @@ def test_few_dense_rows_with_bf16_products(lib, batch, nin, nout):
     y = net.fc_forward(7, x, w, b).cpu().numpy()
     assert rel_l2(y, x.astype(np.float64) @ w.astype(np.float64).T + b) <= _bar(nin)
     net.close()
+
+
+def _fp32_matrix_order(a, b):
+    """a^T b with the sum rounded to fp32 after every two products, as the fp32 matrix instructions do."""
+    s = np.zeros((a.shape[1], b.shape[1]), np.float32)
+    for k in range(0, len(a), 2):
+        s = (s + a[k:k + 2].astype(np.float64).T @ b[k:k + 2].astype(np.float64)).astype(np.float32)
+    return s
+
+
+@pytest.mark.parametrize("kind", ["normal", "relu", "positive"])
+@pytest.mark.parametrize("batch", [16, 20, 32, 64, 200])
+def test_no_further_from_the_exact_sum_than_fp32_products(lib, batch, kind):
+    """The weight gradient of a dense layer (one reduction over the batch, no slices) against float64, and as far as
+    that from it the same product summed as the fp32 matrix instructions sum it.  Behind a ReLU half the products are
+    zero and their additions exact, where a term product of the split is rounded all the same."""
+    n = 128
+    net = lib.AlexNet(dict(S.MINI, name="sums", fc=[n, n, 4]), batch)
+    x, dy = S.make_normal((batch, n), 11), S.make_normal((batch, n), 12)
+    if kind == "relu":
+        x = np.maximum(x, 0)
+    if kind == "positive":
+        x, dy = 1 + np.abs(x) % 1, 1 + np.abs(dy) % 1
+    _, dw, _ = net.fc_backward(7, x, np.zeros((n, n), np.float32), dy)
+    exact = dy.astype(np.float64).T @ x.astype(np.float64)
+    assert rel_l2(dw.cpu().numpy(), exact) <= rel_l2(_fp32_matrix_order(dy, x), exact)
+    net.close()
