@@ -338,6 +338,11 @@ typedef Tile<64, 128, kBKs, 2, 2> S64m;
 static const TileOption kTileOptionsSplit[] = {
     {128, 128, kBKs, 0.94}, {128, 96, kBKs, 0.89}, {128, 64, kBKs, 0.80},
     {64, 128, kBKs, 0.81}};  // the last one for dense layers on at most 64 rows, where a 128-row tile is half empty
+// Reductions of fewer than eight values stay on the fp32 matrix instructions.  Those round once per two products, K/2
+// times; here, whatever the length, the sum of the two sets of accumulators is rounded, and the dropped terms count as
+// much as one rounding again.  A single product is to be correctly rounded (K = 1: 0.43 units of 2^-24 against 0.42, at
+// worst 1.5 against 1.0); from K = 4 on the split products are the closer ones at worst too (2.0 against 2.6).
+constexpr int kSplitMinK = 8;
 // Cheapest (tile, slices) for a launch of the split kernel, as plan_gemm(), with one difference: these kernels fetch
 // one k-tile ahead only, and a workgroup that has its compute unit to itself waits for memory about half the time (a
 // weight gradient of 192 x 128 x 2048 x 72: 105 us in 216 workgroups, see fill), so slices are worth having until two
@@ -425,7 +430,12 @@ static inline bool pointwise(const ConvGeom& c) { return c.k == 1 && c.stride ==
 static inline DenseParams pointwise_A(const ConvGeom& c, const float* x) {
   return DenseParams{x, c.Cin, c.cg(), (int)c.P(), (uint32_t)(c.in_elems() * 4)};
 }
-static inline bool split_fwd_ok(const ConvGeom& c) { return pointwise(c) && c.cg() % 4 == 0 && c.og() % 4 == 0; }
+static inline bool split_fwd_ok(const ConvGeom& c) {
+  return pointwise(c) && c.cg() % 4 == 0 && c.og() % 4 == 0 && c.cg() >= kSplitMinK;
+}
+static inline bool split_bwdw_ok(const ConvGeom& c) {
+  return pointwise(c) && c.cg() % 4 == 0 && c.og() % 4 == 0 && c.P() >= kSplitMinK;
+}
 static GemmPlan split_fwd_plan(const ConvGeom& c) {
   const GemmDims d = fwd_dims(c);
   return plan_split(d.M, d.N, d.K, d.groups, (double)c.out_elems() * 4, 8);
@@ -491,7 +501,7 @@ size_t conv_bwd_weight_ws_floats(const ConvGeom& c) {
       if (p.ns > 1) n = std::max(n, (size_t)p.ns * c.w_elems());
       if (run_mode(c)) n = std::max(n, (size_t)bwdw_plan(c, true, bf, table).ns * run_w_elems(c));
     }
-  if (split_fwd_ok(c)) {
+  if (split_bwdw_ok(c)) {
     bool swapped;
     const int ns = split_bwdw_plan(c, &swapped).ns;
     if (ns > 1) n = std::max(n, (size_t)ns * c.w_elems());
@@ -767,7 +777,7 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
   GemmDims d = bwdw_dims(c);
   if (run) d.M = run_k(c);
   const bool av = run || bwdw_A_vec(c, x), bv = bwdw_B_vec(c, dy);
-  if (!g_bf16 && !run && split_fwd_ok(c) && av && bv) {
+  if (!g_bf16 && !run && split_bwdw_ok(c) && av && bv) {
     bool swapped;
     const GemmPlan p = split_bwdw_plan(c, &swapped);
     const long slab = (long)d.M * d.N;
@@ -1019,12 +1029,22 @@ struct EpiFcAct {
 
 static inline bool vec_ok(const float* p, long ld) { return aligned16(p) && ld % 4 == 0; }
 
-// 16-byte loads: on the bf16 matrix cores, tile and slices by `p`; else on the fp32 ones
+// Which kernels take a dense fp32 product, and its tile and slices
+static inline bool fc_split_ok(bool vec, int K) { return vec && K >= kSplitMinK; }
+static GemmPlan fc_product_plan(int B, int N, int K, bool vec, bool bf) {
+  if (!bf && fc_split_ok(vec, K)) return fc_plan(B, N, K);
+  GemmPlan p{128, 128, 0, 0};
+  p.ns = fc_split(B, N, K, &p.kchunk, bf);
+  return p;
+}
+// 16-byte loads and K long enough: on the bf16 matrix cores; else on the fp32 ones
 template <template <int> class SA, template <int> class SB, template <int, int, bool> class ALT,
           template <int, int, bool> class BLT, class Epi>
 static int launch_dense(bool vec, const GemmPlan& p, const DenseParams& a, const DenseParams& b, const Epi& ep, int M,
                         int N, int K, hipStream_t st) {
-  if (vec) return by_tile_split<SA, SB>(p, a, b, ep, M, N, K, 1, st);
+  if (fc_split_ok(vec, K)) return by_tile_split<SA, SB>(p, a, b, ep, M, N, K, 1, st);
+  if (vec)
+    return launch_tile<T128, ALT<128, kBK, true>, BLT<128, kBK, true>, Epi>(a, b, ep, M, N, K, p.kchunk, p.ns, 1, st);
   return launch_tile<T128, ALT<128, kBK, false>, BLT<128, kBK, false>, Epi>(a, b, ep, M, N, K, p.kchunk, p.ns, 1, st);
 }
 
@@ -1044,9 +1064,7 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
   if (vec && fc_rows_ok(B, in))
     return bf ? launch_fc_rows<true>(B, in, out, x, w, act, y, y16, st) : launch_fc_rows<false>(B, in, out, x, w, act, y, y16, st);
   const bool s16 = bf && x16 && w16 && fc_bf16_stored_ok(in, out) && aligned16(x16) && aligned16(w16);
-  GemmPlan p{128, 128, 0, 0};
-  if (vec && !bf) p = fc_plan(B, out, in);
-  else p.ns = fc_split(B, out, in, &p.kchunk, bf);
+  const GemmPlan p = fc_product_plan(B, out, in, vec, bf);
   const int ns = p.ns, kchunk = p.kchunk;
   DenseParams a{x, in, 0, B, (uint32_t)((size_t)B * in * 4)};
   DenseParams b{w, in, 0, out, (uint32_t)((size_t)out * in * 4)};
@@ -1076,9 +1094,7 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
                        float* ws, hipStream_t st, const uint16_t* dy16, const uint16_t* w16, uint16_t* dx16) {
   const bool vec = vec_ok(dy, out) && vec_ok(w, in), bf = g_bf16 && vec;
   const bool s16 = bf && dy16 && w16 && fc_bf16_stored_ok(in, out) && aligned16(dy16) && aligned16(w16);
-  GemmPlan p{128, 128, 0, 0};
-  if (vec && !bf) p = fc_plan(B, in, out);
-  else p.ns = fc_split(B, in, out, &p.kchunk, bf);
+  const GemmPlan p = fc_product_plan(B, in, out, vec, bf);
   const int ns = p.ns, kchunk = p.kchunk;
   DenseParams a{dy, out, 0, B, (uint32_t)((size_t)B * out * 4)};
   DenseParams b{w, in, 0, in, (uint32_t)((size_t)out * in * 4)};
@@ -1114,7 +1130,7 @@ int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy
                                                              round_up(B, kBKbf), 1, 1, st);
   if (g_bf16 && vec)
     return launch_tile_bf<B128, BfDenseR, BfDenseR, EpiSlab>(a, b, ep, out, in, B, round_up(B, kBKbf), 1, 1, st);
-  const GemmPlan p = vec ? plan_split(out, in, B, 1, 0, 1) : GemmPlan{128, 128, 1, round_up(B, kBK)};
+  const GemmPlan p = fc_split_ok(vec, B) ? plan_split(out, in, B, 1, 0, 1) : GemmPlan{128, 128, 1, round_up(B, kBK)};
   return launch_dense<SplitRowInner, SplitRowInner, DenseRowInner, DenseRowInner>(vec, p, a, b, ep, out, in, B, st);
 }
 

@@ -105,3 +105,17 @@ def test_no_further_from_the_exact_sum_than_fp32_products(lib, batch, kind):
     exact = dy.astype(np.float64).T @ x.astype(np.float64)
     assert rel_l2(dw.cpu().numpy(), exact) <= rel_l2(_fp32_matrix_order(dy, x), exact)
     net.close()
+
+
+def test_products_of_single_values_are_correctly_rounded(lib):
+    """A reduction over one value is one multiplication: the result is the product rounded once, bit for bit -- the
+    weight gradients of a dense layer and of a 1x1 layer on 1x1 maps at a batch of one."""
+    wl = dict(S.MINI, name="ones", crop=1, raw=1, conv=[(8, 1, 1, 0, 1, 0, 0)] * 5, fc=[64, 132, 4])
+    net = lib.AlexNet(wl, 1)
+    x, dy = S.make_normal((1, 64), 21), S.make_normal((1, 132), 22)
+    _, dw, _ = net.fc_backward(7, x, np.zeros((132, 64), np.float32), dy)
+    assert np.array_equal(dw.cpu().numpy(), dy.T * x)
+    x, dy = S.make_normal((1, 8, 1, 1), 23), S.make_normal((1, 8, 1, 1), 24)
+    dw, _ = net.conv_backward_weight(2, x, dy, (8, 8, 1, 1))
+    assert np.array_equal(dw.cpu().numpy().reshape(8, 8), dy.reshape(8, 1) * x.reshape(1, 8))
+    net.close()
