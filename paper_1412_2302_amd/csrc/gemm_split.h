@@ -12,8 +12,13 @@
 // fp32 MFMA rounds its sum once per two.  (All six terms in one set of accumulators round six times per 16: 2.2e-7 of
 // the result at K = 192 and 7.1e-7 at 2048 against 7.7e-8 and 2.8e-7 so, 2.5e-7 and 8.3e-7 for the fp32 MFMA -- but
 // where half the products are zero, as behind a ReLU, the fp32 MFMA rounds less often and a single set was less exact
-// than it at every length, 1.28 times its error at K = 64, 1.14 at 9216.)  An infinite operand gives NaN (its remainder
-// is inf - inf), as inf * 0 does.
+// than it at every length, 1.28 times its error at K = 64, 1.14 at 9216.)
+//
+// An operand that is infinite, or finite but rounds to infinity as bf16 (from 3.396e38 up), has a NaN among its terms
+// (inf - inf), and a term product may overflow where the whole one does not: either way the sum is not finite.  A
+// workgroup that finds such a sum in its tile computes the tile once more with the fp32 matrix instructions, so
+// infinities, NaNs and sums close to overflow come out as those give them; finite sums prove that nothing was lost.  The
+// look at the sums costs about 1 % of a product (72 of 6272 x 128 x 192: 171 -> 174 us).
 //
 // Why: v_mfma_f32_32x32x16_bf16 does 1024 flop per SIMD and clock, v_mfma_f32_32x32x2_f32 does 64; six of the
 // former are 16/6 = 2.7 times as fast as the latter for the same contraction.
@@ -93,6 +98,12 @@ AX_HD SplitPair split_pair(float x, float y) {
   return s;
 }
 
+// The tile as plain fp32 in LDS, [row][k], for the second computation of a tile whose sums are not finite
+constexpr int kRawLd = kBKs + 1;
+AX_HD void raw_store_quad(float* lds, int row, int kq, const float4& v) {
+  float* d = lds + row * kRawLd + 4 * kq;
+  d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+}
 // four consecutive k (quad kq of the tile) of one row of a k-contiguous operand
 template <int RP>
 AX_HD void split_store_quad(uint32_t* lds, int row, int kq, const float4& v) {
@@ -131,12 +142,20 @@ struct SplitRowStore {
       d[(p * 2 * RP + SP) * 4] = s1.t[p];
     }
   }
+  static AX_HD void raw_half(float* lds, int rq, int kp, int half, const float4& a, const float4& b) {
+    float* d = lds + (4 * rq + 2 * half) * kRawLd + 2 * kp;
+    d[0] = half ? a.z : a.x;
+    d[1] = half ? b.z : b.x;
+    d[kRawLd] = half ? a.w : a.y;
+    d[kRawLd + 1] = half ? b.w : b.y;
+  }
 };
 
 // ---- loaders --------------------------------------------------------------------
 //   fetch(r, kleft)        issue the loads of the next k-tile, of which kleft k are left, and step on; a k-tile past
 //                          the end (kleft <= 0) reads nothing and returns zeros
 //   store_step(s, lds, r)  split and store part s of what fetch() brought
+//   raw_step(s, lds, r)    store it as it is, [row][k] with rows kRawLd apart
 // Byte offsets run along with k; rows outside the operand start at kOob and stay outside: a reduction spans less
 // than 2 GiB.
 
@@ -172,6 +191,10 @@ struct SplitKInner {
   AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
     const int idx = tid + s * kThreads;
     if (kWhole || idx < NQ) split_store_quad<RP>(lds, idx / QK, kq, r[s]);
+  }
+  AX_HD void raw_step(int s, float* lds, const float4* r) const {
+    const int idx = tid + s * kThreads;
+    if (kWhole || idx < NQ) raw_store_quad(lds, idx / QK, kq, r[s]);
   }
 };
 
@@ -210,6 +233,10 @@ struct SplitRowInner {
   AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
     const int u = s >> 1, idx = tid + u * kThreads;
     if (kWhole || idx < NU) St::store_half(lds, St::quad(idx), St::pair(idx), s & 1, r[2 * u], r[2 * u + 1]);
+  }
+  AX_HD void raw_step(int s, float* lds, const float4* r) const {
+    const int u = s >> 1, idx = tid + u * kThreads;
+    if (kWhole || idx < NU) St::raw_half(lds, St::quad(idx), St::pair(idx), s & 1, r[2 * u], r[2 * u + 1]);
   }
 };
 
@@ -255,6 +282,9 @@ struct SplitRun {
   }
   AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
     split_store_quad<RP>(lds, (tid + s * kThreads) / QK, kq, r[s]);
+  }
+  AX_HD void raw_step(int s, float* lds, const float4* r) const {
+    raw_store_quad(lds, (tid + s * kThreads) / QK, kq, r[s]);
   }
 };
 // Its transpose (weight gradient): k = output pixel, row = one of the k*C floats of a kernel row.  The whole quads of
@@ -338,12 +368,20 @@ struct SplitRunT {
   AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
     if (NU == kThreads || tid < NU) St::store_half(lds, St::quad(tid), St::pair(tid), s & 1, r[0], r[1]);
   }
+  AX_HD void raw_step(int s, float* lds, const float4* r) const {
+    if (NU == kThreads || tid < NU) St::raw_half(lds, St::quad(tid), St::pair(tid), s & 1, r[0], r[1]);
+  }
 };
 
 template <class L>
 AX_HD void split_store_all(const L& l, uint32_t* lds, const float4* r) {
 #pragma unroll
   for (int s = 0; s < L::NS; ++s) l.store_step(s, lds, r);
+}
+template <class L>
+AX_HD void raw_store_all(const L& l, float* lds, const float4* r) {
+#pragma unroll
+  for (int s = 0; s < L::NS; ++s) l.raw_step(s, lds, r);
 }
 // 16-byte unit that holds k octet kh of `row` in plane p
 template <class L>
@@ -431,6 +469,45 @@ __device__ __forceinline__ void split_groups(const uint32_t* as, const uint32_t*
   }
 }
 
+// acc = the tile once more, by the fp32 matrix instructions (see above): rarely run, so short rather than fast
+template <class T, class AL, class BL, bool TR>
+__device__ __forceinline__ void split_redo(const typename AL::Params& ap, const typename BL::Params& bp, int g, int m0,
+                                           int n0, int kbeg, int kend, float* as, float* bs,
+                                           v16f (&acc)[T::TM][T::TN]) {
+  static_assert(AL::UNITS * 4 >= T::BM * kRawLd && BL::UNITS * 4 >= T::BN * kRawLd, "the fp32 tile fits the terms' LDS");
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // so that nothing derived from it is kept from before the main loop: 10 registers a lane
+  AL al(ap, g, tid, m0, kbeg);
+  BL bl(bp, g, tid, n0, kbeg);
+  const int lane = tid & 63, wave = tid >> 6;
+  const float* a = as + ((wave % T::WAVES_M) * (T::TM * 32) + (lane & 31)) * kRawLd + (lane >> 5);
+  const float* b = bs + ((wave / T::WAVES_M) * (T::TN * 32) + (lane & 31)) * kRawLd + (lane >> 5);
+#pragma unroll
+  for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  for (int kleft = kend - kbeg; kleft > 0; kleft -= T::BK) {
+    float4 ra[AL::NL], rb[BL::NL];
+    al.fetch(ra, kleft);
+    bl.fetch(rb, kleft);
+    __syncthreads();  // the waves are done with what was there
+    raw_store_all(al, as, ra);
+    raw_store_all(bl, bs, rb);
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < T::BK; k += 2)
+#pragma unroll
+      for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < T::TN; ++j) {
+          const float x = a[32 * i * kRawLd + k], y = b[32 * j * kRawLd + k];
+          acc[i][j] = TR ? MfmaBlock<32>::mma(y, x, acc[i][j]) : MfmaBlock<32>::mma(x, y, acc[i][j]);
+        }
+  }
+}
+
 // Workgroups per compute unit: 128 x 128 has 128 accumulators a lane, which with everything else is 212 registers; 96 or
 // 64 leave room for three.
 template <class T>
@@ -502,6 +579,21 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
       for (int j = 0; j < T::TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] += lo[i][j][r];
+    float top = 0.f;  // the largest magnitude, NaN if there is one: one v_maximum3_f32 for two sums
+#pragma unroll
+    for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2)
+          top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top, fabsf(acc[i][j][r])),
+                                              fabsf(acc[i][j][r + 1]));
+    const bool bad = __any(!(top <= 3.402823466e38f));
+    if (lane == 0) As[0][wave] = bad;
+    __syncthreads();
+    if ((As[0][0] | As[0][1] | As[0][2] | As[0][3]) != 0)
+      split_redo<T, AL, BL, Epi::kTransposed>(ap, bp, (int)g, m0, n0, kbeg, kend, reinterpret_cast<float*>(As[0]),
+                                              reinterpret_cast<float*>(Bs[0]), acc);
   }
 
 #pragma unroll

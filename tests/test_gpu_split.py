@@ -119,3 +119,58 @@ def test_products_of_single_values_are_correctly_rounded(lib):
     dw, _ = net.conv_backward_weight(2, x, dy, (8, 8, 1, 1))
     assert np.array_equal(dw.cpu().numpy().reshape(8, 8), dy.reshape(8, 1) * x.reshape(1, 8))
     net.close()
+
+
+def _same_values(got, exact, k):
+    """Infinities and NaNs where and as fp32 sums have them, everything else within the bar."""
+    with np.errstate(over="ignore"):
+        want = exact.astype(np.float32)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+    fin = np.isfinite(want)
+    scale = np.abs(exact[fin]).max()  # magnitudes up to the largest fp32 number
+    assert rel_l2(got[fin] / scale, exact[fin] / scale) <= _bar(k)
+
+
+# value of one operand element, of the others it is multiplied with: an infinity, a NaN, a finite value that rounds to
+# infinity as bf16, a product of two such roundings beyond the fp32 range where the product itself is not
+@pytest.mark.parametrize("value,other", [(np.inf, 1.0), (-np.inf, 1.0), (np.nan, 1.0), (3.4e38, 1e-3),
+                                         (1.9999 * 2.0 ** 63, 2.0 ** 63.5)])
+@pytest.mark.parametrize("batch,n", [(8, 64), (130, 100)])
+def test_operands_that_are_not_finite_or_close_to_overflow(lib, batch, n, value, other):
+    net = lib.AlexNet(dict(S.MINI, name="range", fc=[n, n, 4]), batch)
+    x, w = np.abs(S.make_normal((batch, n), 31)) + 0.5, np.abs(S.make_normal((n, n), 32)) + 0.5
+    x[3, 5] = value
+    w[:, 5] = np.where(np.arange(n) % 7 == 0, 0, w[:, 5] * other)  # inf * 0 is NaN
+    zero = np.zeros(n, np.float32)
+    x64, w64 = x.astype(np.float64), w.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        y, dx, dw = x64 @ w64.T, x64 @ w64, x64.T @ x64
+    _same_values(net.fc_forward(7, x, w, zero).cpu().numpy(), y, n)
+    with np.errstate(invalid="ignore"):
+        _same_values(net.fc_forward(7, x, w, zero, relu=True).cpu().numpy(), np.where(y > 0, y, 0), n)
+    gx, gw, _ = net.fc_backward(7, x, w, x)  # the gradient of the layer is x too
+    _same_values(gx.cpu().numpy(), dx, n)
+    _same_values(gw.cpu().numpy(), dw, batch)
+    net.close()
+
+
+def test_first_layer_with_infinite_pictures(lib):
+    """The first layer's products (runs of whole kernel rows): an infinite pixel reaches the outputs whose window holds
+    it as an infinity, and no other."""
+    wl = dict(S.MINI, name="pictures", crop=41, raw=41)
+    net = lib.AlexNet(wl, 2)
+    x, w = np.abs(S.make_normal((2, 3, 41, 41), 41)) + 0.5, np.abs(S.make_normal((16, 3, 7, 7), 42)) + 0.5
+    x[1, 2, 20, 20] = np.inf
+    y = net.conv_forward(1, x, w, None, relu=True).cpu().numpy().reshape(2, 16, 18, 18)
+    hit = np.zeros(y.shape, bool)
+    hit[1, :, 7:11, 7:11] = True  # windows 2q .. 2q + 6 that hold 20
+    assert np.array_equal(np.isinf(y), hit) and not np.isnan(y).any()
+    dy = np.abs(S.make_normal((2, 16, 18, 18), 43)) + 0.5
+    dw, _ = net.conv_backward_weight(1, x, dy, w.shape)
+    dw = dw.cpu().numpy()
+    hit = np.zeros(dw.shape, bool)
+    hit[:, 2, 0::2, 0::2] = True  # 20 = 2q + r for an even r
+    assert np.array_equal(np.isinf(dw), hit) and not np.isnan(dw).any()
+    net.close()
