@@ -1,8 +1,11 @@
 // fp32 products on the bf16 matrix cores: every fp32 operand value is split into three bf16 terms,
 //
-//   x = h + m + l,   h = bf16(x), m = bf16(x - h), l = x - h - m     (all three exact: 8 + 8 + 8 significand bits)
+//   2^24 x = h + m + l,   h = bf16(2^24 x), m = bf16(2^24 x - h), l = 2^24 x - h - m     (8 + 8 + 8 significand bits)
 //
-// and a product a*b is the sum of the six term products that matter,
+// exact for every |x| below 2^103: the factor puts the last bit of the smallest number, 2^-149, where bf16 has one too.
+// (Without it the terms of operands below 2^-110 lost bits, 2.6e-5 of the value at 1e-36; the multiplication costs 2 to
+// 3 % of a product.)  The sums are multiplied by 2^-48 in return.  A product a*b is the sum of the six term products that
+// matter,
 //
 //   hh + hm + mh + mm + hl + lh,
 //
@@ -14,11 +17,10 @@
 // where half the products are zero, as behind a ReLU, the fp32 MFMA rounds less often and a single set was less exact
 // than it at every length, 1.28 times its error at K = 64, 1.14 at 9216.)
 //
-// An operand that is infinite, or finite but rounds to infinity as bf16 (from 3.396e38 up), has a NaN among its terms
-// (inf - inf), and a term product may overflow where the whole one does not: either way the sum is not finite.  A
-// workgroup that finds such a sum in its tile computes the tile once more with the fp32 matrix instructions, so
-// infinities, NaNs and sums close to overflow come out as those give them; finite sums prove that nothing was lost.  The
-// look at the sums costs about 1 % of a product (72 of 6272 x 128 x 192: 171 -> 174 us).
+// An operand that is infinite, or becomes so (from 2^103 up), has a NaN among its terms (inf - inf), and sums from 2^80
+// up overflow: either way a sum is not finite.  A workgroup that finds one in its tile computes the tile once more with
+// the fp32 matrix instructions, so infinities, NaNs and large numbers come out as those give them; finite sums prove that
+// nothing was lost.  The look at the sums costs about 1 % of a product (72 of 6272 x 128 x 192: 171 -> 174 us).
 //
 // Why: v_mfma_f32_32x32x16_bf16 does 1024 flop per SIMD and clock, v_mfma_f32_32x32x2_f32 does 64; six of the
 // former are 16/6 = 2.7 times as fast as the latter for the same contraction.
@@ -27,7 +29,7 @@
 // 216 -> 170 (second, transformed), 128 -> 93 (third), 97 -> 78 (fourth); weight gradients 353 -> 218, 239 -> 149, 154 ->
 // 104, 131 -> 104, 87 -> 51 us; dense layers, forward, 116 -> 97 us.  4096 x 4608 x 2048 alone: 101 -> 160 TFLOP/s at half
 // the matrix cores' issue rate; the clock falls from 2.2 to 1.7 GHz in such a run, so power bounds it as much as the
-// splitting (88 vector instructions per 24 MFMAs and wave) does.  The products of the transformed layers are short
+// splitting (104 vector instructions per 24 MFMAs and wave) does.  The products of the transformed layers are short
 // (K = 128 .. 256) and move 3 - 3.8 TB/s as well.
 //
 // The second set of accumulators costs registers: the 128 x 128 tile fits a compute unit twice instead of three times
@@ -74,7 +76,8 @@ AX_HD float bf_hi(uint32_t w) {
   return f;
 #endif
 }
-// the three terms of x (low halves) and y (high halves)
+constexpr float kSplitScale = 16777216.f, kSplitUnscale = 1.f / 281474976710656.f;  // 2^24, 2^-48
+// the three terms of 2^24 x (low halves) and 2^24 y (high halves)
 struct SplitPair {
   uint32_t t[kPlanes];
 };
@@ -91,6 +94,8 @@ AX_HD uint32_t split_pack(float lo, float hi) {
 }
 AX_HD SplitPair split_pair(float x, float y) {
   SplitPair s;
+  x *= kSplitScale;
+  y *= kSplitScale;
   s.t[0] = split_pack(x, y);
   const float rx = x - bf_lo(s.t[0]), ry = y - bf_hi(s.t[0]);
   s.t[1] = split_pack(rx, ry);
@@ -578,7 +583,7 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
 #pragma unroll
       for (int j = 0; j < T::TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] += lo[i][j][r];
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = (acc[i][j][r] + lo[i][j][r]) * kSplitUnscale;
     float top = 0.f;  // the largest magnitude, NaN if there is one: one v_maximum3_f32 for two sums
 #pragma unroll
     for (int i = 0; i < T::TM; ++i)

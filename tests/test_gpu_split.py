@@ -174,3 +174,19 @@ def test_first_layer_with_infinite_pictures(lib):
     hit[:, 2, 0::2, 0::2] = True  # 20 = 2q + r for an even r
     assert np.array_equal(np.isinf(dw), hit) and not np.isnan(dw).any()
     net.close()
+
+
+@pytest.mark.parametrize("size", [1e-33, 1e-36, 1e-38])
+def test_operands_close_to_the_smallest_normal_numbers(lib, size):
+    """Values down to 2^-126: every one of their 24 bits counts."""
+    batch, n = 40, 64
+    net = lib.AlexNet(dict(S.MINI, name="small", fc=[n, n, 4]), batch)
+    x, w, dy = (S.make_normal(s, 51 + i) for i, s in enumerate([(batch, n), (n, n), (batch, n)]))
+    x = (np.sign(x) * (1 + np.abs(x)) * size * 1.2).astype(np.float32)
+    w, dy = 64 * w, 64 * dy  # the sums themselves stay normal numbers
+    x64, w64, dy64 = (a.astype(np.float64) for a in (x, w, dy))
+    y = net.fc_forward(7, x, w, np.zeros(n, np.float32)).cpu().numpy()
+    assert rel_l2(y / size, x64 @ w64.T / size) <= _bar(n)
+    _, dw, _ = net.fc_backward(7, x, w, dy)
+    assert rel_l2(dw.cpu().numpy() / size, dy64.T @ x64 / size) <= _bar(batch)
+    net.close()
