@@ -393,9 +393,9 @@ template <class L>
 AX_HD int split_unit(int p, int kh, int row) {
   return (p * 2 + kh) * L::RP + L::pos(row);
 }
-// the six term products, largest first: planes of A and B
-AX_HD int split_plane_a(int q) { return q == 2 || q == 3 ? 1 : q == 5 ? 2 : 0; }
-AX_HD int split_plane_b(int q) { return q == 1 || q == 3 ? 1 : q == 4 ? 2 : 0; }
+// the six term products, hh first, by planes of B: planes of A and B
+AX_HD int split_plane_a(int q) { return q < 3 ? q : q < 5 ? q - 3 : 0; }
+AX_HD int split_plane_b(int q) { return q < 3 ? 0 : q < 5 ? 1 : 2; }
 constexpr int kSplitProducts = 6;
 
 // A weight gradient with its operands exchanged (rows of the product = columns of the result): ws[z][n][m] = v.  The
@@ -448,17 +448,16 @@ __device__ __forceinline__ void split_groups(const uint32_t* as, const uint32_t*
                                              SplitFrags<BL, T::TN>& fb, v16f (&hi)[T::TM][T::TN],
                                              v16f (&lo)[T::TM][T::TN], AL& al, BL& bl, uint32_t* as_next, uint32_t* bs_next, float4* ra, float4* rb, int kleft) {
   if constexpr (Q < kSplitProducts) {
-    // the terms of a plane are read shortly before their first use, so that two planes are live at a time
+    // the terms of a plane are read shortly before their first use, so that three planes of A and two of B are live at
+    // a time (with both by turns it was three of each, and 128 x 96 spilled)
     if constexpr (Q == 0) {
       fa.template read<0>(as);
       fb.template read<0>(bs);
-      fb.template read<1>(bs);
+      fa.template read<1>(as);
     }
-    if constexpr (Q == 1) fa.template read<1>(as);
-    if constexpr (Q == 3) {
-      fb.template read<2>(bs);
-      fa.template read<2>(as);
-    }
+    if constexpr (Q == 1) fa.template read<2>(as);
+    if constexpr (Q == 2) fb.template read<1>(bs);
+    if constexpr (Q == 4) fb.template read<2>(bs);
 #pragma unroll
     for (int i = 0; i < T::TM; ++i)
 #pragma unroll
