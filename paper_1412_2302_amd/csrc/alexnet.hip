@@ -174,10 +174,9 @@ static bool use_winograd(const alexnet_config_t& c, const ConvGeom& g) {
 // layer) 263 | 205, 8 (1.2 to 3.6) 310 | 300; with the line at 4 GFLOP 16 pictures (2.4 to 7.2) 351 | 372 and training
 // on 24 (3.6 to 11) 1391 | 1420.  Training the small nets of the tests, batch 256: 682 | 603 and 590 | 513.
 constexpr double kWinoMinFlops = 2e9;
-// Forward flops of the convolutions from which (fp32) the dense-layer update starts a stage later -- batch 37 of the full
-// net, 49 GFLOP, either way alike, 128, 170 GFLOP, 0.8 % faster -- and (bf16) an inference pass makes its weight copies on
-// the side stream: its first layer needs one of them, and with little to hide them under the two streams' meeting costs
-// more (batch 16 341 against 320 us, the small nets 147 and 166 against 109 and 134; batch 100, 133 GFLOP, 694 against 713).
+// Forward flops of the convolutions from which a bf16 handle's inference pass makes its weight copies on the side stream:
+// its first layer needs one of them, and with little to hide them under the two streams' meeting costs more (batch 16 341
+// against 320 us, the small nets 147 and 166 against 109 and 134; batch 100, 133 GFLOP, 694 against 713).
 constexpr double kForkFlops = 100e9;
 static bool winograd_in_pass(const ConvGeom& g) { return 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k >= kWinoMinFlops; }
 
@@ -331,9 +330,9 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     const ConvGeom& g = n->st[i].g;
     conv_flops += 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k;
   }
-  const bool fp32 = c.precision == ALEXNET_PRECISION_FP32, large = conv_flops >= kForkFlops;
-  n->upd_fork_stage = fp32 && large ? kStages - 2 : kStages - 1;
-  n->fork_inference = fp32 || large;
+  const bool fp32 = c.precision == ALEXNET_PRECISION_FP32;
+  n->upd_fork_stage = fp32 ? kStages - 2 : kStages - 1;
+  n->fork_inference = fp32 || conv_flops >= kForkFlops;
   n->fc16 = c.precision == ALEXNET_PRECISION_BF16 && n->fc[0].w_off % 4 == 0;
   for (int j = 0; j < kFc; ++j) n->fc16 = n->fc16 && fc_bf16_stored_ok(n->fc[j].in, n->fc[j].out);
   n->fcw16 = n->fc16 ? a.take<uint16_t>(n->n_weights - n->fc[0].w_off) : nullptr;
@@ -621,11 +620,11 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     // Fork of the dense-layer update, behind this stage's pooling adjoint: that kernel is bound by bandwidth like the
     // update and would be starved by it.  Early (the update is as long as the rest of a small batch's backward pass)
     // and held to one workgroup per CU, it costs the products beside it about what it moves.  Step with the fork in
-    // front of conv5 / conv4 / conv3 / conv2's weight gradient: batch 37 1488 / 1493 / 1504 / 1532 us, batch 128 3297 /
-    // 3253 / 3256 / 3282, batch 256 5819 / 5771 / 5779 / 5823, bf16 batch 64 1503 / 1499 / 1490 / 1556, batch 256 within
-    // 1 %; at 1024 workgroups in front of conv1's weight gradient (the products bound it when they were fp32 MFMAs)
-    // 1591, 3278 us.  So behind the last stage where the rest of the pass is short (bf16; see kForkFlops), one stage
-    // later otherwise.
+    // front of conv5 | conv4 | conv3's weight gradient, us, the best of five runs three times over, all within 0.3 %:
+    //   fp32  batch 24 1275 | 1274 | 1311   37 1523 | 1510 | 1528   64 2056 | 2047 | 2058   128 3378 | 3359 | 3346
+    //         256 6153 | 6121 | 6087
+    //   bf16  batch 32 1180 | 1190 | 1199   64 1506 | 1499 | 1491   128 2083 | 2091 | 2103   256 3446 | 3413 | 3412
+    // So fp32 takes conv4, never slower than conv5; for bf16 nothing is better than conv5 at every size.
     auto fork_update = [&]() -> int {
       AX_HIP(hipEventRecord(n->ev_fc_done, st));
       AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_fc_done, 0));
