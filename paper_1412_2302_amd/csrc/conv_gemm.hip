@@ -1,5 +1,6 @@
-// Convolution forward, backward-data and backward-weight as implicit GEMMs on
-// the fp32 MFMA core (gemm.h), and the dense layers on the same core.
+// Convolution forward, backward-data and backward-weight as implicit GEMMs, and the dense layers, on three cores: fp32
+// operands on the bf16 matrix cores (gemm_split.h: pointwise, first and dense layers that can be read 16 bytes at a
+// time), fp32 matrix instructions (gemm.h: everything else in fp32) and bf16 operands (gemm_bf16.h, gemm16.h).
 #include <algorithm>
 
 #include "gemm16.h"
@@ -30,6 +31,10 @@ typedef Tile<128, 48, kBK48, 4, 1, 16> T48;
 struct GemmPlan {
   int bm, bn, ns, kchunk;
 };
+// what the second launch of a product in slices costs besides its traffic: the small nets' 15 us products are better
+// sliced than whole (346 against 357 us a step with the price at 6 us); between 2 and 6 us every larger pass, fp32 or
+// bf16, stays within 0.3 %
+constexpr double kSecondLaunch = 4e-6;
 struct TileOption {
   int bm, bn, bk;
   double eff;  // fraction of the per-CU fp32 MFMA rate this tile reaches on a long reduction
@@ -47,7 +52,7 @@ typedef Tile<256, 128, kBKbf, 2, 2> B256;
 typedef Tile<256, 96, kBKbf, 4, 1> B256n96;
 static const TileOption kTileOptionsBf[] = {{128, 128, kBKbf, 3.2}, {128, 64, kBKbf, 2.2}, {256, 128, kBKbf, 4.2}};
 
-// precision of the GEMMs launched by the calling thread: 0 fp32 MFMA, 1 bf16 MFMA with fp32 accumulation
+// precision of the GEMMs launched by the calling thread: 0 fp32 operands, 1 operands rounded to bf16; fp32 accumulation
 static thread_local int g_bf16 = 0;
 void set_gemm_precision(int bf16) { g_bf16 = bf16 ? 1 : 0; }
 
@@ -69,9 +74,7 @@ static GemmPlan plan_gemm(int M, int N, int K, int groups, double out_bytes, int
       if (max_chunk && per * bk > max_chunk) continue;  // the workgroup's k range must fit its pixel table
       const double rounds = (double)ceil_div(tiles * s, 256);
       double t = rounds * t_tile * per / ktiles + 4e-6;
-      // a second launch of a few microseconds (6 here: the small nets' 15 us products stay whole, 357 against 346 us a
-      // step)
-      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + 4e-6;
+      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + kSecondLaunch;
       if (t < best_t * 0.98) {  // prefer earlier (larger, unsplit) candidates unless clearly better
         best_t = t;
         best = GemmPlan{to.bm, to.bn, s, per * bk};
@@ -365,7 +368,7 @@ static GemmPlan plan_split(int M, int N, int K, int groups, double out_bytes, in
       if (s > 1 && c > 4 * most) break;  // more slices only add traffic
       const double fill = c >= most ? 1.0 : c == 2 ? 0.85 : 0.5;
       double t = c * t_tile * per / ktiles / fill + 4e-6;
-      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + 6e-6;
+      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + kSecondLaunch;
       if (t < best_t * 0.98) {
         best_t = t;
         best = GemmPlan{to.bm, to.bn, s, per * kBKs};
@@ -841,7 +844,7 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
 // y = act(x w^T + b),  dx = gate(dy w),  dw = dy^T x.  The batch is the small
 // dimension, so forward and backward-data split the reduction over several
 // workgroups and finish in a second kernel that also applies the activation.
-// The dense layers always use the 128 x 128 tile.
+// bf16 products, and fp32 ones that gemm_split.h does not take, use the 128 x 128 tile (fc_split); the others fc_plan.
 
 static int fc_split(int B, int N, int K, int* kchunk, bool bf) {
   const int bk = bf ? kBKbf : kBK;
@@ -855,7 +858,7 @@ static int fc_split(int B, int N, int K, int* kchunk, bool bf) {
     if (ceil_div(ktiles, per) != s) continue;
     if (s > 1 && per < 6) break;
     double t = (double)ceil_div(tiles * s, 256) * t_tile * per / ktiles;
-    if (s > 1) t += (s + 1) * (double)B * N * 4 / 2.5e12;
+    if (s > 1) t += (s + 1) * (double)B * N * 4 / 2.5e12 + kSecondLaunch;
     if (t < best_t * 0.98) {
       best_t = t;
       best = s;
