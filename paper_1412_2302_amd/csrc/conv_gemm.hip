@@ -262,11 +262,10 @@ static int launch_tile192(const Im2colParams& a, const DenseParams& b, const Epi
   typedef Unit16<Im2colKTap16<128, kBKbf, MODE>, 128, kBKbf> AL;
   typedef Unit16<DenseKInner16<192, kBKbf>, 192, kBKbf> BL;
   const int gx = ceil_div(d.M, 128), gy = d.N / 192;
-  const SplitGrid grid{make_fastdiv((uint32_t)gx), make_fastdiv((uint32_t)gy), make_fastdiv(1u)};
   KernelScope ks("gemm_bf16", g_algo_flops > 0 ? g_algo_flops : 2.0 * d.M * d.N * (double)d.K * d.groups,
                  gemm_bytes(d.M, d.N, d.K, d.groups), st);
   hipLaunchKernelGGL((gemm16_kernel<B192, AL, BL, Epi>), dim3((unsigned)(gx * gy * d.groups)), dim3(kThreads), 0, st, a, b,
-                     e, d.M, d.N, d.K, d.K, grid);
+                     e, d.M, d.N, d.K, make_fastdiv((uint32_t)gx), make_fastdiv((uint32_t)gy));
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }

@@ -8,7 +8,7 @@
 //  * One register set between memory and LDS: a k-tile's loads are stored to LDS first thing in the iteration before
 //    it is needed, and the next ones are issued at once into the same registers, addresses ready, with the whole
 //    k-tile to arrive.  That leaves room for a third workgroup per CU beside 96 accumulators.
-//  * The place of a workgroup in the grid is worked out on the scalar unit (SplitGrid).
+//  * The place of a workgroup in the grid is worked out on the scalar unit, as in gemm_split.h.
 //
 // Measured against gemm_bf16.h on the convolutions of a batch of 256 (bit for bit the same results): tiles of 256 x 128
 // and 128 x 128 within 2 %, 128 x 64 3 % slower, so those stay there.  What it is for is 128 x 192 (wave tile 64 x 96: five
@@ -96,23 +96,20 @@ __device__ __forceinline__ void tile16(const uint32_t* as, const uint32_t* bs, F
 
 template <class T, class AL, class BL, class Epi>
 __global__ void __launch_bounds__(kThreads, 3)
-gemm16_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int N, int K, int kchunk, SplitGrid grid) {
+gemm16_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int N, int K, FastDiv gx, FastDiv gy) {
   __shared__ __attribute__((aligned(16))) uint32_t As[2][AL::UNITS * 4];
   __shared__ __attribute__((aligned(16))) uint32_t Bs[2][BL::UNITS * 4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % T::WAVES_M, wn = wave / T::WAVES_M;
   const uint32_t total = gridDim.x, L = blockIdx.x, q8 = total >> 3, r8 = total & 7, xcd = L & 7;
   const uint32_t tile = xcd * q8 + min(xcd, r8) + (L >> 3);  // as in xcd_tile
-  const uint32_t rest = fdiv(tile, grid.gy), z = fdiv(rest, grid.gx), g = fdiv(z, grid.nsplit);
-  const int split = (int)(z - g * grid.nsplit.d);
-  const int m0 = (int)(rest - z * grid.gx.d) * T::BM, n0 = (int)(tile - rest * grid.gy.d) * T::BN;
-  const int kbeg = split * kchunk;
-  const int kend = min(K, kbeg + kchunk);
-  const int nt = kend > kbeg ? (kend - kbeg + T::BK - 1) / T::BK : 0;
+  const uint32_t rest = fdiv(tile, gy), g = fdiv(rest, gx);
+  const int m0 = (int)(rest - g * gx.d) * T::BM, n0 = (int)(tile - rest * gy.d) * T::BN;
+  const int nt = (K + T::BK - 1) / T::BK;
 
   AL al(ap, (int)g, tid, m0);
   BL bl(bp, (int)g, tid, n0);
-  ep.set_group((int)g, (int)z);
+  ep.set_group((int)g, (int)g);
 
   v16f acc[T::TM][T::TN];
 #pragma unroll
@@ -127,27 +124,27 @@ gemm16_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int
     const int a_off = (kh * AL::RP + wm * (T::TM * 32) + (lane & 31)) * 4;
     const int b_off = (kh * BL::RP + wn * (T::TN * 32) + (lane & 31)) * 4;
     float4 ra[AL::NL], rb[BL::NL];
-    plan_all(al, kbeg, kend);
-    plan_all(bl, kbeg, kend);
+    plan_all(al, 0, K);
+    plan_all(bl, 0, K);
     al.fetch(ra);
     bl.fetch(rb);
-    plan_all(al, kbeg + T::BK, kend);
-    plan_all(bl, kbeg + T::BK, kend);
+    plan_all(al, T::BK, K);
+    plan_all(bl, T::BK, K);
 #pragma unroll
     for (int s = 0; s < AL::NL; ++s) al.store_step(s, As[0], ra);
 #pragma unroll
     for (int s = 0; s < BL::NL; ++s) bl.store_step(s, Bs[0], rb);
     al.fetch(ra);
     bl.fetch(rb);
-    plan_all(al, kbeg + 2 * T::BK, kend);
-    plan_all(bl, kbeg + 2 * T::BK, kend);
+    plan_all(al, 2 * T::BK, K);
+    plan_all(bl, 2 * T::BK, K);
     __syncthreads();
     for (int t = 0; t < nt; ++t) {
       const int p = t & 1;
       Frags16<AL, T::TM> fa;
       Frags16<BL, T::TN> fb;
       tile16<T, AL, BL>(As[p] + a_off, Bs[p] + b_off, fa, fb, acc, al, bl, As[p ^ 1], Bs[p ^ 1], ra, rb,
-                        kbeg + (t + 3) * T::BK, kend);
+                        (t + 3) * T::BK, K);
       __syncthreads();
     }
   }
