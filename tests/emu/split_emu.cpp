@@ -338,6 +338,8 @@ int main() {
     run_case<S96>(2, 75, 76, 96, 11, 4, 1);   // 17 pixels a row: a k-tile crosses a row's end, and a picture's
     run_case<S96>(3, 41, 45, 20, 7, 2, 3);    // runs of 24, slices that start inside a run and inside a row
     run_case<S128>(1, 22, 36, 132, 5, 1, 2);  // runs of 16, 32 pixels a row
+    run_case<S96>(2, 40, 44, 20, 8, 2, 2);    // rows of 24 floats, none left over behind the whole quads
+    run_case<S96>(2, 38, 42, 100, 6, 2, 1);   // rows of 18 floats, two left over
   }
   conv16_case<Tile<128, 192, 32, 2, 2>, IM2COL_FWD>(3, 7, 64, 384, 2);
   conv16_case<Tile<128, 192, 32, 2, 2>, IM2COL_T1>(3, 7, 384, 128, 2);

@@ -190,3 +190,23 @@ def test_operands_close_to_the_smallest_normal_numbers(lib, size):
     _, dw, _ = net.fc_backward(7, x, w, dy)
     assert rel_l2(dw.cpu().numpy() / size, dy64.T @ x64 / size) <= _bar(batch)
     net.close()
+
+
+@pytest.mark.parametrize("batch,nin,nout", [(1, 8, 8), (2, 260, 12), (4, 2048, 9)])
+def test_few_dense_rows_round_both_operands_to_bf16(lib, batch, nin, nout):
+    """Operands with all their bits: the result is the fp32 sum of the operands rounded to the nearest bf16, ties to even,
+    and neither the unrounded product nor that of values cut off."""
+    def nearest(a):
+        u = a.view(np.uint32).astype(np.uint64)
+        return ((u + 0x7FFF + ((u >> 16) & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32).astype(np.float64)
+
+    def cut(a):
+        return (a.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32).astype(np.float64)
+    net = lib.AlexNet(dict(S.MINI, name="rows", fc=[nin, nout, 4]), batch, precision=1)
+    x, w, b = S.make_normal((batch, nin), 61), S.make_normal((nout, nin), 62), np.zeros(nout, np.float32)
+    x[:, 0] = np.float32(1 + 2.0 ** -8)  # ties: down to 1, up to 1 + 2^-6
+    w[:, 1] = np.float32(1 + 3 * 2.0 ** -8)
+    y = net.fc_forward(7, x, w, b).cpu().numpy()
+    assert rel_l2(y, nearest(x) @ nearest(w).T) <= _bar(nin)
+    assert rel_l2(y, cut(x) @ cut(w).T) > 1e-4 and rel_l2(y, x.astype(np.float64) @ w.astype(np.float64).T) > 1e-4
+    net.close()
