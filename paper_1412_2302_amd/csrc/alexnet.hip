@@ -619,7 +619,9 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     }
     // Fork of the dense-layer update, behind this stage's pooling adjoint: that kernel is bound by bandwidth like the
     // update and would be starved by it.  Early (the update is as long as the rest of a small batch's backward pass)
-    // and held to one workgroup per CU, it costs the products beside it about what it moves.  Step with the fork in
+    // and held to one workgroup per CU, it costs the products beside it about what it moves (at four per CU batch 1, 8 and
+    // 16 take 744, 1188 and 1236 us instead of 664, 1113 and 1149, bf16 batch 4 and 16 888 and 1054 instead of 804 and
+    // 985).  Step with the fork in
     // front of conv5 | conv4 | conv3's weight gradient, us, the best of five runs three times over, all within 0.3 %:
     //   fp32  batch 24 1275 | 1274 | 1311   37 1523 | 1510 | 1528   64 2056 | 2047 | 2058   128 3378 | 3359 | 3346
     //         256 6153 | 6121 | 6087
@@ -758,7 +760,7 @@ static int stage_of(alexnet* n, int32_t layer, Stage** s) {
 extern "C" {
 
 const char* alexnet_last_error(void) { return ax::get_error(); }
-const char* alexnet_version(void) { return "alexnet-hip gfx950 fp32-mfma 0.1"; }
+const char* alexnet_version(void) { return "alexnet-hip gfx950 0.1"; }
 
 int alexnet_profile_begin(void) {
   if (g_profiler) {

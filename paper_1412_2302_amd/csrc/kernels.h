@@ -31,8 +31,8 @@ int launch_wino_dw_batch(const WgradTail& t, hipStream_t st);
 int launch_wgrad_tail(const WgradTail& t, hipStream_t st);
 
 // ---- convolution as implicit GEMM (conv_gemm.hip) ---------------------------
-// Arithmetic of the GEMMs the calling thread launches from now on: 0 = fp32 MFMA, 1 = operands rounded to
-// bf16 (nearest even) on their way into LDS, products accumulated in fp32.  Operands that cannot be read
+// Arithmetic of the GEMMs the calling thread launches from now on: 0 = fp32 operands, 1 = operands rounded to
+// bf16 (nearest even) on their way into LDS; products accumulated in fp32.  Operands that cannot be read
 // 16 bytes at a time keep the fp32 kernels.
 void set_gemm_precision(int bf16);
 // `ws` is split-k scratch of at least the matching *_ws_floats() floats (may be null when that is 0)
