@@ -178,6 +178,9 @@ constexpr double kWinoMinFlops = 2e9;
 // its first layer needs one of them, and with little to hide them under the two streams' meeting costs more (batch 16 341
 // against 320 us, the small nets 147 and 166 against 109 and 134; batch 100, 133 GFLOP, 694 against 713).
 constexpr double kForkFlops = 100e9;
+// The same from which an fp32 handle's dense-layer update starts one stage later (see run_backward): batch 23 of the full
+// net, where the two places cost the same.
+constexpr double kLateUpdateFlops = 30e9;
 static bool winograd_in_pass(const ConvGeom& g) { return 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k >= kWinoMinFlops; }
 
 static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
@@ -331,7 +334,7 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     conv_flops += 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k;
   }
   const bool fp32 = c.precision == ALEXNET_PRECISION_FP32;
-  n->upd_fork_stage = fp32 ? kStages - 2 : kStages - 1;
+  n->upd_fork_stage = fp32 && conv_flops >= kLateUpdateFlops ? kStages - 2 : kStages - 1;
   n->fork_inference = fp32 || conv_flops >= kForkFlops;
   n->fc16 = c.precision == ALEXNET_PRECISION_BF16 && n->fc[0].w_off % 4 == 0;
   for (int j = 0; j < kFc; ++j) n->fc16 = n->fc16 && fc_bf16_stored_ok(n->fc[j].in, n->fc[j].out);
@@ -619,14 +622,14 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     }
     // Fork of the dense-layer update, behind this stage's pooling adjoint: that kernel is bound by bandwidth like the
     // update and would be starved by it.  Early (the update is as long as the rest of a small batch's backward pass)
-    // and held to one workgroup per CU, it costs the products beside it about what it moves (at four per CU batch 1, 8 and
-    // 16 take 744, 1188 and 1236 us instead of 664, 1113 and 1149, bf16 batch 4 and 16 888 and 1054 instead of 804 and
-    // 985).  Step with the fork in
-    // front of conv5 | conv4 | conv3's weight gradient, us, the best of five runs three times over, all within 0.3 %:
-    //   fp32  batch 24 1275 | 1274 | 1311   37 1523 | 1510 | 1528   64 2056 | 2047 | 2058   128 3378 | 3359 | 3346
-    //         256 6153 | 6121 | 6087
+    // and held to one workgroup per CU, it costs the products beside it about what it moves (at four per CU batch 1 and
+    // 16 take 744 and 1236 us instead of 664 and 1149, bf16 batch 4 and 16 888 and 1054 instead of 804 and 985).  Step
+    // with the fork in front of conv5 | conv4 | conv3's weight gradient, us, the best of five runs two or three times
+    // over, all within 0.3 %:
+    //   fp32  batch 1 635 | 665   12 1088 | 1102   16 1122 | 1130   20 1178 | 1180   24 1275 | 1274 | 1311
+    //         37 1523 | 1510 | 1528   64 2056 | 2047 | 2058   128 3378 | 3359 | 3346   256 6153 | 6121 | 6087
     //   bf16  batch 32 1180 | 1190 | 1199   64 1506 | 1499 | 1491   128 2083 | 2091 | 2103   256 3446 | 3413 | 3412
-    // So fp32 takes conv4, never slower than conv5; for bf16 nothing is better than conv5 at every size.
+    // So fp32 takes conv4 from batch 23 up (kLateUpdateFlops); for bf16 nothing is better than conv5 at every size.
     auto fork_update = [&]() -> int {
       AX_HIP(hipEventRecord(n->ev_fc_done, st));
       AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_fc_done, 0));
