@@ -25,12 +25,12 @@
 // Why: v_mfma_f32_32x32x16_bf16 does 1024 flop per SIMD and clock, v_mfma_f32_32x32x2_f32 does 64; six of the
 // former are 16/6 = 2.7 times as fast as the latter for the same contraction.
 //
-// Measured inside a batch-128 training step against the fp32 MFMA kernels: forward products 282 -> 199 us (first layer),
-// 216 -> 170 (second, transformed), 128 -> 93 (third), 97 -> 78 (fourth); weight gradients 353 -> 218, 239 -> 149, 154 ->
-// 104, 131 -> 104, 87 -> 51 us; dense layers, forward, 116 -> 97 us.  4096 x 4608 x 2048 alone: 101 -> 160 TFLOP/s at half
-// the matrix cores' issue rate; the clock falls from 2.2 to 1.7 GHz in such a run, so power bounds it as much as the
-// splitting (104 vector instructions per 24 MFMAs and wave) does.  The products of the transformed layers are short
-// (K = 128 .. 256) and move 3 - 3.8 TB/s as well.
+// Measured inside a batch-128 training step against the fp32 MFMA kernels: forward products 282 -> 205 us (first layer),
+// 216 -> 185 (second, transformed), 128 -> 106 (third), 97 -> 94 (fourth); weight gradients 353 -> 226, 239 -> 153, 154 ->
+// 96, 87 -> 55 us (fifth); dense layers, forward, 116 -> 98 us.  4096 x 4608 x 2048 alone: 101 -> 150 TFLOP/s at half the
+// matrix cores' issue rate; the clock falls from 2.2 to 1.7 GHz in such a run, so power bounds it as much as the splitting
+// (104 vector instructions per 24 MFMAs and wave) does.  The products of the transformed layers are short (K = 128 .. 256)
+// and move 2.5 - 3.5 TB/s as well.
 //
 // The second set of accumulators costs registers: the 128 x 128 tile fits a compute unit twice instead of three times
 // (its LDS with two row-contiguous operands, 55,296 bytes, allows no more anyway), 128 x 96 and 128 x 64 three times.
