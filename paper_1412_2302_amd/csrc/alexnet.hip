@@ -82,12 +82,14 @@ struct Stage {
   size_t w_off, b_off;  // offsets into the flat parameter vector
   float *act, *lrn_out, *pool_out, *dact, *d_lrn, *d_out, *wb;
   float *wino_du, *wino_slices;  // weight-gradient products and their split-k slices (transformed stages)
+  float* wave_slices;   // slices of the weight gradient (wave stages)
   float* wphase;        // weights regrouped by phase for a strided backward-data pass (null when not used)
   // 3x3 unit-stride stages run through the F(4x4, 3x3) transforms: the transformed input of the forward pass
   // (kept for the weight gradient) and the transformed taps of the forward and backward-data passes
   bool wino;     // forward and weight gradient
   bool wino_bx;  // data gradient too
   bool wino_pass;  // in training and inference passes too (see winograd_in_pass)
+  bool wave;       // every product of the stage's passes is a small one (gemm_wave.h), which reads fp32 tensors and wf only
   float *wino_v, *wino_u, *wino_ub;
   float *wrun, *dwrun;  // run-mode copies of the weights and their gradient (null when not used)
   // bf16 handles: copies in bf16 (nearest even) of the stage's GEMM operands -- input, output gradient, and the
@@ -153,6 +155,7 @@ struct alexnet {
   size_t gemm_ws_floats, colsum_ws_floats_;
   int flat;  // flatten size feeding fc6
   int upd_fork_stage;   // stage of the backward pass beside which the dense-layer update starts on the side stream
+  bool fork_train;      // training steps make the weights' forms and update the dense layers on the side stream
   bool fork_inference;  // inference passes make the weights' forms on the side stream
   // The dense layers hold 96 % of the parameters and finish their backward pass first: their update, which is
   // bound by memory bandwidth, runs on this stream under the convolution backward pass, which is not.
@@ -270,6 +273,7 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
 
   // ---- workspace ----
   Arena a{base, 0};
+  const bool bf = c.precision == ALEXNET_PRECISION_BF16;
   const size_t in_elems = (size_t)c.batch * c.crop_h * c.crop_w * c.in_c;
   for (int s = 0; s < kSlots; ++s) {
     n->input[s] = a.take<float>(in_elems);
@@ -294,8 +298,9 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     s.wphase = conv_phase_mode(s.g) ? a.take<float>(conv_phase_w_floats(s.g)) : nullptr;
     s.wrun = conv_run_mode(s.g) ? a.take<float>(conv_run_w_floats(s.g)) : nullptr;
     s.dwrun = conv_run_mode(s.g) ? a.take<float>(conv_run_w_floats(s.g)) : nullptr;
-    s.b16 = c.precision == ALEXNET_PRECISION_BF16 && conv_bf16_stored_ok(s.g) && s.w_off % 4 == 0;
-    s.r16 = c.precision == ALEXNET_PRECISION_BF16 && !s.b16 && conv_run16_ok(s.g) && s.w_off % 4 == 0;
+    s.wave = wave_conv_fwd_ok(s.g, bf) && (i == 0 ? wave_conv_bwd_weight_ok(s.g, bf) : wave_conv_bwd_ok(s.g, bf));
+    s.b16 = c.precision == ALEXNET_PRECISION_BF16 && !s.wave && conv_bf16_stored_ok(s.g) && s.w_off % 4 == 0;
+    s.r16 = c.precision == ALEXNET_PRECISION_BF16 && !s.wave && !s.b16 && conv_run16_ok(s.g) && s.w_off % 4 == 0;
     s.x16 = s.b16 ? a.take<uint16_t>(s.g.in_elems()) : s.r16 ? a.take<uint16_t>(conv_run16_x_elems(s.g)) : nullptr;
     s.x16_own = s.x16;
     s.dy16 = s.b16 ? a.take<uint16_t>(ae) : nullptr;
@@ -304,6 +309,8 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     s.wino = use_winograd(c, s.g) && s.w_off % 4 == 0 && s.b_off % 4 == 0;
     s.wino_bx = s.wino && wino_bwd_data_ok(s.g);
     s.wino_pass = s.wino && winograd_in_pass(s.g);
+    if (s.wino_pass) s.wave = false;
+    s.wave_slices = s.wave && wave_conv_bwd_weight_ws_floats(s.g) ? a.take<float>(wave_conv_bwd_weight_ws_floats(s.g)) : nullptr;
     s.wino_v = s.wino ? a.take<float>(wino_v_floats(s.g)) : nullptr;
     s.wino_u = s.wino ? a.take<float>(wino_u_floats(s.g)) : nullptr;
     s.wino_ub = s.wino_bx ? a.take<float>(wino_u_floats(s.g)) : nullptr;
@@ -337,7 +344,15 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
   n->upd_fork_stage = fp32 && conv_flops >= kLateUpdateFlops ? kStages - 2 : kStages - 1;
   n->fork_inference = fp32 || conv_flops >= kForkFlops;
   n->fc16 = c.precision == ALEXNET_PRECISION_BF16 && n->fc[0].w_off % 4 == 0;
-  for (int j = 0; j < kFc; ++j) n->fc16 = n->fc16 && fc_bf16_stored_ok(n->fc[j].in, n->fc[j].out);
+  bool fc_wave = true;
+  for (int j = 0; j < kFc; ++j) {
+    const Dense& f = n->fc[j];
+    n->fc16 = n->fc16 && fc_bf16_stored_ok(f.in, f.out);
+    fc_wave = fc_wave && wave_fc_fwd_ok(c.batch, f.in, f.out, bf) && wave_fc_bwd_ok(c.batch, f.in, f.out, bf);
+  }
+  n->fc16 = n->fc16 && !fc_wave;
+  n->fork_train = !fc_wave;
+  for (int i = 0; i < kStages; ++i) n->fork_train = n->fork_train || !n->st[i].wave;
   n->fcw16 = n->fc16 ? a.take<uint16_t>(n->n_weights - n->fc[0].w_off) : nullptr;
   n->flat16 = n->fc16 ? a.take<uint16_t>((size_t)c.batch * n->flat) : nullptr;
   for (int j = 0; j < kFc; ++j) {
@@ -414,7 +429,7 @@ static int stage_fwd(alexnet* n, Stage& s, const float* x, const float* wf, cons
     if (!taps_ready) AX_TRY(launch_run16_pack(wf, s.wf16, s.g.k, s.g.Cin, (int)(conv_run16_w_elems(s.g) / ((size_t)s.g.k * s.g.Cout)), s.g.Cout, st));
     return launch_conv_fwd_run16(s.g, s.x16, s.wf16, bias, relu, y, n->gemm_ws, st, y16);
   }
-  if (s.wrun) AX_TRY(launch_conv_run_pack(s.g, wf, s.wrun, st));
+  if (s.wrun && !wave_conv_fwd_ok(s.g, n->cfg.precision == ALEXNET_PRECISION_BF16)) AX_TRY(launch_conv_run_pack(s.g, wf, s.wrun, st));
   return launch_conv_fwd(s.g, x, wf, s.wrun, bias, relu, y, n->gemm_ws, st, nullptr, nullptr, y16);
 }
 // have_v: the forward pass of the same minibatch left its form of x in place (s.wino_v, the transform of x; s.x16,
@@ -569,22 +584,15 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     const float* x = j == 0 ? n->st[kStages - 1].out() : n->fc[j - 1].act;
     const uint16_t* x16 = j == 0 ? n->flat16 : n->fc[j - 1].act16;
     const uint16_t* w16 = n->fc16 ? n->fcw16 + (f.w_off - n->fc[0].w_off) : nullptr;
-    {
-      ProfContext pc(f.lab[2]);
-      AX_TRY(launch_fc_bwd_weight(c.batch, f.in, f.out, x, f.dz, n->grads + f.w_off, st, x16, f.dz16));
-      AX_TRY(colsum_batch_add(bias_sums, f.dz, c.batch, f.out, n->grads + f.b_off, n->colsum_ws, &bias_ws_used));
-    }
+    AX_TRY(colsum_batch_add(bias_sums, f.dz, c.batch, f.out, n->grads + f.b_off, n->colsum_ws, &bias_ws_used));
+    Stage& last = n->st[kStages - 1];
+    // fc(j-1) output is ReLU+dropout: it is positive exactly where the gradient passes
+    const float* gate = j > 0 ? n->fc[j - 1].act : last.plain() ? last.act : nullptr;
     ProfContext pc(f.lab[3]);
-    if (j > 0) {
-      // fc(j-1) output is ReLU+dropout: it is positive exactly where the gradient passes
-      AX_TRY(launch_fc_bwd_data(c.batch, f.in, f.out, f.dz, n->params + f.w_off, n->fc[j - 1].act, n->fc[j - 1].dz,
-                                n->gemm_ws, st, f.dz16, w16, n->fc[j - 1].dz16));
-    } else {
-      Stage& last = n->st[kStages - 1];
-      AX_TRY(launch_fc_bwd_data(c.batch, f.in, f.out, f.dz, n->params + f.w_off, last.plain() ? last.act : nullptr,
-                                last.d_out, n->gemm_ws, st, f.dz16, w16, nullptr));
-    }
+    AX_TRY(launch_fc_bwd(c.batch, f.in, f.out, x, f.dz, n->params + f.w_off, gate, j > 0 ? n->fc[j - 1].dz : last.d_out,
+                         n->grads + f.w_off, n->gemm_ws, st, x16, f.dz16, w16, j > 0 ? n->fc[j - 1].dz16 : nullptr));
   }
+  bool waited = false;      // for the side stream's forms of the weights
   bool dy16_ready = false;  // the kernel that made this stage's output gradient also left its bf16 copy in s.dy16
   for (int i = kStages - 1; i >= 0; --i) {
     Stage& s = n->st[i];
@@ -639,6 +647,23 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     };
     if (early_update && i == n->upd_fork_stage) AX_TRY(fork_update());
     const float* x = i == 0 ? in : n->st[i - 1].out();
+    if (s.wave) {  // both gradients at once, from the forward weights
+      const bool bf = conv_bwd_weight_bf16(s.g, x, s.dact);
+      if (!bias_done)
+        AX_TRY(colsum_batch_add(bias_sums, s.dact, s.g.P(), s.g.Cout, n->grads + s.b_off, n->colsum_ws, &bias_ws_used));
+      ProfContext pc(s.lab[i > 0 ? 3 : 2]);
+      dy16_ready = false;
+      if (i == 0) {
+        AX_TRY(launch_wave_conv_bwd_weight(s.g, x, s.dact, n->grads + s.w_off, s.wave_slices, bf, st, &wgrad_tail));
+        continue;
+      }
+      Stage& prev = n->st[i - 1];
+      uint16_t* below16 = (prev.plain() && prev.b16) ? prev.dy16 : nullptr;
+      AX_TRY(launch_wave_conv_bwd(s.g, x, s.dact, n->params + s.w_off, prev.plain() ? prev.act : nullptr, prev.d_out, below16,
+                                  n->grads + s.w_off, s.wave_slices, bf, st, &wgrad_tail));
+      dy16_ready = below16 != nullptr;
+      continue;
+    }
     {
       ProfContext pc(s.lab[2]);
       AX_TRY(stage_bwd_weight(n, s, x, s.dact, n->grads + s.w_off, true, st, true, &wgrad_tail, dy16_ready));
@@ -649,7 +674,8 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       ProfContext pc(s.lab[3]);
       Stage& prev = n->st[i - 1];
       if (early_update) {  // the side stream re-packed the weights during the forward pass
-        if (i == kStages - 1) AX_HIP(hipStreamWaitEvent(st, n->ev_wb_done, 0));
+        if (!waited) AX_HIP(hipStreamWaitEvent(st, n->ev_wb_done, 0));
+        waited = true;
       } else {
         AX_TRY(launch_conv_weight_wb(n->params + s.w_off, s.wb, s.g.Cout, s.g.cg(), s.g.k, s.g.groups, st));
       }
@@ -933,13 +959,14 @@ int alexnet_train_step(alexnet_t* n, int32_t slot, const int32_t* d_labels, uint
   // the dense-layer weights start at a 16-byte boundary of the flat vector in every AlexNet-like shape; if not,
   // one update at the end
   const size_t fc_begin = n->fc[0].w_off;
-  const bool early = fc_begin % 4 == 0 && n->n_weights % 4 == 0;
+  const bool early = n->fork_train && fc_begin % 4 == 0 && n->n_weights % 4 == 0;
   if (early) {
     // the backward-data packing of the convolution weights depends on the weights only: it runs on the side
     // stream under the forward pass
     AX_TRY(fork_forward_weights(n, true, S(stream)));
     for (int i = 1; i < kStages; ++i) {
       Stage& s = n->st[i];
+      if (s.wave) continue;
       ProfContext pc(s.lab[3]);
       AX_TRY(launch_conv_weight_wb(n->params + s.w_off, s.wb, s.g.Cout, s.g.cg(), s.g.k, s.g.groups, n->upd_stream));
       if (s.wino_bx && s.wino_pass) AX_TRY(launch_wino_filter_bwd(s.g, s.wb, s.wino_ub, n->upd_stream));

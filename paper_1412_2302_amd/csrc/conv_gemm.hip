@@ -3,6 +3,7 @@
 // time), fp32 matrix instructions (gemm.h: everything else in fp32) and bf16 operands (gemm_bf16.h, gemm16.h).
 #include <algorithm>
 
+#include "fc_epilogue.h"
 #include "gemm16.h"
 #include "kernels.h"
 
@@ -57,7 +58,7 @@ static thread_local int g_bf16 = 0;
 void set_gemm_precision(int bf16) { g_bf16 = bf16 ? 1 : 0; }
 
 static GemmPlan plan_gemm(int M, int N, int K, int groups, double out_bytes, int max_s, bool bf = false,
-                          bool allow48 = false, int max_chunk = 0, bool allow256 = false) {
+                          bool allow48 = false, int max_chunk = 0, bool allow256 = false, double* t_out = nullptr) {
   const TileOption* opts = bf ? kTileOptionsBf : kTileOptions;
   const int nopts = bf ? (allow256 ? 3 : 2) : (allow48 ? 4 : 3);
   GemmPlan best{128, 128, 1, ceil_div(K, opts[0].bk) * opts[0].bk};
@@ -81,9 +82,9 @@ static GemmPlan plan_gemm(int M, int N, int K, int groups, double out_bytes, int
       }
     }
   }
+  if (t_out) *t_out = best_t;
   return best;
 }
-
 
 // Algorithmic flops of the launch being prepared (2 x multiply-adds of the
 // operation, not of the padded GEMM); 0 means "use 2*M*N*K".
@@ -319,7 +320,7 @@ __global__ void slab_finish_kernel(const float* __restrict__ ws, int ns, int gro
   if (gate && !(gate[i] > 0.f)) v = 0.f;
   out[i] = v;
 }
-static int launch_slab_finish(const float* ws, int ns, int groups, long M, int N, const float* bias, int relu,
+int launch_slab_finish(const float* ws, int ns, int groups, long M, int N, const float* bias, int relu,
                               const float* gate, float* out, hipStream_t st) {
   const size_t total = (size_t)M * groups * N;
   KernelScope ks("slab_finish", 0, (double)total * 4.0 * (ns + 1 + (gate ? 1 : 0)), st);
@@ -340,11 +341,6 @@ typedef Tile<64, 128, kBKs, 2, 2> S64m;
 static const TileOption kTileOptionsSplit[] = {
     {128, 128, kBKs, 0.94}, {128, 96, kBKs, 0.89}, {128, 64, kBKs, 0.80},
     {64, 128, kBKs, 0.81}};  // the last one for dense layers on at most 64 rows, where a 128-row tile is half empty
-// Reductions of fewer than eight values stay on the fp32 matrix instructions.  Those round once per two products, K/2
-// times; here, whatever the length, the sum of the two sets of accumulators is rounded, and the dropped terms count as
-// much as one rounding again.  A single product is to be correctly rounded (K = 1: 0.43 units of 2^-24 against 0.42, at
-// worst 1.5 against 1.0); from K = 4 on the split products are the closer ones at worst too (2.0 against 2.6).
-constexpr int kSplitMinK = 8;
 // Cheapest (tile, slices) for a launch of the split kernel, as plan_gemm(), with one difference: these kernels fetch
 // one k-tile ahead only, and a workgroup that has its compute unit to itself waits for memory about half the time (a
 // weight gradient of 192 x 128 x 2048 x 72: 105 us in 216 workgroups, see fill), so slices are worth having until two
@@ -410,11 +406,11 @@ static int by_tile_split(const GemmPlan& p, const DenseParams& a, const DensePar
 // The first layer in run mode: a k-tile passes at most one run's end and one row's end of the loaders SplitRun and
 // SplitRunT.
 static inline bool split_run_ok(const ConvGeom& c) { return run_mode(c) && run_len(c) >= kBKs && c.Wo >= kBKs && c.Cout % 4 == 0; }
-static GemmPlan split_run_fwd_plan(const ConvGeom& c) {
-  return plan_split((int)c.P(), c.Cout, run_k(c), 1, (double)c.out_elems() * 4, 8);
+static GemmPlan split_run_fwd_plan(const ConvGeom& c, double* t_out = nullptr) {
+  return plan_split((int)c.P(), c.Cout, run_k(c), 1, (double)c.out_elems() * 4, 8, t_out);
 }
-static GemmPlan split_run_bwdw_plan(const ConvGeom& c) {
-  return plan_split(c.k * c.k * c.Cin, c.Cout, (int)c.P(), 1, (double)c.w_elems() * 4, 256);
+static GemmPlan split_run_bwdw_plan(const ConvGeom& c, double* t_out = nullptr) {
+  return plan_split(c.k * c.k * c.Cin, c.Cout, (int)c.P(), 1, (double)c.w_elems() * 4, 256, t_out);
 }
 // A of either product by tile, B = packed weights or output gradient
 template <template <int> class ALT, class AP, class Epi>
@@ -438,17 +434,18 @@ static inline bool split_fwd_ok(const ConvGeom& c) {
 static inline bool split_bwdw_ok(const ConvGeom& c) {
   return pointwise(c) && c.cg() % 4 == 0 && c.og() % 4 == 0 && c.P() >= kSplitMinK;
 }
-static GemmPlan split_fwd_plan(const ConvGeom& c) {
+static GemmPlan split_fwd_plan(const ConvGeom& c, double* t_out = nullptr) {
   const GemmDims d = fwd_dims(c);
-  return plan_split(d.M, d.N, d.K, d.groups, (double)c.out_elems() * 4, 8);
+  return plan_split(d.M, d.N, d.K, d.groups, (double)c.out_elems() * 4, 8, t_out);
 }
 // weight gradient: the operands may change places, whichever way the tiles cover the result with less padding
-static GemmPlan split_bwdw_plan(const ConvGeom& c, bool* swapped) {
+static GemmPlan split_bwdw_plan(const ConvGeom& c, bool* swapped, double* t_out = nullptr) {
   const GemmDims d = bwdw_dims(c);
   double t[2];
   const GemmPlan p = plan_split(d.M, d.N, d.K, d.groups, (double)c.w_elems() * 4, 256, &t[0]);
   const GemmPlan q = plan_split(d.N, d.M, d.K, d.groups, (double)c.w_elems() * 4, 256, &t[1]);
   *swapped = t[1] < 0.98 * t[0];
+  if (t_out) *t_out = t[*swapped];
   return *swapped ? q : p;
 }
 
@@ -463,20 +460,50 @@ static int by_tile_tap(const GemmPlan& p, const Im2colParams& a, const DensePara
 }
 
 // t48: the 48-column tile may be used (its loaders need a k-tile of 32 inside one tap)
-static GemmPlan run16_fwd_plan(const ConvGeom& c);
+static GemmPlan run16_fwd_plan(const ConvGeom& c, double* t_out = nullptr);
 // t256: the 256-row tile may be used (bf16-stored operands)
-static GemmPlan fwd_plan(const ConvGeom& c, bool run, bool bf, bool t48 = false, bool t256 = false) {
+static GemmPlan fwd_plan(const ConvGeom& c, bool run, bool bf, bool t48 = false, bool t256 = false,
+                         double* t_out = nullptr) {
   const GemmDims d = fwd_dims(c);
-  return plan_gemm(d.M, d.N, run ? run_k(c) : d.K, d.groups, (double)c.out_elems() * 4, 8, bf, t48, 0, t256);
+  return plan_gemm(d.M, d.N, run ? run_k(c) : d.K, d.groups, (double)c.out_elems() * 4, 8, bf, t48, 0, t256, t_out);
 }
-static GemmPlan bwdd_plan(const ConvGeom& c, bool bf, bool t48 = false, bool t256 = false) {
+static GemmPlan bwdd_plan(const ConvGeom& c, bool bf, bool t48 = false, bool t256 = false, double* t_out = nullptr) {
   const GemmDims d = bwdd_dims(c);
-  return plan_gemm(d.M, d.N, d.K, d.groups, (double)c.in_elems() * 4, 8, bf, t48, 0, t256);
+  return plan_gemm(d.M, d.N, d.K, d.groups, (double)c.in_elems() * 4, 8, bf, t48, 0, t256, t_out);
 }
-static GemmPlan bwdw_plan(const ConvGeom& c, bool run, bool bf, bool table = false) {
+static GemmPlan bwdw_plan(const ConvGeom& c, bool run, bool bf, bool table = false, double* t_out = nullptr) {
   const GemmDims d = bwdw_dims(c);
   return plan_gemm(run ? run_k(c) : d.M, d.N, d.K, d.groups, (double)(run ? run_w_elems(c) : c.w_elems()) * 4, 256,
-                   bf, false, table ? kMaxTableK : 0);
+                   bf, false, table ? kMaxTableK : 0, false, t_out);
+}
+// what the kernels of this file take for a product, by their planners
+double tile_seconds_fwd(const ConvGeom& c, bool bf) {
+  double t = 0;
+  if (bf && run16_mode(c))
+    run16_fwd_plan(c, &t);
+  else if (!bf && split_fwd_ok(c))
+    split_fwd_plan(c, &t);
+  else if (!bf && split_run_ok(c))
+    split_run_fwd_plan(c, &t);
+  else
+    fwd_plan(c, run_mode(c) && c.Cout % 4 == 0, bf, false, false, &t);
+  return t;
+}
+double tile_seconds_bwd_data(const ConvGeom& c, bool bf) {
+  double t = 0;
+  bwdd_plan(c, bf, false, false, &t);
+  return t;
+}
+double tile_seconds_bwd_weight(const ConvGeom& c, bool bf) {
+  double t = 0;
+  bool swapped;
+  if (!bf && split_bwdw_ok(c))
+    split_bwdw_plan(c, &swapped, &t);
+  else if (!bf && split_run_ok(c))
+    split_run_bwdw_plan(c, &t);
+  else
+    bwdw_plan(c, run_mode(c), bf, false, &t);
+  return t;
 }
 // scratch sizes cover every variant (generic / run mode, fp32 / bf16) of the op
 size_t conv_fwd_ws_floats(const ConvGeom& c) {
@@ -488,11 +515,13 @@ size_t conv_fwd_ws_floats(const ConvGeom& c) {
   if (run16_mode(c)) ns = std::max(ns, run16_fwd_plan(c).ns);
   if (split_fwd_ok(c)) ns = std::max(ns, split_fwd_plan(c).ns);
   if (split_run_ok(c)) ns = std::max(ns, split_run_fwd_plan(c).ns);
+  ns = std::max(ns, wave_conv_fwd_slices(c));
   return ns > 1 ? (size_t)ns * c.out_elems() : 0;
 }
 size_t conv_bwd_data_ws_floats(const ConvGeom& c) {
   const int ns = std::max(std::max(bwdd_plan(c, false).ns, bwdd_plan(c, true).ns),
-                          std::max(bwdd_plan(c, false, true).ns, bwdd_plan(c, true, false, true).ns));
+                          std::max(std::max(bwdd_plan(c, false, true).ns, bwdd_plan(c, true, false, true).ns),
+                                   wave_conv_bwd_data_slices(c)));
   return ns > 1 ? (size_t)ns * c.in_elems() : 0;
 }
 size_t conv_bwd_weight_ws_floats(const ConvGeom& c) {
@@ -509,7 +538,7 @@ size_t conv_bwd_weight_ws_floats(const ConvGeom& c) {
     if (ns > 1) n = std::max(n, (size_t)ns * c.w_elems());
   }
   if (split_run_ok(c)) n = std::max(n, (size_t)split_run_bwdw_plan(c).ns * c.w_elems());
-  return n;
+  return std::max(n, wave_conv_bwd_weight_ws_floats(c));
 }
 
 // ---- run mode helpers: padded copies of the forward weights / of their gradient ----
@@ -557,6 +586,9 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
     const float* y; uint16_t* y16; size_t n; hipStream_t st; bool pending;
   } copy{y, y16, (size_t)c.out_elems(), st, false};
   auto finish = [&copy](int rc) { return rc == ALEXNET_OK && copy.pending ? launch_to_bf16(copy.y, copy.y16, copy.n, copy.st) : rc; };
+  if (wave_conv_fwd_ok(c, g_bf16))
+    return launch_wave_conv_fwd(c, x, wf, bias, relu, y, y16, ws,
+                                g_bf16 && (run_mode(c) ? c.Cout % 4 == 0 : fwd_A_vec(c, x) && fwd_B_vec(c, wf)), st);
   const bool run = wrun && run_mode(c) && c.Cout % 4 == 0;
   AlgoFlops af(conv_flops(c), conv_bytes(c));
   GemmDims d = fwd_dims(c);
@@ -636,9 +668,9 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
 bool conv_run16_ok(const ConvGeom& c) { return run16_mode(c); }
 size_t conv_run16_x_elems(const ConvGeom& c) { return run16_mode(c) ? (size_t)run16_x_elems(c) : 0; }
 size_t conv_run16_w_elems(const ConvGeom& c) { return run16_mode(c) ? (size_t)run16_w_elems(c) : 0; }
-static GemmPlan run16_fwd_plan(const ConvGeom& c) {
+static GemmPlan run16_fwd_plan(const ConvGeom& c, double* t_out) {
   const GemmDims d = fwd_dims(c);
-  return plan_gemm(d.M, d.N, run16_k(c), 1, (double)c.out_elems() * 4, 8, true, false, 0, true);
+  return plan_gemm(d.M, d.N, run16_k(c), 1, (double)c.out_elems() * 4, 8, true, false, 0, true, t_out);
 }
 struct ConvRun16 {
   template <class T, class Epi>
@@ -717,6 +749,8 @@ int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, co
     copy.pending = dx16 != nullptr;
     return finish(launch_conv_bwd_data_phases(c, dy, wf, wphase, dx, st));
   }
+  if (wave_conv_bwd_data_ok(c, g_bf16))
+    return launch_wave_conv_bwd_data(c, dy, wf, gate, dx, dx16, ws, g_bf16 && bwdd_A_vec(c, dy) && bwdd_B_vec(c, wf), st);
   const GemmDims d = bwdd_dims(c);
   AlgoFlops af(conv_flops(c), conv_bytes(c));
   if (g_bf16 && dy16 && wb16 && conv_bf16_stored_ok(c) && aligned16(dy16) && aligned16(wb16)) {
@@ -770,10 +804,18 @@ int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, co
   return finish(launch_slab_finish(ws, p.ns, d.groups, d.M, d.N, nullptr, 0, gate, dx, st));
 }
 
+bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy) {
+  return g_bf16 && (run_mode(c) || bwdw_A_vec(c, x)) && bwdw_B_vec(c, dy);
+}
+
 // defer_ns (generic layout only): the split-k slices are left in ws, [group][slice][slab], and their number is
 // returned there for the caller to add them up later (1: the result is in dwf already)
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
                            hipStream_t st, int* defer_ns, const uint16_t* x16, const uint16_t* dy16) {
+  if (wave_conv_bwd_weight_ok(c, g_bf16)) {
+    if (defer_ns) *defer_ns = 1;
+    return launch_wave_conv_bwd_weight(c, x, dy, dwf, ws, conv_bwd_weight_bf16(c, x, dy), st);
+  }
   const bool run = dwrun && run_mode(c) && bwdw_B_vec(c, dy);
   AlgoFlops af(conv_flops(c), conv_bytes(c));
   GemmDims d = bwdw_dims(c);
@@ -845,7 +887,7 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
 // workgroups and finish in a second kernel that also applies the activation.
 // bf16 products, and fp32 ones that gemm_split.h does not take, use the 128 x 128 tile (fc_split); the others fc_plan.
 
-static int fc_split(int B, int N, int K, int* kchunk, bool bf) {
+static int fc_split(int B, int N, int K, int* kchunk, bool bf, double* t_out = nullptr) {
   const int bk = bf ? kBKbf : kBK;
   const int ktiles = ceil_div(K, bk);
   const long tiles = (long)ceil_div(B, 128) * ceil_div(N, 128);
@@ -865,9 +907,21 @@ static int fc_split(int B, int N, int K, int* kchunk, bool bf) {
     }
   }
   *kchunk = best_per * bk;
+  if (t_out) *t_out = best_t;
   return best;
 }
-static GemmPlan fc_plan(int B, int N, int K) { return plan_split(B, N, K, 1, (double)B * N * 4, 64, nullptr, B <= 64); }
+static GemmPlan fc_plan(int B, int N, int K, double* t_out = nullptr) {
+  return plan_split(B, N, K, 1, (double)B * N * 4, 64, t_out, B <= 64);
+}
+double tile_seconds_dense(int M, int N, int K, bool bf) {
+  double t = 0;
+  int kc;
+  if (bf)
+    fc_split(M, N, K, &kc, true, &t);
+  else
+    fc_plan(M, N, K, &t);
+  return t;
+}
 size_t fc_ws_floats(int B, int in, int out) {
   int kc;
   size_t n = 0;
@@ -1008,27 +1062,6 @@ static int launch_fc_rows(int B, int in, int out, const float* x, const float* w
   return ALEXNET_OK;
 }
 
-// An unsliced dense product finishes itself: y = act(v + bias), as fc_fwd_finish_kernel does behind slices.
-struct EpiFcAct {
-  static constexpr bool kTransposed = true;
-  float* y;
-  long ldc;
-  FcAct act;
-  uint16_t* y16;  // may be null
-  AX_HD void set_group(int /*g*/, int /*z*/) {}
-  __device__ void apply(int m, int n, float v) const {
-    const size_t i = (size_t)m * ldc + n;
-    if (act.bias) v += act.bias[n];
-    if (act.relu) v = v > 0.f ? v : 0.f;
-    if (act.dropout && !dropout_keep(act.key, act.tag, i, act.thresh24)) v = 0.f;
-    y[i] = v * act.scale;
-    if (y16) store_bf16(y16 + i, v * act.scale);
-  }
-  __device__ void apply4(int m, int n, float4 v) const {
-    apply(m, n, v.x); apply(m, n + 1, v.y); apply(m, n + 2, v.z); apply(m, n + 3, v.w);
-  }
-};
-
 static inline bool vec_ok(const float* p, long ld) { return aligned16(p) && ld % 4 == 0; }
 
 // Which kernels take a dense fp32 product, and its tile and slices
@@ -1065,6 +1098,7 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
   const bool vec = vec_ok(x, in) && vec_ok(w, in), bf = g_bf16 && vec;
   if (vec && fc_rows_ok(B, in))
     return bf ? launch_fc_rows<true>(B, in, out, x, w, act, y, y16, st) : launch_fc_rows<false>(B, in, out, x, w, act, y, y16, st);
+  if (wave_fc_fwd_ok(B, in, out, g_bf16)) return launch_wave_fc_fwd(B, in, out, x, w, act, y, y16, bf, st);
   const bool s16 = bf && x16 && w16 && fc_bf16_stored_ok(in, out) && aligned16(x16) && aligned16(w16);
   const GemmPlan p = fc_product_plan(B, out, in, vec, bf);
   const int ns = p.ns, kchunk = p.kchunk;
@@ -1118,6 +1152,17 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
                      dx16);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
+}
+
+int launch_fc_bwd(int B, int in, int out, const float* x, const float* dy, const float* w, const float* gate, float* dx,
+                  float* dw, float* ws, hipStream_t st, const uint16_t* x16, const uint16_t* dy16, const uint16_t* w16,
+                  uint16_t* dx16) {
+  if (wave_fc_bwd_ok(B, in, out, g_bf16)) {
+    const bool bf = g_bf16 && vec_ok(dy, out) && vec_ok(w, in) && vec_ok(x, in);
+    return launch_wave_fc_bwd(B, in, out, x, dy, w, gate, dx, dx16, dw, bf, st);
+  }
+  AX_TRY(launch_fc_bwd_weight(B, in, out, x, dy, dw, st, x16, dy16));
+  return launch_fc_bwd_data(B, in, out, dy, w, gate, dx, ws, st, dy16, w16, dx16);
 }
 
 int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy, float* dw, hipStream_t st,

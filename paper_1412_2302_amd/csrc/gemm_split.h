@@ -55,6 +55,11 @@ namespace ax {
 
 constexpr int kPlanes = 3;
 constexpr int kBKs = 16;  // depth of a k-tile: one MFMA step
+// Reductions of fewer than eight values stay on the fp32 matrix instructions.  Those round once per two products, K/2
+// times; here, whatever the length, the sum of the two sets of accumulators is rounded, and the dropped terms count as
+// much as one rounding again.  A single product is to be correctly rounded (K = 1: 0.43 units of 2^-24 against 0.42, at
+// worst 1.5 against 1.0); from K = 4 on the split products are the closer ones at worst too (2.0 against 2.6).
+constexpr int kSplitMinK = 8;
 
 AX_HD float bf_lo(uint32_t w) {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -8,7 +8,7 @@
 namespace ax {
 
 // The tail of the weight gradient of a transformed stage -- adding up the split-k slices of the products, then
-// the transform back to taps -- can be put off to the end of a backward pass and run for all such stages in two
+// the transform back to taps --, or the slices of a small product (gemm_wave.h; total = 0), can be put off to the end of a backward pass and run for all such stages in two
 // launches: each of those kernels is too short to fill the chip on its own.  The slices and the products then
 // need memory of their own until the tail runs.
 constexpr int kMaxWgradJobs = 5;
@@ -121,6 +121,49 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
                        uint16_t* dx16 = nullptr);
 int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy, float* dw, hipStream_t st,
                          const uint16_t* x16 = nullptr, const uint16_t* dy16 = nullptr);
+
+// both gradients: dw, and dx as launch_fc_bwd_data gives it
+int launch_fc_bwd(int B, int in, int out, const float* x, const float* dy, const float* w, const float* gate, float* dx,
+                  float* dw, float* ws, hipStream_t st, const uint16_t* x16, const uint16_t* dy16, const uint16_t* w16,
+                  uint16_t* dx16);
+
+// Seconds that the tile kernels take for a product, by their planners; bf: in a handle with bf16 products
+double tile_seconds_fwd(const ConvGeom& c, bool bf);
+double tile_seconds_bwd_data(const ConvGeom& c, bool bf);
+double tile_seconds_bwd_weight(const ConvGeom& c, bool bf);
+double tile_seconds_dense(int M, int N, int K, bool bf);
+// out[m][g*N + n] = post(the sum of ns slabs ws[g][slice][m][n])
+int launch_slab_finish(const float* ws, int ns, int groups, long M, int N, const float* bias, int relu, const float* gate,
+                       float* out, hipStream_t st);
+
+// ---- small products (wave_gemm.hip) ------------------------------------------
+// ..._ok: the product is one of those, by its sizes and the handle's precision.  They read fp32 tensors and the packed forward
+// weights only; bf in a launch: both operands are rounded to bf16.  conv_bwd_weight_bf16: whether the calling thread's
+// precision has that so for a weight gradient.  ws as for the launches they stand in for.
+bool wave_conv_fwd_ok(const ConvGeom& c, bool bf);
+bool wave_conv_bwd_data_ok(const ConvGeom& c, bool bf);
+bool wave_conv_bwd_weight_ok(const ConvGeom& c, bool bf);
+bool wave_conv_bwd_ok(const ConvGeom& c, bool bf);  // both gradients in one launch
+bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy);
+int wave_conv_fwd_slices(const ConvGeom& c);
+int wave_conv_bwd_data_slices(const ConvGeom& c);
+size_t wave_conv_bwd_weight_ws_floats(const ConvGeom& c);
+int launch_wave_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const float* bias, int relu, float* y,
+                         uint16_t* y16, float* ws, bool bf, hipStream_t st);
+int launch_wave_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, const float* gate, float* dx,
+                              uint16_t* dx16, float* ws, bool bf, hipStream_t st);
+// slices: the weight gradient's scratch, wave_conv_bwd_weight_ws_floats() floats; tail: they are added up by
+// launch_wgrad_tail() and are this stage's own until then
+int launch_wave_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* slices, bool bf,
+                                hipStream_t st, WgradTail* tail = nullptr);
+int launch_wave_conv_bwd(const ConvGeom& c, const float* x, const float* dy, const float* wf, const float* gate, float* dx,
+                         uint16_t* dx16, float* dwf, float* slices, bool bf, hipStream_t st, WgradTail* tail);
+bool wave_fc_fwd_ok(int B, int in, int out, bool bf);
+bool wave_fc_bwd_ok(int B, int in, int out, bool bf);
+int launch_wave_fc_fwd(int B, int in, int out, const float* x, const float* w, const FcAct& act, float* y, uint16_t* y16,
+                       bool bf, hipStream_t st);
+int launch_wave_fc_bwd(int B, int in, int out, const float* x, const float* dy, const float* w, const float* gate, float* dx,
+                       uint16_t* dx16, float* dw, bool bf, hipStream_t st);
 
 // ---- bandwidth-bound kernels (ops.hip) --------------------------------------
 int launch_fill(float* p, size_t n, float v, hipStream_t st);
