@@ -686,6 +686,7 @@ int launch_conv_fwd_run16(const ConvGeom& c, const uint16_t* x4, const uint16_t*
     set_error("conv run16: geometry or alignment does not allow it");
     return ALEXNET_EINVAL;
   }
+  if (first16_ok(c)) return launch_first16(c, x4, wk, bias, relu, y, y16, st);
   AlgoFlops af(conv_flops(c), conv_bytes(c));
   GemmDims d = fwd_dims(c);
   d.K = run16_k(c);

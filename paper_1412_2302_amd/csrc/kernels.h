@@ -62,6 +62,10 @@ size_t conv_run16_x_elems(const ConvGeom& c);
 size_t conv_run16_w_elems(const ConvGeom& c);
 int launch_conv_fwd_run16(const ConvGeom& c, const uint16_t* x4, const uint16_t* wk, const float* bias, int relu,
                           float* y, float* ws, hipStream_t st, uint16_t* y16 = nullptr);
+// the same with the weights and a piece of the picture in LDS (first_layer.hip), for the geometries that fit there
+bool first16_ok(const ConvGeom& c);
+int launch_first16(const ConvGeom& c, const uint16_t* x4, const uint16_t* wk, const float* bias, int relu, float* y,
+                   uint16_t* y16, hipStream_t st);
 // Strided, ungrouped, ungated backward-data runs by phases when `wphase` (conv_phase_w_floats() floats of
 // scratch) is given; it then reads the forward weights wf instead of wb.
 bool conv_phase_mode(const ConvGeom& c);
