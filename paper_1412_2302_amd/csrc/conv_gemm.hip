@@ -1,10 +1,11 @@
 // Convolution forward, backward-data and backward-weight as implicit GEMMs, and the dense layers, on three cores: fp32
 // operands on the bf16 matrix cores (gemm_split.h: pointwise, first and dense layers that can be read 16 bytes at a
-// time), fp32 matrix instructions (gemm.h: everything else in fp32) and bf16 operands (gemm_bf16.h, gemm16.h).
+// time), fp32 matrix instructions (gemm.h: everything else in fp32) and bf16 operands (gemm_bf16.h, gemm16.h, gemm_direct.h).
 #include <algorithm>
 
 #include "fc_epilogue.h"
 #include "gemm16.h"
+#include "gemm_direct.h"
 #include "kernels.h"
 
 namespace ax {
@@ -270,6 +271,96 @@ static int launch_tile192(const Im2colParams& a, const DenseParams& b, const Epi
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
+// ---- operands straight to LDS (gemm_direct.h) ----
+// Workgroups on the busiest compute unit run in rounds of as many as it holds; a round of n takes first[n-1] + each[n-1] * the
+// megaflops of a tile microseconds.  Fitted to (tile, workgroups, MFLOP a tile, us): 128 x 64: 2028 37.7 97.8, 2028 28.3 81.8,
+// 510 37.7 29.1, 510 18.9 19.1; 128 x 128: 1014 75.5 87.8, 676 56.6 59.5, 255 75.5 31.8, 170 56.6 24.6, 340 56.6 33.1; 192 x
+// 128: 452 169.9 82.3, 452 84.9 49.6, 171 113 39.2, 114 84.9 31.3.
+struct DirectTile {
+  int bm, bn, occ;
+  double first[3], each[3];
+};
+static const DirectTile kDirectTiles[] = {{128, 64, 3, {7, 9.1, 12.2}, {0.32, 0.53, 0.585}},
+                                          {128, 128, 2, {3, 8, 0}, {0.38, 0.476, 0}},
+                                          {192, 128, 2, {7.5, 17, 0}, {0.28, 0.385, 0}}};
+struct DirectPlan {
+  int tile, ns, per;  // per: k-tiles of a slice
+};
+static DirectPlan plan_direct(const GemmDims& d, double out_bytes, double* t_out = nullptr) {
+  DirectPlan best{0, 1, ceil_div(d.K, kBKd)};
+  double best_t = 1e30;
+  const int ktiles = ceil_div(d.K, kBKd);
+  for (int o = 0; o < 3; ++o) {
+    const DirectTile& to = kDirectTiles[o];
+    const long tiles = (long)ceil_div(d.M, to.bm) * ceil_div(d.N, to.bn) * d.groups;
+    for (int s = 1; s <= 8 && s <= ktiles; ++s) {
+      const int per = ceil_div(ktiles, s);
+      if (ceil_div(ktiles, per) != s || (s > 1 && per < 4)) continue;
+      const int c = ceil_div(tiles * s, 256), rest = c % to.occ;
+      const double f = 2e-6 * to.bm * to.bn * (double)per * kBKd;
+      double t = c / to.occ * (to.first[to.occ - 1] + to.each[to.occ - 1] * f);
+      if (rest) t += to.first[rest - 1] + to.each[rest - 1] * f;
+      t *= 1e-6;
+      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + kSecondLaunch;
+      if (t < 0.98 * best_t) {
+        best_t = t;
+        best = DirectPlan{o, s, per};
+      }
+    }
+  }
+  if (t_out) *t_out = best_t + 2e-6;
+  return best;
+}
+// Channels per group that are no multiple of 64 cost instructions for every k-tile: there the tiles of gemm_bf16.h have to be
+// a fifth slower by their planner (second layer, 48 channels: at batch 256 six full rounds of 256-row tiles, which stay; at 37,
+// 100 and 128 three rounds, the last one part empty: inference 374 and 610 us, training 1943; here 360, 586, 1917).
+static bool direct_pays(const GemmDims& d, int Cg, int taps, double out_bytes) {
+  if (taps > kDirectTaps) return false;
+  if (Cg % kBKd == 0) return true;
+  double direct, tiles;
+  plan_direct(d, out_bytes, &direct);
+  plan_gemm(d.M, d.N, d.K, d.groups, out_bytes, 8, true, false, 0, d.N % 128 == 0, &tiles);
+  return 1.2 * direct < tiles;
+}
+static bool direct_fwd_ok(const ConvGeom& c) {
+  const GemmDims d = fwd_dims(c);
+  return conv_bf16_stored_ok(c) && !(c.cg() % kBKbf == 0 && tile192_ok(d)) &&
+         direct_pays(d, c.cg(), c.k * c.k, (double)c.out_elems() * 4);
+}
+static bool direct_bwd_data_ok(const ConvGeom& c) {
+  return conv_bf16_stored_ok(c) && direct_pays(bwdd_dims(c), c.og(), c.k * c.k, (double)c.in_elems() * 4);
+}
+template <int BM, int BN, int WM, int WN, int MINB, int MODE, class Epi>
+static int launch_direct_tile(const DirectPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e,
+                              const GemmDims& d, hipStream_t st) {
+  DirectJob j;
+  j.a = a;
+  j.b = b;
+  j.M = d.M;
+  j.N = d.N;
+  j.K = d.K;
+  j.tiles_per_slice = p.per;
+  const int gx = ceil_div(d.M, BM), gy = ceil_div(d.N, BN);
+  j.gx = make_fastdiv((uint32_t)gx);
+  j.gy = make_fastdiv((uint32_t)gy);
+  j.ns = make_fastdiv((uint32_t)p.ns);
+  KernelScope ks("gemm_bf16", g_algo_flops > 0 ? g_algo_flops : 2.0 * d.M * d.N * (double)d.K * d.groups,
+                 gemm_bytes(d.M, d.N, d.K, d.groups), st);
+  const dim3 grid((unsigned)((long)gx * gy * d.groups * p.ns));
+  if (a.Cg % kBKd == 0)
+    hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WM, WN, MINB, true, MODE, Epi>), grid, dim3(kThreads), 0, st, j, e);
+  else
+    hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, WM, WN, MINB, false, MODE, Epi>), grid, dim3(kThreads), 0, st, j, e);
+  AX_LAUNCH_CHECK();
+  return ALEXNET_OK;
+}
+template <int MODE, class Epi>
+static int launch_direct(const DirectPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e, const GemmDims& d,
+                         hipStream_t st) {
+  if (p.tile == 0) return launch_direct_tile<128, 64, 4, 1, 3, MODE, Epi>(p, a, b, e, d, st);
+  if (p.tile == 1) return launch_direct_tile<128, 128, 2, 2, 2, MODE, Epi>(p, a, b, e, d, st);
+  return launch_direct_tile<192, 128, 2, 2, 2, MODE, Epi>(p, a, b, e, d, st);
+}
 template <class F, class Epi>
 static int by_tile_16(const GemmPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e, const GemmDims& d,
                       hipStream_t st) {
@@ -481,6 +572,8 @@ double tile_seconds_fwd(const ConvGeom& c, bool bf) {
   double t = 0;
   if (bf && run16_mode(c))
     run16_fwd_plan(c, &t);
+  else if (bf && direct_fwd_ok(c))
+    plan_direct(fwd_dims(c), (double)c.out_elems() * 4, &t);
   else if (!bf && split_fwd_ok(c))
     split_fwd_plan(c, &t);
   else if (!bf && split_run_ok(c))
@@ -491,7 +584,10 @@ double tile_seconds_fwd(const ConvGeom& c, bool bf) {
 }
 double tile_seconds_bwd_data(const ConvGeom& c, bool bf) {
   double t = 0;
-  bwdd_plan(c, bf, false, false, &t);
+  if (bf && direct_bwd_data_ok(c))
+    plan_direct(bwdd_dims(c), (double)c.in_elems() * 4, &t);
+  else
+    bwdd_plan(c, bf, false, false, &t);
   return t;
 }
 double tile_seconds_bwd_weight(const ConvGeom& c, bool bf) {
@@ -515,13 +611,15 @@ size_t conv_fwd_ws_floats(const ConvGeom& c) {
   if (run16_mode(c)) ns = std::max(ns, run16_fwd_plan(c).ns);
   if (split_fwd_ok(c)) ns = std::max(ns, split_fwd_plan(c).ns);
   if (split_run_ok(c)) ns = std::max(ns, split_run_fwd_plan(c).ns);
+  if (direct_fwd_ok(c)) ns = std::max(ns, plan_direct(fwd_dims(c), (double)c.out_elems() * 4).ns);
   ns = std::max(ns, wave_conv_fwd_slices(c));
   return ns > 1 ? (size_t)ns * c.out_elems() : 0;
 }
 size_t conv_bwd_data_ws_floats(const ConvGeom& c) {
-  const int ns = std::max(std::max(bwdd_plan(c, false).ns, bwdd_plan(c, true).ns),
+  int ns = std::max(std::max(bwdd_plan(c, false).ns, bwdd_plan(c, true).ns),
                           std::max(std::max(bwdd_plan(c, false, true).ns, bwdd_plan(c, true, false, true).ns),
                                    wave_conv_bwd_data_slices(c)));
+  if (direct_bwd_data_ok(c)) ns = std::max(ns, plan_direct(bwdd_dims(c), (double)c.in_elems() * 4).ns);
   return ns > 1 ? (size_t)ns * c.in_elems() : 0;
 }
 size_t conv_bwd_weight_ws_floats(const ConvGeom& c) {
@@ -595,6 +693,14 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
   if (g_bf16 && x16 && wf16 && !run && conv_bf16_stored_ok(c) && aligned16(x16) && aligned16(wf16)) {
     const Im2colParams a = im2col16(fwd_A(c, nullptr), x16);
     const DenseParams b = fwd_B16k(c, wf16);
+    if (direct_fwd_ok(c)) {
+      const DirectPlan p = plan_direct(d, (double)c.out_elems() * 4);
+      if (p.ns == 1)
+        return launch_direct<IM2COL_FWD>(p, a, b, EpiBiasAct{y, c.Cout, bias, relu, c.og(), 0, 0, y16}, d, st);
+      copy.pending = y16 != nullptr;
+      AX_TRY(launch_direct<IM2COL_FWD>(p, a, b, EpiSlab{ws, (long)d.M * d.N, d.N, nullptr}, d, st));
+      return finish(launch_slab_finish(ws, p.ns, d.groups, d.M, d.N, bias, relu, nullptr, y, st));
+    }
     const GemmPlan p = fwd_plan(c, false, true, false, d.N % 128 == 0);  // 256-row tiles only without padded columns
     const bool tap = tap_ok(a, d, kBKbf);
     if (tap && tile192_ok(d))
@@ -757,6 +863,13 @@ int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, co
   if (g_bf16 && dy16 && wb16 && conv_bf16_stored_ok(c) && aligned16(dy16) && aligned16(wb16)) {
     const Im2colParams a = im2col16(bwdd_A(c, nullptr), dy16);
     const DenseParams b = bwdd_B16k(c, wb16);
+    if (direct_bwd_data_ok(c)) {
+      const DirectPlan p = plan_direct(d, (double)c.in_elems() * 4);
+      if (p.ns == 1) return launch_direct<IM2COL_T1>(p, a, b, EpiGate{dx, c.Cin, gate, c.cg(), 0, 0, dx16}, d, st);
+      copy.pending = dx16 != nullptr;
+      AX_TRY(launch_direct<IM2COL_T1>(p, a, b, EpiSlab{ws, (long)d.M * d.N, d.N, nullptr}, d, st));
+      return finish(launch_slab_finish(ws, p.ns, d.groups, d.M, d.N, nullptr, 0, gate, dx, st));
+    }
     const GemmPlan p = bwdd_plan(c, true, false, d.N % 128 == 0);
     const bool tap = tap_ok(a, d, kBKbf);
     if (tap && tile192_ok(d))
