@@ -82,6 +82,7 @@ struct Stage {
   size_t w_off, b_off;  // offsets into the flat parameter vector
   float *act, *lrn_out, *pool_out, *dact, *d_lrn, *d_out, *wb;
   float *wino_du, *wino_slices;  // weight-gradient products and their split-k slices (transformed stages)
+  float* direct_slices;  // weight-gradient slices of a stage on bf16 tensors (weight_direct.hip), kept until the end of the pass
   float* wave_slices;   // slices of the weight gradient (wave stages)
   float* wphase;        // weights regrouped by phase for a strided backward-data pass (null when not used)
   // 3x3 unit-stride stages run through the F(4x4, 3x3) transforms: the transformed input of the forward pass
@@ -305,6 +306,9 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     s.x16_own = s.x16;
     s.dy16 = s.b16 ? a.take<uint16_t>(ae) : nullptr;
     s.wf16 = s.b16 ? a.take<uint16_t>(s.g.w_elems()) : s.r16 ? a.take<uint16_t>(conv_run16_w_elems(s.g)) : nullptr;
+    s.direct_slices = s.b16 && direct_bwd_weight_ok(s.g) && direct_bwd_weight_slices(s.g) > 1
+                          ? a.take<float>((size_t)direct_bwd_weight_slices(s.g) * s.g.w_elems())
+                          : nullptr;
     s.wb16 = s.b16 ? a.take<uint16_t>(s.g.w_elems()) : nullptr;
     s.wino = use_winograd(c, s.g) && s.w_off % 4 == 0 && s.b_off % 4 == 0;
     s.wino_bx = s.wino && wino_bwd_data_ok(s.g);
@@ -446,6 +450,11 @@ static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* d
   if (b16_usable(s, x, dy)) {
     if (!have_v) AX_TRY(launch_to_bf16(x, s.x16, (size_t)s.g.in_elems(), st));
     if (!dy16_ready) AX_TRY(launch_to_bf16(dy, s.dy16, (size_t)s.g.out_elems(), st));
+    if (tail && s.direct_slices) {
+      int ns = 1;
+      AX_TRY(launch_conv_bwd_weight(s.g, x, dy, dwf, nullptr, s.direct_slices, st, &ns, s.x16, s.dy16));
+      return add_weight_slices(s.g, s.direct_slices, ns, dwf, tail, st);
+    }
     return launch_conv_bwd_weight(s.g, x, dy, dwf, nullptr, n->gemm_ws, st, nullptr, s.x16, s.dy16);
   }
   return launch_conv_bwd_weight(s.g, x, dy, dwf, s.dwrun, n->gemm_ws, st);

@@ -245,14 +245,6 @@ struct ConvGatherTap16 {
         a, b, e, d.M, d.N, d.K, kchunk, ns, d.groups, st);
   }
 };
-struct ConvWeightGradTable16 {
-  template <class T, class Epi>
-  static int go(const Im2colParams& a, const DenseParams& b, const Epi& e, const GemmDims& d, int kchunk, int ns,
-                hipStream_t st) {
-    return launch_tile_bf<T, Im2colRowTable16<T::BM, T::BK>, DenseRowInner16<T::BN, T::BK>, Epi>(
-        a, b, e, d.M, d.N, d.K, kchunk, ns, d.groups, st, (size_t)std::min(kchunk, d.K) * sizeof(PixelEntry));
-  }
-};
 // 192 columns per group and enough 128 x 192 tiles for two workgroups per CU (at batch 64, 172 tiles, the 128 x 64 tile of
 // gemm_bf16.h is the faster one, 33 against 38 us; at batch 256, 676 tiles, 83 against 107)
 typedef Tile<128, 192, kBKbf, 2, 2> B192;
@@ -636,6 +628,7 @@ size_t conv_bwd_weight_ws_floats(const ConvGeom& c) {
     if (ns > 1) n = std::max(n, (size_t)ns * c.w_elems());
   }
   if (split_run_ok(c)) n = std::max(n, (size_t)split_run_bwdw_plan(c).ns * c.w_elems());
+  if (direct_bwd_weight_ok(c)) n = std::max(n, (size_t)direct_bwd_weight_slices(c) * c.w_elems());
   return std::max(n, wave_conv_bwd_weight_ws_floats(c));
 }
 
@@ -963,6 +956,12 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
     if (defer_ns) *defer_ns = 1;
     return launch_reduce_slabs_unpack(p.ns > 1 ? ws : dwrun, p.ns, slab, c.k, kc / 4 * 4, kc, c.Cout, dwf, st);
   }
+  if (bf && !run && x16 && dy16 && direct_bwd_weight_ok(c) && aligned16(x16) && aligned16(dy16)) {
+    const int ns = direct_bwd_weight_slices(c);
+    AX_TRY(launch_direct_bwd_weight(c, x16, dy16, ns > 1 ? ws : dwf, st));
+    if (defer_ns) *defer_ns = ns;
+    return defer_ns || ns == 1 ? ALEXNET_OK : launch_reduce_slabs(ws, ns, (long)d.M * d.N, d.groups, dwf, st);
+  }
   bool table = av && bv && table_ok(a, d) && (!bf || d.K % kBKbf == 0);
   GemmPlan p = bwdw_plan(c, run, bf, table);
   if (table && p.kchunk > kMaxTableK) {  // no split count within reach keeps the k range inside the table
@@ -972,10 +971,7 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
   const long slab = (long)d.M * d.N;
   float* out = run ? dwrun : dwf;
   EpiSlab ep{p.ns > 1 ? ws : out, slab, d.N, nullptr};
-  const bool s16 = bf && table && !run && x16 && dy16 && conv_bf16_stored_ok(c) && aligned16(x16) && aligned16(dy16);
-  if (s16)
-    AX_TRY((by_tile_bf<ConvWeightGradTable16>(p, im2col16(a, x16), dense16(bwdw_B(c, dy), dy16), ep, d, st)));
-  else if (bf && table)
+  if (bf && table)
     AX_TRY((by_tile_bf<ConvWeightGradTableBf>(p, a, bwdw_B(c, dy), ep, d, st)));
   else if (bf)
     AX_TRY((by_tile_bf<ConvWeightGradBf>(p, a, bwdw_B(c, dy), ep, d, st)));

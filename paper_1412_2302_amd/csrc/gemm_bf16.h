@@ -424,6 +424,7 @@ struct DenseRowInner16 {
   }
 };
 
+// (no launcher takes this one: weight_direct.hip has the weight gradients; the CPU emulation checks it with the others)
 // transpose of the implicit im2col (rows = (r,s,c), k = pixels: backward-weight) over a bf16 tensor, through the
 // workgroup's pixel table (see Im2colRowTable): whole k-tiles, at most 31 taps; a unit = eight channels of one tap
 // at two consecutive pixels

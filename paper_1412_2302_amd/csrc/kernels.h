@@ -8,7 +8,7 @@
 namespace ax {
 
 // The tail of the weight gradient of a transformed stage -- adding up the split-k slices of the products, then
-// the transform back to taps --, or the slices of a small product (gemm_wave.h; total = 0), can be put off to the end of a backward pass and run for all such stages in two
+// the transform back to taps --, or the slices of a direct one (gemm_wave.h, weight_direct.hip; total = 0), can be put off to the end of a backward pass and run for all such stages in two
 // launches: each of those kernels is too short to fill the chip on its own.  The slices and the products then
 // need memory of their own until the tail runs.
 constexpr int kMaxWgradJobs = 5;
@@ -146,6 +146,12 @@ int launch_slab_finish(const float* ws, int ns, int groups, long M, int N, const
 // precision has that so for a weight gradient.  ws as for the launches they stand in for.
 bool wave_conv_fwd_ok(const ConvGeom& c, bool bf);
 bool wave_conv_bwd_data_ok(const ConvGeom& c, bool bf);
+// dwf = the sum of ns slices of a weight gradient, [group][slice][slab], now or (tail) at the end of the pass; ns = 1: nothing to do
+int add_weight_slices(const ConvGeom& c, const float* slices, int ns, float* dwf, WgradTail* tail, hipStream_t st);
+// weight gradients over operands stored as bf16 (weight_direct.hip): out gets ns slabs of every group, [group][slice][slab]
+bool direct_bwd_weight_ok(const ConvGeom& c);
+int direct_bwd_weight_slices(const ConvGeom& c);
+int launch_direct_bwd_weight(const ConvGeom& c, const uint16_t* x16, const uint16_t* dy16, float* out, hipStream_t st);
 bool wave_conv_bwd_weight_ok(const ConvGeom& c, bool bf);
 bool wave_conv_bwd_ok(const ConvGeom& c, bool bf);  // both gradients in one launch
 bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy);

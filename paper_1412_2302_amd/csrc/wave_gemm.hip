@@ -194,7 +194,7 @@ static auto bwd_weight_job(const ConvGeom& c, const float* x, const float* dy, f
                                                      EpiSlab{out, (long)d.M * d.N, d.N, nullptr, 0}, d.M, d.N, d.K,
                                                      d.groups, ns);
 }
-static int add_slices(const ConvGeom& c, const float* slices, int ns, float* dwf, WgradTail* tail, hipStream_t st) {
+int add_weight_slices(const ConvGeom& c, const float* slices, int ns, float* dwf, WgradTail* tail, hipStream_t st) {
   const GemmDims d = bwdw_dims(c);
   const long slab = (long)d.M * d.N;
   if (ns == 1) return ALEXNET_OK;
@@ -235,7 +235,7 @@ int launch_wave_conv_bwd_weight(const ConvGeom& c, const float* x, const float* 
   const double fl = conv_work(c), by = conv_moved(c);
   AX_TRY((bf ? launch_job(bwd_weight_job<true>(c, x, dy, out, ns), fl, by, st)
              : launch_job(bwd_weight_job<false>(c, x, dy, out, ns), fl, by, st)));
-  return add_slices(c, slices, ns, dwf, tail, st);
+  return add_weight_slices(c, slices, ns, dwf, tail, st);
 }
 int launch_wave_conv_bwd(const ConvGeom& c, const float* x, const float* dy, const float* wf, const float* gate, float* dx,
                          uint16_t* dx16, float* dwf, float* slices, bool bf, hipStream_t st, WgradTail* tail) {
@@ -245,7 +245,7 @@ int launch_wave_conv_bwd(const ConvGeom& c, const float* x, const float* dy, con
   const EpiGate ep = gate_of(c, gate, dx, dx16);
   AX_TRY((bf ? launch_jobs(bwd_weight_job<true>(c, x, dy, out, ns), bwd_data_job<true>(c, dy, wf, ep, 1), fl, by, st)
              : launch_jobs(bwd_weight_job<false>(c, x, dy, out, ns), bwd_data_job<false>(c, dy, wf, ep, 1), fl, by, st)));
-  return add_slices(c, slices, ns, dwf, tail, st);
+  return add_weight_slices(c, slices, ns, dwf, tail, st);
 }
 
 // ------------------------------------------------------------ dense layers ---

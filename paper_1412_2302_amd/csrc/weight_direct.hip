@@ -1,0 +1,264 @@
+// Weight gradients of the convolutions of bf16 handles, over operands stored as bf16 (see gemm_bf16.h).
+//
+// The reduction runs over pixels, along which neither operand is contiguous: in LDS they stand as in memory, rows of 64
+// channels per pixel, while a matrix instruction wants eight pixels of one channel in a lane.  gemm_bf16.h's kernel, which this
+// one replaces, fetched two pixels into registers, interleaved them and wrote pairs to LDS, to read a fragment in four words.
+// Here the loads go to LDS directly (gemm_direct.h: two stages of 64 k, a builtin for the wait), and ds_read_b64_tr_b16
+// transposes on the way out.
+//
+// LDS: blocks of 64 rows (channels of a tap, output channels), a row of 128 bytes per pixel, eight 16-byte slots; slot s of
+// pixel k holds octet s ^ 4*((k >> 1) & 1), so that the four pixels x 64 bytes that half a wave reads lie in different banks.
+// A load fills eight pixels of one block; its lane keeps one octet of rows, hence one tap, whatever the pixel.  A wave decodes
+// the 64 pixels of its next four k-tiles at once, one per lane, and passes origin and mask of the taps outside on by shuffles:
+// no table, so no limit on the length of a slice and no k-tile left to other kernels.
+//
+// Product alone, batch 256 and 64, us: second layer 144 and 39 (797 TFLOP/s at 256), third 90 and 29, fourth 84 and 27, fifth
+// 46 and 20.  In a training pass, gemm_bf16.h's kernel | here: batch 256 second layer 248 | 137, third 136 | 86, fourth 137 |
+// 87, fifth, beside the dense layers' update, 106 | 84; batch 64 70 | 45, 67 | 32, 97 | 77, 49 | 32.  What bounds it: at 128 x
+// 128 the reads from LDS (a kilobyte for each matrix instruction of a wave, as much as LDS gives), at 192 x 128 power.
+//
+// A training pass adds up the slices of all layers at its end, see WgradTail: the sums of a layer, in a launch of their own
+// beside the dense layers' update, took 14 to 450 us, by where that kernel's workgroups had found room.
+#include <algorithm>
+
+#include "gemm_direct.h"
+#include "kernels.h"
+
+namespace ax {
+
+// One weight-gradient product: C[(r,s,c)][o] = sum over pixels of x[pixel + tap][c] * dy[pixel][o]
+struct DirectTJob {
+  Im2colParams a;
+  DenseParams b;
+  int M, N, K, tiles_per_slice;
+  FastDiv gx, gy, ns;
+};
+
+typedef short v4s __attribute__((ext_vector_type(4)));
+// Sixteen lanes read a block of 4 k x 16 rows (lane i: four rows from 4*(i%4) at k i/4); lane i gets row i at the four k.
+__device__ __forceinline__ v4s read_transposed(const char* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int MINB, class Epi>
+__global__ void __launch_bounds__(256, MINB) gemm_direct_t_kernel(DirectTJob j, Epi ep) {
+  static_assert(WAVES_M * WAVES_N == 4 && BM % 64 == 0 && BN % 64 == 0, "four waves, blocks of 64");
+  constexpr int TM = BM / (32 * WAVES_M), TN = BN / (32 * WAVES_N);
+  constexpr int CA = BM / 64, CB = BN / 64;  // blocks of 64 rows
+  constexpr int kBlock = kBKd * 8;           // units of a block: 64 k of eight octets
+  __shared__ __attribute__((aligned(16))) v4u stage0[(CA + CB) * kBlock];
+  __shared__ __attribute__((aligned(16))) v4u stage1[(CA + CB) * kBlock];
+  const Im2colParams& ap = j.a;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+  const uint32_t total = gridDim.x, L = blockIdx.x, q8 = total >> 3, r8 = total & 7, xcd = L & 7;
+  const uint32_t tile = xcd * q8 + min(xcd, r8) + (L >> 3);  // as in xcd_tile
+  const uint32_t rest = fdiv(tile, j.gy), z = fdiv(rest, j.gx), g = fdiv(z, j.ns);
+  const int m0 = (int)(rest - z * j.gx.d) * BM, n0 = (int)(tile - rest * j.gy.d) * BN;
+  const int first = (int)(z - g * j.ns.d) * j.tiles_per_slice;
+  const int nt = min((j.K + kBKd - 1) / kBKd - first, j.tiles_per_slice);
+  const BufView av = make_view(ap.x, ap.bytes);
+  const BufView bv = make_view(reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(j.b.p) + (long)g * j.b.gstride),
+                               j.b.bytes - (uint32_t)(g * j.b.gstride * 2));
+
+  // A load brings the octets of eight pixels in one block: lane = (pixel, slot).  A wave loads pixels 16*wave .. 16*wave + 15.
+  const int sub = lane >> 3, oct = (lane & 7) ^ (4 * ((sub >> 1) & 1));
+  uint32_t tapoff[CA], tapmask[CA], bcol[CB];
+#pragma unroll
+  for (int b = 0; b < CA; ++b) {
+    const int m = m0 + 64 * b + 8 * oct;
+    const bool in = m < j.M;
+    const TapCoord t = decode_tap(in ? m : 0, ap);
+    tapoff[b] = (((uint32_t)t.r * (uint32_t)ap.W + (uint32_t)t.s) * (uint32_t)ap.Ctot + (uint32_t)t.c +
+                 (uint32_t)((int)g * ap.c_stride_g)) * 2u;
+    tapmask[b] = in ? 1u << (t.r * ap.kw + t.s) : 0x80000000u;
+  }
+#pragma unroll
+  for (int b = 0; b < CB; ++b) {
+    const int n = n0 + 64 * b + 8 * oct;
+    bcol[b] = n < j.N ? (uint32_t)n * 2u : kOob;  // less than 2^31 is added: stays outside
+  }
+  ep.set_group((int)g, (int)z);
+
+  uint32_t pbase = 0, poutside = 0;  // of this lane's pixel: 16*wave + lane % 16 of k-tile t + lane / 16, t a multiple of four
+  auto load = [&](v4u* st, int t) {
+    const int k0 = (first + t) * kBKd + 16 * wave;
+    if ((t & 3) == 0) {
+      const int p = k0 + (lane >> 4) * kBKd + (lane & 15);
+      const bool in = p < ap.P;
+      const PixCoord c = decode_pixel(in ? p : 0, ap);
+      const int y0 = c.y * ap.stride - ap.pad, x0 = c.x * ap.stride_x - ap.pad_x;
+      pbase = row_base<IM2COL_FWD, 2>(ap, c.n, y0, x0, 0);
+      poutside = in ? ~taps_inside<IM2COL_FWD>(ap, y0, x0) | 0x80000000u : 0xffffffffu;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int from = (t & 3) * 16 + i * 8 + sub;
+      const uint32_t base = (uint32_t)__shfl((int)pbase, from), outside = (uint32_t)__shfl((int)poutside, from);
+#pragma unroll
+      for (int b = 0; b < CA; ++b)
+        load_lds16(av, st + b * kBlock + (2 * wave + i) * 64, outside & tapmask[b] ? kOob : base + tapoff[b], 0);
+      const uint32_t brow = (uint32_t)(k0 + i * 8 + sub) * (uint32_t)j.b.ld * 2u;  // past the last pixel: outside
+#pragma unroll
+      for (int b = 0; b < CB; ++b) load_lds16(bv, st + (CA + b) * kBlock + (2 * wave + i) * 64, brow + bcol[b], 0);
+    }
+  };
+
+  v16f acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int jj = 0; jj < TN; ++jj)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][jj][r] = 0.f;
+  // Element e of a lane's eight values is k = 8*(e/4) + 4*kh + e%4 of a step, in both operands.  Bytes of lane (k, rows) in a
+  // block, for its first and its second 32 rows:
+  const int l16 = lane & 15, kk = l16 >> 2, half_row = ((lane >> 4) & 1) * 2 + ((l16 & 3) >> 1);
+  const int lane_k = (4 * (lane >> 5) + kk) * 128 + (l16 & 1) * 8;
+  const int at0 = lane_k + (half_row ^ (4 * (kk >> 1))) * 16, at1 = at0 ^ 64;
+  int a_at[TM], b_at[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int blk = wm * TM + i;
+    a_at[i] = (blk >> 1) * (kBlock * 16) + (blk & 1 ? at1 : at0);
+  }
+#pragma unroll
+  for (int jj = 0; jj < TN; ++jj) {
+    const int blk = wn * TN + jj;
+    b_at[jj] = (CA + (blk >> 1)) * (kBlock * 16) + (blk & 1 ? at1 : at0);
+  }
+  auto multiply = [&](const v4u* st) {
+    const char* s = reinterpret_cast<const char*>(st);
+    struct Two {
+      v4s lo, hi;
+    };
+#pragma unroll
+    for (int ks = 0; ks < kBKd / 16; ++ks) {
+      v8bf a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        a[i] = __builtin_bit_cast(v8bf, Two{read_transposed(s + a_at[i] + ks * 2048), read_transposed(s + a_at[i] + ks * 2048 + 1024)});
+#pragma unroll
+      for (int jj = 0; jj < TN; ++jj)
+        b[jj] = __builtin_bit_cast(v8bf, Two{read_transposed(s + b_at[jj] + ks * 2048), read_transposed(s + b_at[jj] + ks * 2048 + 1024)});
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int jj = 0; jj < TN; ++jj)
+          acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[jj], acc[i][jj], 0, 0, 0);
+    }
+  };
+  if (nt > 0) {
+    load(stage0, 0);
+    int t = 0;
+    for (; t + 2 < nt; t += 2) {
+      direct_barrier();
+      load(stage1, t + 1);
+      multiply(stage0);
+      direct_barrier();
+      load(stage0, t + 2);
+      multiply(stage1);
+    }
+    direct_barrier();
+    if (t + 1 < nt) {
+      load(stage1, t + 1);
+      multiply(stage0);
+      direct_barrier();
+      multiply(stage1);
+    } else {
+      multiply(stage0);
+    }
+  }
+
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int jj = 0; jj < TN; ++jj) {
+      const int n = n0 + wn * (TN * 32) + jj * 32 + (lane & 31);
+      if (n >= j.N) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + wm * (TM * 32) + i * 32 + acc_row(lane, r);
+        if (m < j.M) ep.apply(m, n, acc[i][jj][r]);
+      }
+    }
+}
+
+// Time of a product in slices, as plan_direct() has it: workgroups on the busiest compute unit in rounds of as many as it
+// holds, n of them first[n-1] + each[n-1] * MFLOP of a tile's slice.  Fitted to 330 launches (second to fifth layer, batch 64
+// and 256, 1 to 48 slices), which it meets within 7 %.  Adding the slabs up takes 2.6 us and, right behind the product, 8 TB/s; a training pass adds up all
+// layers' slabs at its end, when they have gone to memory and back: 3 TB/s.
+struct DirectTTile {
+  int bm, bn, occ;
+  double first[3], each[3];
+};
+static const DirectTTile kDirectTTiles[] = {{128, 64, 3, {0.9, 4.0, 3.0}, {0.636, 0.765, 0.97}},
+                                            {128, 128, 2, {4.0, 4.5, 0}, {0.388, 0.50, 0}},
+                                            {192, 128, 2, {5.2, 7.6, 0}, {0.328, 0.437, 0}}};
+constexpr int kDirectTSlices = 64;
+struct DirectTPlan {
+  int tile, ns, per;  // per: k-tiles of a slice
+};
+static DirectTPlan plan_direct_t(const GemmDims& d) {
+  const int ktiles = ceil_div(d.K, kBKd);
+  DirectTPlan best{0, 1, ktiles};
+  double best_t = 1e30;
+  for (int o = 0; o < 3; ++o) {
+    const DirectTTile& to = kDirectTTiles[o];
+    const long tiles = (long)ceil_div(d.M, to.bm) * ceil_div(d.N, to.bn) * d.groups;
+    for (int s = 1; s <= kDirectTSlices && s <= ktiles; ++s) {
+      const int per = ceil_div(ktiles, s);
+      if (ceil_div(ktiles, per) != s) continue;
+      const int c = ceil_div(tiles * s, 256), rest = c % to.occ;
+      const double f = 2e-6 * to.bm * to.bn * (double)per * kBKd;
+      double t = c / to.occ * (to.first[to.occ - 1] + to.each[to.occ - 1] * f);
+      if (rest) t += to.first[rest - 1] + to.each[rest - 1] * f;
+      if (s > 1) t += 2.6 + (s + 1) * 4e-6 * d.M * d.N * (double)d.groups / 3;
+      if (t < best_t) {
+        best_t = t;
+        best = DirectTPlan{o, s, per};
+      }
+    }
+  }
+  return best;
+}
+bool direct_bwd_weight_ok(const ConvGeom& c) { return conv_bf16_stored_ok(c) && c.k * c.k < kDirectTaps; }
+int direct_bwd_weight_slices(const ConvGeom& c) { return plan_direct_t(bwdw_dims(c)).ns; }
+template <int BM, int BN, int WM, int WN, int MINB, class Epi>
+static int launch_direct_t_tile(const DirectTPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e,
+                                const GemmDims& d, double bytes, hipStream_t st) {
+  DirectTJob j;
+  j.a = a;
+  j.b = b;
+  j.M = d.M;
+  j.N = d.N;
+  j.K = d.K;
+  j.tiles_per_slice = p.per;
+  const int gx = ceil_div(d.M, BM), gy = ceil_div(d.N, BN);
+  j.gx = make_fastdiv((uint32_t)gx);
+  j.gy = make_fastdiv((uint32_t)gy);
+  j.ns = make_fastdiv((uint32_t)p.ns);
+  KernelScope ks("gemm_bf16", 2.0 * d.M * d.N * (double)d.K * d.groups,
+                 bytes, st);
+  hipLaunchKernelGGL((gemm_direct_t_kernel<BM, BN, WM, WN, MINB, Epi>), dim3((unsigned)((long)gx * gy * d.groups * p.ns)),
+                     dim3(kThreads), 0, st, j, e);
+  AX_LAUNCH_CHECK();
+  return ALEXNET_OK;
+}
+template <class Epi>
+static int launch_direct_t(const DirectTPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e, const GemmDims& d,
+                           double bytes, hipStream_t st) {
+  if (p.tile == 0) return launch_direct_t_tile<128, 64, 4, 1, 3>(p, a, b, e, d, bytes, st);
+  if (p.tile == 1) return launch_direct_t_tile<128, 128, 2, 2, 2>(p, a, b, e, d, bytes, st);
+  return launch_direct_t_tile<192, 128, 2, 2, 2>(p, a, b, e, d, bytes, st);
+}
+
+int launch_direct_bwd_weight(const ConvGeom& c, const uint16_t* x16, const uint16_t* dy16, float* out, hipStream_t st) {
+  const GemmDims d = bwdw_dims(c);
+  const EpiSlab ep{out, (long)d.M * d.N, d.N, nullptr};
+  const double bytes = 4.0 * ((double)c.in_elems() + (double)c.w_elems() + (double)c.out_elems());
+  return launch_direct_t(plan_direct_t(d), im2col16(bwdw_A(c, nullptr), x16),
+                         dense16(bwdw_B(c, nullptr), dy16), ep, d, bytes, st);
+}
+
+}  // namespace ax
