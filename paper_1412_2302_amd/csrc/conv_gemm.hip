@@ -1035,6 +1035,10 @@ double tile_seconds_dense(int M, int N, int K, bool bf) {
 size_t fc_ws_floats(int B, int in, int out) {
   int kc;
   size_t n = 0;
+  if (fc_bf16_stored_ok(in, out)) {
+    n = std::max(n, (size_t)dense_plan(B, out, in).ns * B * out);
+    n = std::max(n, (size_t)dense_plan(B, in, out).ns * B * in);
+  }
   for (int bf = 0; bf < 2; ++bf) {
     n = std::max(n, (size_t)fc_split(B, out, in, &kc, bf) * B * out);
     n = std::max(n, (size_t)fc_split(B, in, out, &kc, bf) * B * in);
@@ -1196,11 +1200,18 @@ static int launch_dense(bool vec, const GemmPlan& p, const DenseParams& a, const
 typedef BfRowMajor<DenseKInner<128, kBKbf, true>, 128, kBKbf> BfDenseK;
 typedef BfDenseRowInner<128, kBKbf> BfDenseR;
 
-typedef DenseKInner16<128, kBKbf> Dense16K;
-typedef DenseRowInner16<128, kBKbf> Dense16R;
 bool fc_bf16_stored_ok(int in, int out) { return in % 8 == 0 && out % 8 == 0; }
-static inline DenseParams dense16_of(const uint16_t* p, long ld, int rows, size_t elems) {
-  return DenseParams{reinterpret_cast<const float*>(p), ld, 0, rows, (uint32_t)(elems * 2)};
+
+// A dense layer is a 1 x 1 convolution over pictures of one pixel
+static int launch_dense_direct(const DensePlan& dp, int B, int in, int out, const uint16_t* x16, const uint16_t* w16,
+                               const EpiSlab& e, hipStream_t st) {
+  const ConvGeom c{B, 1, 1, in, out, 1, 1, 0, 1, 1, 1};
+  const Im2colParams a = im2col16(fwd_A(c, nullptr), x16);
+  const DenseParams b = fwd_B16k(c, w16);
+  const GemmDims d = fwd_dims(c);
+  const DirectPlan p{0, dp.ns, dp.per};
+  if (dp.tall) return launch_direct_tile<128, 128, 2, 2, 2, IM2COL_FWD>(p, a, b, e, d, st);
+  return launch_direct_tile<64, 128, 2, 2, 3, IM2COL_FWD>(p, a, b, e, d, st);
 }
 
 int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const FcAct& act, float* y, float* ws,
@@ -1211,16 +1222,13 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
   if (wave_fc_fwd_ok(B, in, out, g_bf16)) return launch_wave_fc_fwd(B, in, out, x, w, act, y, y16, bf, st);
   const bool s16 = bf && x16 && w16 && fc_bf16_stored_ok(in, out) && aligned16(x16) && aligned16(w16);
   const GemmPlan p = fc_product_plan(B, out, in, vec, bf);
-  const int ns = p.ns, kchunk = p.kchunk;
+  const DensePlan dp = dense_plan(B, out, in);
+  const int ns = s16 ? dp.ns : p.ns, kchunk = p.kchunk;
   DenseParams a{x, in, 0, B, (uint32_t)((size_t)B * in * 4)};
   DenseParams b{w, in, 0, out, (uint32_t)((size_t)out * in * 4)};
   // both operands run along k = in
   auto product = [&](const auto& ep) -> int {
     typedef std::decay_t<decltype(ep)> Epi;
-    if (s16)
-      return launch_tile_bf<B128, Dense16K, Dense16K, Epi>(dense16_of(x16, in, B, (size_t)B * in),
-                                                           dense16_of(w16, in, out, (size_t)out * in), ep, B, out, in,
-                                                           kchunk, ns, 1, st);
     if (bf) return launch_tile_bf<B128, BfDenseK, BfDenseK, Epi>(a, b, ep, B, out, in, kchunk, ns, 1, st);
     return launch_dense<SplitKInner, SplitKInner, DenseKInner, DenseKInner>(vec, p, a, b, ep, B, out, in, st);
   };
@@ -1228,7 +1236,11 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
   // more there than a second launch (128 rows 256 wide: 456 against 434 us per small training step), and so do mask and
   // gate in the bf16 kernels, whose blocks are not transposed (438 against 434; 30 rows 200 wide 363 against 357).
   if (ns == 1 && !bf && (B <= 32 || !act.dropout)) return product(EpiFcAct{y, out, act, y16});
-  AX_TRY(product(EpiSlab{ws, (long)B * out, out, nullptr}));
+  const EpiSlab slabs{ws, (long)B * out, out, nullptr};
+  if (s16)
+    AX_TRY(launch_dense_direct(dp, B, in, out, x16, w16, slabs, st));
+  else
+    AX_TRY(product(slabs));
   const size_t total = (size_t)B * out;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1), st);
   hipLaunchKernelGGL(fc_fwd_finish_kernel, dim3(ceil_div(total, 256)), dim3(256), 0, st, ws, ns, B, out, act, y, y16);
@@ -1241,21 +1253,20 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
   const bool vec = vec_ok(dy, out) && vec_ok(w, in), bf = g_bf16 && vec;
   const bool s16 = bf && dy16 && w16 && fc_bf16_stored_ok(in, out) && aligned16(dy16) && aligned16(w16);
   const GemmPlan p = fc_product_plan(B, in, out, vec, bf);
-  const int ns = p.ns, kchunk = p.kchunk;
+  const int ns = s16 ? dense_plan(B, in, out).ns : p.ns, kchunk = p.kchunk;
   DenseParams a{dy, out, 0, B, (uint32_t)((size_t)B * out * 4)};
   DenseParams b{w, in, 0, in, (uint32_t)((size_t)out * in * 4)};
   // A runs along k = out, B along its rows = in
   auto product = [&](const auto& ep) -> int {
     typedef std::decay_t<decltype(ep)> Epi;
-    if (s16)
-      return launch_tile_bf<B128, Dense16K, Dense16R, Epi>(dense16_of(dy16, out, B, (size_t)B * out),
-                                                           dense16_of(w16, in, in, (size_t)out * in), ep, B, in, out,
-                                                           kchunk, ns, 1, st);
     if (bf) return launch_tile_bf<B128, BfDenseK, BfDenseR, Epi>(a, b, ep, B, in, out, kchunk, ns, 1, st);
     return launch_dense<SplitKInner, SplitRowInner, DenseKInner, DenseRowInner>(vec, p, a, b, ep, B, in, out, st);
   };
   if (ns == 1 && !bf) return product(EpiGate{dx, in, gate, in, 0, 0, dx16});  // see launch_fc_fwd
-  AX_TRY(product(EpiSlab{ws, (long)B * in, in, nullptr}));
+  if (s16)
+    AX_TRY(launch_direct_dense_bwd_data(B, in, out, dy16, w16, ws, st));
+  else
+    AX_TRY(product(EpiSlab{ws, (long)B * in, in, nullptr}));
   const size_t total = (size_t)B * in;
   KernelScope ks("fc_finish", 0, (double)total * 4.0 * (ns + 1 + (gate ? 1 : 0)), st);
   hipLaunchKernelGGL(fc_bwd_finish_kernel, dim3(ceil_div(total, 256)), dim3(256), 0, st, ws, ns, total, gate, dx,
@@ -1282,9 +1293,7 @@ int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy
   EpiSlab ep{dw, (long)out * in, in, nullptr};
   const bool vec = vec_ok(dy, out) && vec_ok(x, in);
   if (g_bf16 && vec && x16 && dy16 && fc_bf16_stored_ok(in, out) && aligned16(x16) && aligned16(dy16))
-    return launch_tile_bf<B128, Dense16R, Dense16R, EpiSlab>(dense16_of(dy16, out, out, (size_t)B * out),
-                                                             dense16_of(x16, in, in, (size_t)B * in), ep, out, in, B,
-                                                             round_up(B, kBKbf), 1, 1, st);
+    return launch_direct_dense_bwd_weight(B, in, out, x16, dy16, dw, st);
   if (g_bf16 && vec)
     return launch_tile_bf<B128, BfDenseR, BfDenseR, EpiSlab>(a, b, ep, out, in, B, round_up(B, kBKbf), 1, 1, st);
   const GemmPlan p = fc_split_ok(vec, B) ? plan_split(out, in, B, 1, 0, 1) : GemmPlan{128, 128, 1, round_up(B, kBK)};

@@ -42,6 +42,30 @@ struct DirectJob {
   FastDiv gx, gy, ns;
 };
 
+// Products of dense layers, rows = pictures: they wait for the weights, which come from memory once, so that what counts is how
+// many loads are on their way.  Two workgroups per compute unit by slices of the reduction (at least two k-tiles each), from
+// 64-row tiles unless there are more than 32 of 128 rows.  With sums and activation in front of gemm_bf16.h's 128 x 128 | here,
+// us, 4096 and 1000 outputs: batch 256 of 9216, 4096, 4096 inputs 57, 32, 21 | 41, 27, 16, data gradients 64, 34, 19 | 52, 25,
+// 17; batch 64 35, 22, 15 | 31, 20, 12 and 51, 21, 16 | 37, 16, 12.  One workgroup per compute unit (256 rows, 9216 inputs):
+// 72; four: 49 and more.
+struct DensePlan {
+  bool tall;  // 128 x 128, else 64 x 128
+  int ns, per;
+};
+inline DensePlan dense_plan(int rows, int cols, int K) {
+  const int ktiles = (K + kBKd - 1) / kBKd;
+  DensePlan p;
+  p.tall = (long)((rows + 127) / 128) * ((cols + 127) / 128) > 32;
+  const long tiles = (long)((rows + (p.tall ? 127 : 63)) / (p.tall ? 128 : 64)) * ((cols + 127) / 128);
+  long ns = 512 / tiles;
+  ns = ns > 32 ? 32 : ns;
+  ns = ns > ktiles / 2 ? ktiles / 2 : ns;
+  ns = ns < 1 ? 1 : ns;
+  p.per = (int)((ktiles + ns - 1) / ns);
+  p.ns = (ktiles + p.per - 1) / p.per;
+  return p;
+}
+
 // Taps of a kernel (at most 32) that lie inside the tensor, seen from (y0, x0): bit r*kw + s
 template <int MODE>
 AX_HD uint32_t taps_inside(const Im2colParams& g, int y0, int x0) {

@@ -152,6 +152,9 @@ int add_weight_slices(const ConvGeom& c, const float* slices, int ns, float* dwf
 bool direct_bwd_weight_ok(const ConvGeom& c);
 int direct_bwd_weight_slices(const ConvGeom& c);
 int launch_direct_bwd_weight(const ConvGeom& c, const uint16_t* x16, const uint16_t* dy16, float* out, hipStream_t st);
+// dense layers over operands stored as bf16: dx as dense_plan()'s slabs, dw whole
+int launch_direct_dense_bwd_data(int B, int in, int out, const uint16_t* dy16, const uint16_t* w16, float* slabs, hipStream_t st);
+int launch_direct_dense_bwd_weight(int B, int in, int out, const uint16_t* x16, const uint16_t* dy16, float* dw, hipStream_t st);
 bool wave_conv_bwd_weight_ok(const ConvGeom& c, bool bf);
 bool wave_conv_bwd_ok(const ConvGeom& c, bool bf);  // both gradients in one launch
 bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy);

@@ -40,7 +40,9 @@ __device__ __forceinline__ v4s read_transposed(const char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int MINB, class Epi>
+// A_K: the first operand is contiguous along the reduction, a.x[row][k] with a.Cg values of k (gradients of dense layers'
+// inputs), and stands in LDS as in gemm_direct.h; the second one is transposed on the way out all the same.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int MINB, bool A_K, class Epi>
 __global__ void __launch_bounds__(256, MINB) gemm_direct_t_kernel(DirectTJob j, Epi ep) {
   static_assert(WAVES_M * WAVES_N == 4 && BM % 64 == 0 && BN % 64 == 0, "four waves, blocks of 64");
   constexpr int TM = BM / (32 * WAVES_M), TN = BN / (32 * WAVES_N);
@@ -63,7 +65,14 @@ __global__ void __launch_bounds__(256, MINB) gemm_direct_t_kernel(DirectTJob j, 
 
   // A load brings the octets of eight pixels in one block: lane = (pixel, slot).  A wave loads pixels 16*wave .. 16*wave + 15.
   const int sub = lane >> 3, oct = (lane & 7) ^ (4 * ((sub >> 1) & 1));
-  uint32_t tapoff[CA], tapmask[CA], bcol[CB];
+  constexpr int NA = BM / 32;  // A_K: loads per lane and k-tile, eight rows each
+  const int k_oct = (lane & 7) ^ sub;
+  uint32_t tapoff[CA], tapmask[CA], bcol[CB], arow[NA];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int m = m0 + (i * 4 + wave) * 8 + sub;
+    arow[i] = m < j.M ? ((uint32_t)m * (uint32_t)ap.Cg + 8u * k_oct) * 2u : kOob;
+  }
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
     const int m = m0 + 64 * b + 8 * oct;
@@ -83,7 +92,12 @@ __global__ void __launch_bounds__(256, MINB) gemm_direct_t_kernel(DirectTJob j, 
   uint32_t pbase = 0, poutside = 0;  // of this lane's pixel: 16*wave + lane % 16 of k-tile t + lane / 16, t a multiple of four
   auto load = [&](v4u* st, int t) {
     const int k0 = (first + t) * kBKd + 16 * wave;
-    if ((t & 3) == 0) {
+    if (A_K) {
+      const uint32_t k = (uint32_t)(first + t) * kBKd;
+      const bool in = (int)k + 8 * k_oct < j.K;
+#pragma unroll
+      for (int i = 0; i < NA; ++i) load_lds16(av, st + (i * 4 + wave) * 64, in ? arow[i] + 2u * k : kOob, 0);
+    } else if ((t & 3) == 0) {
       const int p = k0 + (lane >> 4) * kBKd + (lane & 15);
       const bool in = p < ap.P;
       const PixCoord c = decode_pixel(in ? p : 0, ap);
@@ -93,11 +107,13 @@ __global__ void __launch_bounds__(256, MINB) gemm_direct_t_kernel(DirectTJob j, 
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int from = (t & 3) * 16 + i * 8 + sub;
-      const uint32_t base = (uint32_t)__shfl((int)pbase, from), outside = (uint32_t)__shfl((int)poutside, from);
+      if (!A_K) {
+        const int from = (t & 3) * 16 + i * 8 + sub;
+        const uint32_t base = (uint32_t)__shfl((int)pbase, from), outside = (uint32_t)__shfl((int)poutside, from);
 #pragma unroll
-      for (int b = 0; b < CA; ++b)
-        load_lds16(av, st + b * kBlock + (2 * wave + i) * 64, outside & tapmask[b] ? kOob : base + tapoff[b], 0);
+        for (int b = 0; b < CA; ++b)
+          load_lds16(av, st + b * kBlock + (2 * wave + i) * 64, outside & tapmask[b] ? kOob : base + tapoff[b], 0);
+      }
       const uint32_t brow = (uint32_t)(k0 + i * 8 + sub) * (uint32_t)j.b.ld * 2u;  // past the last pixel: outside
 #pragma unroll
       for (int b = 0; b < CB; ++b) load_lds16(bv, st + (CA + b) * kBlock + (2 * wave + i) * 64, brow + bcol[b], 0);
@@ -111,16 +127,17 @@ __global__ void __launch_bounds__(256, MINB) gemm_direct_t_kernel(DirectTJob j, 
     for (int jj = 0; jj < TN; ++jj)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][jj][r] = 0.f;
-  // Element e of a lane's eight values is k = 8*(e/4) + 4*kh + e%4 of a step, in both operands.  Bytes of lane (k, rows) in a
-  // block, for its first and its second 32 rows:
+  // Element e of a lane's eight values is k = 8*(e/4) + 4*kh + e%4 of a step, in both operands; A_K: k = 8*kh + e.  Bytes of lane
+  // (k, rows) in a block, for its first and its second 32 rows:
+  constexpr int kSecond = A_K ? 512 : 1024;  // from the first four of them to the second
   const int l16 = lane & 15, kk = l16 >> 2, half_row = ((lane >> 4) & 1) * 2 + ((l16 & 3) >> 1);
-  const int lane_k = (4 * (lane >> 5) + kk) * 128 + (l16 & 1) * 8;
+  const int kh = lane >> 5, lane_k = ((A_K ? 8 : 4) * kh + kk) * 128 + (l16 & 1) * 8;
   const int at0 = lane_k + (half_row ^ (4 * (kk >> 1))) * 16, at1 = at0 ^ 64;
   int a_at[TM], b_at[TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int blk = wm * TM + i;
-    a_at[i] = (blk >> 1) * (kBlock * 16) + (blk & 1 ? at1 : at0);
+    a_at[i] = A_K ? (blk * 32 + (lane & 31)) * 128 : (blk >> 1) * (kBlock * 16) + (blk & 1 ? at1 : at0);
   }
 #pragma unroll
   for (int jj = 0; jj < TN; ++jj) {
@@ -137,10 +154,11 @@ __global__ void __launch_bounds__(256, MINB) gemm_direct_t_kernel(DirectTJob j, 
       v8bf a[TM], b[TN];
 #pragma unroll
       for (int i = 0; i < TM; ++i)
-        a[i] = __builtin_bit_cast(v8bf, Two{read_transposed(s + a_at[i] + ks * 2048), read_transposed(s + a_at[i] + ks * 2048 + 1024)});
+        a[i] = A_K ? __builtin_bit_cast(v8bf, *reinterpret_cast<const v4u*>(s + a_at[i] + ((2 * ks + kh) ^ (lane & 7)) * 16))
+                   : __builtin_bit_cast(v8bf, Two{read_transposed(s + a_at[i] + ks * 2048), read_transposed(s + a_at[i] + ks * 2048 + kSecond)});
 #pragma unroll
       for (int jj = 0; jj < TN; ++jj)
-        b[jj] = __builtin_bit_cast(v8bf, Two{read_transposed(s + b_at[jj] + ks * 2048), read_transposed(s + b_at[jj] + ks * 2048 + 1024)});
+        b[jj] = __builtin_bit_cast(v8bf, Two{read_transposed(s + b_at[jj] + ks * 2048), read_transposed(s + b_at[jj] + ks * 2048 + kSecond)});
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -224,7 +242,7 @@ static DirectTPlan plan_direct_t(const GemmDims& d) {
 }
 bool direct_bwd_weight_ok(const ConvGeom& c) { return conv_bf16_stored_ok(c) && c.k * c.k < kDirectTaps; }
 int direct_bwd_weight_slices(const ConvGeom& c) { return plan_direct_t(bwdw_dims(c)).ns; }
-template <int BM, int BN, int WM, int WN, int MINB, class Epi>
+template <int BM, int BN, int WM, int WN, int MINB, bool A_K = false, class Epi>
 static int launch_direct_t_tile(const DirectTPlan& p, const Im2colParams& a, const DenseParams& b, const Epi& e,
                                 const GemmDims& d, double bytes, hipStream_t st) {
   DirectTJob j;
@@ -240,7 +258,7 @@ static int launch_direct_t_tile(const DirectTPlan& p, const Im2colParams& a, con
   j.ns = make_fastdiv((uint32_t)p.ns);
   KernelScope ks("gemm_bf16", 2.0 * d.M * d.N * (double)d.K * d.groups,
                  bytes, st);
-  hipLaunchKernelGGL((gemm_direct_t_kernel<BM, BN, WM, WN, MINB, Epi>), dim3((unsigned)((long)gx * gy * d.groups * p.ns)),
+  hipLaunchKernelGGL((gemm_direct_t_kernel<BM, BN, WM, WN, MINB, A_K, Epi>), dim3((unsigned)((long)gx * gy * d.groups * p.ns)),
                      dim3(kThreads), 0, st, j, e);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
@@ -259,6 +277,35 @@ int launch_direct_bwd_weight(const ConvGeom& c, const uint16_t* x16, const uint1
   const double bytes = 4.0 * ((double)c.in_elems() + (double)c.w_elems() + (double)c.out_elems());
   return launch_direct_t(plan_direct_t(d), im2col16(bwdw_A(c, nullptr), x16),
                          dense16(bwdw_B(c, nullptr), dy16), ep, d, bytes, st);
+}
+
+// ---- dense layers ----
+int launch_direct_dense_bwd_data(int B, int in, int out, const uint16_t* dy16, const uint16_t* w16, float* slabs, hipStream_t st) {
+  const GemmDims d{B, in, out, 1};
+  const ConvGeom rows{B, 1, 1, out, in, 1, 1, 0, 1, 1, 1};
+  DenseParams b;
+  b.p = reinterpret_cast<const float*>(w16); b.ld = in; b.gstride = 0; b.R = in; b.bytes = (uint32_t)((size_t)in * out * 2);
+  const Im2colParams a = im2col16(fwd_A(rows, nullptr), dy16);
+  const EpiSlab e{slabs, (long)B * in, in, nullptr};
+  const double bytes = 4.0 * ((double)B * (in + out) + (double)in * out);
+  const DensePlan dp = dense_plan(B, in, out);
+  const DirectTPlan p{0, dp.ns, dp.per};
+  if (dp.tall) return launch_direct_t_tile<128, 128, 2, 2, 2, true>(p, a, b, e, d, bytes, st);
+  return launch_direct_t_tile<64, 128, 2, 2, 3, true>(p, a, b, e, d, bytes, st);
+}
+// The weight gradient of a 1 x 1 convolution over pictures of one pixel, with the operands' parts exchanged.  Its reduction is
+// the batch, so that it waits for its stores; 128-row tiles from 65 pictures up (batch 64, 9216 x 4096: 28 us in those, 26 in
+// these; 256: 50 and 59).  gemm_bf16.h | here: batch 256 49, 27, 13 | 50, 20, 11 us, batch 64 33, 18, 10 | 26, 13, 7.
+int launch_direct_dense_bwd_weight(int B, int in, int out, const uint16_t* x16, const uint16_t* dy16, float* dw, hipStream_t st) {
+  const GemmDims d{out, in, B, 1};
+  const ConvGeom c{B, 1, 1, out, in, 1, 1, 0, 1, 1, 1};
+  const Im2colParams a = im2col16(bwdw_A(c, nullptr), dy16);
+  const DenseParams b = dense16(bwdw_B(c, nullptr), x16);
+  const EpiSlab e{dw, (long)out * in, in, nullptr};
+  const double bytes = 4.0 * ((double)B * (in + out) + (double)in * out);
+  const DirectTPlan p{0, 1, ceil_div(B, kBKd)};
+  if (B > 64) return launch_direct_t_tile<128, 128, 2, 2, 2>(p, a, b, e, d, bytes, st);
+  return launch_direct_t_tile<64, 128, 2, 2, 3>(p, a, b, e, d, bytes, st);
 }
 
 }  // namespace ax
