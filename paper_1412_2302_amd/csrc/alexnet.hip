@@ -306,7 +306,9 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
     s.x16_own = s.x16;
     s.dy16 = s.b16 ? a.take<uint16_t>(ae) : nullptr;
     s.wf16 = s.b16 ? a.take<uint16_t>(s.g.w_elems()) : s.r16 ? a.take<uint16_t>(conv_run16_w_elems(s.g)) : nullptr;
-    s.direct_slices = s.b16 && direct_bwd_weight_ok(s.g) && direct_bwd_weight_slices(s.g) > 1
+    const size_t first = s.r16 && first_weight_ok(s.g) ? (size_t)first_weight_slices(s.g) * s.g.w_elems() : 0;
+    gws = std::max(gws, first);
+    s.direct_slices = first ? a.take<float>(first) : s.b16 && direct_bwd_weight_ok(s.g) && direct_bwd_weight_slices(s.g) > 1
                           ? a.take<float>((size_t)direct_bwd_weight_slices(s.g) * s.g.w_elems())
                           : nullptr;
     s.wb16 = s.b16 ? a.take<uint16_t>(s.g.w_elems()) : nullptr;
@@ -456,6 +458,13 @@ static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* d
       return add_weight_slices(s.g, s.direct_slices, ns, dwf, tail, st);
     }
     return launch_conv_bwd_weight(s.g, x, dy, dwf, nullptr, n->gemm_ws, st, nullptr, s.x16, s.dy16);
+  }
+  if (s.r16 && first_weight_ok(s.g)) {
+    if (!have_v) AX_TRY(launch_pad4_bf16(x, s.x16, (size_t)s.g.Q(), s.g.Cin, st));
+    const int ns = first_weight_slices(s.g);
+    float* slices = ns == 1 ? dwf : tail ? s.direct_slices : n->gemm_ws;
+    AX_TRY(launch_first_weight(s.g, s.x16, dy, slices, st));
+    return add_weight_slices(s.g, slices, ns, dwf, tail, st);
   }
   return launch_conv_bwd_weight(s.g, x, dy, dwf, s.dwrun, n->gemm_ws, st);
 }

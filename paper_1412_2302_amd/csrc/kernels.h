@@ -148,6 +148,10 @@ bool wave_conv_fwd_ok(const ConvGeom& c, bool bf);
 bool wave_conv_bwd_data_ok(const ConvGeom& c, bool bf);
 // dwf = the sum of ns slices of a weight gradient, [group][slice][slab], now or (tail) at the end of the pass; ns = 1: nothing to do
 int add_weight_slices(const ConvGeom& c, const float* slices, int ns, float* dwf, WgradTail* tail, hipStream_t st);
+// weight gradient of the first layer over four-channel bf16 pictures (first_weight.hip): slabs of [(r, s, c)][o]
+bool first_weight_ok(const ConvGeom& c);
+int first_weight_slices(const ConvGeom& c);
+int launch_first_weight(const ConvGeom& c, const uint16_t* x4, const float* dy, float* slabs, hipStream_t st);
 // weight gradients over operands stored as bf16 (weight_direct.hip): out gets ns slabs of every group, [group][slice][slab]
 bool direct_bwd_weight_ok(const ConvGeom& c);
 int direct_bwd_weight_slices(const ConvGeom& c);
