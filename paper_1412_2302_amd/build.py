@@ -18,7 +18,7 @@ LIB = os.path.join(HERE, "libalexnet_hip.so")
 SOURCES = ["alexnet.hip", "conv_gemm.hip", "wave_gemm.hip", "first_layer.hip", "first_weight.hip", "weight_direct.hip", "ops.hip", "winograd.hip", "loader.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-Wall", "-Wno-unused-function",
-    # packed fp32 VALU ops are kept off on the test machines
+    # packed fp32 VALU ops are kept off
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 

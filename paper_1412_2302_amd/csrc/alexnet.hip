@@ -654,8 +654,9 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     // over, all within 0.3 %:
     //   fp32  batch 1 635 | 665   12 1088 | 1102   16 1122 | 1130   20 1178 | 1180   24 1275 | 1274 | 1311
     //         37 1523 | 1510 | 1528   64 2056 | 2047 | 2058   128 3378 | 3359 | 3346   256 6153 | 6121 | 6087
-    //   bf16  batch 32 1180 | 1190 | 1199   64 1506 | 1499 | 1491   128 2083 | 2091 | 2103   256 3446 | 3413 | 3412
-    // So fp32 takes conv4 from batch 23 up (kLateUpdateFlops); for bf16 nothing is better than conv5 at every size.
+    //   bf16  batch 32 1056 | 1054   64 1308 | 1315   128 1880 | 1849   200 2635 | 2614   256 2973 | 3345
+    // So fp32 takes conv4 from batch 23 up (kLateUpdateFlops).  bf16 stays with conv5: in front of conv4 a product that fills
+    // all but a few CUs may come first, whose room draws the update's workgroups there, and it takes 800 us instead of 310.
     auto fork_update = [&]() -> int {
       AX_HIP(hipEventRecord(n->ev_fc_done, st));
       AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_fc_done, 0));
