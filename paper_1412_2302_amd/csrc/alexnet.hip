@@ -123,10 +123,12 @@ struct Dense {
 struct Arena {
   char* base;
   size_t off;
+  std::vector<WorkspacePiece>* pieces;  // may be null: where to list what is taken
   template <class T>
   T* take(size_t n) {
     off = (off + 255) & ~(size_t)255;
     T* p = base ? reinterpret_cast<T*>(base + off) : nullptr;
+    if (pieces) pieces->push_back(WorkspacePiece{off, n * sizeof(T)});
     off += n * sizeof(T);
     return p;
   }
@@ -187,7 +189,7 @@ constexpr double kForkFlops = 100e9;
 constexpr double kLateUpdateFlops = 30e9;
 static bool winograd_in_pass(const ConvGeom& g) { return 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k >= kWinoMinFlops; }
 
-static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
+static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector<WorkspacePiece>* pieces = nullptr) {
   const alexnet_config_t& c = *cfg;
   if (c.batch <= 0 || c.in_c <= 0 || c.crop_h <= 0 || c.crop_w <= 0 || c.raw_h < c.crop_h || c.raw_w < c.crop_w) {
     set_error("bad batch/input size");
@@ -273,7 +275,7 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
   n->n_params = off;
 
   // ---- workspace ----
-  Arena a{base, 0};
+  Arena a{base, 0, pieces};
   const bool bf = c.precision == ALEXNET_PRECISION_BF16;
   const size_t in_elems = (size_t)c.batch * c.crop_h * c.crop_w * c.in_c;
   for (int s = 0; s < kSlots; ++s) {
@@ -391,6 +393,12 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base) {
   return ALEXNET_OK;
 }
 
+int ax::workspace_pieces(const alexnet_config_t* cfg, std::vector<WorkspacePiece>* out) {
+  alexnet tmp;
+  memset(&tmp, 0, sizeof tmp);
+  return plan(&tmp, cfg, nullptr, out);
+}
+
 static inline hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 static inline bool aligned256(const void* p) { return ((uintptr_t)p & 255) == 0; }
 
@@ -452,12 +460,16 @@ static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* d
   if (b16_usable(s, x, dy)) {
     if (!have_v) AX_TRY(launch_to_bf16(x, s.x16, (size_t)s.g.in_elems(), st));
     if (!dy16_ready) AX_TRY(launch_to_bf16(dy, s.dy16, (size_t)s.g.out_elems(), st));
-    if (tail && s.direct_slices) {
-      int ns = 1;
-      AX_TRY(launch_conv_bwd_weight(s.g, x, dy, dwf, nullptr, s.direct_slices, st, &ns, s.x16, s.dy16));
-      return add_weight_slices(s.g, s.direct_slices, ns, dwf, tail, st);
+    // Here, in the plan and in the operators alike: operands stored as bf16 go to the kernel that reads them.  (Left to
+    // launch_conv_bwd_weight(), which takes a small product first, other slices than planned were written; and the small
+    // product was the slower one, second layer of the mini net at batch 400: 25 us of product against 13.)
+    if (direct_bwd_weight_ok(s.g)) {
+      const int ns = direct_bwd_weight_slices(s.g);
+      float* slices = ns == 1 ? dwf : tail ? s.direct_slices : n->gemm_ws;
+      AX_TRY(launch_direct_bwd_weight(s.g, s.x16, s.dy16, slices, st));
+      return add_weight_slices(s.g, slices, ns, dwf, tail, st);
     }
-    return launch_conv_bwd_weight(s.g, x, dy, dwf, nullptr, n->gemm_ws, st, nullptr, s.x16, s.dy16);
+    return launch_conv_bwd_weight(s.g, x, dy, dwf, nullptr, n->gemm_ws, st);
   }
   if (s.r16 && first_weight_ok(s.g)) {
     if (!have_v) AX_TRY(launch_pad4_bf16(x, s.x16, (size_t)s.g.Q(), s.g.Cin, st));

@@ -918,7 +918,7 @@ bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy) {
 // defer_ns (generic layout only): the split-k slices are left in ws, [group][slice][slab], and their number is
 // returned there for the caller to add them up later (1: the result is in dwf already)
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
-                           hipStream_t st, int* defer_ns, const uint16_t* x16, const uint16_t* dy16) {
+                           hipStream_t st, int* defer_ns) {
   if (wave_conv_bwd_weight_ok(c, g_bf16)) {
     if (defer_ns) *defer_ns = 1;
     return launch_wave_conv_bwd_weight(c, x, dy, dwf, ws, conv_bwd_weight_bf16(c, x, dy), st);
@@ -955,12 +955,6 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
     AX_TRY((by_tile_run<SplitRunT>(p, run_t_params(a, kc), bwdw_B(c, dy), ep, c.k * kc, c.Cout, d.K, st)));
     if (defer_ns) *defer_ns = 1;
     return launch_reduce_slabs_unpack(p.ns > 1 ? ws : dwrun, p.ns, slab, c.k, kc / 4 * 4, kc, c.Cout, dwf, st);
-  }
-  if (bf && !run && x16 && dy16 && direct_bwd_weight_ok(c) && aligned16(x16) && aligned16(dy16)) {
-    const int ns = direct_bwd_weight_slices(c);
-    AX_TRY(launch_direct_bwd_weight(c, x16, dy16, ns > 1 ? ws : dwf, st));
-    if (defer_ns) *defer_ns = ns;
-    return defer_ns || ns == 1 ? ALEXNET_OK : launch_reduce_slabs(ws, ns, (long)d.M * d.N, d.groups, dwf, st);
   }
   bool table = av && bv && table_ok(a, d) && (!bf || d.K % kBKbf == 0);
   GemmPlan p = bwdw_plan(c, run, bf, table);

@@ -2,10 +2,18 @@
 // device pointers in the internal channel-last layout unless a name says
 // otherwise; every function only enqueues work on `st` and returns a status.
 #pragma once
+#include <vector>
+
 #include "common.h"
 #include "conv_plan.h"
 
 namespace ax {
+
+// A buffer of a handle's workspace.  workspace_pieces() lists them all (for tests: what a pass writes has to stay inside one)
+struct WorkspacePiece {
+  size_t offset, bytes;
+};
+int workspace_pieces(const alexnet_config_t* cfg, std::vector<WorkspacePiece>* out);
 
 // The tail of the weight gradient of a transformed stage -- adding up the split-k slices of the products, then
 // the transform back to taps --, or the slices of a direct one (gemm_wave.h, weight_direct.hip; total = 0), can be put off to the end of a backward pass and run for all such stages in two
@@ -74,8 +82,7 @@ int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, co
                          const float* gate, float* dx, float* ws, hipStream_t st, const uint16_t* dy16 = nullptr,
                          const uint16_t* wb16 = nullptr, uint16_t* dx16 = nullptr);
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
-                           hipStream_t st, int* defer_ns = nullptr, const uint16_t* x16 = nullptr,
-                           const uint16_t* dy16 = nullptr);
+                           hipStream_t st, int* defer_ns = nullptr);
 
 // ---- 3x3 and 5x5 unit-stride convolutions through F(4x4, 3x3) (winograd.hip) ----
 // All tensors 16-byte aligned, channels per group multiples of 4.  V: wino_v_floats(), U / Ub / dU:
