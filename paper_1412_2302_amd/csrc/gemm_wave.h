@@ -103,8 +103,8 @@ struct WaveRow {
   }
 };
 
-// implicit im2col, rows = pixels, k = (r, s, c) or a run-mode (r, j); channels per group a multiple of four.  Table: per
-// quad of k its byte offset from a pixel's origin and the bits of its tap.
+// implicit im2col, rows = pixels, k = (r, s, c); channels per group a multiple of four.  Table: per quad of k its byte offset
+// from a pixel's origin and the bits of its tap.
 template <int MODE>
 struct WaveIm2col {
   static_assert(MODE == IM2COL_FWD || MODE == IM2COL_T1, "unit-step gathers only");
@@ -137,7 +137,41 @@ struct WaveIm2col {
   }
 };
 
-// its transpose, rows = (r, s, c), k = pixels.  Table: per pixel the byte offset of its origin and the taps inside.
+// The same with k = a run-mode (r, j < run).  The quad at a run's end may hold floats of the pixels behind the window, of the
+// next row's or the next picture's: they meet zero weights, but an infinity or a NaN among them would still reach the sum, so
+// they are read as zero.  Table: also, in an offset's two lowest bits, how many of its floats after the first are the window's.
+struct WaveRunAParams {
+  Im2colParams g;
+  int kc;  // floats of a kernel row's window; run = g.Cg: kc rounded up to a multiple of four
+};
+struct WaveRunA {
+  typedef WaveIm2col<IM2COL_FWD> Gather;
+  static constexpr int kWords = Gather::kWords;
+  typedef WaveRunAParams Params;
+  Gather in;
+  AX_HD WaveRunA(const Params& a, int grp, int row, int kbeg, int kend, const uint32_t* table)
+      : in(a.g, grp, row, kbeg, kend, table) {}
+  static AX_HD void build(const Params& p, uint32_t* table, int kbeg, int kend, int tid, int threads) {
+    Gather::build(p.g, table, kbeg, kend, tid, threads);
+    for (int q = tid; q < wave_steps16(kend - kbeg) / 4; q += threads) {
+      const int k = kbeg + 4 * q, n = p.kc - (k - (int)fdiv((uint32_t)k, p.g.d_cg) * p.g.Cg);
+      table[2 * q] |= (uint32_t)(n < 4 ? n - 1 : 3);
+    }
+  }
+  AX_HD void load(float4* r, int k) const {
+    const uint32_t* t = in.table + k / 2;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const uint32_t last = t[2 * q] & 3u, tap = t[2 * q + 1];
+      r[q] = buf_ld4(in.v, (in.taps & tap) == tap ? in.base + (t[2 * q] & ~3u) : kOob);
+      r[q].y = last > 0 ? r[q].y : 0.f;
+      r[q].z = last > 1 ? r[q].z : 0.f;
+      r[q].w = last > 2 ? r[q].w : 0.f;
+    }
+  }
+};
+
+// the transpose of the im2col, rows = (r, s, c), k = pixels.  Table: per pixel the byte offset of its origin and the taps inside.
 struct WaveIm2colT {
   static constexpr int kWords = kWaveMaxPixels * 2;
   typedef Im2colParams Params;

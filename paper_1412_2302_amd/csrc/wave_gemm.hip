@@ -154,8 +154,8 @@ static int conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
     if (run_mode(c)) {
       const WaveRunParams b{DenseParams{wf, c.Cout, 0, c.Cout, (uint32_t)(c.w_elems() * 4)}, c.k * c.Cin, run_len(c),
                             make_fastdiv((uint32_t)run_len(c))};
-      return launch_job(wave_job<WaveIm2col<IM2COL_FWD>, WaveRunB, Epi, BF>(run_A(c, x), b, ep, d.M, d.N, run_k(c), 1, ns), fl,
-                        by, st);
+      return launch_job(wave_job<WaveRunA, WaveRunB, Epi, BF>(WaveRunAParams{run_A(c, x), c.k * c.Cin}, b, ep, d.M, d.N,
+                                                             run_k(c), 1, ns), fl, by, st);
     }
     DenseParams b = fwd_B(c, wf);
     b.bytes = (uint32_t)(c.w_elems() / c.groups * 4);  // of a group

@@ -91,6 +91,32 @@ def test_infinities_and_large_numbers(lib):
     net.close()
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("cin,cout,k,stride,crop", [(3, 6, 5, 2, 33), (3, 12, 7, 2, 37), (1, 4, 3, 1, 20), (2, 10, 3, 1, 14),
+                                                    (3, 7, 2, 1, 9), (3, 9, 13, 2, 27)])
+def test_pixels_beside_a_window_do_not_reach_it(lib, cin, cout, k, stride, crop, precision):
+    """First layers in run mode, whose last quad of a kernel row reaches past the window: into the next pixels, the next row, the
+    next picture.  Infinities and NaNs in every third picture come out where 64 bits have them and nowhere else."""
+    rest = [(8, 3, 4, 1, 1, 0, 0), (8, 3, 4, 1, 1, 0, 0), (8, 3, 4, 1, 1, 0, 0), (8, 3, 1, 1, 1, 0, 0)]
+    net, batch = lib.AlexNet(net_of([(cout, k, stride, 0, 1, 0, 0)] + rest, crop, [8, 8, 4], cin), 7, precision=precision), 7
+    rng = np.random.default_rng(crop)
+    x = rng.standard_normal((batch, cin, crop, crop)).astype(np.float32)
+    w = rng.standard_normal((cout, cin, k, k)).astype(np.float32)
+    if precision:
+        x, w = (torch.from_numpy(a).bfloat16().float().numpy() for a in (x, w))
+    for n in range(0, batch, 3):
+        for at in ((0, 0), (0, crop - 1), (crop - 1, 0), tuple(rng.integers(0, crop, 2))):
+            x[n, rng.integers(0, cin), at[0], at[1]] = rng.choice([np.inf, -np.inf, np.nan])
+    with np.errstate(all="ignore"):
+        want = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double(), stride=stride).numpy()
+    got = net.conv_forward(1, cuda(x), cuda(w), None, False).cpu().numpy().reshape(want.shape)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    ok = np.isfinite(want)
+    assert rel_l2(got[ok], want[ok]) <= 2e-6
+    net.close()
+
+
 @pytest.mark.parametrize("name,batch", [("odd_channels", 19), ("large_kernel", 9), ("one_pixel", 33), ("one_channel", 12),
                                         ("odd_channels", 150)])
 def test_steps_on_edge_nets(lib, name, batch):
