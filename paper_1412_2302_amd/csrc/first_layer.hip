@@ -67,7 +67,8 @@ __device__ __forceinline__ void first_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int NB, bool Y16>
+// ODD: an odd number of octets, whose last step has one of its own only
+template <int NB, bool Y16, bool ODD>
 __global__ void __launch_bounds__(kFirstThreads, 2) first_layer_kernel(FirstGeom g) {
   typedef uint32_t v4u __attribute__((ext_vector_type(4)));
   __shared__ __attribute__((aligned(16))) v4u lds[kFirstUnits];
@@ -133,10 +134,13 @@ __global__ void __launch_bounds__(kFirstThreads, 2) first_layer_kernel(FirstGeom
     const int rr = (int)fdiv((uint32_t)q, g.d_run_oct), o = q - rr * g.run_oct, pos = (int)fdiv((uint32_t)o, g.d_planes);
     unit_tab[h] = rr * row_units + (o - pos * g.planes) * g.plane_units + pos;
   }
+  // ODD: the octet behind the last one meets zero weights, and a picture's infinity must not: it is a unit behind the picture,
+  // which stays zero.
+  const int zero = g.patch_rows * row_units - (int)(a0 - pl);
   auto unit_at = [&](int s) {  // of octet 2s + kh
     const int t = s < 32 ? unit_tab[0] : unit_tab[1], l = 2 * s & 63;
     const int u0 = __builtin_amdgcn_readlane(t, l), u1 = __builtin_amdgcn_readlane(t, l + 1);
-    return kh ? u1 : u0;
+    return kh ? (!ODD || s + 1 < steps ? u1 : zero) : u0;
   };
   float bias[NB];
 #pragma unroll
@@ -234,14 +238,19 @@ int launch_first16(const ConvGeom& c, const uint16_t* x4, const uint16_t* wk, co
                  4.0 * ((double)c.in_elems() + (double)c.w_elems() + (double)c.out_elems()), st);
   const dim3 grid(std::min(g.items, 256)), block(kFirstThreads);
   const int nb = ceil_div(c.Cout, 32);
-#define AX_FIRST(NB)                                                                                 \
-  if (y16) hipLaunchKernelGGL((first_layer_kernel<NB, true>), grid, block, 0, st, g);               \
-  else hipLaunchKernelGGL((first_layer_kernel<NB, false>), grid, block, 0, st, g)
+  const bool odd = g.octets % 2 != 0;
+#define AX_FIRST_AS(NB, ODD)                                                                            \
+  if (y16) hipLaunchKernelGGL((first_layer_kernel<NB, true, ODD>), grid, block, 0, st, g);              \
+  else hipLaunchKernelGGL((first_layer_kernel<NB, false, ODD>), grid, block, 0, st, g)
+#define AX_FIRST(NB)                       \
+  if (odd) { AX_FIRST_AS(NB, true); }      \
+  else { AX_FIRST_AS(NB, false); }
   if (nb == 1) { AX_FIRST(1); }
   else if (nb == 2) { AX_FIRST(2); }
   else if (nb == 3) { AX_FIRST(3); }
   else { AX_FIRST(4); }
 #undef AX_FIRST
+#undef AX_FIRST_AS
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }

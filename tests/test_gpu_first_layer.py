@@ -37,18 +37,37 @@ def test_first_layer_against_fp64(lib, in_c, crop, cout, k, stride, batch):
     net.close()
 
 
-def test_pictures_next_to_each_other_do_not_mix(lib):
-    """One picture full of infinities: the rows of a tile past a picture's end, and the padded pixels, come from others."""
-    wl, batch = net_of(3, 131, 96, 11, 4), 24
-    net = lib.AlexNet(wl, batch, precision=1)
+@pytest.mark.parametrize("in_c,crop,cout,k,stride,batch", [
+    (3, 131, 96, 11, 4, 24), (3, 160, 72, 9, 2, 12), (1, 200, 40, 5, 4, 60), (2, 253, 8, 15, 6, 40), (3, 227, 136, 11, 4, 5)])
+def test_infinities_reach_their_own_windows_only(lib, in_c, crop, cout, k, stride, batch):
+    """The rows of a tile past a picture's end come from the next picture and must not show.  A kernel row is read in pairs of
+    pixels: behind an odd one the next pixel in memory, at a row's end the next row's first, meets zero weights, so that an
+    infinity there makes a NaN.  That much and no more: the reference has the same extra column, everything else is as it is
+    without infinities, bit for bit."""
+    net = lib.AlexNet(net_of(in_c, crop, cout, k, stride), batch, precision=1)
     rng = np.random.default_rng(2)
-    x = rng.standard_normal((batch, 3, 131, 131)).astype(np.float32)
-    w = cuda(rng.standard_normal((96, 3, 11, 11)).astype(np.float32))
-    clean = net.conv_forward(1, cuda(x), w, None).cpu().numpy().reshape(batch, -1)
-    x[7] = np.inf
-    got = net.conv_forward(1, cuda(x), w, None).cpu().numpy().reshape(batch, -1)
-    keep = np.arange(batch) != 7
-    assert np.isfinite(got[keep]).mean() > 0.99 and not np.isfinite(got[7]).any()
-    same = np.isfinite(got[keep])
-    assert np.array_equal(got[keep][same], clean[keep][same])
+    x = rng.standard_normal((batch, in_c, crop, crop)).astype(np.float32)
+    w = cuda(rng.standard_normal((cout, in_c, k, k)).astype(np.float32))
+    clean = net.conv_forward(1, cuda(x), w, None).cpu().numpy()
+    x[batch // 3] = np.inf
+    for n in (0, batch - 1):
+        for at in ((0, 0), (0, crop - 1), (crop - 1, 0), tuple(rng.integers(0, crop, 2))):
+            x[n, rng.integers(0, in_c), at[0], at[1]] = rng.choice([np.inf, -np.inf, np.nan])
+    got = net.conv_forward(1, cuda(x), w, None).cpu().numpy()
+    xt, wt = torch.from_numpy(x).bfloat16().double(), w.cpu().bfloat16().double()
+    if k % 2:
+        rows = xt.permute(1, 0, 2, 3).reshape(in_c, -1, crop)
+        behind = torch.cat([rows[:, 1:, :1], torch.zeros(in_c, 1, 1, dtype=torch.double)], 1)
+        xt = torch.cat([rows, behind], 2).reshape(in_c, batch, crop, crop + 1).permute(1, 0, 2, 3)
+        wt = torch.nn.functional.pad(wt, (0, 1))
+    # the reference multiplies its zero weights too: one product after the other, as F.conv2d need not
+    cols = torch.nn.functional.unfold(xt, (k, k + k % 2), stride=stride)
+    want = torch.matmul(wt.flatten(1), cols).numpy().reshape(got.shape)
+    finite = np.isfinite(want)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)].astype(np.float32))
+    got, clean = (a.reshape(batch, -1) for a in (got, clean))
+    finite = finite.reshape(batch, -1)
+    assert finite.any() and not finite.all()
+    assert np.array_equal(got[finite], clean[finite])
     net.close()
