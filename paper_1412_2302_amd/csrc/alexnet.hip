@@ -104,7 +104,7 @@ struct Stage {
   uint16_t* x16_own;  // the stage's own x16; in a training or inference pass the first layer's x16 points at the
                       // padded copy that preprocessing left beside the input slot instead
   uint8_t* slot;
-  char lab[4][16];  // profiling labels: stage, .fwd, .bwd_w, .bwd_x
+  char lab[5][16];  // profiling labels: stage, .fwd, .bwd_w, .bwd_x, .bwd (both gradients in one launch)
   long act_elems() const { return g.out_elems(); }
   long out_elems() const { return (long)g.B * Hp * Wp * g.Cout; }
   const float* out() const { return pool ? pool_out : lrn ? lrn_out : act; }
@@ -116,7 +116,7 @@ struct Dense {
   size_t w_off, b_off;
   float *act, *dz;
   uint16_t *act16, *dz16;  // bf16 copies for the products of a bf16 handle (null otherwise)
-  char lab[4][16];
+  char lab[5][16];
 };
 
 // Bump allocator over the caller's workspace; with base == null it only sizes.
@@ -245,6 +245,7 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector
     snprintf(s.lab[1], 16, "conv%d.fwd", i + 1);
     snprintf(s.lab[2], 16, "conv%d.bwd_w", i + 1);
     snprintf(s.lab[3], 16, "conv%d.bwd_x", i + 1);
+    snprintf(s.lab[4], 16, "conv%d.bwd", i + 1);
     s.w_off = off;
     off += (size_t)s.g.w_elems();
     C = cv.cout; H = s.Hp; W = s.Wp;
@@ -265,6 +266,7 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector
     snprintf(n->fc[j].lab[1], 16, "fc%d.fwd", kStages + 1 + j);
     snprintf(n->fc[j].lab[2], 16, "fc%d.bwd_w", kStages + 1 + j);
     snprintf(n->fc[j].lab[3], 16, "fc%d.bwd_x", kStages + 1 + j);
+    snprintf(n->fc[j].lab[4], 16, "fc%d.bwd", kStages + 1 + j);
     n->fc[j].w_off = off;
     off += (size_t)in * c.fc[j];
     in = c.fc[j];
@@ -618,9 +620,21 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     Stage& last = n->st[kStages - 1];
     // fc(j-1) output is ReLU+dropout: it is positive exactly where the gradient passes
     const float* gate = j > 0 ? n->fc[j - 1].act : last.plain() ? last.act : nullptr;
+    float* dx = j > 0 ? n->fc[j - 1].dz : last.d_out;
+    uint16_t* dx16 = j > 0 ? n->fc[j - 1].dz16 : nullptr;
+    const float* w = n->params + f.w_off;
+    float* dw = n->grads + f.w_off;
+    if (wave_fc_bwd_ok(c.batch, f.in, f.out, c.precision == ALEXNET_PRECISION_BF16)) {
+      ProfContext pc(f.lab[4]);
+      AX_TRY(launch_fc_bwd(c.batch, f.in, f.out, x, f.dz, w, gate, dx, dw, st, dx16));
+      continue;
+    }
+    {
+      ProfContext pc(f.lab[2]);
+      AX_TRY(launch_fc_bwd_weight(c.batch, f.in, f.out, x, f.dz, dw, st, x16, f.dz16));
+    }
     ProfContext pc(f.lab[3]);
-    AX_TRY(launch_fc_bwd(c.batch, f.in, f.out, x, f.dz, n->params + f.w_off, gate, j > 0 ? n->fc[j - 1].dz : last.d_out,
-                         n->grads + f.w_off, n->gemm_ws, st, x16, f.dz16, w16, j > 0 ? n->fc[j - 1].dz16 : nullptr));
+    AX_TRY(launch_fc_bwd_data(c.batch, f.in, f.out, f.dz, w, gate, dx, n->gemm_ws, st, f.dz16, w16, dx16));
   }
   bool waited = false;      // for the side stream's forms of the weights
   bool dy16_ready = false;  // the kernel that made this stage's output gradient also left its bf16 copy in s.dy16
@@ -682,7 +696,7 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       const bool bf = conv_bwd_weight_bf16(s.g, x, s.dact);
       if (!bias_done)
         AX_TRY(colsum_batch_add(bias_sums, s.dact, s.g.P(), s.g.Cout, n->grads + s.b_off, n->colsum_ws, &bias_ws_used));
-      ProfContext pc(s.lab[i > 0 ? 3 : 2]);
+      ProfContext pc(s.lab[i > 0 ? 4 : 2]);
       dy16_ready = false;
       if (i == 0) {
         AX_TRY(launch_wave_conv_bwd_weight(s.g, x, s.dact, n->grads + s.w_off, s.wave_slices, bf, st, &wgrad_tail));

@@ -1270,14 +1270,9 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
 }
 
 int launch_fc_bwd(int B, int in, int out, const float* x, const float* dy, const float* w, const float* gate, float* dx,
-                  float* dw, float* ws, hipStream_t st, const uint16_t* x16, const uint16_t* dy16, const uint16_t* w16,
-                  uint16_t* dx16) {
-  if (wave_fc_bwd_ok(B, in, out, g_bf16)) {
-    const bool bf = g_bf16 && vec_ok(dy, out) && vec_ok(w, in) && vec_ok(x, in);
-    return launch_wave_fc_bwd(B, in, out, x, dy, w, gate, dx, dx16, dw, bf, st);
-  }
-  AX_TRY(launch_fc_bwd_weight(B, in, out, x, dy, dw, st, x16, dy16));
-  return launch_fc_bwd_data(B, in, out, dy, w, gate, dx, ws, st, dy16, w16, dx16);
+                  float* dw, hipStream_t st, uint16_t* dx16) {
+  const bool bf = g_bf16 && vec_ok(dy, out) && vec_ok(w, in) && vec_ok(x, in);
+  return launch_wave_fc_bwd(B, in, out, x, dy, w, gate, dx, dx16, dw, bf, st);
 }
 
 int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy, float* dw, hipStream_t st,

@@ -133,10 +133,9 @@ int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, 
 int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy, float* dw, hipStream_t st,
                          const uint16_t* x16 = nullptr, const uint16_t* dy16 = nullptr);
 
-// both gradients: dw, and dx as launch_fc_bwd_data gives it
+// both gradients in one launch, where wave_fc_bwd_ok(): dw, and dx as launch_fc_bwd_data gives it
 int launch_fc_bwd(int B, int in, int out, const float* x, const float* dy, const float* w, const float* gate, float* dx,
-                  float* dw, float* ws, hipStream_t st, const uint16_t* x16, const uint16_t* dy16, const uint16_t* w16,
-                  uint16_t* dx16);
+                  float* dw, hipStream_t st, uint16_t* dx16);
 
 // Seconds that the tile kernels take for a product, by their planners; bf: in a handle with bf16 products
 double tile_seconds_fwd(const ConvGeom& c, bool bf);

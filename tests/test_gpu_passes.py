@@ -81,6 +81,23 @@ def test_step_with_some_stages_transformed_and_others_direct(lib):
         assert transformed(names, what) == [2, 3], what
 
 
+@pytest.mark.parametrize("wl,batch,precision,paired", [(S.MINI, 16, 0, True), (S.MINI, 16, 1, True), (S.ALEXNET, 8, 0, False),
+                                                       (S.ALEXNET, 8, 1, False)])
+def test_profile_names_every_gradient(lib, wl, batch, precision, paired):
+    """A product's time is found under its layer and pass: both gradients under .bwd where they are one launch, else each under
+    its own name."""
+    net = lib.AlexNet(wl, batch, precision=precision)
+    x, labels = S.make_float_batch(batch, wl["in_c"], wl["crop"], wl["crop"], wl["fc"][-1], 3)
+    net.set_input(cuda(x), 0)
+    names, _ = kernels_of(lib, lambda: net.forward_backward(cuda(labels), 0))
+    products = {n.split(":")[0] for n in names if n.split(":")[-1].startswith("gemm")}
+    for layer in ("fc6", "fc7", "fc8", "conv2"):
+        want = {layer + ".fwd"} | ({layer + ".bwd"} if paired else {layer + ".bwd_w", layer + ".bwd_x"})
+        assert {p for p in products if p.startswith(layer + ".")} == want
+    assert "conv1.bwd_w" in products
+    net.close()
+
+
 # ------------------------------------------------------------- inference ---
 def spread_params(net, seed):
     """Weights N(0, 1/fan_in) and small biases: logits of order one."""
