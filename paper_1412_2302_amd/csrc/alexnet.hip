@@ -91,6 +91,7 @@ struct Stage {
   bool wino_bx;  // data gradient too
   bool wino_pass;  // in training and inference passes too (see winograd_in_pass)
   bool wave;       // every product of the stage's passes is a small one (gemm_wave.h), which reads fp32 tensors and wf only
+  bool wave_fwd;   // the forward product is
   float *wino_v, *wino_u, *wino_ub;
   float *wrun, *dwrun;  // run-mode copies of the weights and their gradient (null when not used)
   // bf16 handles: copies in bf16 (nearest even) of the stage's GEMM operands -- input, output gradient, and the
@@ -158,6 +159,7 @@ struct alexnet {
   size_t gemm_ws_floats, colsum_ws_floats_;
   int flat;  // flatten size feeding fc6
   int upd_fork_stage;   // stage of the backward pass beside which the dense-layer update starts on the side stream
+  bool beside;          // the dense layers are no small products: their update is worth a stream of its own
   bool fork_train;      // training steps make the weights' forms and update the dense layers on the side stream
   bool fork_inference;  // inference passes make the weights' forms on the side stream
   // The dense layers hold 96 % of the parameters and finish their backward pass first: their update, which is
@@ -279,6 +281,11 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector
   // ---- workspace ----
   Arena a{base, 0, pieces};
   const bool bf = c.precision == ALEXNET_PRECISION_BF16;
+  n->beside = false;
+  for (int j = 0; j < kFc; ++j) {
+    const Dense& f = n->fc[j];
+    n->beside = n->beside || !wave_fc_fwd_ok(c.batch, f.in, f.out, bf) || !wave_fc_bwd_ok(c.batch, f.in, f.out, bf);
+  }
   const size_t in_elems = (size_t)c.batch * c.crop_h * c.crop_w * c.in_c;
   for (int s = 0; s < kSlots; ++s) {
     n->input[s] = a.take<float>(in_elems);
@@ -303,7 +310,8 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector
     s.wphase = conv_phase_mode(s.g) ? a.take<float>(conv_phase_w_floats(s.g)) : nullptr;
     s.wrun = conv_run_mode(s.g) ? a.take<float>(conv_run_w_floats(s.g)) : nullptr;
     s.dwrun = conv_run_mode(s.g) ? a.take<float>(conv_run_w_floats(s.g)) : nullptr;
-    s.wave = wave_conv_fwd_ok(s.g, bf) && (i == 0 ? wave_conv_bwd_weight_ok(s.g, bf) : wave_conv_bwd_ok(s.g, bf));
+    s.wave_fwd = wave_conv_fwd_ok(s.g, bf);
+    s.wave = s.wave_fwd && (i == 0 ? wave_conv_bwd_weight_ok(s.g, bf) : wave_conv_bwd_ok(s.g, bf, n->beside));
     s.b16 = c.precision == ALEXNET_PRECISION_BF16 && !s.wave && conv_bf16_stored_ok(s.g) && s.w_off % 4 == 0;
     s.r16 = c.precision == ALEXNET_PRECISION_BF16 && !s.wave && !s.b16 && conv_run16_ok(s.g) && s.w_off % 4 == 0;
     s.x16 = s.b16 ? a.take<uint16_t>(s.g.in_elems()) : s.r16 ? a.take<uint16_t>(conv_run16_x_elems(s.g)) : nullptr;
@@ -319,7 +327,7 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector
     s.wino = use_winograd(c, s.g) && s.w_off % 4 == 0 && s.b_off % 4 == 0;
     s.wino_bx = s.wino && wino_bwd_data_ok(s.g);
     s.wino_pass = s.wino && winograd_in_pass(s.g);
-    if (s.wino_pass) s.wave = false;
+    if (s.wino_pass) s.wave = s.wave_fwd = false;
     s.wave_slices = s.wave && wave_conv_bwd_weight_ws_floats(s.g) ? a.take<float>(wave_conv_bwd_weight_ws_floats(s.g)) : nullptr;
     s.wino_v = s.wino ? a.take<float>(wino_v_floats(s.g)) : nullptr;
     s.wino_u = s.wino ? a.take<float>(wino_u_floats(s.g)) : nullptr;
@@ -353,15 +361,9 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector
   const bool fp32 = c.precision == ALEXNET_PRECISION_FP32;
   n->upd_fork_stage = fp32 && conv_flops >= kLateUpdateFlops ? kStages - 2 : kStages - 1;
   n->fork_inference = fp32 || conv_flops >= kForkFlops;
-  n->fc16 = c.precision == ALEXNET_PRECISION_BF16 && n->fc[0].w_off % 4 == 0;
-  bool fc_wave = true;
-  for (int j = 0; j < kFc; ++j) {
-    const Dense& f = n->fc[j];
-    n->fc16 = n->fc16 && fc_bf16_stored_ok(f.in, f.out);
-    fc_wave = fc_wave && wave_fc_fwd_ok(c.batch, f.in, f.out, bf) && wave_fc_bwd_ok(c.batch, f.in, f.out, bf);
-  }
-  n->fc16 = n->fc16 && !fc_wave;
-  n->fork_train = !fc_wave;
+  n->fc16 = bf && n->beside && n->fc[0].w_off % 4 == 0;
+  for (int j = 0; j < kFc; ++j) n->fc16 = n->fc16 && fc_bf16_stored_ok(n->fc[j].in, n->fc[j].out);
+  n->fork_train = n->beside;
   for (int i = 0; i < kStages; ++i) n->fork_train = n->fork_train || !n->st[i].wave;
   n->fcw16 = n->fc16 ? a.take<uint16_t>(n->n_weights - n->fc[0].w_off) : nullptr;
   n->flat16 = n->fc16 ? a.take<uint16_t>((size_t)c.batch * n->flat) : nullptr;
@@ -437,7 +439,7 @@ static int stage_fwd(alexnet* n, Stage& s, const float* x, const float* wf, cons
   }
   if (b16_usable(s, x, wf)) {
     if (!x16_ready) AX_TRY(launch_to_bf16(x, s.x16, (size_t)s.g.in_elems(), st));
-    if (!taps_ready) AX_TRY(launch_to_bf16_transposed(wf, s.wf16, s.g.groups, s.g.kf(), s.g.og(), st));
+    if (!taps_ready && !s.wave_fwd) AX_TRY(launch_to_bf16_transposed(wf, s.wf16, s.g.groups, s.g.kf(), s.g.og(), st));
     return launch_conv_fwd(s.g, x, wf, nullptr, bias, relu, y, n->gemm_ws, st, s.x16, s.wf16, y16);
   }
   if (s.r16) {  // x16_ready: s.x16 holds the pictures padded to four channels
@@ -448,6 +450,10 @@ static int stage_fwd(alexnet* n, Stage& s, const float* x, const float* wf, cons
   if (s.wrun && !wave_conv_fwd_ok(s.g, n->cfg.precision == ALEXNET_PRECISION_BF16)) AX_TRY(launch_conv_run_pack(s.g, wf, s.wrun, st));
   return launch_conv_fwd(s.g, x, wf, s.wrun, bias, relu, y, n->gemm_ws, st, nullptr, nullptr, y16);
 }
+// Whether one gradient of a stage may be a small product: beside a large update such a product is worth it for both at once or
+// not at all (see wave_conv_bwd_ok; one by one, 8 pictures of the full net 1007 us a step, 954 with tiles).  The first layer's
+// comes last, when the update is through.
+static bool small_ok(const alexnet* n, const Stage& s, bool in_pass) { return !in_pass || !n->beside || &s == &n->st[0]; }
 // have_v: the forward pass of the same minibatch left its form of x in place (s.wino_v, the transform of x; s.x16,
 // its bf16 copy)
 // tail: put the end of a transformed stage's weight gradient off to launch_wgrad_tail() (see WgradTail)
@@ -471,7 +477,7 @@ static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* d
       AX_TRY(launch_direct_bwd_weight(s.g, s.x16, s.dy16, slices, st));
       return add_weight_slices(s.g, slices, ns, dwf, tail, st);
     }
-    return launch_conv_bwd_weight(s.g, x, dy, dwf, nullptr, n->gemm_ws, st);
+    return launch_conv_bwd_weight(s.g, x, dy, dwf, nullptr, n->gemm_ws, st, nullptr, small_ok(n, s, in_pass));
   }
   if (s.r16 && first_weight_ok(s.g)) {
     if (!have_v) AX_TRY(launch_pad4_bf16(x, s.x16, (size_t)s.g.Q(), s.g.Cin, st));
@@ -480,7 +486,7 @@ static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* d
     AX_TRY(launch_first_weight(s.g, s.x16, dy, slices, st));
     return add_weight_slices(s.g, slices, ns, dwf, tail, st);
   }
-  return launch_conv_bwd_weight(s.g, x, dy, dwf, s.dwrun, n->gemm_ws, st);
+  return launch_conv_bwd_weight(s.g, x, dy, dwf, s.dwrun, n->gemm_ws, st, nullptr, small_ok(n, s, in_pass));
 }
 // taps_ready: the forms of wb are in place (s.wino_ub; s.wb16); yt_ready: so is that of dy (n->wino_a, the
 // transformed output gradient; s.dy16): stage_bwd_weight of the same minibatch ran just before
@@ -497,9 +503,9 @@ static int stage_bwd_data(alexnet* n, Stage& s, const float* dy, const float* wf
   if (b16_usable(s, dy, wb)) {
     if (!yt_ready) AX_TRY(launch_to_bf16(dy, s.dy16, (size_t)s.g.out_elems(), st));
     if (!taps_ready) AX_TRY(launch_to_bf16_transposed(wb, s.wb16, s.g.groups, s.g.kb(), s.g.cg(), st));
-    return launch_conv_bwd_data(s.g, dy, wf, wb, nullptr, gate, dx, n->gemm_ws, st, s.dy16, s.wb16, dx16);
+    return launch_conv_bwd_data(s.g, dy, wf, wb, nullptr, gate, dx, n->gemm_ws, st, s.dy16, s.wb16, dx16, small_ok(n, s, in_pass));
   }
-  return launch_conv_bwd_data(s.g, dy, wf, wb, wphase, gate, dx, n->gemm_ws, st, nullptr, nullptr, dx16);
+  return launch_conv_bwd_data(s.g, dy, wf, wb, wphase, gate, dx, n->gemm_ws, st, nullptr, nullptr, dx16, small_ok(n, s, in_pass));
 }
 
 // --------------------------------------------------------------- passes ------
@@ -754,7 +760,7 @@ static int fork_forward_weights(alexnet* n, bool train, hipStream_t st) {
     Stage& s = n->st[i];
     ProfContext pc(s.lab[1]);
     if (s.wino_pass) AX_TRY(launch_wino_filter(s.g, n->params + s.w_off, s.wino_u, n->upd_stream));
-    if (s.b16)
+    if (s.b16 && !s.wave_fwd)
       AX_TRY(launch_to_bf16_transposed(n->params + s.w_off, s.wf16, s.g.groups, s.g.kf(), s.g.og(), n->upd_stream));
     if (s.r16)
       AX_TRY(launch_run16_pack(n->params + s.w_off, s.wf16, s.g.k, s.g.Cin,

@@ -839,7 +839,7 @@ static int launch_conv_bwd_data_phases(const ConvGeom& c, const float* dy, const
 
 int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, const float* wb, float* wphase,
                          const float* gate, float* dx, float* ws, hipStream_t st, const uint16_t* dy16,
-                         const uint16_t* wb16, uint16_t* dx16) {
+                         const uint16_t* wb16, uint16_t* dx16, bool small) {
   // dx16: also leave a bf16 copy of dx there (see launch_conv_fwd)
   struct Copy16 {
     const float* y; uint16_t* y16; size_t n; hipStream_t st; bool pending;
@@ -849,7 +849,7 @@ int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, co
     copy.pending = dx16 != nullptr;
     return finish(launch_conv_bwd_data_phases(c, dy, wf, wphase, dx, st));
   }
-  if (wave_conv_bwd_data_ok(c, g_bf16))
+  if (small && wave_conv_bwd_data_ok(c, g_bf16))
     return launch_wave_conv_bwd_data(c, dy, wf, gate, dx, dx16, ws, g_bf16 && bwdd_A_vec(c, dy) && bwdd_B_vec(c, wf), st);
   const GemmDims d = bwdd_dims(c);
   AlgoFlops af(conv_flops(c), conv_bytes(c));
@@ -918,8 +918,8 @@ bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy) {
 // defer_ns (generic layout only): the split-k slices are left in ws, [group][slice][slab], and their number is
 // returned there for the caller to add them up later (1: the result is in dwf already)
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
-                           hipStream_t st, int* defer_ns) {
-  if (wave_conv_bwd_weight_ok(c, g_bf16)) {
+                           hipStream_t st, int* defer_ns, bool small) {
+  if (small && wave_conv_bwd_weight_ok(c, g_bf16)) {
     if (defer_ns) *defer_ns = 1;
     return launch_wave_conv_bwd_weight(c, x, dy, dwf, ws, conv_bwd_weight_bf16(c, x, dy), st);
   }

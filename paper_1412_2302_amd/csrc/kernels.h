@@ -78,11 +78,12 @@ int launch_first16(const ConvGeom& c, const uint16_t* x4, const uint16_t* wk, co
 // scratch) is given; it then reads the forward weights wf instead of wb.
 bool conv_phase_mode(const ConvGeom& c);
 size_t conv_phase_w_floats(const ConvGeom& c);
+// small: a small product (gemm_wave.h) may take it, here and below
 int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, const float* wb, float* wphase,
                          const float* gate, float* dx, float* ws, hipStream_t st, const uint16_t* dy16 = nullptr,
-                         const uint16_t* wb16 = nullptr, uint16_t* dx16 = nullptr);
+                         const uint16_t* wb16 = nullptr, uint16_t* dx16 = nullptr, bool small = true);
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
-                           hipStream_t st, int* defer_ns = nullptr);
+                           hipStream_t st, int* defer_ns = nullptr, bool small = true);
 
 // ---- 3x3 and 5x5 unit-stride convolutions through F(4x4, 3x3) (winograd.hip) ----
 // All tensors 16-byte aligned, channels per group multiples of 4.  V: wino_v_floats(), U / Ub / dU:
@@ -166,7 +167,7 @@ int launch_direct_bwd_weight(const ConvGeom& c, const uint16_t* x16, const uint1
 int launch_direct_dense_bwd_data(int B, int in, int out, const uint16_t* dy16, const uint16_t* w16, float* slabs, hipStream_t st);
 int launch_direct_dense_bwd_weight(int B, int in, int out, const uint16_t* x16, const uint16_t* dy16, float* dw, hipStream_t st);
 bool wave_conv_bwd_weight_ok(const ConvGeom& c, bool bf);
-bool wave_conv_bwd_ok(const ConvGeom& c, bool bf);  // both gradients in one launch
+bool wave_conv_bwd_ok(const ConvGeom& c, bool bf, bool beside);  // both gradients in one launch; beside: a large update
 bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy);
 int wave_conv_fwd_slices(const ConvGeom& c);
 int wave_conv_bwd_data_slices(const ConvGeom& c);

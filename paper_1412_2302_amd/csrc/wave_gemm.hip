@@ -27,15 +27,26 @@ struct WavePlan {
   double blocks, steps;  // of the launch; of a workgroup
   double seconds;
 };
+// Waves per workgroup, for a launch of so many workgroups whose longest reduction has so many steps
+static int wave_count(double blocks, double steps) {
+  if (blocks <= 256 && steps > 8) return 16;
+  return blocks <= 512 && steps > 4 ? 8 : 4;
+}
+// The chain of steps that one wave of so many has, at `link` seconds each; counts where it outlasts the chip's share of the work.
+static double chain_seconds(double steps, int waves, double link) { return kWaveLaunch + std::ceil(steps / waves) * link; }
+// of a data gradient: a lane reads 32 bytes of a row of og weights at a time, and past a cache line each lane's row is in a line
+// of its own (rows of 128 bytes and less, mini and midi net: 0.7 to 0.85 us a step)
+static double data_link(const ConvGeom& c) { return c.og() > 32 ? 1.3e-6 : 0.8e-6; }
 // max_k: longest slice the tables hold
-static WavePlan wave_plan(long M, long N, long K, int groups, bool bf, long max_k) {
+static WavePlan wave_plan(long M, long N, long K, int groups, bool bf, long max_k, double link = 0) {
   const double blocks = (double)ceil_div(M, kWaveTile) * ceil_div(N, kWaveTile) * groups;
   const int steps = ceil_div(K, 16), least = ceil_div(K, max_k);
   WavePlan best{least, 0, 0, 1e30};
   for (int ns = least; ns <= least + 15; ++ns) {
     const int per = ceil_div(steps, ns);
     if (ns > least && (per < 4 || ceil_div(steps, per) != ns)) continue;
-    const double t = wave_seconds(blocks * ns, per, bf) + (ns > 1 ? kWaveFinish : 0);
+    const double t = std::max(wave_seconds(blocks * ns, per, bf), chain_seconds(per, wave_count(blocks * ns, per), link)) +
+                     (ns > 1 ? kWaveFinish : 0);
     if (t < 0.98 * best.seconds) best = WavePlan{ns, blocks * ns, (double)per, t};
   }
   return best;
@@ -58,11 +69,6 @@ static WaveJob<AL, BL, Epi, BF> wave_job(const typename AL::Params& a, const typ
   j.ns = make_fastdiv((uint32_t)ns);
   j.blocks = (uint32_t)(gx * gy * groups * ns);
   return j;
-}
-// Waves per workgroup, for a launch of so many workgroups whose longest reduction has so many steps
-static int wave_count(uint32_t blocks, int steps) {
-  if (blocks <= 256 && steps > 8) return 16;
-  return blocks <= 512 && steps > 4 ? 8 : 4;
 }
 template <class J>
 static int launch_job(const J& j, double flops, double bytes, hipStream_t st) {
@@ -99,7 +105,7 @@ static WavePlan fwd_plan(const ConvGeom& c, bool bf) {
 }
 static WavePlan bwd_data_plan(const ConvGeom& c, bool bf) {
   const GemmDims d = bwdd_dims(c);
-  return wave_plan(d.M, d.N, d.K, d.groups, bf, kWaveMaxK);
+  return wave_plan(d.M, d.N, d.K, d.groups, bf, kWaveMaxK, data_link(c));
 }
 static WavePlan bwd_weight_plan(const ConvGeom& c, bool bf) {
   const GemmDims d = bwdw_dims(c);
@@ -122,13 +128,20 @@ bool wave_conv_bwd_data_ok(const ConvGeom& c, bool bf) {
 bool wave_conv_bwd_weight_ok(const ConvGeom& c, bool bf) {
   return bwd_weight_fits(c) && bwd_weight_plan(c, bf).seconds < tile_floor(tile_seconds_bwd_weight(c, bf), bf, true);
 }
-// in one launch the data gradient is not sliced
-bool wave_conv_bwd_ok(const ConvGeom& c, bool bf) {
+// Both gradients in one launch, where the data gradient is not sliced.  beside: large dense layers are updated meanwhile, which
+// slows these kernels more than tiles.  Full net, fp32, tiles against small products by the profiler, us, and what the work
+// alone comes to: fourth layer, 2, 4, 6 and 8 pictures 46 | 53 (17), 58 | 75 (30), 67 | 98 (42), 82 | 131 (55); fifth, 4, 8 and 12
+// 50 | 39 (21), 70 | 57 (38), 79 | 97 (55); chains of 50 and 54 steps, second and third layer, 2 pictures 40 | 77 (33) and 51 | 91
+// (19); bf16 alike.  With the work alone compared, whole steps at 2 to 12 pictures took 1 to 4 % more than with tiles.
+constexpr double kWaveBeside = 1.6;
+bool wave_conv_bwd_ok(const ConvGeom& c, bool bf, bool beside) {
   if (!bwd_data_fits(c) || !bwd_weight_fits(c) || c.kb() > kWaveMaxK) return false;
   const WavePlan w = bwd_weight_plan(c, bf);
   const GemmDims d = bwdd_dims(c);
-  const double x = (double)ceil_div(d.M, kWaveTile) * ceil_div(d.N, kWaveTile) * d.groups * ceil_div(d.K, 16);
-  return wave_seconds(w.blocks + x / w.steps, w.steps, bf) + (w.ns > 1 ? kWaveFinish : 0) <
+  const double blocks = (double)ceil_div(d.M, kWaveTile) * ceil_div(d.N, kWaveTile) * d.groups, steps = ceil_div(d.K, 16);
+  const double work = wave_seconds(w.blocks + blocks * steps / w.steps, w.steps, bf) * (beside ? kWaveBeside : 1);
+  const double chain = chain_seconds(steps, wave_count(w.blocks + blocks, std::max(w.steps, steps)), data_link(c));
+  return std::max(work, chain) + (w.ns > 1 ? kWaveFinish : 0) <
          tile_floor(tile_seconds_bwd_data(c, bf), bf) + tile_floor(tile_seconds_bwd_weight(c, bf), bf, true);
 }
 int wave_conv_fwd_slices(const ConvGeom& c) {
