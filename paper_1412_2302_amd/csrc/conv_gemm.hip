@@ -266,13 +266,15 @@ static int launch_tile192(const Im2colParams& a, const DenseParams& b, const Epi
 // ---- operands straight to LDS (gemm_direct.h) ----
 // Workgroups on the busiest compute unit run in rounds of as many as it holds; a round of n takes first[n-1] + each[n-1] * the
 // megaflops of a tile microseconds.  Fitted to (tile, workgroups, MFLOP a tile, us): 128 x 64: 2028 37.7 97.8, 2028 28.3 81.8,
-// 510 37.7 29.1, 510 18.9 19.1; 128 x 128: 1014 75.5 87.8, 676 56.6 59.5, 255 75.5 31.8, 170 56.6 24.6, 340 56.6 33.1; 192 x
-// 128: 452 169.9 82.3, 452 84.9 49.6, 171 113 39.2, 114 84.9 31.3.
+// 510 37.7 29.1, 510 18.9 19.1, 132 28.3 18, 132 37.7 24.1, 128 56.6 29.2, 66 18.9 12; 128 x 128: 1014 75.5 87.8, 676 56.6 59.5,
+// 255 75.5 31.8, 170 56.6 24.6, 340 56.6 33.1; 192 x 128: 452 169.9 82.3, 452 84.9 49.6, 171 113 39.2, 114 84.9 31.3.
+// Slices only where 128 x 64 tiles leave compute units without one (the sums move 4 to 6 TB/s; third layer, 258 tiles and more,
+// forward of 37 pictures 26 us either way, data gradient of 64 31 whole, 34 in slices).
 struct DirectTile {
   int bm, bn, occ;
   double first[3], each[3];
 };
-static const DirectTile kDirectTiles[] = {{128, 64, 3, {7, 9.1, 12.2}, {0.32, 0.53, 0.585}},
+static const DirectTile kDirectTiles[] = {{128, 64, 3, {5, 9.1, 12.2}, {0.46, 0.53, 0.585}},
                                           {128, 128, 2, {3, 8, 0}, {0.38, 0.476, 0}},
                                           {192, 128, 2, {7.5, 17, 0}, {0.28, 0.385, 0}}};
 struct DirectPlan {
@@ -282,10 +284,11 @@ static DirectPlan plan_direct(const GemmDims& d, double out_bytes, double* t_out
   DirectPlan best{0, 1, ceil_div(d.K, kBKd)};
   double best_t = 1e30;
   const int ktiles = ceil_div(d.K, kBKd);
+  const int most = (long)ceil_div(d.M, 128) * ceil_div(d.N, 64) * d.groups > 256 ? 1 : 8;
   for (int o = 0; o < 3; ++o) {
     const DirectTile& to = kDirectTiles[o];
     const long tiles = (long)ceil_div(d.M, to.bm) * ceil_div(d.N, to.bn) * d.groups;
-    for (int s = 1; s <= 8 && s <= ktiles; ++s) {
+    for (int s = 1; s <= most && s <= ktiles; ++s) {
       const int per = ceil_div(ktiles, s);
       if (ceil_div(ktiles, per) != s || (s > 1 && per < 4)) continue;
       const int c = ceil_div(tiles * s, 256), rest = c % to.occ;
@@ -293,7 +296,7 @@ static DirectPlan plan_direct(const GemmDims& d, double out_bytes, double* t_out
       double t = c / to.occ * (to.first[to.occ - 1] + to.each[to.occ - 1] * f);
       if (rest) t += to.first[rest - 1] + to.each[rest - 1] * f;
       t *= 1e-6;
-      if (s > 1) t += (s + 1) * out_bytes / 2.5e12 + kSecondLaunch;
+      if (s > 1) t += (s + 1) * out_bytes / 6e12 + kSecondLaunch;
       if (t < 0.98 * best_t) {
         best_t = t;
         best = DirectPlan{o, s, per};
