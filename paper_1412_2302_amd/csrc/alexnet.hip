@@ -438,7 +438,8 @@ static int stage_fwd(alexnet* n, Stage& s, const float* x, const float* wf, cons
     return y16 ? launch_to_bf16(y, y16, (size_t)s.g.out_elems(), st) : ALEXNET_OK;
   }
   if (b16_usable(s, x, wf)) {
-    if (!x16_ready) AX_TRY(launch_to_bf16(x, s.x16, (size_t)s.g.in_elems(), st));
+    // a small forward product reads x and wf; in a pass the weight gradient takes x16
+    if (!x16_ready && (in_pass || !s.wave_fwd)) AX_TRY(launch_to_bf16(x, s.x16, (size_t)s.g.in_elems(), st));
     if (!taps_ready && !s.wave_fwd) AX_TRY(launch_to_bf16_transposed(wf, s.wf16, s.g.groups, s.g.kf(), s.g.og(), st));
     return launch_conv_fwd(s.g, x, wf, nullptr, bias, relu, y, n->gemm_ws, st, s.x16, s.wf16, y16);
   }

@@ -19,9 +19,10 @@ static double wave_seconds(double blocks, double steps, bool bf) {
 }
 // bf16 tiles the planner has at 7 us took 13 (36 workgroups), and have weights converted for them first; weight gradients of
 // 16 output channels 29 where it has 19
-static double tile_floor(double seconds, bool bf, bool weight = false) {
-  return bf && seconds < (weight ? 25e-6 : 18e-6) ? seconds + 5e-6 : seconds;
+static double tile_floor(double seconds, bool bf, double below = 18e-6, double extra = 5e-6) {
+  return bf && seconds < below ? seconds + extra : seconds;
 }
+constexpr double kWeightBelow = 25e-6;
 struct WavePlan {
   int ns;
   double blocks, steps;  // of the launch; of a workgroup
@@ -121,12 +122,16 @@ static bool bwd_data_fits(const ConvGeom& c) {
   return spatial(c) && c.stride == 1 && c.og() % 4 == 0 && c.k <= kWaveMaxSide && c.kb() >= kSplitMinK;
 }
 static bool bwd_weight_fits(const ConvGeom& c) { return spatial(c) && c.k <= kWaveMaxSide && c.P() >= kSplitMinK; }
-bool wave_conv_fwd_ok(const ConvGeom& c, bool bf) { return fwd_fits(c) && fwd_plan(c, bf).seconds < tile_floor(tile_seconds_fwd(c, bf), bf); }
+bool wave_conv_fwd_ok(const ConvGeom& c, bool bf) {
+  return fwd_fits(c) && fwd_plan(c, bf).seconds < tile_floor(tile_seconds_fwd(c, bf), bf, 18e-6, conv_bf16_stored_ok(c) ? 3e-6 : 5e-6);
+}
+// On its own a data gradient with long rows of weights (see data_link) is better off in tiles, slices or not: bf16, second layer
+// of the full net on 2 pictures 9 | 20 us, third and fourth on 4 8 | 18 and 7 | 15, fifth on 8 8 | 20.
 bool wave_conv_bwd_data_ok(const ConvGeom& c, bool bf) {
-  return bwd_data_fits(c) && bwd_data_plan(c, bf).seconds < tile_floor(tile_seconds_bwd_data(c, bf), bf);
+  return bwd_data_fits(c) && c.og() <= 64 && bwd_data_plan(c, bf).seconds < tile_floor(tile_seconds_bwd_data(c, bf), bf);
 }
 bool wave_conv_bwd_weight_ok(const ConvGeom& c, bool bf) {
-  return bwd_weight_fits(c) && bwd_weight_plan(c, bf).seconds < tile_floor(tile_seconds_bwd_weight(c, bf), bf, true);
+  return bwd_weight_fits(c) && bwd_weight_plan(c, bf).seconds < tile_floor(tile_seconds_bwd_weight(c, bf), bf, kWeightBelow);
 }
 // Both gradients in one launch, where the data gradient is not sliced.  beside: large dense layers are updated meanwhile, which
 // slows these kernels more than tiles.  Full net, fp32, tiles against small products by the profiler, us, and what the work
@@ -142,7 +147,7 @@ bool wave_conv_bwd_ok(const ConvGeom& c, bool bf, bool beside) {
   const double work = wave_seconds(w.blocks + blocks * steps / w.steps, w.steps, bf) * (beside ? kWaveBeside : 1);
   const double chain = chain_seconds(steps, wave_count(w.blocks + blocks, std::max(w.steps, steps)), data_link(c));
   return std::max(work, chain) + (w.ns > 1 ? kWaveFinish : 0) <
-         tile_floor(tile_seconds_bwd_data(c, bf), bf) + tile_floor(tile_seconds_bwd_weight(c, bf), bf, true);
+         tile_floor(tile_seconds_bwd_data(c, bf), bf) + tile_floor(tile_seconds_bwd_weight(c, bf), bf, kWeightBelow);
 }
 int wave_conv_fwd_slices(const ConvGeom& c) {
   return fwd_fits(c) ? std::max(fwd_plan(c, false).ns, fwd_plan(c, true).ns) : 1;
