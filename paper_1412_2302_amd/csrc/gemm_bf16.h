@@ -196,47 +196,6 @@ struct BfIm2colRowTable {
 // kernel and its fragment reads do not change.  All of them need extents that are multiples of 8 elements
 // (channels per group, total channels, rows) and 16-byte aligned tensors; the launcher checks that.
 
-// word j of the (k, k+1) pairs of eight rows: a = rows r..r+7 at k, b = the same rows at k+1
-AX_HD uint32_t bf_pair_lo(uint32_t a, uint32_t b) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_perm(b, a, 0x05040100u);
-#else
-  return (a & 0xffffu) | (b << 16);
-#endif
-}
-AX_HD uint32_t bf_pair_hi(uint32_t a, uint32_t b) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_perm(b, a, 0x07060302u);
-#else
-  return (a >> 16) | (b & 0xffff0000u);
-#endif
-}
-AX_HD uint32_t f_bits(float f) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __float_as_uint(f);
-#else
-  uint32_t u;
-  memcpy(&u, &f, 4);
-  return u;
-#endif
-}
-// rows r..r+7 at k (a) and k+1 (b), eight bf16 each -> eight words of (k, k+1) pairs at d[0..7]
-AX_HD void bf_store_pairs(uint32_t* d, const float4& a, const float4& b) {
-  const uint32_t a0 = f_bits(a.x), a1 = f_bits(a.y), a2 = f_bits(a.z), a3 = f_bits(a.w);
-  const uint32_t b0 = f_bits(b.x), b1 = f_bits(b.y), b2 = f_bits(b.z), b3 = f_bits(b.w);
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-  v4u lo, hi;
-  lo[0] = bf_pair_lo(a0, b0); lo[1] = bf_pair_hi(a0, b0); lo[2] = bf_pair_lo(a1, b1); lo[3] = bf_pair_hi(a1, b1);
-  hi[0] = bf_pair_lo(a2, b2); hi[1] = bf_pair_hi(a2, b2); hi[2] = bf_pair_lo(a3, b3); hi[3] = bf_pair_hi(a3, b3);
-  *reinterpret_cast<v4u*>(d) = lo;  // two 16-byte LDS stores
-  *reinterpret_cast<v4u*>(d + 4) = hi;
-#else
-  d[0] = bf_pair_lo(a0, b0); d[1] = bf_pair_hi(a0, b0); d[2] = bf_pair_lo(a1, b1); d[3] = bf_pair_hi(a1, b1);
-  d[4] = bf_pair_lo(a2, b2); d[5] = bf_pair_hi(a2, b2); d[6] = bf_pair_lo(a3, b3); d[7] = bf_pair_hi(a3, b3);
-#endif
-}
-
 // k-contiguous implicit im2col (rows = pixels, k = (r,s,c)) over a bf16 tensor: a load is eight consecutive
 // channels of one tap.  General taps, k tails zero-filled (K and the split chunk are multiples of 8).
 template <int ROWS, int BK, int MODE>
@@ -379,108 +338,6 @@ struct DenseKInner16 {
   AX_HD void store_step(int s, uint32_t* lds, const float4* r) const {
     const int idx = tid + s * kThreads;
     if (kWhole || idx < NQ) *reinterpret_cast<float4*>(lds + (idx / QK) * LDW + 4 * kq) = r[s];
-  }
-};
-
-// row-contiguous dense operand elem(row, k) = p[k*ld + row] stored as bf16 (packed weights, output gradients):
-// a unit = rows 8*rq .. 8*rq+7 at k = 2*kp and 2*kp+1, two loads, interleaved into eight words of pairs
-template <int ROWS, int BK>
-struct DenseRowInner16 {
-  static constexpr int QR = ROWS / 8, NU = QR * (BK / 2), NUT = (NU + kThreads - 1) / kThreads, NL = 2 * NUT, NA = NL,
-                       NS = NUT;
-  static constexpr bool kWhole = NU % kThreads == 0;  // else some threads own no unit in the last round
-  static constexpr bool kRowMajor = false;
-  static constexpr int LDW = ROWS + 4, LDS_WORDS = (BK / 2) * LDW;
-  typedef DenseParams Params;
-  BufView v;
-  int tid;
-  uint32_t ld2;       // leading dimension in bytes
-  uint32_t base[NL];  // byte offset of (k local, row), or kOob
-  Offsets<NL, true> pl;
-  AX_HD DenseRowInner16(const Params& a, int g, int tid_, int row0)
-      : v(make_view(reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(a.p) + (long)g * a.gstride),
-                    a.bytes - (uint32_t)(g * a.gstride * 2))),
-        tid(tid_) {
-    ld2 = (uint32_t)a.ld * 2u;
-#pragma unroll
-    for (int u = 0; u < NUT; ++u) {
-      const int idx = tid + u * kThreads;
-      const int row = row0 + 8 * (idx % QR), kp = idx / QR;
-      const bool in = (kWhole || idx < NU) && row < a.R;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) base[2 * u + h] = in ? (uint32_t)(2 * kp + h) * ld2 + (uint32_t)row * 2u : kOob;
-    }
-  }
-  template <int S>
-  AX_HD void addr_step(int k0, int kend) {
-    const int k = k0 + 2 * ((tid + (S / 2) * kThreads) / QR) + (S & 1);
-    // base may be kOob: adding less than 2^31 to it stays outside every operand
-    pl.off[S] = k < kend ? base[S] + (uint32_t)k0 * ld2 : kOob;
-  }
-  AX_HD void fetch(float4* r) const { pl.fetch(v, r); }
-  AX_HD void store_step(int u, uint32_t* lds, const float4* r) const {
-    const int idx = tid + u * kThreads;
-    if (kWhole || idx < NU) bf_store_pairs(lds + (idx / QR) * LDW + 8 * (idx % QR), r[2 * u], r[2 * u + 1]);
-  }
-};
-
-// (no launcher takes this one: weight_direct.hip has the weight gradients; the CPU emulation checks it with the others)
-// transpose of the implicit im2col (rows = (r,s,c), k = pixels: backward-weight) over a bf16 tensor, through the
-// workgroup's pixel table (see Im2colRowTable): whole k-tiles, at most 31 taps; a unit = eight channels of one tap
-// at two consecutive pixels
-template <int ROWS, int BK>
-struct Im2colRowTable16 {
-  static constexpr int QR = ROWS / 8, NU = QR * (BK / 2), NUT = NU / kThreads, NL = 2 * NUT, NA = NL, NS = NUT;
-  static_assert(NU % kThreads == 0 && kThreads % QR == 0 && NUT >= 1, "every unit of a thread shares its row octet");
-  static constexpr bool kRowMajor = false;
-  static constexpr bool kUsesTable = true;
-  static constexpr int LDW = ROWS + 4, LDS_WORDS = (BK / 2) * LDW;
-  typedef Im2colParams Params;
-  BufView v;
-  int tid, rq;
-  uint32_t tapoff, tapmask;
-  const PixelEntry* tbl;
-  int kbase, klast;
-  Offsets<NL, true> pl;
-  AX_HD Im2colRowTable16(const Params& a, int grp, int tid_, int row0)
-      : v(make_view(a.x, a.bytes)), tid(tid_), tbl(nullptr), kbase(0), klast(0) {
-    rq = tid % QR;
-    const int m = row0 + 8 * rq;
-    const bool in = m < a.kh * a.kw * a.Cg;
-    const TapCoord t = decode_tap(in ? m : 0, a);
-    tapoff = (((uint32_t)t.r * (uint32_t)a.W + (uint32_t)t.s) * (uint32_t)a.Ctot + (uint32_t)t.c +
-              (uint32_t)(grp * a.c_stride_g)) * 2u;
-    tapmask = in ? 1u << (t.r * a.kw + t.s) : 0x80000000u;
-  }
-  static AX_HD void build_table(const Params& g, PixelEntry* table, int kbeg, int kend, int tid) {
-    for (int e = tid; e < kend - kbeg; e += kThreads) {
-      const PixCoord c = decode_pixel(kbeg + e, g);
-      const int y0 = c.y * g.stride - g.pad, x0 = c.x * g.stride_x - g.pad_x;
-      uint32_t inside = 0;
-      int bit = 0;
-      for (int r = 0; r < g.kh; ++r)
-        for (int s2 = 0; s2 < g.kw; ++s2, ++bit)
-          inside |= ((uint32_t)(y0 + r) < (uint32_t)g.H && (uint32_t)(x0 + s2) < (uint32_t)g.W ? 1u : 0u) << bit;
-      PixelEntry pe;
-      pe.base = row_base<IM2COL_FWD, 2>(g, c.n, y0, x0, 0);
-      pe.outside = ~inside | 0x80000000u;
-      table[e] = pe;
-    }
-  }
-  AX_HD void set_table(const PixelEntry* table, int kbeg, int kend) {
-    tbl = table;
-    kbase = kbeg;
-    klast = kend - BK;
-  }
-  template <int S>
-  AX_HD void addr_step(int k0, int kend) {
-    const int kc = k0 < kend ? k0 : klast;  // uniform
-    const PixelEntry pe = tbl[kc - kbase + 2 * ((tid + (S / 2) * kThreads) / QR) + (S & 1)];
-    pl.off[S] = (pe.outside & tapmask) ? kOob : pe.base + tapoff;
-  }
-  AX_HD void fetch(float4* r) const { pl.fetch(v, r); }
-  AX_HD void store_step(int u, uint32_t* lds, const float4* r) const {
-    bf_store_pairs(lds + ((tid + u * kThreads) / QR) * LDW + 8 * rq, r[2 * u], r[2 * u + 1]);
   }
 };
 

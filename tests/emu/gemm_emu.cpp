@@ -427,19 +427,8 @@ static void run_case(const Case& cs) {
         const int kcf = ((d.K + T::BK - 1) / T::BK) * T::BK;
         EpiBiasAct e{y.data(), c.Cout, bias, 1, og, 0};
         const Im2colParams fa = im2col16(fwd_A(c, x), x16);
-        const DenseParams fb = dense16(fwd_B(c, wf), wf16);
-        emu_gemm_bf<T, Im2colKInner16<T::BM, T::BK, IM2COL_FWD>, DenseRowInner16<T::BN, T::BK>, EpiBiasAct>(
-            fa, fb, e, d.M, d.N, d.K, kcf, 1, d.groups);
-        check("fwd16", nm, y, y_ref);
-        if (fa.Cg % T::BK == 0 && c.k * c.k <= 32) {
-          std::fill(y.begin(), y.end(), NAN);
-          emu_gemm_bf<T, Im2colKTap16<T::BM, T::BK, IM2COL_FWD>, DenseRowInner16<T::BN, T::BK>, EpiBiasAct>(
-              fa, fb, e, d.M, d.N, d.K, kcf, 1, d.groups);
-          check("fwd_tap16", nm, y, y_ref);
-        }
-        {  // weights with the reduction contiguous
-          const DenseParams fk = fwd_B16k(c, wfk);
-          std::fill(y.begin(), y.end(), NAN);
+        const DenseParams fk = fwd_B16k(c, wfk);
+        {
           emu_gemm_bf<T, Im2colKInner16<T::BM, T::BK, IM2COL_FWD>, DenseKInner16<T::BN, T::BK>, EpiBiasAct>(
               fa, fk, e, d.M, d.N, d.K, kcf, 1, d.groups);
           check("fwd16k", nm, y, y_ref);
@@ -454,8 +443,8 @@ static void run_case(const Case& cs) {
           const int ns = 3, chunk = (((d.K + T::BK - 1) / T::BK + ns - 1) / ns) * T::BK;
           std::vector<float> ws((size_t)d.groups * ns * d.M * d.N, NAN), ysum(c.out_elems(), 0.f);
           EpiSlab es{ws.data(), (long)d.M * d.N, d.N, nullptr};
-          emu_gemm_bf<T, Im2colKInner16<T::BM, T::BK, IM2COL_FWD>, DenseRowInner16<T::BN, T::BK>, EpiSlab>(
-              fa, fb, es, d.M, d.N, d.K, chunk, ns, d.groups);
+          emu_gemm_bf<T, Im2colKInner16<T::BM, T::BK, IM2COL_FWD>, DenseKInner16<T::BN, T::BK>, EpiSlab>(
+              fa, fk, es, d.M, d.N, d.K, chunk, ns, d.groups);
           for (int g = 0; g < d.groups; ++g)
             for (int sp = 0; sp < ns; ++sp)
               for (int m = 0; m < d.M; ++m)
@@ -475,18 +464,7 @@ static void run_case(const Case& cs) {
         const GemmDims d = bwdd_dims(c);
         EpiGate e{dx.data(), c.Cin, nullptr, cg, 0};
         const Im2colParams ba = im2col16(bwdd_A(c, dy), dy16);
-        const DenseParams bb = dense16(bwdd_B(c, wb), wb16);
-        emu_gemm_bf<T, Im2colKInner16<T::BM, T::BK, IM2COL_T1>, DenseRowInner16<T::BN, T::BK>, EpiGate>(
-            ba, bb, e, d.M, d.N, d.K, ((d.K + T::BK - 1) / T::BK) * T::BK, 1, d.groups);
-        check("bwd_data16", nm, dx, dx_ref);
-        if (ba.Cg % T::BK == 0 && c.k * c.k <= 32) {
-          std::fill(dx.begin(), dx.end(), NAN);
-          emu_gemm_bf<T, Im2colKTap16<T::BM, T::BK, IM2COL_T1>, DenseRowInner16<T::BN, T::BK>, EpiGate>(
-              ba, bb, e, d.M, d.N, d.K, d.K, 1, d.groups);
-          check("bwdd_tap16", nm, dx, dx_ref);
-        }
         const DenseParams bk = bwdd_B16k(c, wbk);
-        std::fill(dx.begin(), dx.end(), NAN);
         emu_gemm_bf<T, Im2colKInner16<T::BM, T::BK, IM2COL_T1>, DenseKInner16<T::BN, T::BK>, EpiGate>(
             ba, bk, e, d.M, d.N, d.K, ((d.K + T::BK - 1) / T::BK) * T::BK, 1, d.groups);
         check("bwd_data16k", nm, dx, dx_ref);
@@ -495,27 +473,6 @@ static void run_case(const Case& cs) {
           emu_gemm_bf<T, Im2colKTap16<T::BM, T::BK, IM2COL_T1>, DenseKInner16<T::BN, T::BK>, EpiGate>(
               ba, bk, e, d.M, d.N, d.K, d.K, 1, d.groups);
           check("bwdd_tap16k", nm, dx, dx_ref);
-        }
-      }
-      {
-        const GemmDims d = bwdw_dims(c);
-        int kchunk;
-        long tiles = (long)((d.M + T::BM - 1) / T::BM) * ((d.N + T::BN - 1) / T::BN) * d.groups;
-        int nsplit = plan_split(tiles, d.K, T::BK, 7, 5, &kchunk);
-        if (d.K % T::BK == 0 && c.k * c.k <= 31 && kchunk % T::BK == 0) {
-          std::vector<float> ws((size_t)d.groups * nsplit * d.M * d.N, NAN);
-          EpiSlab e{ws.data(), (long)d.M * d.N, d.N, nullptr};
-          emu_gemm_bf<T, Im2colRowTable16<T::BM, T::BK>, DenseRowInner16<T::BN, T::BK>, EpiSlab>(
-              im2col16(bwdw_A(c, x), x16), dense16(bwdw_B(c, dy), dy16), e, d.M, d.N, d.K, kchunk, nsplit, d.groups);
-          std::vector<float> dwf(c.w_elems(), 0.f);
-          for (int g = 0; g < d.groups; ++g)
-            for (int sp = 0; sp < nsplit; ++sp)
-              for (long i = 0; i < (long)d.M * d.N; ++i) {
-                const float v = ws[((long)g * nsplit + sp) * d.M * d.N + i];
-                if (v == v) dwf[(long)g * d.M * d.N + i] += v;
-              }
-          snprintf(nm, sizeof nm, "%s/%dx%d/s%d/bf16", cs.name, T::BM, T::BN, nsplit);
-          check("bwd_wgt_tbl16", nm, dwf, dwf_ref);
         }
       }
       delete[] x16; delete[] dy16; delete[] wf16; delete[] wb16; delete[] wfk; delete[] wbk;
@@ -808,7 +765,7 @@ static void dense_case_bf() {
     emu_gemm_bf<T, RIn, RIn, EpiSlab>(a, b, e, Out, In, Bn, 32, 1, 1);
     check("fc_bwd_w", "6x72->36 bf16", dw, ref);
   }
-  {  // the same three products over operands stored as bf16 (extents are multiples of 8: 72, 40)
+  {  // the forward product over operands stored as bf16 (extents are multiples of 8: 72, 40)
     const int Out8 = 40;
     auto to16 = [](const float* src, long n) {
       uint16_t* d = new uint16_t[n];
@@ -816,12 +773,9 @@ static void dense_case_bf() {
       return d;
     };
     float* w8 = new float[Out8 * In];
-    float* dy8 = new float[Bn * Out8];
     for (int i = 0; i < Out8 * In; ++i) w8[i] = frand();
-    for (int i = 0; i < Bn * Out8; ++i) dy8[i] = frand();
-    uint16_t *x16 = to16(x, Bn * In), *w16 = to16(w8, Out8 * In), *dy16 = to16(dy8, Bn * Out8);
+    uint16_t *x16 = to16(x, Bn * In), *w16 = to16(w8, Out8 * In);
     typedef DenseKInner16<128, 32> K16;
-    typedef DenseRowInner16<128, 32> R16;
     {
       const int ns = 2, kc = 64;
       std::vector<float> ws(ns * Bn * Out8, NAN), y(Bn * Out8, 0.f);
@@ -833,25 +787,7 @@ static void dense_case_bf() {
       for (int sp = 0; sp < ns; ++sp) for (int i = 0; i < Bn * Out8; ++i) y[i] += ws[sp * Bn * Out8 + i];
       check("fc_fwd16", "6x72->40 s2", y, ref);
     }
-    {
-      std::vector<float> dx(Bn * In, NAN);
-      std::vector<double> ref(Bn * In, 0.0);
-      for (int n = 0; n < Bn; ++n) for (int o = 0; o < Out8; ++o) for (int i = 0; i < In; ++i) ref[n * In + i] += (double)dy8[n * Out8 + o] * w8[o * In + i];
-      DenseParams a{(const float*)dy16, Out8, 0, Bn, Bn * Out8 * 2}, b{(const float*)w16, In, 0, In, Out8 * In * 2};
-      EpiSlab e{dx.data(), (long)Bn * In, In, nullptr};
-      emu_gemm_bf<T, K16, R16, EpiSlab>(a, b, e, Bn, In, Out8, 64, 1, 1);
-      check("fc_bwd_x16", "6x72->40", dx, ref);
-    }
-    {
-      std::vector<float> dw(Out8 * In, NAN);
-      std::vector<double> ref(Out8 * In, 0.0);
-      for (int n = 0; n < Bn; ++n) for (int o = 0; o < Out8; ++o) for (int i = 0; i < In; ++i) ref[o * In + i] += (double)dy8[n * Out8 + o] * x[n * In + i];
-      DenseParams a{(const float*)dy16, Out8, 0, Out8, Bn * Out8 * 2}, b{(const float*)x16, In, 0, In, Bn * In * 2};
-      EpiSlab e{dw.data(), (long)Out8 * In, In, nullptr};
-      emu_gemm_bf<T, R16, R16, EpiSlab>(a, b, e, Out8, In, Bn, 32, 1, 1);
-      check("fc_bwd_w16", "6x72->40", dw, ref);
-    }
-    delete[] w8; delete[] dy8; delete[] x16; delete[] w16; delete[] dy16;
+    delete[] w8; delete[] x16; delete[] w16;
   }
   delete[] x; delete[] w; delete[] dy;
   g_round_bf = false;

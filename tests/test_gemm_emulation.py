@@ -33,3 +33,15 @@ def test_tile_transforms_of_the_3x3_layers_on_cpu(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
     assert "ALL OK" in r.stdout and "FAIL" not in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_small_product_loaders_on_cpu(tmp_path):
+    """The tables and loaders of the small products, lane by lane with operands of exact size, and the direct kernels' masks."""
+    exe = str(tmp_path / "wave_emu")
+    src = os.path.join(HERE, "emu", "wave_emu.cpp")
+    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-o", exe, src], check=True, timeout=600)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
+    assert "ALL OK" in r.stdout and "FAIL" not in r.stdout
