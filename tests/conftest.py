@@ -21,12 +21,3 @@ def lib():
         pytest.skip("no GPU visible")
     from paper_1412_2302_amd import binding
     return binding
-
-
-@pytest.fixture(autouse=True)
-def _collected(request):
-    """Tests that compare the allocator's figures must not see an earlier test's cycles die."""
-    if "no_alloc" in request.node.nodeid:
-        import gc
-        gc.collect()
-    yield

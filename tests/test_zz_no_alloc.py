@@ -1,5 +1,7 @@
 """The entry point that allocates nothing (alexnet_softmax_xent_static) against the handle-based
 alexnet_softmax_xent: same kernels, so the same bits, on two calls in a row, the second smaller."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -21,6 +23,7 @@ def test_static_softmax_matches_the_handle_based_call_twice_in_a_row(lib):
         dz = torch.full((batch, classes), float("nan"), dtype=torch.float32, device="cuda")
         loss = torch.full((1,), float("nan"), dtype=torch.float32, device="cuda")
         bad = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+        gc.collect()  # handles of earlier tests that died in a cycle must not be freed between the two figures
         before = torch.cuda.memory_allocated()
         lib.softmax_xent_static(zt, lt, dz, loss, bad)
         torch.cuda.synchronize()
