@@ -37,7 +37,7 @@ static float* filled(long n) {
 }
 
 // out[group][slice][m][n], as EpiSlab has it
-template <class AL, class BL>
+template <class AL, class BL, bool EXACT = false>
 static std::vector<double> product(const typename AL::Params& ap, const typename BL::Params& bp, int M, int N, int K, int groups,
                                    int ns) {
   const int kchunk = ((K + 15) / 16 + ns - 1) / ns * 16, threads = 64 * 4;
@@ -58,7 +58,9 @@ static std::vector<double> product(const typename AL::Params& ap, const typename
             for (int lane = 0; lane < 64; ++lane) {
               const int row = lane & 31, kh = 8 * (lane >> 5);
               float4 ra[2], rb[2];
-              AL(ap, g, m0 + row, kbeg, kend, ta.data()).load(ra, k + kh);
+              const AL al(ap, g, m0 + row, kbeg, kend, ta.data());
+              if (EXACT) wave_load_exact(al, ra, k + kh, 0);
+              else al.load(ra, k + kh);
               BL(bp, g, n0 + row, kbeg, kend, tb.data()).load(rb, k + kh);
               memcpy(&a[row][kh], ra, 32);
               memcpy(&b[row][kh], rb, 32);
@@ -118,7 +120,9 @@ static void conv(ConvGeom c, int ns) {
   if (run_mode(c)) {
     const WaveRunParams rb{DenseParams{wf, c.Cout, 0, c.Cout, (uint32_t)(c.w_elems() * 4)}, c.k * c.Cin, run_len(c),
                            make_fastdiv((uint32_t)run_len(c))};
-    check("run forward", c, product<WaveRunA, WaveRunB>(WaveRunAParams{run_A(c, x), c.k * c.Cin}, rb, f.M, f.N, run_k(c), 1, ns), y, ns);
+    const WaveRunAParams ra{run_A(c, x), c.k * c.Cin};
+    check("run forward", c, product<WaveRunA, WaveRunB>(ra, rb, f.M, f.N, run_k(c), 1, ns), y, ns);
+    check("run exact", c, product<WaveRunA, WaveRunB, true>(ra, rb, f.M, f.N, run_k(c), 1, ns), y, ns);
   } else if (cg % 4 == 0) {
     check("forward", c, product<WaveIm2col<IM2COL_FWD>, WaveRow>(fwd_A(c, x), wb, f.M, f.N, f.K, f.groups, ns), y, ns);
   }
