@@ -160,9 +160,10 @@ def measure(torch, B, S, batch, bf16, steps, warmup, overlap=True, keep=False):
     traffic, traffic_source = _traffic(key)
     launches = gemm_calls // prof_steps
     roofline = {
-        "kernel": ("ax::gemm_bf16_kernel (bf16 MFMA" if bf16 else "ax::gemm_split_kernel (fp32 operands as three bf16 terms, bf16 MFMA")
-                  + " implicit-GEMM: conv fwd/bwd-data/bwd-weight, the 36 products of the tile-transformed layers,"
-                    " dense layers)",
+        "kernel": ("ax::gemm_direct_kernel, gemm_direct_t_kernel, gemm_bf16_kernel, first_layer_kernel, first_weight_kernel"
+                   " (bf16 MFMA: conv fwd/bwd-data/bwd-weight, dense layers)" if bf16 else
+                   "ax::gemm_split_kernel (fp32 operands as three bf16 terms, bf16 MFMA implicit-GEMM:"
+                   " conv fwd/bwd-data/bwd-weight, the 36 products of the tile-transformed layers, dense layers)"),
         "bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
         "frac": round(achieved / peak, 4),
         "traffic": traffic, "traffic_source": traffic_source,

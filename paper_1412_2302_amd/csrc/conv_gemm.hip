@@ -562,7 +562,8 @@ static GemmPlan bwdw_plan(const ConvGeom& c, bool run, bool bf, bool table = fal
   return plan_gemm(run ? run_k(c) : d.M, d.N, d.K, d.groups, (double)(run ? run_w_elems(c) : c.w_elems()) * 4, 256,
                    bf, false, table ? kMaxTableK : 0, false, t_out);
 }
-// what the kernels of this file take for a product, by their planners
+// What a product takes in tiles, by the planners of this file.  bf: forward products and data gradients over stored operands
+// where there are such kernels; weight gradients and dense layers over fp32 ones.
 double tile_seconds_fwd(const ConvGeom& c, bool bf) {
   double t = 0;
   if (bf && run16_mode(c))
@@ -992,7 +993,8 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
 // y = act(x w^T + b),  dx = gate(dy w),  dw = dy^T x.  The batch is the small
 // dimension, so forward and backward-data split the reduction over several
 // workgroups and finish in a second kernel that also applies the activation.
-// bf16 products, and fp32 ones that gemm_split.h does not take, use the 128 x 128 tile (fc_split); the others fc_plan.
+// fp32 products use fc_plan, those that gemm_split.h does not take the 128 x 128 tile (fc_split), as do bf16 products over
+// fp32 operands; over stored ones dense_plan() (gemm_direct.h).
 
 static int fc_split(int B, int N, int K, int* kchunk, bool bf, double* t_out = nullptr) {
   const int bk = bf ? kBKbf : kBK;

@@ -16,7 +16,8 @@ struct WorkspacePiece {
 int workspace_pieces(const alexnet_config_t* cfg, std::vector<WorkspacePiece>* out);
 
 // The tail of the weight gradient of a transformed stage -- adding up the split-k slices of the products, then
-// the transform back to taps --, or the slices of a direct one (gemm_wave.h, weight_direct.hip; total = 0), can be put off to the end of a backward pass and run for all such stages in two
+// the transform back to taps --, or the slices of another one (gemm_wave.h, weight_direct.hip, first_weight.hip;
+// total = 0), can be put off to the end of a backward pass and run for all such stages in two
 // launches: each of those kernels is too short to fill the chip on its own.  The slices and the products then
 // need memory of their own until the tail runs.
 constexpr int kMaxWgradJobs = 5;
@@ -63,8 +64,7 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
                     const uint16_t* wf16 = nullptr, uint16_t* y16 = nullptr);
 // The first layer with bf16 products over pictures stored as bf16, four channels per pixel (conv_plan.h, run16):
 // x4 from launch_pad4_bf16 (or the preprocessing kernel), wk from launch_run16_pack.  conv_run16_ok(): the
-// geometry allows it.  (The weight gradient keeps the fp32 pictures: over this view its reduction has 528 rows,
-// five 128-row tiles where the run mode of gemm.h has four, and measured slower.)
+// geometry allows it.  The weight gradient reads the same pictures where first_weight_ok(), else the fp32 ones in run mode.
 bool conv_run16_ok(const ConvGeom& c);
 size_t conv_run16_x_elems(const ConvGeom& c);
 size_t conv_run16_w_elems(const ConvGeom& c);
@@ -138,7 +138,8 @@ int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy
 int launch_fc_bwd(int B, int in, int out, const float* x, const float* dy, const float* w, const float* gate, float* dx,
                   float* dw, hipStream_t st, uint16_t* dx16);
 
-// Seconds that the tile kernels take for a product, by their planners; bf: in a handle with bf16 products
+// Seconds that the tile kernels take for a product, by their planners; bf: in a handle with bf16 products (which kernels, see
+// tile_floor() in wave_gemm.hip)
 double tile_seconds_fwd(const ConvGeom& c, bool bf);
 double tile_seconds_bwd_data(const ConvGeom& c, bool bf);
 double tile_seconds_bwd_weight(const ConvGeom& c, bool bf);

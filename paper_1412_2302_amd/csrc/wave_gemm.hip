@@ -18,7 +18,14 @@ static double wave_seconds(double blocks, double steps, bool bf) {
   return kWaveLaunch + (bf ? kWaveStep16 : kWaveStep) * steps * std::ceil(blocks / 256);
 }
 // bf16 tiles the planner has at 7 us took 13 (36 workgroups), and have weights converted for them first; weight gradients of
-// 16 output channels 29 where it has 19
+// 16 output channels 29 where it has 19.
+// For a stage of a bf16 handle this is a line drawn by whole steps.  tile_seconds_...() has forward products and data gradients
+// from the kernels over stored operands, but weight gradients and dense layers from those of gemm_bf16.h, which fp32 operands
+// would run on; the direct ones take half of that.  By products alone stages would leave much earlier (mini net, second layer,
+// 128 pictures, both gradients: 24 us here, 14 there), but the first to leave brings the side stream, its events and three
+// conversions with it: a step of 128 pictures takes 193 us with small products only, 255 with the gradients in tiles, 296
+// without any; of 200 230, 267, 329.  From 214 pictures on, where this line ends it (midi net: 380), up to 450 small products
+// only would still be 20 to 6 % faster; at 512 they are level.
 static double tile_floor(double seconds, bool bf, double below = 18e-6, double extra = 5e-6) {
   return bf && seconds < below ? seconds + extra : seconds;
 }
