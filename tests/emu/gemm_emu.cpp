@@ -826,8 +826,21 @@ static void check_acc_map() {
   if (!ok) ++failures;
 }
 
+// Padded pictures take 8 bytes a pixel however few channels there are: what a handle accepts (tensors below 2 GiB) may reach
+// kOob in them, and a load that is to be outside would then be inside.
+static void check_padded_pictures() {
+  for (int cin = 1; cin <= 3; ++cin)
+    for (long pixels : {1000L, 0x7ffffffL, 0x8000000L, 0xfffffffL, 0x1ffffff0L / cin}) {
+      ConvGeom c{1, 1, (int)std::min(pixels, 0x1ffffff0L / cin), cin, 8, 1, 1, 0, 1, 1, 1};
+      const bool ok = !run16_mode(c) || (unsigned long)run16_x_elems(c) * 2 <= kOob;
+      if (!ok) ++failures;
+      printf("%-10s %d channels, %ld pixels %s\n", "padded", cin, c.Q(), ok ? "ok" : "FAIL");
+    }
+}
+
 int main() {
   srand(1234);
+  check_padded_pictures();
   check_fastdiv();
   check_acc_map<Tile<128, 128, 16, 2, 2>>();
   check_acc_map<Tile<128, 48, 32, 4, 1, 16>>();
