@@ -183,7 +183,7 @@ inline DenseParams bwdd_B16k(const ConvGeom& c, const uint16_t* wbk) {
 // and padded to a multiple of eight with weights that are zero.  The padding reads values of the next pixels (of
 // the next row at the right edge; nothing past the end of the tensor, where the loads return zero), which meet
 // zero weights.  Reduction length k * run16_len(); the weights are wk[o][(r, s*4 + c)], k-contiguous.
-// Eight bytes a pixel, which may pass 2 GiB where the fp32 pictures of one or two channels do not: those stay in run mode.
+// Eight bytes a pixel, which may pass 2 GiB where fp32 pictures of one channel do not: those stay in run mode.
 inline bool run16_mode(const ConvGeom& c) {
   return run_mode(c) && c.Cin < 4 && c.Cout % 8 == 0 && c.Q() * 8 <= (long)kOob;
 }
