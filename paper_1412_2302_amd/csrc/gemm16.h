@@ -149,18 +149,7 @@ gemm16_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int
     }
   }
 
-#pragma unroll
-  for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < T::TN; ++j) {  // 32 columns of a row per store, as in gemm_bf16_kernel
-      const int n = n0 + wn * (T::TN * 32) + j * 32 + (lane & 31);
-      if (n >= N) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * (T::TM * 32) + i * 32 + acc_row(lane, r);
-        if (m < M) ep.apply(m, n, acc[i][j][r]);
-      }
-    }
+  store_rows(ep, acc, m0 + wm * (T::TM * 32), n0 + wn * (T::TN * 32), M, N, lane);
 }
 #endif  // AX_HOST_EMU
 

@@ -15,6 +15,7 @@
 
 #include <string.h>
 
+#include "epi_rows.h"
 #include "gemm.h"
 
 namespace ax {
@@ -506,21 +507,9 @@ gemm_bf16_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, 
     }
   }
 
-#pragma unroll
-  for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < T::TN; ++j) {
-      // Blocks are not transposed here (A fragment first): register r of a lane is C[acc_row(lane, r)][lane % 32].
-      // These kernels wait on memory rather than on instruction issue, and 4-byte stores that fill whole
-      // 128-byte lines measured faster than the fp32 kernel's 16-byte stores, which touch 32 lines each.
-      const int n = n0 + wn * (T::TN * 32) + j * 32 + (lane & 31);
-      if (n >= N) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * (T::TM * 32) + i * 32 + acc_row(lane, r);
-        if (m < M) ep.apply(m, n, acc[i][j][r]);
-      }
-    }
+  // Blocks are not transposed here (A fragment first): these kernels wait on memory rather than on instruction issue, and
+  // 4-byte stores that fill whole 128-byte lines measured faster than the fp32 kernel's 16-byte stores, which touch 32 lines.
+  store_rows(ep, acc, m0 + wm * (T::TM * 32), n0 + wn * (T::TN * 32), M, N, lane);
 }
 #endif  // AX_HOST_EMU
 

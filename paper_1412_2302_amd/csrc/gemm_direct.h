@@ -27,6 +27,7 @@
 #pragma once
 
 #include "conv_plan.h"
+#include "epi_rows.h"
 #include "gemm_bf16.h"
 
 namespace ax {
@@ -80,6 +81,48 @@ AX_HD uint32_t taps_inside(const Im2colParams& g, int y0, int x0) {
   }
   return inside;
 }
+
+// The tap (bit r*kw + s) and the channel of a lane's octet, k-tile by k-tile.  ONE_TAP: k-tiles divide the channels, the tap's
+// column is carried along.  Otherwise a k-tile goes one step through whole taps and the rest of one, without a branch: lanes
+// stand at different taps (with a loop over the taps passed the second layer's forward product of 64 pictures, 48 channels,
+// took 90 us).
+template <bool ONE_TAP>
+struct TapWalk {
+  int bit, ch, tx;
+  uint32_t tap;
+  int step_taps, step_ch;
+  AX_HD TapWalk(const Im2colParams& a, int k) {
+    bit = (int)fdiv((uint32_t)k, a.d_cg);
+    ch = k - bit * a.Cg;
+    const int ty = (int)fdiv((uint32_t)bit, a.d_kw);
+    tx = bit - ty * a.kw;
+    tap = ((uint32_t)ty * (uint32_t)a.W + (uint32_t)tx) * (uint32_t)a.Ctot * 2u;
+    step_taps = (int)fdiv(kBKd, a.d_cg);
+    step_ch = kBKd - step_taps * a.Cg;
+  }
+  // of the tap, in bytes from a pixel's origin
+  AX_HD uint32_t offset(const Im2colParams& a) const {
+    if (ONE_TAP) return tap;
+    return ((uint32_t)bit + fdiv((uint32_t)bit, a.d_kw) * (uint32_t)(a.W - a.kw)) * (uint32_t)a.Ctot * 2u;
+  }
+  AX_HD void next(const Im2colParams& a) {
+    if (ONE_TAP) {
+      ch += kBKd;
+      if (ch == a.Cg) {
+        ch = 0;
+        ++bit;
+        const bool row = ++tx == a.kw;
+        tap += (uint32_t)(row ? a.W - a.kw + 1 : 1) * (uint32_t)a.Ctot * 2u;
+        tx = row ? 0 : tx;
+      }
+      return;
+    }
+    ch += step_ch;
+    const int over = ch >= a.Cg;
+    bit += step_taps + over;
+    ch -= over ? a.Cg : 0;
+  }
+};
 
 #ifndef AX_HOST_EMU
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
@@ -136,41 +179,29 @@ __global__ void __launch_bounds__(256, MINB) gemm_direct_kernel(DirectJob j, Epi
   }
   ep.set_group((int)g, (int)z);
 
-  // The octet to load next: k, its tap's bit and column, its channel, and its tap's byte offset from a pixel's origin.
-  // ONE_TAP: of the k-tile, the same for every lane; the lane's octet is in rowbase then.
-  int k = first * kBKd;
-  if (!ONE_TAP) k += 8 * oct;
-  int bit = (int)fdiv((uint32_t)k, ap.d_cg), ch = k - bit * ap.Cg, tx = bit - (int)fdiv((uint32_t)bit, ap.d_kw) * ap.kw;
-  uint32_t tap = (fdiv((uint32_t)bit, ap.d_kw) * (uint32_t)ap.W + (uint32_t)tx) * (uint32_t)ap.Ctot * 2u;
+  // The octet to load next: of the k-tile, the same for every lane (ONE_TAP; the lane's octet is in rowbase then), or the lane's own.
+  int k = first * kBKd + (ONE_TAP ? 0 : 8 * oct);
+  TapWalk<ONE_TAP> walk(ap, k);
   uint32_t bk = (uint32_t)(first * kBKd) * 2u;
   auto load = [&](v4u* st) {
-    const uint32_t off = (MODE == IM2COL_FWD ? tap : 0u - tap) + (uint32_t)ch * 2u;
+    const uint32_t tap = walk.offset(ap), off = (MODE == IM2COL_FWD ? tap : 0u - tap) + (uint32_t)walk.ch * 2u;
     const bool in = ONE_TAP || k < j.K;  // the last k-tile may lie partly past the end
+    const uint32_t bit = 1u << (walk.bit & 31), b_off = in ? bk : kOob;  // kOob and less than 2^31: outside
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
-      load_lds16(av, st + (i * 4 + wave) * 64, !in || (outside[i] >> bit) & 1u ? kOob : rowbase[i] + off, 0);
+    for (int i = 0; i < NA; ++i) {
+      const uint32_t out = ONE_TAP ? outside[i] & bit : (in ? outside[i] : 0xffffffffu) & bit;
+      load_lds16(av, st + (i * 4 + wave) * 64, out ? kOob : rowbase[i] + off, 0);
+    }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       if (ONE_TAP)
         load_lds16(bv, st + BM * 8 + (i * 4 + wave) * 64, brow[i], bk);
       else
-        load_lds16(bv, st + BM * 8 + (i * 4 + wave) * 64, in ? brow[i] + bk : kOob, 0);
+        load_lds16(bv, st + BM * 8 + (i * 4 + wave) * 64, brow[i] + b_off, 0);
     }
     bk += kBKd * 2;
     k += kBKd;
-    ch += kBKd;
-    auto next_tap = [&]() {
-      ch -= ap.Cg;
-      bit = (bit + 1) & 31;  // past the end: whichever
-      const bool row = ++tx == ap.kw;
-      tap += (uint32_t)(row ? ap.W - ap.kw + 1 : 1) * (uint32_t)ap.Ctot * 2u;
-      tx = row ? 0 : tx;
-    };
-    if (ONE_TAP) {
-      if (ch == ap.Cg) next_tap();
-    } else {
-      while (ch >= ap.Cg) next_tap();
-    }
+    walk.next(ap);
   };
 
   v16f acc[TM][TN];
@@ -220,18 +251,7 @@ __global__ void __launch_bounds__(256, MINB) gemm_direct_kernel(DirectJob j, Epi
     }
   }
 
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int jj = 0; jj < TN; ++jj) {  // 32 columns of a row per store, as in gemm_bf16_kernel
-      const int n = n0 + wn * (TN * 32) + jj * 32 + (lane & 31);
-      if (n >= j.N) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * (TM * 32) + i * 32 + acc_row(lane, r);
-        if (m < j.M) ep.apply(m, n, acc[i][jj][r]);
-      }
-    }
+  store_rows(ep, acc, m0 + wm * (TM * 32), n0 + wn * (TN * 32), j.M, j.N, lane);
 }
 #endif  // AX_HOST_EMU
 

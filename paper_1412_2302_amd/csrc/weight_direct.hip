@@ -188,18 +188,7 @@ __global__ void __launch_bounds__(256, MINB) gemm_direct_t_kernel(DirectTJob j, 
     }
   }
 
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int jj = 0; jj < TN; ++jj) {
-      const int n = n0 + wn * (TN * 32) + jj * 32 + (lane & 31);
-      if (n >= j.N) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * (TM * 32) + i * 32 + acc_row(lane, r);
-        if (m < j.M) ep.apply(m, n, acc[i][jj][r]);
-      }
-    }
+  store_rows(ep, acc, m0 + wm * (TM * 32), n0 + wn * (TN * 32), j.M, j.N, lane);
 }
 
 // Time of a product in slices, as plan_direct() has it: workgroups on the busiest compute unit in rounds of as many as it
