@@ -413,10 +413,28 @@ struct EpiSlabSwapped {
   float* base;
   AX_HD void set_group(int /*g*/, int z) { base = ws + (long)z * slab; }
   AX_HD void apply(int m, int n, float v) const { base[(long)n * ldc + m] = v; }
-  AX_HD void apply4(int m, int n, float4 v) const {
-    apply(m, n, v.x); apply(m, n + 1, v.y); apply(m, n + 2, v.z); apply(m, n + 3, v.w);
-  }
 };
+// Whether the lanes of a block run along the product's rows (the MFMA's operands exchanged) and not along its columns.  Only here
+// are the rows what lies side by side in memory.  Everything else is stored 32 columns at a time; 16-byte stores of four columns
+// of 32 rows, which these kernels had, touched 32 lines each: transformed products of batch 128 182 -> 164 us (second layer
+// forward), 200 -> 176 (its data gradient), first layer forward 206 -> 189.
+template <class Epi>
+constexpr bool kRowsAcross = std::is_same<Epi, EpiSlabSwapped>::value;
+#ifndef AX_HOST_EMU
+template <int TM, int TN>
+__device__ __forceinline__ void store_rows(const EpiSlabSwapped& e, const v16f (&acc)[TM][TN], int m, int n, int M, int N, int lane) {
+  const uint32_t ld = (uint32_t)e.ldc * 4u;
+  const BufView out = make_view(e.base, (uint32_t)N * ld);
+  uint32_t at[TM];
+  column_offsets<TM>(at, ld, 0, n, m, M, lane);
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) buf_st1(out, at[i] + (uint32_t)(j * 32 + block_row(r)) * ld, acc[i][j][r]);
+}
+#endif
 
 // ================================= kernel ====================================
 #ifndef AX_HOST_EMU
@@ -578,7 +596,7 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
       const int p = t & 1;
       SplitFrags<AL, T::TM> fa;
       SplitFrags<BL, T::TN> fb;
-      split_groups<T, AL, BL, Epi::kTransposed>(As[p] + a_off, Bs[p] + b_off, fa, fb, acc, lo, al, bl, As[p ^ 1], Bs[p ^ 1],
+      split_groups<T, AL, BL, kRowsAcross<Epi>>(As[p] + a_off, Bs[p] + b_off, fa, fb, acc, lo, al, bl, As[p ^ 1], Bs[p ^ 1],
                                                 ra, rb, kend - kbeg - (t + 2) * T::BK);
       __syncthreads();
     }
@@ -601,27 +619,11 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
     if (lane == 0) As[0][wave] = bad;
     __syncthreads();
     if ((As[0][0] | As[0][1] | As[0][2] | As[0][3]) != 0)
-      split_redo<T, AL, BL, Epi::kTransposed>(ap, bp, (int)g, m0, n0, kbeg, kend, reinterpret_cast<float*>(As[0]),
+      split_redo<T, AL, BL, kRowsAcross<Epi>>(ap, bp, (int)g, m0, n0, kbeg, kend, reinterpret_cast<float*>(As[0]),
                                               reinterpret_cast<float*>(Bs[0]), acc);
   }
 
-#pragma unroll
-  for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < T::TN; ++j) {
-      if constexpr (Epi::kTransposed) {
-        store_block<T>(ep, acc[i][j], m0 + wm * (T::TM * 32) + i * 32 + (lane & 31), n0 + wn * (T::TN * 32) + j * 32,
-                       lane, M, N);
-      } else {
-        const int n = n0 + wn * (T::TN * 32) + j * 32 + (lane & 31);
-        if (n >= N) continue;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = m0 + wm * (T::TM * 32) + i * 32 + acc_row(lane, r);
-          if (m < M) ep.apply(m, n, acc[i][j][r]);
-        }
-      }
-    }
+  store_rows(ep, acc, m0 + wm * (T::TM * 32), n0 + wn * (T::TN * 32), M, N, lane);
 }
 #endif  // AX_HOST_EMU
 
