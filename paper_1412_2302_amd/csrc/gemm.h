@@ -123,6 +123,10 @@ __device__ __forceinline__ float4 buf_ld4(const BufView& v, uint32_t off) {
 __device__ __forceinline__ float buf_ld1(const BufView& v, uint32_t off) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(v, (int)off, 0, 0));
 }
+__device__ __forceinline__ void buf_st4(const BufView& v, uint32_t off, const float4& x) {
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, x), v, (int)off, 0, 0);
+}
 #endif
 
 // ---- division by a launch constant -------------------------------------------

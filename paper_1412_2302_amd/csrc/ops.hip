@@ -523,6 +523,13 @@ __device__ __forceinline__ float4 lrn_window_sum_regs(const float* v, int half) 
   }
   return make_float4(s[0], s[1], s[2], s[3]);
 }
+// NET: the network's own normalisation, five channels and s^-3/4, known to the compiler.  The fused kernels were bound by what they
+// compute: with window and exponent looked at for every value the forward kernel had 2241 instructions, and 659 so (first layer of
+// 128 pictures 70 us | 59, second 42 | 35).
+template <bool NET>
+__device__ __forceinline__ int lrn_half(int half) { return NET ? 2 : half; }
+template <bool NET>
+__device__ __forceinline__ float lrn_beta(float beta) { return NET ? 0.75f : beta; }
 __device__ __forceinline__ float4 lrn_window_sum(const float* row, int c, int half) {
   float v[12];
   *reinterpret_cast<float4*>(v) = *reinterpret_cast<const float4*>(row + c - 4);
@@ -530,99 +537,55 @@ __device__ __forceinline__ float4 lrn_window_sum(const float* row, int c, int ha
   *reinterpret_cast<float4*>(v + 8) = *reinterpret_cast<const float4*>(row + c + 4);
   return lrn_window_sum_regs(v, half);
 }
-
-// Where the gradient of the normalised activations comes from: a tensor, or (dy != null) the adjoint of the
-// 3x3 stride-2 max-pool that follows, gathered on the fly from the pooled gradient and the winning taps.
-struct PoolGather {
-  const float* dy;       // [N][Ho][Wo][C]
-  const uint8_t* slot;   // winning tap 0..8 of each pooled element
-  int H, W, Ho, Wo;
-  FastDiv d_w, d_h;
-};
-// The (at most four) pooled windows over an input pixel, as loaded: the reduction is a separate step so
-// that the loads can be issued a trip ahead of their use.
-struct PoolTaps {
-  uint32_t s4[4];    // winning taps of four channels
-  float4 d[4];       // pooled gradient of four channels
-  uint32_t want[4];  // this pixel's tap number in that window; 9 (never a winner) for a window that does not exist
-};
-__device__ __forceinline__ void pool_taps_fetch(const PoolGather& pg, long pix, int c, int C, PoolTaps& t) {
-  const uint32_t q = fdiv((uint32_t)pix, pg.d_w);  // pix < 2^31: a tensor is smaller than 2 GiB
-  const int x = (int)((uint32_t)pix - q * (uint32_t)pg.W);
-  const uint32_t n = fdiv(q, pg.d_h);
-  const int y = (int)(q - n * (uint32_t)pg.H);
-  const int yo_lo = y >= 2 ? (y - 1) / 2 : 0, yo_hi = min(y / 2, pg.Ho - 1);
-  const int xo_lo = x >= 2 ? (x - 1) / 2 : 0, xo_hi = min(x / 2, pg.Wo - 1);
-#pragma unroll
-  for (int wy = 0; wy < 2; ++wy)
-#pragma unroll
-    for (int wx = 0; wx < 2; ++wx) {
-      const int yo = min(yo_lo + wy, yo_hi), xo = min(xo_lo + wx, xo_hi);
-      // a pixel in a last row or column that no window covers has lo > hi: the clamped address is still inside
-      const bool valid = yo_lo + wy <= yo_hi && xo_lo + wx <= xo_hi;
-      const uint32_t o = ((n * (uint32_t)pg.Ho + (uint32_t)yo) * (uint32_t)pg.Wo + (uint32_t)xo) * (uint32_t)C + c;
-      t.want[wy * 2 + wx] = valid ? (uint32_t)((y - 2 * yo) * 3 + (x - 2 * xo)) : 9u;
-      t.s4[wy * 2 + wx] = *reinterpret_cast<const uint32_t*>(pg.slot + o);
-      t.d[wy * 2 + wx] = *reinterpret_cast<const float4*>(pg.dy + o);
-    }
-}
-__device__ __forceinline__ float4 pool_taps_reduce(const PoolTaps& t) {
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const uint32_t s4 = t.s4[w], want = t.want[w];
-    acc.x += (s4 & 0xffu) == want ? t.d[w].x : 0.f;
-    acc.y += ((s4 >> 8) & 0xffu) == want ? t.d[w].y : 0.f;
-    acc.z += ((s4 >> 16) & 0xffu) == want ? t.d[w].z : 0.f;
-    acc.w += (s4 >> 24) == want ? t.d[w].w : 0.f;
-  }
-  return acc;
+template <bool NET>  // two neighbours on either side
+__device__ __forceinline__ float4 lrn_window_sum_net(const float* row, int c, int half) {
+  if (!NET) return lrn_window_sum(row, c, half);
+  float v[12];
+  *reinterpret_cast<float2*>(v + 2) = *reinterpret_cast<const float2*>(row + c - 2);
+  *reinterpret_cast<float4*>(v + 4) = *reinterpret_cast<const float4*>(row + c);
+  *reinterpret_cast<float2*>(v + 8) = *reinterpret_cast<const float2*>(row + c + 4);
+  v[0] = v[1] = v[10] = v[11] = 0.f;
+  return lrn_window_sum_regs(v, 2);
 }
 
-template <bool BWD, bool GATHER>
+template <bool BWD>
 __global__ void __launch_bounds__(256)
 lrn_vec_kernel(const float* __restrict__ a, const float* __restrict__ db, float* __restrict__ out, long pixels, int C,
-               int half, int PB, float k, float alpha, float beta, int relu_gate, PoolGather pg,
-               float* __restrict__ part, uint16_t* __restrict__ out16) {
+               int half, int PB, float k, float alpha, float beta, int relu_gate) {
   extern __shared__ __attribute__((aligned(16))) float sh[];  // [2][PB][kLrnPad + C + kLrnPad]
   const int q = C >> 2;                                        // lanes per pixel
   const int ld = C + 2 * kLrnPad;
   const int pl = threadIdx.x / q, cq = threadIdx.x - pl * q;
   float* sq = sh + (size_t)pl * ld + kLrnPad;
   float* tt = sh + (size_t)PB * ld + (size_t)pl * ld + kLrnPad;
-  if (pl < PB && cq < 2) {  // zero the pads of this pixel's two rows
-    const int o = cq == 0 ? -kLrnPad : C;
-    *reinterpret_cast<float4*>(sq + o) = make_float4(0.f, 0.f, 0.f, 0.f);
-    *reinterpret_cast<float4*>(tt + o) = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int r = threadIdx.x; r < 2 * PB; r += 256) {  // the clipped window's zeros
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    *reinterpret_cast<float4*>(sh + (size_t)r * ld) = zero;
+    *reinterpret_cast<float4*>(sh + (size_t)r * ld + kLrnPad + C) = zero;
   }
   const int c = cq * 4;
-  float4 colsum = make_float4(0.f, 0.f, 0.f, 0.f);  // of this lane's outputs over all its pixels
   // every workgroup makes the same number of trips, so the barriers inside are uniform; the loads of a
   // trip are issued during the trip before
   const long stride = (long)gridDim.x * PB;
   float4 nav = make_float4(0.f, 0.f, 0.f, 0.f), ndv = nav;
-  PoolTaps taps;
   {
     const long pix = (long)blockIdx.x * PB + pl;
     if (pl < PB && pix < pixels) {
       nav = *reinterpret_cast<const float4*>(a + pix * C + c);
-      if (BWD && GATHER) pool_taps_fetch(pg, pix, c, C, taps);
-      if (BWD && !GATHER) ndv = *reinterpret_cast<const float4*>(db + pix * C + c);
+      if (BWD) ndv = *reinterpret_cast<const float4*>(db + pix * C + c);
     }
   }
   for (long first = (long)blockIdx.x * PB; first < pixels; first += stride) {
     const long pix = first + pl;
     const bool on = pl < PB && pix < pixels;
     const float4 av = nav;
-    float4 dv = ndv;
-    if (BWD && GATHER && on) dv = pool_taps_reduce(taps);
+    const float4 dv = ndv;
     if (on) *reinterpret_cast<float4*>(sq + c) = make_float4(av.x * av.x, av.y * av.y, av.z * av.z, av.w * av.w);
     {
       const long npix = pix + stride;
       if (pl < PB && npix < pixels) {
         nav = *reinterpret_cast<const float4*>(a + npix * C + c);
-        if (BWD && GATHER) pool_taps_fetch(pg, npix, c, C, taps);
-        if (BWD && !GATHER) ndv = *reinterpret_cast<const float4*>(db + npix * C + c);
+        if (BWD) ndv = *reinterpret_cast<const float4*>(db + npix * C + c);
       }
     }
     __syncthreads();
@@ -656,30 +619,9 @@ lrn_vec_kernel(const float* __restrict__ a, const float* __restrict__ db, float*
         r.w = av.w > 0.f ? r.w : 0.f;
       }
       *reinterpret_cast<float4*>(out + pix * C + c) = r;
-      if (out16) store_bf16x4(out16 + pix * C + c, r);  // bf16 copy for the products that read the gradient next
-      colsum.x += r.x;
-      colsum.y += r.y;
-      colsum.z += r.z;
-      colsum.w += r.w;
     }
     // the next trip writes the squares, which were last read before the barrier above, and writes the
     // products only after its own first barrier, when every lane is done with this trip's
-  }
-  if (BWD && part) {  // part[workgroup][channel] = sum of this workgroup's outputs, in a fixed order
-    __syncthreads();
-    if (pl < PB) *reinterpret_cast<float4*>(sh + (size_t)pl * C + c) = colsum;
-    __syncthreads();
-    if (pl == 0) {
-      float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int r = 0; r < PB; ++r) {
-        const float4 v = *reinterpret_cast<const float4*>(sh + (size_t)r * C + c);
-        t.x += v.x;
-        t.y += v.y;
-        t.z += v.z;
-        t.w += v.w;
-      }
-      *reinterpret_cast<float4*>(part + (size_t)blockIdx.x * C + c) = t;
-    }
   }
 }
 
@@ -688,6 +630,7 @@ lrn_vec_kernel(const float* __restrict__ a, const float* __restrict__ db, float*
 // four channels of a pixel and reads that pixel's channels c-4 .. c+7 itself), then pools out of LDS.  The
 // normalised tensor never goes to memory.  Same arithmetic and tie-break (first maximum in row-major tap
 // order) as the separate kernels.
+template <bool NET>
 __global__ void __launch_bounds__(256)
 lrn_pool_fwd_kernel(const float* __restrict__ a, float* __restrict__ y, uint8_t* __restrict__ slot, int H, int W,
                     int C, int Ho, int Wo, int PH, int PW, int tiles_y, int tiles_x, int half, float k, float alpha,
@@ -720,8 +663,13 @@ lrn_pool_fwd_kernel(const float* __restrict__ a, float* __restrict__ y, uint8_t*
         const float* px = src + (valid ? ((size_t)ly * W + lx) * C : 0) + c;
         m[u] = *reinterpret_cast<const float4*>(px);
         l[u] = h[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (c >= 4) l[u] = *reinterpret_cast<const float4*>(px - 4);
-        if (c + 4 < C) h[u] = *reinterpret_cast<const float4*>(px + 4);
+        if (NET) {
+          if (c >= 4) *reinterpret_cast<float2*>(&l[u].z) = *reinterpret_cast<const float2*>(px - 2);
+          if (c + 4 < C) *reinterpret_cast<float2*>(&h[u].x) = *reinterpret_cast<const float2*>(px + 4);
+        } else {
+          if (c >= 4) l[u] = *reinterpret_cast<const float4*>(px - 4);
+          if (c + 4 < C) h[u] = *reinterpret_cast<const float4*>(px + 4);
+        }
         ly += dq;
         lx += dr;
         if (lx >= iw) {
@@ -738,11 +686,11 @@ lrn_pool_fwd_kernel(const float* __restrict__ a, float* __restrict__ y, uint8_t*
                              sq_rounded(l[u].w), sq_rounded(m[u].x), sq_rounded(m[u].y),
                              sq_rounded(m[u].z), sq_rounded(m[u].w), sq_rounded(h[u].x),
                              sq_rounded(h[u].y), sq_rounded(h[u].z), sq_rounded(h[u].w)};
-        const float4 w = lrn_window_sum_regs(v, half);
+        const float4 w = lrn_window_sum_regs(v, lrn_half<NET>(half));
         if (pxl < np)
           *reinterpret_cast<float4*>(bbuf + (size_t)pxl * C + c) = make_float4(
-              m[u].x * neg_pow(k + alpha * w.x, beta), m[u].y * neg_pow(k + alpha * w.y, beta),
-              m[u].z * neg_pow(k + alpha * w.z, beta), m[u].w * neg_pow(k + alpha * w.w, beta));
+              m[u].x * neg_pow(k + alpha * w.x, lrn_beta<NET>(beta)), m[u].y * neg_pow(k + alpha * w.y, lrn_beta<NET>(beta)),
+              m[u].z * neg_pow(k + alpha * w.z, lrn_beta<NET>(beta)), m[u].w * neg_pow(k + alpha * w.w, lrn_beta<NET>(beta)));
       }
     }
   }
@@ -756,7 +704,7 @@ lrn_pool_fwd_kernel(const float* __restrict__ a, float* __restrict__ y, uint8_t*
     }
     const float* win = bbuf + ((size_t)(2 * oy) * iw + 2 * ox) * C + c;
     float4 best = *reinterpret_cast<const float4*>(win);
-    uint32_t bs = 0;
+    uint32_t tx0 = 0, tx1 = 0, tx2 = 0, tx3 = 0;  // winning tap of each channel
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -764,15 +712,162 @@ lrn_pool_fwd_kernel(const float* __restrict__ a, float* __restrict__ y, uint8_t*
         if (r == 0 && s2 == 0) continue;
         const float4 b = *reinterpret_cast<const float4*>(win + ((size_t)r * iw + s2) * C);
         const uint32_t tap = (uint32_t)(r * 3 + s2);
-        if (b.x > best.x) { best.x = b.x; bs = (bs & 0xffffff00u) | tap; }
-        if (b.y > best.y) { best.y = b.y; bs = (bs & 0xffff00ffu) | (tap << 8); }
-        if (b.z > best.z) { best.z = b.z; bs = (bs & 0xff00ffffu) | (tap << 16); }
-        if (b.w > best.w) { best.w = b.w; bs = (bs & 0x00ffffffu) | (tap << 24); }
+        if (b.x > best.x) { best.x = b.x; tx0 = tap; }
+        if (b.y > best.y) { best.y = b.y; tx1 = tap; }
+        if (b.z > best.z) { best.z = b.z; tx2 = tap; }
+        if (b.w > best.w) { best.w = b.w; tx3 = tap; }
       }
+    const uint32_t bs = tx0 | tx1 << 8 | tx2 << 16 | tx3 << 24;
     const size_t e = (((size_t)n * Ho + py0 + oy) * Wo + px0 + ox) * C + c;
     *reinterpret_cast<float4*>(y + e) = best;
     if (y16) store_bf16x4(y16 + e, best);  // bf16 copy for the product that reads the pooled tensor next
     *reinterpret_cast<uint32_t*>(slot + e) = bs;
+  }
+}
+
+// The adjoint of the two, gated by the ReLU, with the bias gradient's partial sums (C % 4 == 0).  A lane owns four channels of a
+// block of 2 x 2 pixels: those lie under the same four pooled windows at most, with taps that are known, so that a window is
+// loaded once for four pixels and nine comparisons serve them, where pixel by pixel there were sixteen loads and comparisons.
+// A workgroup walks over neighbouring blocks, workgroups of one XCD over neighbouring runs of them; the loads of a trip are
+// issued during the trip before.  128 pictures 91 -> 66 us (first layer) and 62 -> 48 (second), 256 in bf16 181 -> 144 and 129 ->
+// 107: 5 TB/s.  126 registers; with squares and products kept in registers 28 of them spilled, 313 us.
+struct PoolLrnBwd {
+  const float *a, *dy;   // [N][H][W][C], [N][Ho][Wo][C]
+  const uint8_t* slot;   // winning tap 0..8 of each pooled element
+  float* out;
+  uint16_t* out16;       // may be null: a bf16 copy of out
+  float* part;           // may be null: part[workgroup][channel], the sums of the workgroup's outputs
+  uint32_t blocks;       // N * by * bx
+  int H, W, C, Ho, Wo, half, PB, relu_gate;
+  float k, alpha, beta;
+  uint32_t bytes, pooled;  // of a; elements of dy
+  FastDiv bx, by;
+};
+template <bool NET>
+__global__ void __launch_bounds__(256, 3) pool_lrn_bwd_kernel(PoolLrnBwd g) {
+  extern __shared__ __attribute__((aligned(16))) float sh[];  // [2][4 * PB][kLrnPad + C + kLrnPad]: squares, products
+  const int C = g.C, q = C >> 2, ld = C + 2 * kLrnPad, pl = threadIdx.x / q, c = (threadIdx.x - pl * q) * 4;
+  const bool lane_on = pl < g.PB;
+  float* const sq = sh + (size_t)(4 * pl) * ld + kLrnPad;
+  float* const tt = sq + (size_t)(4 * g.PB) * ld;
+  for (int r = threadIdx.x; r < 8 * g.PB; r += 256) {  // the clipped window's zeros
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    *reinterpret_cast<float4*>(sh + (size_t)r * ld) = zero;
+    *reinterpret_cast<float4*>(sh + (size_t)r * ld + kLrnPad + C) = zero;
+  }
+  const BufView av = make_view(g.a, g.bytes), dyv = make_view(g.dy, g.pooled * 4u),
+                sv = make_view(reinterpret_cast<const float*>(g.slot), g.pooled), ov = make_view(g.out, g.bytes);
+  const uint32_t trips = (g.blocks + g.PB - 1) / g.PB, G = gridDim.x, q8 = G >> 3, r8 = G & 7, xcd = blockIdx.x & 7;
+  const uint32_t place = xcd * q8 + min(xcd, r8) + (blockIdx.x >> 3);
+  const uint32_t begin = (uint32_t)((uint64_t)place * trips / G) * g.PB;
+  const uint32_t end = min((uint32_t)((uint64_t)(place + 1) * trips / G) * g.PB, g.blocks);
+  float4 na[4], nd[4];  // the next block's pixels and windows, row by row
+  uint32_t ns[4], nat, nin;  // winning taps; offset of the first pixel, which of the four there are
+  auto corner = [&](int p) { return ((p % 2 ? 1u : 0u) + (p < 2 ? 0u : (uint32_t)g.W)) * (uint32_t)C * 4u; };
+  auto fetch = [&](uint32_t b) {
+    const uint32_t row = fdiv(b, g.bx), n = fdiv(row, g.by);
+    const int j = (int)(b - row * g.bx.d), i = (int)(row - n * g.by.d);
+    const bool on = lane_on && b < end;
+    const uint32_t e = ((n * (uint32_t)g.H + 2u * i) * (uint32_t)g.W + 2u * j) * (uint32_t)C + (uint32_t)c;
+    const uint32_t w = ((n * (uint32_t)g.Ho + (uint32_t)i) * (uint32_t)g.Wo + (uint32_t)j) * (uint32_t)C + (uint32_t)c;
+    const bool right = 2 * j + 1 < g.W, down = 2 * i + 1 < g.H;
+    nat = e * 4u;
+    nin = on ? (right ? 3u : 1u) * (down ? 5u : 1u) : 0u;  // bits 0 to 3
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const bool in = on && (p % 2 == 0 || right) && (p < 2 || down);
+      na[p] = buf_ld4(av, in ? nat + corner(p) : kOob);
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {  // windows (i - 1 + p/2, j - 1 + p%2); zero where there is none, and zeros add nothing
+      const int y = i - 1 + p / 2, x = j - 1 + p % 2;
+      const bool in = on && y >= 0 && y < g.Ho && x >= 0 && x < g.Wo;
+      const uint32_t o = w - (p % 2 ? 0u : (uint32_t)C) - (p < 2 ? (uint32_t)(g.Wo * C) : 0u);
+      nd[p] = buf_ld4(dyv, in ? o * 4u : kOob);
+      ns[p] = __float_as_uint(buf_ld1(sv, in ? o : kOob));
+    }
+  };
+  float4 colsum = make_float4(0.f, 0.f, 0.f, 0.f);  // of this lane's outputs over all its pixels
+  fetch(begin + pl);
+  for (uint32_t first = begin; first < end; first += g.PB) {
+    float4 x[4], d[4];
+    const uint32_t at = nat, in = nin;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      x[p] = na[p];
+      d[p] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    auto add = [&](float4& t, int w, uint32_t tap) {
+      t.x += (ns[w] & 0xffu) == tap ? nd[w].x : 0.f;
+      t.y += ((ns[w] >> 8) & 0xffu) == tap ? nd[w].y : 0.f;
+      t.z += ((ns[w] >> 16) & 0xffu) == tap ? nd[w].z : 0.f;
+      t.w += (ns[w] >> 24) == tap ? nd[w].w : 0.f;
+    };
+    add(d[0], 0, 8); add(d[0], 1, 6); add(d[0], 2, 2); add(d[0], 3, 0);
+    add(d[1], 1, 7); add(d[1], 3, 1);
+    add(d[2], 2, 5); add(d[2], 3, 3);
+    add(d[3], 3, 4);
+    if (lane_on) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        *reinterpret_cast<float4*>(sq + p * ld + c) = make_float4(x[p].x * x[p].x, x[p].y * x[p].y, x[p].z * x[p].z, x[p].w * x[p].w);
+    }
+    fetch(first + g.PB + pl);
+    __syncthreads();
+    float4 f[4];  // s^-beta
+    if (lane_on) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const float4 w = lrn_window_sum_net<NET>(sq + p * ld, c, g.half);
+        const float4 u = make_float4(g.k + g.alpha * w.x, g.k + g.alpha * w.y, g.k + g.alpha * w.z, g.k + g.alpha * w.w);
+        const float beta = lrn_beta<NET>(g.beta);
+        f[p] = make_float4(neg_pow(u.x, beta), neg_pow(u.y, beta), neg_pow(u.z, beta), neg_pow(u.w, beta));
+        *reinterpret_cast<float4*>(tt + p * ld + c) =
+            make_float4(d[p].x * x[p].x * neg_pow_over_s(u.x, f[p].x, beta), d[p].y * x[p].y * neg_pow_over_s(u.y, f[p].y, beta),
+                        d[p].z * x[p].z * neg_pow_over_s(u.z, f[p].z, beta), d[p].w * x[p].w * neg_pow_over_s(u.w, f[p].w, beta));
+      }
+    }
+    __syncthreads();
+    if (lane_on) {
+      const float h = 2.f * g.alpha * lrn_beta<NET>(g.beta);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const float4 acc = lrn_window_sum_net<NET>(tt + p * ld, c, g.half);
+        float4 r = make_float4(d[p].x * f[p].x - h * x[p].x * acc.x, d[p].y * f[p].y - h * x[p].y * acc.y,
+                               d[p].z * f[p].z - h * x[p].z * acc.z, d[p].w * f[p].w - h * x[p].w * acc.w);
+        if (g.relu_gate) {
+          r.x = x[p].x > 0.f ? r.x : 0.f;
+          r.y = x[p].y > 0.f ? r.y : 0.f;
+          r.z = x[p].z > 0.f ? r.z : 0.f;
+          r.w = x[p].w > 0.f ? r.w : 0.f;
+        }
+        const uint32_t o = at + corner(p);
+        buf_st4(ov, in >> p & 1u ? o : kOob, r);
+        if (g.out16 && (in >> p & 1u)) store_bf16x4(g.out16 + o / 4, r);
+        colsum.x += r.x;
+        colsum.y += r.y;
+        colsum.z += r.z;
+        colsum.w += r.w;
+      }
+    }
+    // the next trip writes the squares, which were last read before the barrier above, and the products only after its own
+    // first barrier, when every lane is done with this trip's
+  }
+  if (g.part) {  // in a fixed order
+    __syncthreads();
+    if (lane_on) *reinterpret_cast<float4*>(sh + (size_t)pl * C + c) = colsum;
+    __syncthreads();
+    if (pl == 0) {
+      float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int r = 0; r < g.PB; ++r) {
+        const float4 v = *reinterpret_cast<const float4*>(sh + (size_t)r * C + c);
+        t.x += v.x;
+        t.y += v.y;
+        t.z += v.z;
+        t.w += v.w;
+      }
+      *reinterpret_cast<float4*>(g.part + (size_t)blockIdx.x * C + c) = t;
+    }
   }
 }
 
@@ -791,8 +886,8 @@ int launch_lrn_fwd(const float* a, float* b, long pixels, int C, int n, float k,
   if (lrn_vec_ok(a, b, b, C, half)) {
     const int PB = 256 / (C / 4);
     const size_t lds = (size_t)2 * PB * (C + 2 * kLrnPad) * sizeof(float);
-    hipLaunchKernelGGL((lrn_vec_kernel<false, false>), dim3(lrn_grid(pixels, PB)), dim3(256), lds, st, a, nullptr, b,
-                       pixels, C, half, PB, k, alpha, beta, 0, PoolGather{}, nullptr, nullptr);
+    hipLaunchKernelGGL((lrn_vec_kernel<false>), dim3(lrn_grid(pixels, PB)), dim3(256), lds, st, a, nullptr, b,
+                       pixels, C, half, PB, k, alpha, beta, 0);
   } else {
     hipLaunchKernelGGL(lrn_fwd_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, a, b, total, C, half, k, alpha,
                        beta);
@@ -809,8 +904,8 @@ int launch_lrn_bwd(const float* a, const float* db, float* da, long pixels, int 
   if (lrn_vec_ok(a, db, da, C, half)) {
     const int PB = 256 / (C / 4);
     const size_t lds = (size_t)2 * PB * (C + 2 * kLrnPad) * sizeof(float);
-    hipLaunchKernelGGL((lrn_vec_kernel<true, false>), dim3(lrn_grid(pixels, PB)), dim3(256), lds, st, a, db, da,
-                       pixels, C, half, PB, k, alpha, beta, relu_gate, PoolGather{}, nullptr, nullptr);
+    hipLaunchKernelGGL((lrn_vec_kernel<true>), dim3(lrn_grid(pixels, PB)), dim3(256), lds, st, a, db, da,
+                       pixels, C, half, PB, k, alpha, beta, relu_gate);
   } else {
     hipLaunchKernelGGL(lrn_bwd_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, a, db, da, total, C, half, k,
                        alpha, beta, relu_gate);
@@ -870,27 +965,41 @@ int launch_lrn_pool_fwd(const float* a, float* y, uint8_t* slot, int N, int H, i
   const int tiles_y = ceil_div(Ho, PH), tiles_x = ceil_div(Wo, PW);
   const size_t lds = (size_t)(2 * PH + 1) * (2 * PW + 1) * C * sizeof(float);
   KernelScope ks("lrn_pool_fwd", 0, (double)N * H * W * C * 4.0 + (double)total * 5.0, st);
-  hipLaunchKernelGGL(lrn_pool_fwd_kernel, dim3((unsigned)(N * tiles_y * tiles_x)), dim3(256), lds, st, a, y, slot, H, W,
+  const auto kernel = n == 5 && beta == 0.75f ? lrn_pool_fwd_kernel<true> : lrn_pool_fwd_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(N * tiles_y * tiles_x)), dim3(256), lds, st, a, y, slot, H, W,
                      C, Ho, Wo, PH, PW, tiles_y, tiles_x, n / 2, k, alpha, beta, y16);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
 
-size_t lrn_part_rows(long pixels, int C) { return (size_t)lrn_grid(pixels, 256 / (C / 4)); }
+// Blocks of 2 x 2 pixels that a workgroup of the adjoint takes at a time: a lane for each of their channel quads, and at most 36
+// KiB of LDS, which leaves four workgroups to a compute unit
+static int pool_lrn_blocks(int C) { return std::max(1, std::min(256 / (C / 4), 36 * 1024 / (32 * (C + 2 * kLrnPad)))); }
+size_t lrn_part_rows(int N, int H, int W, int C) {
+  return (size_t)std::min<long>(ceil_div((long)N * ((H + 1) / 2) * ((W + 1) / 2), pool_lrn_blocks(C)), kLrnMaxBlocks);
+}
 int launch_pool_lrn_bwd(const float* a, const float* dy, const uint8_t* slot, float* da, int N, int H, int W, int C,
                         int Ho, int Wo, int n, float k, float alpha, float beta, int relu_gate, float* colsum_out,
                         float* part, hipStream_t st, bool partials_only, uint16_t* da16) {
   const long pixels = (long)N * H * W;
   if (!pixels) return ALEXNET_OK;
-  const int PB = 256 / (C / 4);
-  const int blocks = lrn_grid(pixels, PB);
+  const int blocks = (int)lrn_part_rows(N, H, W, C);
   const bool sums = colsum_out || partials_only;
   {
     KernelScope ks("pool_lrn_bwd", 0, (double)pixels * C * 8.0 + (double)N * Ho * Wo * C * 5.0, st);
-    const size_t lds = (size_t)2 * PB * (C + 2 * kLrnPad) * sizeof(float);
-    const PoolGather pg{dy, slot, H, W, Ho, Wo, make_fastdiv((uint32_t)W), make_fastdiv((uint32_t)H)};
-    hipLaunchKernelGGL((lrn_vec_kernel<true, true>), dim3(blocks), dim3(256), lds, st, a, nullptr, da, pixels, C, n / 2,
-                       PB, k, alpha, beta, relu_gate, pg, sums ? part : nullptr, da16);
+    PoolLrnBwd g;
+    g.a = a; g.dy = dy; g.slot = slot; g.out = da; g.out16 = da16; g.part = sums ? part : nullptr;
+    const int bx = (W + 1) / 2, by = (H + 1) / 2;
+    g.blocks = (uint32_t)N * by * bx;
+    g.H = H; g.W = W; g.C = C; g.Ho = Ho; g.Wo = Wo; g.half = n / 2; g.PB = pool_lrn_blocks(C); g.relu_gate = relu_gate;
+    g.k = k; g.alpha = alpha; g.beta = beta;
+    g.bytes = (uint32_t)(pixels * C * 4);
+    g.pooled = (uint32_t)((long)N * Ho * Wo * C);
+    g.bx = make_fastdiv((uint32_t)bx);
+    g.by = make_fastdiv((uint32_t)by);
+    const size_t lds = (size_t)8 * g.PB * (C + 2 * kLrnPad) * sizeof(float);
+    const auto kernel = n == 5 && beta == 0.75f ? pool_lrn_bwd_kernel<true> : pool_lrn_bwd_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), lds, st, g);
     AX_LAUNCH_CHECK();
   }
   if (colsum_out && !partials_only) {
