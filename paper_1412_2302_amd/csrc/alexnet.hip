@@ -487,7 +487,9 @@ static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* d
     AX_TRY(launch_first_weight(s.g, s.x16, dy, slices, st));
     return add_weight_slices(s.g, slices, ns, dwf, tail, st);
   }
-  return launch_conv_bwd_weight(s.g, x, dy, dwf, s.dwrun, n->gemm_ws, st, nullptr, small_ok(n, s, in_pass));
+  // the first layer's slices may wait in the scratch that the products share: it is the last product of a pass
+  return launch_conv_bwd_weight(s.g, x, dy, dwf, s.dwrun, n->gemm_ws, st, nullptr, small_ok(n, s, in_pass),
+                                &s == &n->st[0] ? tail : nullptr);
 }
 // taps_ready: the forms of wb are in place (s.wino_ub; s.wb16); yt_ready: so is that of dy (n->wino_a, the
 // transformed output gradient; s.dy16): stage_bwd_weight of the same minibatch ran just before
@@ -607,7 +609,8 @@ static int update_range(alexnet* n, size_t begin, size_t end, hipStream_t st) {
 
 // early_update: also start the update of the dense-layer weights on the side stream as soon as the dense
 // layers' backward pass is done (the caller updates the rest and joins, see alexnet_train_step)
-static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_update = false) {
+// upd (may be null): what the last launches update beside finishing the gradients; loss: the mean loss they leave
+static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_update, const SgdArgs* upd, const LossJob& loss) {
   const alexnet_config_t& c = n->cfg;
   set_gemm_precision(c.precision);
   // Bias gradients (column sums of every layer's output gradient) not made by a fused kernel on the way are
@@ -744,12 +747,8 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     set_error("bias gradients: %zu floats of partial sums in a workspace of %zu", bias_ws_used, n->colsum_ws_floats_);
     return ALEXNET_EINVAL;
   }
-  {
-    ProfContext pct("wgrad_tail");
-    AX_TRY(launch_wgrad_tail(wgrad_tail, st));
-  }
-  ProfContext pcb("bias_grads");
-  return launch_colsum_batch(bias_sums, st);
+  ProfContext pct("grad_tail");
+  return launch_grad_tail(wgrad_tail, bias_sums, loss, upd, st);
 }
 
 // Everything a forward pass derives from the weights -- transformed taps, bf16 copies -- is made on the side stream,
@@ -789,15 +788,14 @@ static int run_inference(alexnet* n, const float* in, uint16_t* in16, hipStream_
 }
 
 static int fwd_bwd(alexnet* n, int32_t slot, const int32_t* d_labels, uint64_t step, float* d_loss, hipStream_t st,
-                   bool early_update = false) {
+                   bool early_update = false, const SgdArgs* upd = nullptr) {
   const alexnet_config_t& c = n->cfg;
   AX_TRY(run_forward(n, n->input[slot], true, step, st, early_update ? n->ev_u_done : nullptr, n->input16[slot],
                      early_update && n->fc16 ? n->ev_fcw_done : nullptr));
   Dense& last = n->fc[kFc - 1];
   AX_TRY(launch_softmax_xent(last.act, d_labels, c.batch, last.out, 0, last.dz, n->row_loss, n->err_flag, st));
   if (n->fc16) AX_TRY(launch_to_bf16(last.dz, last.dz16, (size_t)c.batch * last.out, st));
-  AX_TRY(launch_mean_loss(n->row_loss, c.batch, d_loss, st));
-  return run_backward(n, n->input[slot], st, early_update);
+  return run_backward(n, n->input[slot], st, early_update, upd, LossJob{n->row_loss, c.batch, d_loss});
 }
 
 static int apply_update(alexnet* n, hipStream_t st) {
@@ -967,21 +965,19 @@ int alexnet_preprocess(alexnet_t* n, const uint8_t* d_raw, const float* d_mean, 
   REQUIRE(n && d_raw && d_mean, ALEXNET_EINVAL, "alexnet_preprocess: null argument");
   REQUIRE(slot == 0 || slot == 1, ALEXNET_EINVAL, "alexnet_preprocess: slot must be 0 or 1");
   const alexnet_config_t& c = n->cfg;
-  const uint64_t key = step_key(c.seed, step);
-  AX_TRY(launch_crop_params(key, c.batch, c.raw_w - c.crop_w + 1, c.raw_h - c.crop_h + 1, n->crop_x[slot],
-                            n->crop_y[slot], n->flip[slot], S(stream)));
-  return launch_preprocess(d_raw, d_mean, n->crop_x[slot], n->crop_y[slot], n->flip[slot], c.batch, c.in_c, c.raw_h,
-                           c.raw_w, c.crop_h, c.crop_w, n->input[slot], S(stream), n->input16[slot]);
+  const CropRule rule{1, step_key(c.seed, step), c.raw_w - c.crop_w + 1, c.raw_h - c.crop_h + 1, 0, 0,
+                      n->crop_x[slot], n->crop_y[slot], n->flip[slot]};
+  return launch_preprocess(d_raw, d_mean, rule, c.batch, c.in_c, c.raw_h, c.raw_w, c.crop_h, c.crop_w, n->input[slot], S(stream),
+                           n->input16[slot]);
 }
 
 int alexnet_preprocess_center(alexnet_t* n, const uint8_t* d_raw, const float* d_mean, int32_t slot, void* stream) {
   REQUIRE(n && d_raw && d_mean, ALEXNET_EINVAL, "alexnet_preprocess_center: null argument");
   REQUIRE(slot == 0 || slot == 1, ALEXNET_EINVAL, "alexnet_preprocess_center: slot must be 0 or 1");
   const alexnet_config_t& c = n->cfg;
-  AX_TRY(launch_crop_center(c.batch, (c.raw_w - c.crop_w) / 2, (c.raw_h - c.crop_h) / 2, n->crop_x[slot],
-                            n->crop_y[slot], n->flip[slot], S(stream)));
-  return launch_preprocess(d_raw, d_mean, n->crop_x[slot], n->crop_y[slot], n->flip[slot], c.batch, c.in_c, c.raw_h,
-                           c.raw_w, c.crop_h, c.crop_w, n->input[slot], S(stream), n->input16[slot]);
+  const CropRule rule{0, 0, 1, 1, (c.raw_w - c.crop_w) / 2, (c.raw_h - c.crop_h) / 2, n->crop_x[slot], n->crop_y[slot], n->flip[slot]};
+  return launch_preprocess(d_raw, d_mean, rule, c.batch, c.in_c, c.raw_h, c.raw_w, c.crop_h, c.crop_w, n->input[slot], S(stream),
+                           n->input16[slot]);
 }
 
 int alexnet_set_input(alexnet_t* n, const float* d_input_nchw, int32_t slot, void* stream) {
@@ -1026,11 +1022,10 @@ int alexnet_train_step(alexnet_t* n, int32_t slot, const int32_t* d_labels, uint
     }
     AX_HIP(hipEventRecord(n->ev_wb_done, n->upd_stream));
   }
-  AX_TRY(fwd_bwd(n, slot, d_labels, step, d_loss, S(stream), early));
-  if (!early) return apply_update(n, S(stream));
-  // convolution weights and all biases, the two ends of the flat vector, in one launch
-  AX_TRY(launch_sgd_update_two(n->params, n->mom, n->grads, fc_begin, n->n_weights, n->n_params, n->n_weights,
-                               n->cfg.lr, n->cfg.momentum, n->cfg.weight_decay, S(stream)));
+  // all biases, and the weights: of the convolutions, or all where the dense layers' are not updated on the side stream
+  const SgdArgs upd{n->params, n->mom, n->grads, early ? fc_begin : n->n_weights, n->cfg.lr, n->cfg.momentum, n->cfg.weight_decay};
+  AX_TRY(fwd_bwd(n, slot, d_labels, step, d_loss, S(stream), early, &upd));
+  if (!early) return ALEXNET_OK;
   AX_HIP(hipStreamWaitEvent(S(stream), n->ev_upd_done, 0));      // join the dense-layer update
   return ALEXNET_OK;
 }

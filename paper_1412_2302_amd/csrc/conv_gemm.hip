@@ -922,7 +922,7 @@ bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy) {
 // defer_ns (generic layout only): the split-k slices are left in ws, [group][slice][slab], and their number is
 // returned there for the caller to add them up later (1: the result is in dwf already)
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
-                           hipStream_t st, int* defer_ns, bool small) {
+                           hipStream_t st, int* defer_ns, bool small, WgradTail* tail) {
   if (small && wave_conv_bwd_weight_ok(c, g_bf16)) {
     if (defer_ns) *defer_ns = 1;
     return launch_wave_conv_bwd_weight(c, x, dy, dwf, ws, conv_bwd_weight_bf16(c, x, dy), st);
@@ -958,6 +958,15 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
     EpiSlab ep{p.ns > 1 ? ws : dwrun, slab, c.Cout, nullptr};
     AX_TRY((by_tile_run<SplitRunT>(p, run_t_params(a, kc), bwdw_B(c, dy), ep, c.k * kc, c.Cout, d.K, st)));
     if (defer_ns) *defer_ns = 1;
+    if (tail && tail->n < kMaxWgradJobs) {
+      WgradJob j{};
+      j.slices = p.ns > 1 ? ws : dwrun;
+      j.dU = dwf;
+      j.slab = slab;
+      j.nsplit = p.ns; j.groups36 = 1; j.k = c.k; j.head = kc / 4 * 4; j.kc = kc; j.cout = c.Cout;
+      wgrad_tail_add(*tail, j);
+      return ALEXNET_OK;
+    }
     return launch_reduce_slabs_unpack(p.ns > 1 ? ws : dwrun, p.ns, slab, c.k, kc / 4 * 4, kc, c.Cout, dwf, st);
   }
   bool table = av && bv && table_ok(a, d) && (!bf || d.K % kBKbf == 0);

@@ -17,9 +17,10 @@ int workspace_pieces(const alexnet_config_t* cfg, std::vector<WorkspacePiece>* o
 
 // The tail of the weight gradient of a transformed stage -- adding up the split-k slices of the products, then
 // the transform back to taps --, or the slices of another one (gemm_wave.h, weight_direct.hip, first_weight.hip;
-// total = 0), can be put off to the end of a backward pass and run for all such stages in two
-// launches: each of those kernels is too short to fill the chip on its own.  The slices and the products then
-// need memory of their own until the tail runs.
+// total = 0; the first layer's fp32 one, whose rows are put in order on the way: cout > 0), can be put off to the end
+// of a backward pass and run for all such stages in two launches, together with the bias gradients' sums: each of those
+// kernels is too short to fill the chip on its own.  The slices and the products then need memory of their own until
+// the tail runs.
 constexpr int kMaxWgradJobs = 5;
 struct WgradJob {
   const float* slices;  // [groups36][nsplit][slab]; unused when nsplit == 1 (the products are in dU already)
@@ -28,6 +29,7 @@ struct WgradJob {
   long slab, total;     // floats per product group; threads of the transform back
   int nsplit, groups36, groups, Na, Nb, k, nsub;
   int vec;              // set by wgrad_tail_add: the slices are added 16 bytes at a time
+  int head, kc, cout;   // cout > 0: see launch_reduce_slabs_unpack
 };
 struct WgradTail {
   WgradJob job[kMaxWgradJobs];
@@ -35,9 +37,6 @@ struct WgradTail {
   int n = 0, blocks_r = 0, blocks_t = 0;
 };
 void wgrad_tail_add(WgradTail& t, const WgradJob& job);  // t.n < kMaxWgradJobs
-int launch_reduce_slabs_batch(const WgradTail& t, hipStream_t st);
-int launch_wino_dw_batch(const WgradTail& t, hipStream_t st);
-int launch_wgrad_tail(const WgradTail& t, hipStream_t st);
 
 // ---- convolution as implicit GEMM (conv_gemm.hip) ---------------------------
 // Arithmetic of the GEMMs the calling thread launches from now on: 0 = fp32 operands, 1 = operands rounded to
@@ -83,7 +82,7 @@ int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, co
                          const float* gate, float* dx, float* ws, hipStream_t st, const uint16_t* dy16 = nullptr,
                          const uint16_t* wb16 = nullptr, uint16_t* dx16 = nullptr, bool small = true);
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
-                           hipStream_t st, int* defer_ns = nullptr, bool small = true);
+                           hipStream_t st, int* defer_ns = nullptr, bool small = true, WgradTail* tail = nullptr);
 
 // ---- 3x3 and 5x5 unit-stride convolutions through F(4x4, 3x3) (winograd.hip) ----
 // All tensors 16-byte aligned, channels per group multiples of 4.  V: wino_v_floats(), U / Ub / dU:
@@ -201,10 +200,17 @@ int launch_to_bf16_transposed(const float* src, uint16_t* dst, int G, int K, int
 int launch_pad4_bf16(const float* x, uint16_t* x4, size_t pixels, int C, hipStream_t st);
 int launch_run16_pack(const float* wf, uint16_t* wk, int k, int C, int run, int cout, hipStream_t st);
 int launch_fill_bytes(void* p, size_t nbytes, hipStream_t st);  // zero fill, nbytes % 4 == 0
-int launch_crop_params(uint64_t key, int B, int range_x, int range_y, int32_t* ox, int32_t* oy, int32_t* flip,
-                       hipStream_t st);
-int launch_preprocess(const uint8_t* raw, const float* mean, const int32_t* ox, const int32_t* oy,
-                      const int32_t* flip, int B, int C, int RH, int RW, int CH, int CW, float* out, hipStream_t st,
+// Crops and mirroring of a minibatch's pictures: drawn from the key, or (random = 0) the same offsets for all, not mirrored.
+// x, y, mirror [B]: where the preprocessing leaves them.
+struct CropRule {
+  int random;
+  uint64_t key;
+  int range_x, range_y;
+  int32_t off_x, off_y;
+  int32_t *x, *y, *mirror;
+};
+int launch_preprocess(const uint8_t* raw, const float* mean, const CropRule& rule, int B, int C, int RH, int RW, int CH, int CW,
+                      float* out, hipStream_t st,
                       uint16_t* out4 = nullptr);  // out4: also the pictures as bf16, four channels per pixel (C <= 4)
 // d4 (may be null, C < 4): also the pixels as bf16 with four channels each (launch_pad4_bf16)
 int launch_nchw_to_nhwc(const float* src, float* dst, int N, int C, int H, int W, hipStream_t st,
@@ -241,16 +247,21 @@ int launch_pool_argmax_canonical(const uint8_t* slot, int32_t* out_nchw, int N, 
 int launch_softmax_xent(const float* z, const int32_t* labels, int B, int classes, int mode, float* out,
                         float* row_loss, int32_t* err_flag, hipStream_t st);
 int launch_mean_loss(const float* row_loss, int B, float* loss, hipStream_t st);
+struct LossJob {
+  const float* row_loss;
+  int B;
+  float* loss;
+};
 int launch_colsum(const float* m, long rows, int cols, float* out, float* ws, hipStream_t st);
 size_t colsum_ws_floats(long rows, int cols);
 // Several column sums in two launches: add the jobs (each takes its partial sums from ws at *ws_used and moves
-// that on by colsum_batch_ws_floats(rows, cols)), then launch; every input must still hold its values then.
+// that on by colsum_batch_ws_floats(rows, cols)), then launch_grad_tail(); every input must still hold its values then.
 constexpr int kMaxColsumJobs = 8;
 struct ColsumJob {
   const float* m;
   float *part, *out;
   long rows;
-  int cols, rpb, nparts;
+  int cols, rpb, nparts, vec;
 };
 struct ColsumBatch {
   ColsumJob job[kMaxColsumJobs];
@@ -259,7 +270,18 @@ struct ColsumBatch {
 };
 int colsum_batch_add(ColsumBatch& b, const float* m, long rows, int cols, float* out, float* ws, size_t* ws_used);
 size_t colsum_batch_ws_floats(long rows, int cols);
-int launch_colsum_batch(const ColsumBatch& b, hipStream_t st);
+// What an update writes: elements [0, n) of the vectors, all weights, and the biases that the column sums are for
+struct SgdArgs {
+  float *w, *v;
+  const float* g;
+  size_t n;
+  float lr, mu, wd;
+};
+// The end of a backward pass: slices and bias gradients added up, transformed stages' products back to taps, the mean loss;
+// u (may be null): then the update, in the launches that finish the gradients as far as that goes.
+int launch_grad_tail(const WgradTail& t, const ColsumBatch& b, const LossJob& loss, const SgdArgs* u, hipStream_t st);
+int launch_grad_sums(const WgradTail& t, const ColsumBatch& b, const LossJob& loss, hipStream_t st);  // the first launch
+int launch_bias_sums(const ColsumBatch& b, const SgdArgs* u, hipStream_t st);  // the second where no stage is transformed
 int launch_reduce_slabs(const float* ws, int nsplit, long slab, int groups, float* out, hipStream_t st);
 // one result by cout columns: the first k*head rows are (r, j < head), the rest (r, j = head .. kc - 1); packed to rows
 // r*kc + j, rows with j >= kc (padded runs: head > kc) dropped
@@ -268,10 +290,6 @@ int launch_reduce_slabs_unpack(const float* ws, int nsplit, long slab, int k, in
 // max_blocks: upper limit of the grid (0: the default, four workgroups per CU)
 int launch_sgd_update(float* w, float* v, const float* g, size_t n, size_t n_decay, float lr, float mu, float wd,
                       hipStream_t st, unsigned max_blocks = 0);
-// the same for elements [0, n1) and [begin2, end2) of the vectors in one launch (n1 and begin2 multiples of four);
-// positions below n_decay are decayed
-int launch_sgd_update_two(float* w, float* v, const float* g, size_t n1, size_t begin2, size_t end2, size_t n_decay,
-                          float lr, float mu, float wd, hipStream_t st);
 int launch_average(float* a, float* b, size_t n, hipStream_t st);
 int launch_avg_grad_update(float* wa, float* va, const float* ga, float* wb, float* vb, const float* gb, size_t n,
                            size_t n_decay, float lr, float mu, float wd, hipStream_t st);

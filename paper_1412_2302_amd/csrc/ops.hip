@@ -7,6 +7,7 @@
 
 #include <algorithm>
 
+#include "grad_sums.h"
 #include "kernels.h"
 
 namespace ax {
@@ -153,35 +154,24 @@ int launch_copy(const float* src, float* dst, size_t n, hipStream_t st) {
 
 // ------------------------------------------------------------ preprocess ---
 // Paper Section 2.1 (footnote): mean subtraction, random crop, random flip.
-__global__ void crop_params_kernel(uint64_t key, int B, int range_x, int range_y, int32_t* ox, int32_t* oy,
-                                   int32_t* flip) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= B) return;
-  ox[n] = (int32_t)((rand_u64(key, TAG_CROP_X, n) >> 32) % (uint64_t)range_x);
-  oy[n] = (int32_t)((rand_u64(key, TAG_CROP_Y, n) >> 32) % (uint64_t)range_y);
-  flip[n] = (int32_t)(rand_u64(key, TAG_FLIP, n) >> 63);
+// Where picture n's crop starts and whether it is mirrored, worked out by whoever reads it; the picture's first row leaves it in
+// memory.  (A launch of its own in front of the pictures, whose every row then waited for its three numbers, took 5 us.)
+struct Crop {
+  int x, y, mirror;
+};
+__device__ __forceinline__ Crop crop_of(const CropRule& r, uint32_t n) {
+  Crop c{r.off_x, r.off_y, 0};
+  if (r.random) {  // the upper 32 bits modulo the range
+    c.x = (int)((uint32_t)(rand_u64(r.key, TAG_CROP_X, n) >> 32) % (uint32_t)r.range_x);
+    c.y = (int)((uint32_t)(rand_u64(r.key, TAG_CROP_Y, n) >> 32) % (uint32_t)r.range_y);
+    c.mirror = (int)(rand_u64(r.key, TAG_FLIP, n) >> 63);
+  }
+  return c;
 }
-// the central crop, not mirrored (validation)
-__global__ void crop_center_kernel(int B, int off_x, int off_y, int32_t* ox, int32_t* oy, int32_t* flip) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= B) return;
-  ox[n] = off_x;
-  oy[n] = off_y;
-  flip[n] = 0;
-}
-int launch_crop_center(int B, int off_x, int off_y, int32_t* ox, int32_t* oy, int32_t* flip, hipStream_t st) {
-  KernelScope ks("crop_params", 0, (double)B * 12.0, st);
-  hipLaunchKernelGGL(crop_center_kernel, dim3(grid_for(B, 64)), dim3(64), 0, st, B, off_x, off_y, ox, oy, flip);
-  AX_LAUNCH_CHECK();
-  return ALEXNET_OK;
-}
-int launch_crop_params(uint64_t key, int B, int range_x, int range_y, int32_t* ox, int32_t* oy, int32_t* flip,
-                       hipStream_t st) {
-  KernelScope ks("crop_params", 0, (double)B * 12.0, st);
-  hipLaunchKernelGGL(crop_params_kernel, dim3(grid_for(B, 64)), dim3(64), 0, st, key, B, range_x, range_y, ox, oy,
-                     flip);
-  AX_LAUNCH_CHECK();
-  return ALEXNET_OK;
+__device__ __forceinline__ void keep_crop(const CropRule& r, uint32_t n, const Crop& c) {
+  r.x[n] = c.x;
+  r.y[n] = c.y;
+  r.mirror[n] = c.mirror;
 }
 
 // ---- pictures: four pixels of every channel per thread, the channel-last rows through LDS ----
@@ -228,18 +218,19 @@ constexpr int kPreRows = 4;  // rows (waves) per workgroup
 // 124; it moves 99 and 302 MB.
 template <int C>
 __global__ void __launch_bounds__(64 * kPreRows)
-preprocess_pictures_kernel(const uint8_t* __restrict__ raw, const float* __restrict__ mean, const int32_t* __restrict__ ox,
-                           const int32_t* __restrict__ oy, const int32_t* __restrict__ flip, uint32_t rows, int RH,
+preprocess_pictures_kernel(const uint8_t* __restrict__ raw, const float* __restrict__ mean, CropRule rule, uint32_t rows, int RH,
                            int RW, int CH, int CW, FastDiv div_ch, float* __restrict__ out,
                            uint16_t* __restrict__ out4) {
   __shared__ __attribute__((aligned(16))) float lds[kPreRows][256 * C];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const uint32_t row = blockIdx.x * kPreRows + wave;  // n*CH + y
   const bool live = row < rows;
   const uint32_t n = live ? fdiv(row, div_ch) : 0, y = live ? row - n * (uint32_t)CH : 0;
   const uint32_t plane = (uint32_t)(RH * RW);
-  const int x0 = ox[n], mirror = flip[n];
-  const uint32_t src_row = ((uint32_t)oy[n] + y) * (uint32_t)RW;
+  const Crop crop = crop_of(rule, n);
+  if (live && y == 0 && lane == 0) keep_crop(rule, n, crop);
+  const int x0 = crop.x, mirror = crop.mirror;
+  const uint32_t src_row = ((uint32_t)crop.y + y) * (uint32_t)RW;
   const uint8_t* rp = raw + (size_t)n * C * plane + src_row;
   const float* mp = mean + src_row;
   for (int xc = 0; xc < CW; xc += 256) {  // the same for the whole workgroup
@@ -283,17 +274,18 @@ preprocess_pictures_kernel(const uint8_t* __restrict__ raw, const float* __restr
 }
 // any number of channels: a wave per row, one element per lane, one division by C each
 __global__ void __launch_bounds__(64 * kPreRows)
-preprocess_kernel(const uint8_t* __restrict__ raw, const float* __restrict__ mean, const int32_t* __restrict__ ox,
-                  const int32_t* __restrict__ oy, const int32_t* __restrict__ flip, uint32_t rows, int C, int RH,
+preprocess_kernel(const uint8_t* __restrict__ raw, const float* __restrict__ mean, CropRule rule, uint32_t rows, int C, int RH,
                   int RW, int CH, int CW, FastDiv div_c, FastDiv div_ch, float* __restrict__ out,
                   uint16_t* __restrict__ out4) {
-  const uint32_t row = blockIdx.x * kPreRows + (threadIdx.x >> 6);  // n*CH + y, the same for the whole wave
+  const uint32_t row = blockIdx.x * kPreRows + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // n*CH + y
   if (row >= rows) return;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t n = fdiv(row, div_ch), y = row - n * (uint32_t)CH;
   const uint32_t plane = (uint32_t)(RH * RW);
-  const int32_t x0 = ox[n], mirror = flip[n];
-  const uint32_t src_row = ((uint32_t)oy[n] + y) * (uint32_t)RW;
+  const Crop crop = crop_of(rule, n);
+  if (y == 0 && lane == 0) keep_crop(rule, n, crop);
+  const int32_t x0 = crop.x, mirror = crop.mirror;
+  const uint32_t src_row = ((uint32_t)crop.y + y) * (uint32_t)RW;
   const uint8_t* rp = raw + (size_t)n * C * plane + src_row;
   const float* mp = mean + src_row;
   const uint32_t len = (uint32_t)(CW * C);
@@ -318,8 +310,7 @@ preprocess_kernel(const uint8_t* __restrict__ raw, const float* __restrict__ mea
     }
   }
 }
-int launch_preprocess(const uint8_t* raw, const float* mean, const int32_t* ox, const int32_t* oy,
-                      const int32_t* flip, int B, int C, int RH, int RW, int CH, int CW, float* out, hipStream_t st,
+int launch_preprocess(const uint8_t* raw, const float* mean, const CropRule& rule, int B, int C, int RH, int RW, int CH, int CW, float* out, hipStream_t st,
                       uint16_t* out4) {
   if (out4 && C > 4) {
     set_error("preprocess: the four-channel bf16 copy needs at most four channels");
@@ -338,16 +329,16 @@ int launch_preprocess(const uint8_t* raw, const float* mean, const int32_t* ox, 
     const dim3 grid(ceil_div(rows, kPreRows)), block(64 * kPreRows);
     const FastDiv div_ch = make_fastdiv((uint32_t)CH);
     if (C == 1)
-      hipLaunchKernelGGL(preprocess_pictures_kernel<1>, grid, block, 0, st, raw, mean, ox, oy, flip, rows, RH, RW, CH, CW,
+      hipLaunchKernelGGL(preprocess_pictures_kernel<1>, grid, block, 0, st, raw, mean, rule, rows, RH, RW, CH, CW,
                          div_ch, out, out4);
     else
-      hipLaunchKernelGGL(preprocess_pictures_kernel<3>, grid, block, 0, st, raw, mean, ox, oy, flip, rows, RH, RW, CH, CW,
+      hipLaunchKernelGGL(preprocess_pictures_kernel<3>, grid, block, 0, st, raw, mean, rule, rows, RH, RW, CH, CW,
                          div_ch, out, out4);
     AX_LAUNCH_CHECK();
     return ALEXNET_OK;
   }
-  hipLaunchKernelGGL(preprocess_kernel, dim3(ceil_div(rows, kPreRows)), dim3(64 * kPreRows), 0, st, raw, mean, ox, oy,
-                     flip, rows, C, RH, RW, CH, CW, make_fastdiv((uint32_t)C), make_fastdiv((uint32_t)CH), out, out4);
+  hipLaunchKernelGGL(preprocess_kernel, dim3(ceil_div(rows, kPreRows)), dim3(64 * kPreRows), 0, st, raw, mean, rule,
+                     rows, C, RH, RW, CH, CW, make_fastdiv((uint32_t)C), make_fastdiv((uint32_t)CH), out, out4);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
@@ -1225,12 +1216,15 @@ int launch_softmax_xent(const float* z, const int32_t* labels, int B, int classe
   return ALEXNET_OK;
 }
 
-__global__ void __launch_bounds__(256) mean_loss_kernel(const float* __restrict__ row_loss, int B, float* loss) {
+__device__ __forceinline__ void mean_loss_block(const float* __restrict__ row_loss, int B, float* loss) {
   __shared__ float sh[4];
   float s = 0.f;
   for (int j = threadIdx.x; j < B; j += blockDim.x) s += row_loss[j];
   s = block_reduce(s, sh, false);
   if (threadIdx.x == 0) *loss = s / (float)B;
+}
+__global__ void __launch_bounds__(256) mean_loss_kernel(const float* __restrict__ row_loss, int B, float* loss) {
+  mean_loss_block(row_loss, B, loss);
 }
 int launch_mean_loss(const float* row_loss, int B, float* loss, hipStream_t st) {
   KernelScope ks("mean_loss", 0, (double)B * 4.0, st);
@@ -1291,46 +1285,9 @@ __global__ void __launch_bounds__(256)
 colsum_stage1(const float* __restrict__ m, long rows, int cols, int rpb, float* __restrict__ part) {
   colsum_stage1_block<VEC>(m, rows, cols, rpb, part, blockIdx.x, blockIdx.y);
 }
-__device__ __forceinline__ void colsum_stage2_block(const float* __restrict__ part, int nparts, int cols,
-                                                    float* __restrict__ out, int stripe) {
-  __shared__ float sh[4][64];
-  const int cl = threadIdx.x & 63, pl = threadIdx.x >> 6;
-  const int col = stripe * 64 + cl;
-  float s = 0.f;
-  if (col < cols) {
-#pragma unroll 8
-    for (int p = pl; p < nparts; p += 4) s += part[(size_t)p * cols + col];  // eight loads in flight, added in order
-  }
-  sh[pl][cl] = s;
-  __syncthreads();
-  if (pl == 0 && col < cols) out[col] = (sh[0][cl] + sh[1][cl]) + (sh[2][cl] + sh[3][cl]);
-}
 __global__ void __launch_bounds__(256)
 colsum_stage2(const float* __restrict__ part, int nparts, int cols, float* __restrict__ out) {
-  colsum_stage2_block(part, nparts, cols, out, blockIdx.x);
-}
-// Several column sums in two launches (the bias gradients of a backward pass, whose inputs all still exist at
-// its end).  The jobs' grids are laid end to end: a workgroup finds its job from the running totals (first1,
-// first2) and its place in that job's own grid.  Same arithmetic and order per job as colsum_stage1 +
-// colsum_stage2.
-__device__ __forceinline__ int colsum_job_of(const int* first, int n, int block) {
-  int j = 0;
-#pragma unroll
-  for (int k = 1; k < kMaxColsumJobs; ++k)
-    if (k < n && block >= first[k]) j = k;
-  return j;
-}
-template <bool VEC>
-__global__ void __launch_bounds__(256) colsum_batch_stage1(ColsumBatch b) {
-  const int ji = colsum_job_of(b.first1, b.n, blockIdx.x);
-  const ColsumJob& j = b.job[ji];
-  const int local = blockIdx.x - b.first1[ji], stripes = (j.cols + 63) / 64;
-  colsum_stage1_block<VEC>(j.m, j.rows, j.cols, j.rpb, j.part, local % stripes, local / stripes);
-}
-__global__ void __launch_bounds__(256) colsum_batch_stage2(ColsumBatch b) {
-  const int ji = colsum_job_of(b.first2, b.n, blockIdx.x);
-  const ColsumJob& j = b.job[ji];
-  colsum_stage2_block(j.part, j.nparts, j.cols, j.out, blockIdx.x - b.first2[ji]);
+  colsum_stage2_block(part, nparts, cols, out, blockIdx.x, SgdArgs{});
 }
 // rows per workgroup: enough row chunks for ~1024 workgroups, at least 64 rows each
 static int colsum_rows_per_block(long rows, int cols) {
@@ -1371,6 +1328,7 @@ int colsum_batch_add(ColsumBatch& b, const float* m, long rows, int cols, float*
   j.m = m; j.rows = rows; j.cols = cols; j.out = out;
   j.rpb = colsum_rows_per_block(rows, cols);
   j.nparts = ceil_div(rows, j.rpb);
+  j.vec = cols % 4 == 0 && aligned16(m);
   j.part = ws + *ws_used;
   *ws_used += ((size_t)j.nparts * cols + 3) / 4 * 4;  // every job's partials start on a 16-byte boundary
   const int stripes = ceil_div(cols, 64), k = b.n - 1;
@@ -1381,25 +1339,7 @@ int colsum_batch_add(ColsumBatch& b, const float* m, long rows, int cols, float*
   return ALEXNET_OK;
 }
 size_t colsum_batch_ws_floats(long rows, int cols) { return (colsum_ws_floats(rows, cols) + 3) / 4 * 4; }
-int launch_colsum_batch(const ColsumBatch& b, hipStream_t st) {
-  if (b.n == 0) return ALEXNET_OK;
-  bool vec = true;
-  double bytes = 0;
-  for (int i = 0; i < b.n; ++i) {
-    const ColsumJob& j = b.job[i];
-    vec = vec && j.cols % 4 == 0 && aligned16(j.m);
-    bytes += (double)j.rows * j.cols * 4.0;
-  }
-  KernelScope ks("colsum", 0, bytes, st);
-  if (vec)
-    hipLaunchKernelGGL((colsum_batch_stage1<true>), dim3(b.blocks1), dim3(256), 0, st, b);
-  else
-    hipLaunchKernelGGL((colsum_batch_stage1<false>), dim3(b.blocks1), dim3(256), 0, st, b);
-  AX_LAUNCH_CHECK();
-  hipLaunchKernelGGL(colsum_batch_stage2, dim3(b.blocks2), dim3(256), 0, st, b);
-  AX_LAUNCH_CHECK();
-  return ALEXNET_OK;
-}
+__global__ void __launch_bounds__(256) colsum_batch_stage2(ColsumBatch b) { colsum_batch_block2(b, blockIdx.x, SgdArgs{}); }
 
 // out[g][i] = sum_s ws[g*nsplit + s][i]  (split-k partial slabs)
 __device__ __forceinline__ void reduce_slabs_block(const float* __restrict__ ws, int nsplit, size_t slab, int groups,
@@ -1427,12 +1367,11 @@ reduce_slabs_kernel(const float* __restrict__ ws, int nsplit, size_t slab, int g
 }
 // The same for one result whose rows are runs padded to `run` entries (run mode of the first layer's weight
 // gradient): row (r, j) goes to row r*kc + j of the packed layout, the padding rows j >= kc nowhere.
-__global__ void __launch_bounds__(256)
-reduce_slabs_unpack_kernel(const float* __restrict__ ws, int nsplit, size_t slab, int k, int head, int kc, int cout,
-                           float* __restrict__ out) {
+__device__ __forceinline__ void reduce_slabs_unpack_block(const float* __restrict__ ws, int nsplit, size_t slab, int k, int head,
+                                                          int kc, int cout, float* __restrict__ out, unsigned block) {
   __shared__ float sh[4][64];
   const int el = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const size_t i = (size_t)blockIdx.x * 64 + el;
+  const size_t i = (size_t)block * 64 + el;
   float s = 0.f;
   if (i < slab) {
     const float* p = ws + i;
@@ -1452,6 +1391,11 @@ reduce_slabs_unpack_kernel(const float* __restrict__ ws, int nsplit, size_t slab
     }
     if (j < kc) out[((size_t)r * kc + j) * cout + o] = (sh[0][el] + sh[1][el]) + (sh[2][el] + sh[3][el]);
   }
+}
+__global__ void __launch_bounds__(256)
+reduce_slabs_unpack_kernel(const float* __restrict__ ws, int nsplit, size_t slab, int k, int head, int kc, int cout,
+                           float* __restrict__ out) {
+  reduce_slabs_unpack_block(ws, nsplit, slab, k, head, kc, cout, out, blockIdx.x);
 }
 int launch_reduce_slabs_unpack(const float* ws, int nsplit, long slab, int k, int head, int kc, int cout, float* out,
                                hipStream_t st) {
@@ -1492,17 +1436,38 @@ __global__ void __launch_bounds__(256)
 reduce_slabs_vec_kernel(const float* __restrict__ ws, int nsplit, size_t slab, int groups, float* __restrict__ out) {
   reduce_slabs_vec_block(ws, nsplit, slab, groups, out, blockIdx.x);
 }
-// the same for several results in one launch (see WgradTail): the jobs' grids laid end to end
-__global__ void __launch_bounds__(256) reduce_slabs_batch_kernel(WgradTail t) {
+// The first launch of a backward pass's end: slices of several results (see WgradTail), the first half of the bias gradients'
+// sums and the mean loss, the jobs' grids laid end to end.  One after the other, with the update behind them, they were seven
+// launches of an fp32 step on 128 pictures, 92 us of it; three now, 77.  Mini net, 16 pictures: 5 | 2 of its launches, and with the
+// crops 134 us | 127.
+__global__ void __launch_bounds__(256) reduce_slabs_batch_kernel(WgradTail t, ColsumBatch b, LossJob l) {
+  const int block = blockIdx.x;
+  if (block >= t.blocks_r + b.blocks1) {
+    mean_loss_block(l.row_loss, l.B, l.loss);
+    return;
+  }
+  if (block >= t.blocks_r) {
+    const int ji = colsum_job_of(b.first1, b.n, block - t.blocks_r);
+    const ColsumJob& j = b.job[ji];
+    const int local = block - t.blocks_r - b.first1[ji], stripes = (j.cols + 63) / 64;
+    if (j.vec)  // uniform over the workgroup
+      colsum_stage1_block<true>(j.m, j.rows, j.cols, j.rpb, j.part, local % stripes, local / stripes);
+    else
+      colsum_stage1_block<false>(j.m, j.rows, j.cols, j.rpb, j.part, local % stripes, local / stripes);
+    return;
+  }
   int ji = 0;
 #pragma unroll
   for (int k = 1; k < kMaxWgradJobs; ++k)
-    if (k < t.n && (int)blockIdx.x >= t.first_r[k]) ji = k;
+    if (k < t.n && block >= t.first_r[k]) ji = k;
   const WgradJob& j = t.job[ji];
-  if (j.vec)  // uniform over the workgroup
-    reduce_slabs_vec_block(j.slices, j.nsplit, (size_t)j.slab, j.groups36, j.dU, blockIdx.x - t.first_r[ji]);
+  const unsigned local = block - t.first_r[ji];
+  if (j.cout)
+    reduce_slabs_unpack_block(j.slices, j.nsplit, (size_t)j.slab, j.k, j.head, j.kc, j.cout, j.dU, local);
+  else if (j.vec)
+    reduce_slabs_vec_block(j.slices, j.nsplit, (size_t)j.slab, j.groups36, j.dU, local);
   else
-    reduce_slabs_block(j.slices, j.nsplit, (size_t)j.slab, j.groups36, j.dU, blockIdx.x - t.first_r[ji]);
+    reduce_slabs_block(j.slices, j.nsplit, (size_t)j.slab, j.groups36, j.dU, local);
 }
 void wgrad_tail_add(WgradTail& t, const WgradJob& job) {
   const int k = t.n++;
@@ -1511,16 +1476,16 @@ void wgrad_tail_add(WgradTail& t, const WgradJob& job) {
   j.vec = reduce_vec_ok(j.slices, j.dU, j.nsplit, j.slab) ? 1 : 0;
   t.first_r[k] = t.blocks_r;
   t.first_t[k] = t.blocks_t;
-  if (j.nsplit > 1) t.blocks_r += reduce_blocks(j.vec != 0, j.slab, j.groups36);
+  if (j.cout || j.nsplit > 1) t.blocks_r += reduce_blocks(j.vec != 0 && !j.cout, j.slab, j.groups36);
   t.blocks_t += ceil_div(j.total, 256);
 }
-int launch_reduce_slabs_batch(const WgradTail& t, hipStream_t st) {
-  if (t.blocks_r == 0) return ALEXNET_OK;
-  double bytes = 0;
+int launch_grad_sums(const WgradTail& t, const ColsumBatch& b, const LossJob& loss, hipStream_t st) {
+  double bytes = loss.B * 4.0;
   for (int i = 0; i < t.n; ++i)
-    if (t.job[i].nsplit > 1) bytes += (double)t.job[i].slab * t.job[i].groups36 * 4.0 * (t.job[i].nsplit + 1);
+    if (t.job[i].cout || t.job[i].nsplit > 1) bytes += (double)t.job[i].slab * t.job[i].groups36 * 4.0 * (t.job[i].nsplit + 1);
+  for (int i = 0; i < b.n; ++i) bytes += (double)b.job[i].rows * b.job[i].cols * 4.0;
   KernelScope ks("reduce_slabs", 0, bytes, st);
-  hipLaunchKernelGGL(reduce_slabs_batch_kernel, dim3(t.blocks_r), dim3(256), 0, st, t);
+  hipLaunchKernelGGL(reduce_slabs_batch_kernel, dim3(t.blocks_r + b.blocks1 + 1), dim3(256), 0, st, t, b, loss);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
@@ -1541,40 +1506,44 @@ int launch_reduce_slabs(const float* ws, int nsplit, long slab, int groups, floa
 // ---------------------------------------------------------------- update ---
 // v <- mu v - lr (g + wd w);  w <- w + v.  Elements below n_decay are weights
 // (decayed), the rest are biases (not decayed).
-// Two pieces of the vectors in one launch: elements [0, n1) and [n1 + gap, n + gap) (n1 a multiple of four, or
-// gap = 0); n_decay counts positions in the vectors, not elements of the launch.
-__global__ void __launch_bounds__(256)
-sgd_update_kernel(float* __restrict__ w, float* __restrict__ v, const float* __restrict__ g, size_t n, size_t n1,
-                  size_t gap, size_t n_decay, float lr, float mu, float wd) {
+__device__ __forceinline__ void sgd_block(float* __restrict__ w, float* __restrict__ v, const float* __restrict__ g, size_t n,
+                                          size_t n_decay, float lr, float mu, float wd, unsigned block, unsigned blocks) {
   // grid-stride over groups of four: a bounded number of workgroups, so that a GEMM running beside this
   // kernel on another stream still finds room on every CU
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q * 4 < n; q += stride) {
-    const size_t e = q * 4, i = e < n1 ? e : e + gap;
-    if (e + 3 < n) {
+  const size_t stride = (size_t)blocks * blockDim.x;
+  for (size_t q = (size_t)block * blockDim.x + threadIdx.x; q * 4 < n; q += stride) {
+    const size_t i = q * 4;
+    if (i + 3 < n) {
       float4 w4 = *reinterpret_cast<float4*>(w + i);
       float4 v4 = *reinterpret_cast<float4*>(v + i);
       const float4 g4 = *reinterpret_cast<const float4*>(g + i);
-      const float d0 = i + 0 < n_decay ? wd : 0.f, d1 = i + 1 < n_decay ? wd : 0.f;
-      const float d2 = i + 2 < n_decay ? wd : 0.f, d3 = i + 3 < n_decay ? wd : 0.f;
-      v4.x = mu * v4.x - lr * (g4.x + d0 * w4.x);
-      v4.y = mu * v4.y - lr * (g4.y + d1 * w4.y);
-      v4.z = mu * v4.z - lr * (g4.z + d2 * w4.z);
-      v4.w = mu * v4.w - lr * (g4.w + d3 * w4.w);
-      w4.x += v4.x;
-      w4.y += v4.y;
-      w4.z += v4.z;
-      w4.w += v4.w;
+      sgd_one(w4.x, v4.x, g4.x, i + 0 < n_decay ? wd : 0.f, lr, mu);
+      sgd_one(w4.y, v4.y, g4.y, i + 1 < n_decay ? wd : 0.f, lr, mu);
+      sgd_one(w4.z, v4.z, g4.z, i + 2 < n_decay ? wd : 0.f, lr, mu);
+      sgd_one(w4.w, v4.w, g4.w, i + 3 < n_decay ? wd : 0.f, lr, mu);
       *reinterpret_cast<float4*>(v + i) = v4;
       *reinterpret_cast<float4*>(w + i) = w4;
     } else {
-      for (size_t j = i; j < n + (e < n1 ? 0 : gap); ++j) {
-        const float d = j < n_decay ? wd : 0.f;
-        v[j] = mu * v[j] - lr * (g[j] + d * w[j]);
-        w[j] += v[j];
+      for (size_t j = i; j < n; ++j) {
+        float wj = w[j], vj = v[j];
+        sgd_one(wj, vj, g[j], j < n_decay ? wd : 0.f, lr, mu);
+        v[j] = vj;
+        w[j] = wj;
       }
     }
   }
+}
+__global__ void __launch_bounds__(256)
+sgd_update_kernel(float* __restrict__ w, float* __restrict__ v, const float* __restrict__ g, size_t n, size_t n_decay, float lr,
+                  float mu, float wd) {
+  sgd_block(w, v, g, n, n_decay, lr, mu, wd, blockIdx.x, gridDim.x);
+}
+// Behind the second half of the bias gradients, and beside their update, that of the weights
+__global__ void __launch_bounds__(256) sgd_colsum_batch_stage2(ColsumBatch b, SgdArgs u) {
+  if ((int)blockIdx.x < b.blocks2)
+    colsum_batch_block2(b, blockIdx.x, u);
+  else
+    sgd_block(u.w, u.v, u.g, u.n, u.n, u.lr, u.mu, u.wd, blockIdx.x - b.blocks2, gridDim.x - b.blocks2);
 }
 constexpr unsigned kUpdateMaxBlocks = 1024;  // 4 per CU
 int launch_sgd_update(float* w, float* v, const float* g, size_t n, size_t n_decay, float lr, float mu, float wd,
@@ -1582,19 +1551,21 @@ int launch_sgd_update(float* w, float* v, const float* g, size_t n, size_t n_dec
   if (!n) return ALEXNET_OK;
   KernelScope ks("sgd_update", 0, (double)n * 20.0, st);
   const unsigned blocks = std::min<unsigned>(grid_for((n + 3) / 4, 256), max_blocks ? max_blocks : kUpdateMaxBlocks);
-  hipLaunchKernelGGL(sgd_update_kernel, dim3(blocks), dim3(256), 0, st, w, v, g, n, n, (size_t)0, n_decay, lr, mu, wd);
+  hipLaunchKernelGGL(sgd_update_kernel, dim3(blocks), dim3(256), 0, st, w, v, g, n, n_decay, lr, mu, wd);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
-// elements [0, n1) and [begin2, end2) of the vectors in one launch; n1 a multiple of four, begin2 >= n1
-int launch_sgd_update_two(float* w, float* v, const float* g, size_t n1, size_t begin2, size_t end2, size_t n_decay,
-                          float lr, float mu, float wd, hipStream_t st) {
-  const size_t n = n1 + (end2 - begin2);
-  if (!n) return ALEXNET_OK;
-  KernelScope ks("sgd_update", 0, (double)n * 20.0, st);
-  const unsigned blocks = std::min<unsigned>(grid_for((n + 3) / 4, 256), kUpdateMaxBlocks);
-  hipLaunchKernelGGL(sgd_update_kernel, dim3(blocks), dim3(256), 0, st, w, v, g, n, n1, begin2 - n1, n_decay, lr, mu,
-                     wd);
+int launch_bias_sums(const ColsumBatch& b, const SgdArgs* u, hipStream_t st) {
+  if (!u) {
+    if (b.n == 0) return ALEXNET_OK;
+    KernelScope ks("colsum", 0, 0, st);
+    hipLaunchKernelGGL(colsum_batch_stage2, dim3(b.blocks2), dim3(256), 0, st, b);
+    AX_LAUNCH_CHECK();
+    return ALEXNET_OK;
+  }
+  KernelScope ks("sgd_update", 0, (double)u->n * 20.0, st);
+  const unsigned blocks = std::min<unsigned>(grid_for((u->n + 3) / 4, 256), kUpdateMaxBlocks);
+  hipLaunchKernelGGL(sgd_colsum_batch_stage2, dim3(b.blocks2 + blocks), dim3(256), 0, st, b, *u);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
@@ -1634,10 +1605,6 @@ int launch_average(float* a, float* b, size_t n, hipStream_t st) {
 
 // Gradient exchange: g = 0.5 (ga + gb), then each replica's own  v <- mu v - lr (g + wd w);  w <- w + v.
 // Replicas that hold the same w and v end up bit-identical (same arithmetic on the same values).
-__device__ __forceinline__ void sgd_one(float& w, float& v, float g, float d, float lr, float mu) {
-  v = mu * v - lr * (g + d * w);
-  w += v;
-}
 __global__ void avg_grad_update_kernel(float* __restrict__ wa, float* __restrict__ va, const float* __restrict__ ga,
                                        float* __restrict__ wb, float* __restrict__ vb, const float* __restrict__ gb,
                                        size_t n, size_t n_decay, float lr, float mu, float wd) {

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 
+#include "grad_sums.h"
 #include "kernels.h"
 
 namespace ax {
@@ -60,7 +61,12 @@ __global__ void __launch_bounds__(256) wino_dw_kernel(int groups, int Na, int Nb
   if (idx < total) wino_dw_thread(groups, Na, Nb, k, nsub, dU, dw, idx);
 }
 // the same for several stages in one launch (see WgradTail): the jobs' grids laid end to end
-__global__ void __launch_bounds__(256) wino_dw_batch_kernel(WgradTail t) {
+// Behind them the second half of the bias gradients, with their update (u.w null: without).
+__global__ void __launch_bounds__(256) wino_dw_colsum_batch_stage2(ColsumBatch b, WgradTail t, SgdArgs u) {
+  if ((int)blockIdx.x >= t.blocks_t) {
+    colsum_batch_block2(b, blockIdx.x - t.blocks_t, u);
+    return;
+  }
   int ji = 0;
 #pragma unroll
   for (int k = 1; k < kMaxWgradJobs; ++k)
@@ -218,7 +224,7 @@ int launch_wino_bwd_weight(const ConvGeom& c, const float* V, const float* dy, f
     }
     int ns = 1;
     AX_TRY(launch_conv_bwd_weight(p, V, yt, dU, nullptr, ws, st, &ns));
-    WgradJob j;
+    WgradJob j{};
     j.slices = ws; j.dU = dU; j.dwf = dwf;
     j.slab = (long)p.kf() * p.og(); j.total = total;
     j.nsplit = ns; j.groups36 = p.groups; j.groups = c.groups; j.Na = c.cg(); j.Nb = c.og(); j.k = c.k;
@@ -235,19 +241,18 @@ int launch_wino_bwd_weight(const ConvGeom& c, const float* V, const float* dy, f
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
-int launch_wino_dw_batch(const WgradTail& t, hipStream_t st) {
-  if (t.blocks_t == 0) return ALEXNET_OK;
+int launch_grad_tail(const WgradTail& t, const ColsumBatch& b, const LossJob& loss, const SgdArgs* u, hipStream_t st) {
+  AX_TRY(launch_grad_sums(t, b, loss, st));
+  if (t.blocks_t == 0) return launch_bias_sums(b, u, st);
   double bytes = 0;
   for (int i = 0; i < t.n; ++i)
     bytes += ((double)t.job[i].slab * t.job[i].groups36 + (double)t.job[i].groups * t.job[i].k * t.job[i].k * t.job[i].Na * t.job[i].Nb) * 4.0;
-  KernelScope ks("wino_dw", 0, bytes, st);
-  hipLaunchKernelGGL(wino_dw_batch_kernel, dim3(t.blocks_t), dim3(256), 0, st, t);
-  AX_LAUNCH_CHECK();
-  return ALEXNET_OK;
-}
-int launch_wgrad_tail(const WgradTail& t, hipStream_t st) {
-  AX_TRY(launch_reduce_slabs_batch(t, st));
-  return launch_wino_dw_batch(t, st);
+  {
+    KernelScope ks("wino_dw", 0, bytes, st);
+    hipLaunchKernelGGL(wino_dw_colsum_batch_stage2, dim3(t.blocks_t + b.blocks2), dim3(256), 0, st, b, t, u ? *u : SgdArgs{});
+    AX_LAUNCH_CHECK();
+  }
+  return u ? launch_sgd_update(u->w, u->v, u->g, u->n, u->n, u->lr, u->mu, u->wd, st) : ALEXNET_OK;
 }
 
 }  // namespace ax
