@@ -620,6 +620,7 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
   size_t bias_ws_used = 0;
   // Likewise the end of every transformed stage's weight gradient (slices added up, products back to taps).
   WgradTail wgrad_tail;
+  bool late[kFc] = {};  // dense layers whose weight gradient is made beside the convolutions
   // dense layers, last to first
   for (int j = kFc - 1; j >= 0; --j) {
     Dense& f = n->fc[j];
@@ -639,7 +640,9 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       AX_TRY(launch_fc_bwd(c.batch, f.in, f.out, x, f.dz, w, gate, dx, dw, st, dx16));
       continue;
     }
-    {
+    // a gradient whose product also updates its weights goes to the side stream with the update
+    late[j] = early_update && fc_bwd_weight_updates(c.batch, f.in, f.out, x, f.dz, x16, f.dz16);
+    if (!late[j]) {
       ProfContext pc(f.lab[2]);
       AX_TRY(launch_fc_bwd_weight(c.batch, f.in, f.out, x, f.dz, dw, st, x16, f.dz16));
     }
@@ -696,7 +699,17 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     auto fork_update = [&]() -> int {
       AX_HIP(hipEventRecord(n->ev_fc_done, st));
       AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_fc_done, 0));
-      AX_TRY(update_range(n, n->fc[0].w_off, n->n_weights, n->upd_stream));
+      for (int j = 0; j < kFc; ++j) {
+        Dense& f = n->fc[j];
+        if (!late[j]) {
+          AX_TRY(update_range(n, f.w_off, f.w_off + (size_t)f.in * f.out, n->upd_stream));
+          continue;
+        }
+        ProfContext pc(f.lab[2]);
+        const SgdArgs u{n->params + f.w_off, n->mom + f.w_off, nullptr, 0, c.lr, c.momentum, c.weight_decay};
+        AX_TRY(launch_fc_bwd_weight(c.batch, f.in, f.out, j == 0 ? n->st[kStages - 1].out() : n->fc[j - 1].act, f.dz,
+                                    n->grads + f.w_off, n->upd_stream, j == 0 ? n->flat16 : n->fc[j - 1].act16, f.dz16, &u));
+      }
       AX_HIP(hipEventRecord(n->ev_upd_done, n->upd_stream));
       return ALEXNET_OK;
     };

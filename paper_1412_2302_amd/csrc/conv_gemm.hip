@@ -1289,17 +1289,29 @@ int launch_fc_bwd(int B, int in, int out, const float* x, const float* dy, const
   return launch_wave_fc_bwd(B, in, out, x, dy, w, gate, dx, dx16, dw, bf, st);
 }
 
+static bool fc_stored_ok(bool vec, int in, int out, const uint16_t* x16, const uint16_t* dy16) {
+  return g_bf16 && vec && x16 && dy16 && fc_bf16_stored_ok(in, out) && aligned16(x16) && aligned16(dy16);
+}
+bool fc_bwd_weight_updates(int B, int in, int out, const float* x, const float* dy, const uint16_t* x16, const uint16_t* dy16) {
+  const bool vec = vec_ok(dy, out) && vec_ok(x, in);
+  return g_bf16 ? fc_stored_ok(vec, in, out, x16, dy16) : fc_split_ok(vec, B);
+}
 int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy, float* dw, hipStream_t st,
-                         const uint16_t* x16, const uint16_t* dy16) {
+                         const uint16_t* x16, const uint16_t* dy16, const SgdArgs* u) {
   DenseParams a{dy, out, 0, out, (uint32_t)((size_t)B * out * 4)};
   DenseParams b{x, in, 0, in, (uint32_t)((size_t)B * in * 4)};
   EpiSlab ep{dw, (long)out * in, in, nullptr};
   const bool vec = vec_ok(dy, out) && vec_ok(x, in);
-  if (g_bf16 && vec && x16 && dy16 && fc_bf16_stored_ok(in, out) && aligned16(x16) && aligned16(dy16))
-    return launch_direct_dense_bwd_weight(B, in, out, x16, dy16, dw, st);
+  if (u && !fc_bwd_weight_updates(B, in, out, x, dy, x16, dy16)) {
+    set_error("fc weight gradient: no kernel updates these weights");
+    return ALEXNET_EINVAL;
+  }
+  if (fc_stored_ok(vec, in, out, x16, dy16)) return launch_direct_dense_bwd_weight(B, in, out, x16, dy16, dw, st, u);
   if (g_bf16 && vec)
     return launch_tile_bf<B128, BfDenseR, BfDenseR, EpiSlab>(a, b, ep, out, in, B, round_up(B, kBKbf), 1, 1, st);
   const GemmPlan p = fc_split_ok(vec, B) ? plan_split(out, in, B, 1, 0, 1) : GemmPlan{128, 128, 1, round_up(B, kBK)};
+  if (u)
+    return by_tile_split<SplitRowInner, SplitRowInner>(p, a, b, EpiSgd{dw, u->w, u->v, in, u->lr, u->mu, u->wd}, out, in, B, 1, st);
   return launch_dense<SplitRowInner, SplitRowInner, DenseRowInner, DenseRowInner>(vec, p, a, b, ep, out, in, B, st);
 }
 

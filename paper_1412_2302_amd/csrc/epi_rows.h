@@ -135,5 +135,36 @@ __device__ __forceinline__ void store_rows(const EpiSlab& e, const v16f (&acc)[T
       for (int j = 0; j < TN; ++j) buf_st1(out, at[j] + (uint32_t)(i * 32 + block_row(r)) * ld, acc[i][j][r]);
 }
 
+template <int TM, int TN>
+__device__ __forceinline__ void store_rows(const EpiSgd& e, const v16f (&acc)[TM][TN], int m, int n, int M, int N, int lane) {
+  const uint32_t ld = (uint32_t)e.ldc * 4u;
+  const BufView g = make_view(e.g, (uint32_t)M * ld), w = make_view(e.w, (uint32_t)M * ld), v = make_view(e.v, (uint32_t)M * ld);
+  uint32_t at[TN];
+  column_offsets<TN>(at, ld, 0, m, n, N, lane);
+  float wb[2][16], vb[2][16];  // of the block at hand and of the next
+  auto ask = [&](int b) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const uint32_t o = at[b % TN] + (uint32_t)(b / TN * 32 + block_row(r)) * ld;
+      wb[b & 1][r] = buf_ld1(w, o);
+      vb[b & 1][r] = buf_ld1(v, o);
+    }
+  };
+  ask(0);
+#pragma unroll
+  for (int b = 0; b < TM * TN; ++b) {
+    if (b + 1 < TM * TN) ask(b + 1);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const uint32_t o = at[b % TN] + (uint32_t)(b / TN * 32 + block_row(r)) * ld;
+      const float x = acc[b / TN][b % TN][r];
+      buf_st1(g, o, x);
+      sgd_one(wb[b & 1][r], vb[b & 1][r], x, e.wd, e.lr, e.mu);
+      buf_st1(v, o, vb[b & 1][r]);
+      buf_st1(w, o, wb[b & 1][r]);
+    }
+  }
+}
+
 }  // namespace ax
 #endif  // AX_HOST_EMU

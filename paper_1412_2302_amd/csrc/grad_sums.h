@@ -1,16 +1,9 @@
-// What several kernels at the end of a backward pass share: the second half of the column sums that make the bias gradients, and
-// the update of one element.
+// What two kernels at the end of a backward pass share: the second half of the column sums that make the bias gradients.
 #pragma once
 
 #include "kernels.h"
 
 namespace ax {
-
-// v <- mu v - lr (g + d w);  w <- w + v
-__device__ __forceinline__ void sgd_one(float& w, float& v, float g, float d, float lr, float mu) {
-  v = mu * v - lr * (g + d * w);
-  w += v;
-}
 
 __device__ __forceinline__ void colsum_stage2_block(const float* __restrict__ part, int nparts, int cols,
                                                     float* __restrict__ out, int stripe, const SgdArgs& u) {

@@ -130,8 +130,12 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
 int launch_fc_bwd_data(int B, int in, int out, const float* dy, const float* w, const float* gate, float* dx,
                        float* ws, hipStream_t st, const uint16_t* dy16 = nullptr, const uint16_t* w16 = nullptr,
                        uint16_t* dx16 = nullptr);
+// u (may be null): also update the weights (u->w, u->v as dw; n and g are not looked at) from the product's registers, where
+// fc_bwd_weight_updates()
+struct SgdArgs;
+bool fc_bwd_weight_updates(int B, int in, int out, const float* x, const float* dy, const uint16_t* x16, const uint16_t* dy16);
 int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy, float* dw, hipStream_t st,
-                         const uint16_t* x16 = nullptr, const uint16_t* dy16 = nullptr);
+                         const uint16_t* x16 = nullptr, const uint16_t* dy16 = nullptr, const SgdArgs* u = nullptr);
 
 // both gradients in one launch, where wave_fc_bwd_ok(): dw, and dx as launch_fc_bwd_data gives it
 int launch_fc_bwd(int B, int in, int out, const float* x, const float* dy, const float* w, const float* gate, float* dx,
@@ -165,7 +169,8 @@ int direct_bwd_weight_slices(const ConvGeom& c);
 int launch_direct_bwd_weight(const ConvGeom& c, const uint16_t* x16, const uint16_t* dy16, float* out, hipStream_t st);
 // dense layers over operands stored as bf16: dx as dense_plan()'s slabs, dw whole
 int launch_direct_dense_bwd_data(int B, int in, int out, const uint16_t* dy16, const uint16_t* w16, float* slabs, hipStream_t st);
-int launch_direct_dense_bwd_weight(int B, int in, int out, const uint16_t* x16, const uint16_t* dy16, float* dw, hipStream_t st);
+int launch_direct_dense_bwd_weight(int B, int in, int out, const uint16_t* x16, const uint16_t* dy16, float* dw, hipStream_t st,
+                                   const SgdArgs* u = nullptr);
 bool wave_conv_bwd_weight_ok(const ConvGeom& c, bool bf);
 bool wave_conv_bwd_ok(const ConvGeom& c, bool bf, bool beside);  // both gradients in one launch; beside: a large update
 bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy);

@@ -285,14 +285,20 @@ int launch_direct_dense_bwd_data(int B, int in, int out, const uint16_t* dy16, c
 // The weight gradient of a 1 x 1 convolution over pictures of one pixel, with the operands' parts exchanged.  Its reduction is
 // the batch, so that it waits for its stores; 128-row tiles from 65 pictures up (batch 64, 9216 x 4096: 28 us in those, 26 in
 // these; 256: 50 and 59).  gemm_bf16.h | here: batch 256 49, 27, 13 | 50, 20, 11 us, batch 64 33, 18, 10 | 26, 13, 7.
-int launch_direct_dense_bwd_weight(int B, int in, int out, const uint16_t* x16, const uint16_t* dy16, float* dw, hipStream_t st) {
+int launch_direct_dense_bwd_weight(int B, int in, int out, const uint16_t* x16, const uint16_t* dy16, float* dw, hipStream_t st,
+                                   const SgdArgs* u) {
   const GemmDims d{out, in, B, 1};
   const ConvGeom c{B, 1, 1, out, in, 1, 1, 0, 1, 1, 1};
   const Im2colParams a = im2col16(bwdw_A(c, nullptr), dy16);
   const DenseParams b = dense16(bwdw_B(c, nullptr), x16);
-  const EpiSlab e{dw, (long)out * in, in, nullptr};
-  const double bytes = 4.0 * ((double)B * (in + out) + (double)in * out);
+  const double bytes = 4.0 * ((double)B * (in + out) + (u ? 5.0 : 1.0) * (double)in * out);
   const DirectTPlan p{0, 1, ceil_div(B, kBKd)};
+  if (u) {
+    const EpiSgd e{dw, u->w, u->v, in, u->lr, u->mu, u->wd};
+    if (B > 64) return launch_direct_t_tile<128, 128, 2, 2, 2>(p, a, b, e, d, bytes, st);
+    return launch_direct_t_tile<64, 128, 2, 2, 3>(p, a, b, e, d, bytes, st);
+  }
+  const EpiSlab e{dw, (long)out * in, in, nullptr};
   if (B > 64) return launch_direct_t_tile<128, 128, 2, 2, 2>(p, a, b, e, d, bytes, st);
   return launch_direct_t_tile<64, 128, 2, 2, 3>(p, a, b, e, d, bytes, st);
 }
