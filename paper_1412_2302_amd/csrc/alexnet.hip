@@ -158,7 +158,6 @@ struct alexnet {
   int32_t* err_flag;
   size_t gemm_ws_floats, colsum_ws_floats_;
   int flat;  // flatten size feeding fc6
-  int upd_fork_stage;   // stage of the backward pass beside which the dense-layer update starts on the side stream
   bool beside;          // the dense layers are no small products: their update is worth a stream of its own
   bool fork_train;      // training steps make the weights' forms and update the dense layers on the side stream
   bool fork_inference;  // inference passes make the weights' forms on the side stream
@@ -186,9 +185,6 @@ constexpr double kWinoMinFlops = 2e9;
 // its first layer needs one of them, and with little to hide them under the two streams' meeting costs more (batch 16 341
 // against 320 us, the small nets 147 and 166 against 109 and 134; batch 100, 133 GFLOP, 694 against 713).
 constexpr double kForkFlops = 100e9;
-// The same from which an fp32 handle's dense-layer update starts one stage later (see run_backward): batch 23 of the full
-// net, where the two places cost the same.
-constexpr double kLateUpdateFlops = 30e9;
 static bool winograd_in_pass(const ConvGeom& g) { return 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k >= kWinoMinFlops; }
 
 static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector<WorkspacePiece>* pieces = nullptr) {
@@ -359,7 +355,6 @@ static int plan(alexnet* n, const alexnet_config_t* cfg, char* base, std::vector
     conv_flops += 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k;
   }
   const bool fp32 = c.precision == ALEXNET_PRECISION_FP32;
-  n->upd_fork_stage = fp32 && conv_flops >= kLateUpdateFlops ? kStages - 2 : kStages - 1;
   n->fork_inference = fp32 || conv_flops >= kForkFlops;
   n->fc16 = bf && n->beside && n->fc[0].w_off % 4 == 0;
   for (int j = 0; j < kFc; ++j) n->fc16 = n->fc16 && fc_bf16_stored_ok(n->fc[j].in, n->fc[j].out);
@@ -685,17 +680,11 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
                             c.lrn_alpha, c.lrn_beta, 1, st));
       dy16_ready = false;
     }
-    // Fork of the dense-layer update, behind this stage's pooling adjoint: that kernel is bound by bandwidth like the
-    // update and would be starved by it.  Early (the update is as long as the rest of a small batch's backward pass)
-    // and held to one workgroup per CU, it costs the products beside it about what it moves (at four per CU batch 1 and
-    // 16 take 744 and 1236 us instead of 664 and 1149, bf16 batch 4 and 16 888 and 1054 instead of 804 and 985).  Step
-    // with the fork in front of conv5 | conv4 | conv3's weight gradient, us, the best of five runs two or three times
-    // over, all within 0.3 %:
-    //   fp32  batch 1 635 | 665   12 1088 | 1102   16 1122 | 1130   20 1178 | 1180   24 1275 | 1274 | 1311
-    //         37 1523 | 1510 | 1528   64 2056 | 2047 | 2058   128 3378 | 3359 | 3346   256 6153 | 6121 | 6087
-    //   bf16  batch 32 1056 | 1054   64 1308 | 1315   128 1880 | 1849   200 2635 | 2614   256 2973 | 3345
-    // So fp32 takes conv4 from batch 23 up (kLateUpdateFlops).  bf16 stays with conv5: in front of conv4 a product that fills
-    // all but a few CUs may come first, whose room draws the update's workgroups there, and it takes 800 us instead of 310.
+    // Fork of the dense layers' update, behind this stage's pooling adjoint: that kernel is bound by bandwidth like the update
+    // and would be starved by it.  The place makes no difference (in front of conv5's to conv2's weight gradient: training on 37,
+    // 128 and 256 pictures 1412 to 1422, 3061 to 3121 and 5608 to 5655 us in two runs of each, bf16 64 and 256 1131 to 1136 and
+    // 2502 to 2510); below eight rows, where the update is a launch of its own, held to one workgroup per CU, it is the shorter
+    // way (batch 1 635 us here, 665 in front of conv4).
     auto fork_update = [&]() -> int {
       AX_HIP(hipEventRecord(n->ev_fc_done, st));
       AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_fc_done, 0));
@@ -713,7 +702,7 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       AX_HIP(hipEventRecord(n->ev_upd_done, n->upd_stream));
       return ALEXNET_OK;
     };
-    if (early_update && i == n->upd_fork_stage) AX_TRY(fork_update());
+    if (early_update && i == kStages - 1) AX_TRY(fork_update());
     const float* x = i == 0 ? in : n->st[i - 1].out();
     if (s.wave) {  // both gradients at once, from the forward weights
       const bool bf = conv_bwd_weight_bf16(s.g, x, s.dact);

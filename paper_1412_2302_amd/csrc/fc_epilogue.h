@@ -27,4 +27,15 @@ struct EpiFcAct {
   }
 };
 
+// as a small product's epilogue (gemm_wave.h)
+__device__ __forceinline__ float wave_ask(const EpiFcAct& e, int, int n) { return e.act.bias ? e.act.bias[n] : -0.f; }
+__device__ __forceinline__ void wave_put(const EpiFcAct& e, int m, int n, float v, float bias) {
+  const size_t i = (size_t)m * e.ldc + n;
+  v += bias;
+  if (e.act.relu) v = v > 0.f ? v : 0.f;
+  if (e.act.dropout && !dropout_keep(e.act.key, e.act.tag, i, e.act.thresh24)) v = 0.f;
+  e.y[i] = v * e.act.scale;
+  if (e.y16) store_bf16(e.y16 + i, v * e.act.scale);
+}
+
 }  // namespace ax

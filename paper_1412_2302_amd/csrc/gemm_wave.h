@@ -305,6 +305,30 @@ AX_HD void wave_load_exact(const L& l, float4* r, int k, long) {
 
 // ================================= kernel ====================================
 #ifndef AX_HOST_EMU
+// What the epilogue reads for an element is asked for in front of the products and handed to it behind the sums: at the end it
+// was one more trip to the cache or to memory in a chain of two or three.
+template <class Epi>
+__device__ __forceinline__ float wave_ask(const Epi&, int /*m*/, int /*n*/) { return 0.f; }
+template <class Epi>
+__device__ __forceinline__ void wave_put(const Epi& e, int m, int n, float v, float /*asked*/) { e.apply(m, n, v); }
+__device__ __forceinline__ float wave_ask(const EpiBiasAct& e, int, int n) { return e.bias ? e.bias[e.col_off + n] : -0.f; }
+__device__ __forceinline__ void wave_put(const EpiBiasAct& e, int m, int n, float v, float bias) {
+  const long o = (long)m * e.ldc + e.col_off + n;
+  v += bias;
+  if (e.relu) v = v > 0.f ? v : 0.f;
+  e.y[o] = v;
+  if (e.y16) store_bf16(e.y16 + o, v);
+}
+__device__ __forceinline__ float wave_ask(const EpiGate& e, int m, int n) {
+  return e.gate ? e.gate[(long)m * e.ldc + e.col_off + n] : 1.f;
+}
+__device__ __forceinline__ void wave_put(const EpiGate& e, int m, int n, float v, float gate) {
+  const long o = (long)m * e.ldc + e.col_off + n;
+  v = gate > 0.f ? v : 0.f;
+  e.dx[o] = v;
+  if (e.dx16) store_bf16(e.dx16 + o, v);
+}
+
 template <int W, int WORDS>
 struct WaveLds {
   float part[W][kWaveTile * kWaveTile];
@@ -355,25 +379,37 @@ __device__ __forceinline__ void wave_tile(const J& j, uint32_t block, Lds& lds) 
   const int kbeg = split * j.kchunk, kend = min(j.K, kbeg + j.kchunk), len = kend - kbeg;
   uint32_t* const ta = lds.table;
   uint32_t* const tb = lds.table + J::AL::kWords;
+  const int kh = 8 * (lane >> 5), kfirst = 16 * wave;
+  constexpr int kStep = 16 * W;
+  // an operand that needs no table is on its way while the other's is made
+  const typename J::BL bl(j.b, (int)g, n0 + (lane & 31), kbeg, kend, tb);
+  float4 rb[2];
+  if (J::BL::kWords == 0 && kfirst < len) bl.load(rb, kfirst + kh);
+  typename J::Epi ep = j.ep;
+  ep.set_group((int)g, (int)z);
+  constexpr int kMine = kWaveTile * kWaveTile / (64 * W);  // of the tile's elements, tid + i * 64 * W
+  float asked[kMine];
+#pragma unroll
+  for (int i = 0; i < kMine; ++i) {
+    const int e = tid + i * 64 * W, m = m0 + e / kWaveTile, n = n0 + e % kWaveTile;
+    asked[i] = m < j.M && n < j.N ? wave_ask(ep, m, n) : 0.f;
+  }
   J::AL::build(j.a, ta, kbeg, kend, tid, 64 * W);
   J::BL::build(j.b, tb, kbeg, kend, tid, 64 * W);
   const typename J::AL al(j.a, (int)g, m0 + (lane & 31), kbeg, kend, ta);
-  const typename J::BL bl(j.b, (int)g, n0 + (lane & 31), kbeg, kend, tb);
-  const int kh = 8 * (lane >> 5), kfirst = 16 * wave;
-  constexpr int kStep = 16 * W;
   if (kJobWords<J> > 0) __syncthreads();
 
   v16f hi, lo;
 #pragma unroll
   for (int r = 0; r < 16; ++r) hi[r] = lo[r] = 0.f;
   if (kfirst < len) {  // uniform
-    float4 ra[2], rb[2];
+    float4 ra[2];
     auto load_a = [&](int k) {  // rounded products are not looked at afterwards
       if (J::BF) wave_load_exact(al, ra, k, 0);
       else al.load(ra, k);
     };
     load_a(kfirst + kh);
-    bl.load(rb, kfirst + kh);
+    if (J::BL::kWords > 0) bl.load(rb, kfirst + kh);
     for (int k = kfirst; k < len; k += kStep) {
       // the registers are free once their values are split: the next step's loads run under this step's products
       const bool more = k + kStep < len;
@@ -433,15 +469,13 @@ __device__ __forceinline__ void wave_tile(const J& j, uint32_t block, Lds& lds) 
       __syncthreads();
     }
   }
-  typename J::Epi ep = j.ep;
-  ep.set_group((int)g, (int)z);
   const int parts = min(W, (len + 15) / 16);  // waves that had a step
 #pragma unroll
-  for (int i = 0; i < kWaveTile * kWaveTile / (64 * W); ++i) {
+  for (int i = 0; i < kMine; ++i) {
     const int e = tid + i * 64 * W, m = m0 + e / kWaveTile, n = n0 + e % kWaveTile;
     float s = 0.f;
     for (int w = 0; w < parts; ++w) s += lds.part[w][e];
-    if (m < j.M && n < j.N) ep.apply(m, n, s);
+    if (m < j.M && n < j.N) wave_put(ep, m, n, s, asked[i]);
   }
 }
 
