@@ -431,14 +431,23 @@ static const TileOption kTileOptionsSplit[] = {
 // one k-tile ahead only, and a workgroup that has its compute unit to itself waits for memory about half the time (a
 // weight gradient of 192 x 128 x 2048 x 72: 105 us in 216 workgroups, see fill), so slices are worth having until two
 // or three workgroups share every unit.
+// rows (may be null): each of the 36 positions has its own number of rows.
 static GemmPlan plan_split(int M, int N, int K, int groups, double out_bytes, int max_s, double* t_out = nullptr,
-                           bool allow64 = false) {
+                           bool allow64 = false, const TileRows* rows = nullptr) {
   GemmPlan best{128, 128, 1, ceil_div(K, kBKs) * kBKs};
   double best_t = 1e30;
   const int ktiles = ceil_div(K, kBKs);
   for (const TileOption& to : kTileOptionsSplit) {
     if (to.bm == 64 && !allow64) continue;
-    const long tiles = (long)ceil_div(M, to.bm) * ceil_div(N, to.bn) * groups;
+    long row_tiles = (long)ceil_div(M, to.bm) * groups;
+    if (rows) {
+      row_tiles = 0;
+      for (int p = 0; p < 36; ++p) {
+        const RowRange r = wino_rows(p, rows->short_y, rows->whole, rows->short_x, rows->tiles);
+        row_tiles += (long)ceil_div(r.hi - r.lo, to.bm) * (groups / 36);
+      }
+    }
+    const long tiles = row_tiles * ceil_div(N, to.bn);
     const double t_tile = 2.0 * to.bm * to.bn * (double)ktiles * kBKs / (0.614e12 * to.eff);
     for (int s = 1; s <= max_s && s <= ktiles; ++s) {
       const int per = ceil_div(ktiles, s);
@@ -461,7 +470,8 @@ static GemmPlan plan_split(int M, int N, int K, int groups, double out_bytes, in
 }
 template <class T, class AL, class BL, class Epi>
 static int launch_tile_split(const typename AL::Params& ap, const typename BL::Params& bp, const Epi& ep, int M, int N,
-                             int K, int kchunk, int nsplit, int groups, hipStream_t st) {
+                             int K, int kchunk, int nsplit, int groups, hipStream_t st, const TileRows* rows = nullptr,
+                             int of = 0) {
   if (M <= 0 || N <= 0) return ALEXNET_OK;
   const int gx = ceil_div(M, T::BM), gy = ceil_div(N, T::BN), gz = groups * nsplit;
   const long total = (long)gx * gy * gz;
@@ -469,7 +479,12 @@ static int launch_tile_split(const typename AL::Params& ap, const typename BL::P
     set_error("GEMM grid too large (%d,%d,%d)", gx, gy, gz);
     return ALEXNET_ESHAPE;
   }
-  const SplitGrid grid{make_fastdiv((uint32_t)gx), make_fastdiv((uint32_t)gy), make_fastdiv((uint32_t)nsplit)};
+  SplitGrid grid{make_fastdiv((uint32_t)gx), make_fastdiv((uint32_t)gy), make_fastdiv((uint32_t)nsplit), 0, {}, 0, 0, 0, 0};
+  if (rows) {
+    grid.of = of;
+    grid.positions = make_fastdiv((uint32_t)(groups / 36));
+    grid.short_y = rows->short_y; grid.whole = rows->whole; grid.short_x = rows->short_x; grid.tiles = rows->tiles;
+  }
   KernelScope ks("gemm", g_algo_flops > 0 ? g_algo_flops : 2.0 * M * N * (double)K * groups,
                  gemm_bytes(M, N, K, groups), st);
   hipLaunchKernelGGL((gemm_split_kernel<T, AL, BL, Epi>), dim3((unsigned)total), dim3(kThreads), 0, st, ap, bp, ep, M,
@@ -480,9 +495,9 @@ static int launch_tile_split(const typename AL::Params& ap, const typename BL::P
 // ALT / BLT: loaders by number of rows
 template <template <int> class ALT, template <int> class BLT, class Epi>
 static int by_tile_split(const GemmPlan& p, const DenseParams& a, const DenseParams& b, const Epi& e, int M, int N, int K,
-                         int groups, hipStream_t st) {
+                         int groups, hipStream_t st, const TileRows* rows = nullptr, int of = 0) {
 #define AX_SPLIT(T) \
-  return launch_tile_split<T, ALT<T::BM>, BLT<T::BN>, Epi>(a, b, e, M, N, K, p.kchunk, p.ns, groups, st)
+  return launch_tile_split<T, ALT<T::BM>, BLT<T::BN>, Epi>(a, b, e, M, N, K, p.kchunk, p.ns, groups, st, rows, of)
   if (p.bm == 64) AX_SPLIT(S64m);
   if (p.bn == 96) AX_SPLIT(S96);
   if (p.bn == 64) AX_SPLIT(S64);
@@ -520,9 +535,9 @@ static inline bool split_fwd_ok(const ConvGeom& c) {
 static inline bool split_bwdw_ok(const ConvGeom& c) {
   return pointwise(c) && c.cg() % 4 == 0 && c.og() % 4 == 0 && c.P() >= kSplitMinK;
 }
-static GemmPlan split_fwd_plan(const ConvGeom& c, double* t_out = nullptr) {
+static GemmPlan split_fwd_plan(const ConvGeom& c, double* t_out = nullptr, const TileRows* rows = nullptr) {
   const GemmDims d = fwd_dims(c);
-  return plan_split(d.M, d.N, d.K, d.groups, (double)c.out_elems() * 4, 8, t_out);
+  return plan_split(d.M, d.N, d.K, d.groups, (double)c.out_elems() * 4, 8, t_out, false, rows);
 }
 // weight gradient: the operands may change places, whichever way the tiles cover the result with less padding
 static GemmPlan split_bwdw_plan(const ConvGeom& c, bool* swapped, double* t_out = nullptr) {
@@ -533,6 +548,10 @@ static GemmPlan split_bwdw_plan(const ConvGeom& c, bool* swapped, double* t_out 
   *swapped = t[1] < 0.98 * t[0];
   if (t_out) *t_out = t[*swapped];
   return *swapped ? q : p;
+}
+
+bool conv_products_split(const ConvGeom& c) {
+  return split_fwd_ok(c) && split_bwdw_ok(c) && !wave_conv_fwd_ok(c, false) && !wave_conv_bwd_weight_ok(c, false);
 }
 
 // ------------------------------------------------------------- convolution ---
@@ -598,8 +617,9 @@ double tile_seconds_bwd_weight(const ConvGeom& c, bool bf) {
   return t;
 }
 // scratch sizes cover every variant (generic / run mode, fp32 / bf16) of the op
-size_t conv_fwd_ws_floats(const ConvGeom& c) {
+size_t conv_fwd_ws_floats(const ConvGeom& c, const TileRows* rows) {
   int ns = 0;
+  if (rows) ns = split_fwd_plan(c, nullptr, rows).ns;
   for (int run = 0; run < 2; ++run)
     for (int bf = 0; bf < 2; ++bf) ns = std::max(ns, fwd_plan(c, run && run_mode(c), bf).ns);
   ns = std::max(ns, fwd_plan(c, false, false, true).ns);
@@ -675,7 +695,7 @@ bool conv_bf16_stored_ok(const ConvGeom& c) { return conv16_ok(c) && c.Cin % 8 =
 
 int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const float* wrun, const float* bias,
                     int relu, float* y, float* ws, hipStream_t st, const uint16_t* x16, const uint16_t* wf16,
-                    uint16_t* y16) {
+                    uint16_t* y16, const TileRows* rows) {
   // y16: also leave a bf16 copy of y there -- written by the epilogue of a single-pass product, else converted
   struct Copy16 {
     const float* y; uint16_t* y16; size_t n; hipStream_t st; bool pending;
@@ -685,7 +705,7 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
     return launch_wave_conv_fwd(c, x, wf, bias, relu, y, y16, ws,
                                 g_bf16 && (run_mode(c) ? c.Cout % 4 == 0 : fwd_A_vec(c, x) && fwd_B_vec(c, wf)), st);
   const bool run = wrun && run_mode(c) && c.Cout % 4 == 0;
-  AlgoFlops af(conv_flops(c), conv_bytes(c));
+  AlgoFlops af(conv_flops(c) * (rows ? rows->share : 1.0), conv_bytes(c) * (rows ? rows->share : 1.0));
   GemmDims d = fwd_dims(c);
   if (g_bf16 && x16 && wf16 && !run && conv_bf16_stored_ok(c) && aligned16(x16) && aligned16(wf16)) {
     const Im2colParams a = im2col16(fwd_A(c, nullptr), x16);
@@ -716,16 +736,20 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
     return finish(launch_slab_finish(ws, p.ns, d.groups, d.M, d.N, bias, relu, nullptr, y, st));
   }
   if (!g_bf16 && split_fwd_ok(c) && fwd_A_vec(c, x) && fwd_B_vec(c, wf)) {
-    const GemmPlan p = split_fwd_plan(c);
+    const GemmPlan p = split_fwd_plan(c, nullptr, rows);
     const DenseParams a = pointwise_A(c, x), b = fwd_B(c, wf);
     copy.pending = y16 != nullptr;
     if (p.ns == 1) {
       EpiBiasAct ep{y, c.Cout, bias, relu, c.og(), 0, 0, nullptr};
-      return finish(by_tile_split<SplitKInner, SplitRowInner>(p, a, b, ep, d.M, d.N, d.K, d.groups, st));
+      return finish(by_tile_split<SplitKInner, SplitRowInner>(p, a, b, ep, d.M, d.N, d.K, d.groups, st, rows, 1));
     }
     EpiSlab ep{ws, (long)d.M * d.N, d.N, nullptr};
-    AX_TRY((by_tile_split<SplitKInner, SplitRowInner>(p, a, b, ep, d.M, d.N, d.K, d.groups, st)));
+    AX_TRY((by_tile_split<SplitKInner, SplitRowInner>(p, a, b, ep, d.M, d.N, d.K, d.groups, st, rows, 1)));
     return finish(launch_slab_finish(ws, p.ns, d.groups, d.M, d.N, bias, relu, nullptr, y, st));
+  }
+  if (rows) {
+    set_error("products of short tiles: no kernel for these operands");
+    return ALEXNET_EINVAL;
   }
   if (run) d.K = run_k(c);
   if (!g_bf16 && run && split_run_ok(c) && aligned16(wrun)) {
@@ -922,13 +946,13 @@ bool conv_bwd_weight_bf16(const ConvGeom& c, const float* x, const float* dy) {
 // defer_ns (generic layout only): the split-k slices are left in ws, [group][slice][slab], and their number is
 // returned there for the caller to add them up later (1: the result is in dwf already)
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
-                           hipStream_t st, int* defer_ns, bool small, WgradTail* tail) {
+                           hipStream_t st, int* defer_ns, bool small, WgradTail* tail, const TileRows* rows) {
   if (small && wave_conv_bwd_weight_ok(c, g_bf16)) {
     if (defer_ns) *defer_ns = 1;
     return launch_wave_conv_bwd_weight(c, x, dy, dwf, ws, conv_bwd_weight_bf16(c, x, dy), st);
   }
   const bool run = dwrun && run_mode(c) && bwdw_B_vec(c, dy);
-  AlgoFlops af(conv_flops(c), conv_bytes(c));
+  AlgoFlops af(conv_flops(c) * (rows ? rows->share : 1.0), conv_bytes(c) * (rows ? rows->share : 1.0));
   GemmDims d = bwdw_dims(c);
   if (run) d.M = run_k(c);
   const bool av = run || bwdw_A_vec(c, x), bv = bwdw_B_vec(c, dy);
@@ -941,13 +965,17 @@ int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, f
     float* out = p.ns > 1 ? ws : dwf;
     if (swapped) {
       EpiSlabSwapped ep{out, slab, d.N, nullptr};
-      AX_TRY((by_tile_split<SplitRowInner, SplitRowInner>(p, bwdw_B(c, dy), a, ep, d.N, d.M, d.K, d.groups, st)));
+      AX_TRY((by_tile_split<SplitRowInner, SplitRowInner>(p, bwdw_B(c, dy), a, ep, d.N, d.M, d.K, d.groups, st, rows, 2)));
     } else {
       EpiSlab ep{out, slab, d.N, nullptr};
-      AX_TRY((by_tile_split<SplitRowInner, SplitRowInner>(p, a, bwdw_B(c, dy), ep, d.M, d.N, d.K, d.groups, st)));
+      AX_TRY((by_tile_split<SplitRowInner, SplitRowInner>(p, a, bwdw_B(c, dy), ep, d.M, d.N, d.K, d.groups, st, rows, 2)));
     }
     if (defer_ns) *defer_ns = p.ns;
     return defer_ns || p.ns == 1 ? ALEXNET_OK : launch_reduce_slabs(ws, p.ns, slab, d.groups, dwf, st);
+  }
+  if (rows) {
+    set_error("products of short tiles: no kernel for these operands");
+    return ALEXNET_EINVAL;
   }
   const bool bf = g_bf16 && av && bv;
   const Im2colParams a = run ? run_A(c, x) : bwdw_A(c, x);

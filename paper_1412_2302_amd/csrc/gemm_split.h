@@ -50,6 +50,7 @@
 #pragma once
 
 #include "gemm_bf16.h"
+#include "wino_rows.h"
 
 namespace ax {
 
@@ -545,9 +546,18 @@ struct SplitMinBlocks {
 // The one-dimensional grid of gx * gy * (groups * nsplit) workgroups (see xcd_tile).  The divisors are constants of the
 // launch, so that a workgroup's place is worked out on the scalar unit and the buffer descriptors that depend on it
 // stay in scalar registers.
+// of: rows (1) or the reduction (2) of the product run over the rows that a group's position has in a transformed layer with short
+// tiles (wino_rows(), group = position * positions.d + group of channels); the sizes of the launch are those of all rows.  Tiles of
+// rows that a group does not have are nobody's, and slices share what there is.
 struct SplitGrid {
   FastDiv gx, gy, nsplit;
+  int of;
+  FastDiv positions;
+  int short_y, whole, short_x, tiles;
 };
+__device__ __forceinline__ void split_row_limit(DenseParams& a, int rows) { a.R = rows; }
+template <class P>
+__device__ __forceinline__ void split_row_limit(P&, int) {}
 template <class T, class AL, class BL, class Epi>
 __global__ void __launch_bounds__(kThreads, (SplitMinBlocks<T>::value))
 gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int N, int K, int kchunk,
@@ -561,9 +571,24 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
   const uint32_t tile = xcd * q8 + min(xcd, r8) + (L >> 3);  // as in xcd_tile
   const uint32_t rest = fdiv(tile, grid.gy), z = fdiv(rest, grid.gx), g = fdiv(z, grid.nsplit);
   const int split = (int)(z - g * grid.nsplit.d);
-  const int m0 = (int)(rest - z * grid.gx.d) * T::BM, n0 = (int)(tile - rest * grid.gy.d) * T::BN;
-  const int kbeg = split * kchunk;
-  const int kend = min(K, kbeg + kchunk);
+  int m0 = (int)(rest - z * grid.gx.d) * T::BM;
+  const int n0 = (int)(tile - rest * grid.gy.d) * T::BN;
+  int kbeg = split * kchunk;
+  int kend = min(K, kbeg + kchunk);
+  if (grid.of != 0) {  // uniform
+    const RowRange r = wino_rows((int)fdiv(g, grid.positions), grid.short_y, grid.whole, grid.short_x, grid.tiles);
+    if (grid.of == 1) {
+      m0 += r.lo;
+      M = r.hi;
+      if (m0 >= M) return;
+      split_row_limit(ap, M);
+    } else {
+      const uint32_t steps = (uint32_t)(r.hi - r.lo + T::BK - 1) / T::BK;
+      const int per = (int)fdiv(steps + grid.nsplit.d - 1, grid.nsplit) * T::BK;
+      kbeg = r.lo + split * per;
+      kend = min(r.hi, kbeg + per);
+    }
+  }
   const int nt = kend > kbeg ? (kend - kbeg + T::BK - 1) / T::BK : 0;
 
   AL al(ap, (int)g, tid, m0, kbeg);

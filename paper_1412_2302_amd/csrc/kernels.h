@@ -44,7 +44,8 @@ void wgrad_tail_add(WgradTail& t, const WgradJob& job);  // t.n < kMaxWgradJobs
 // 16 bytes at a time keep the fp32 kernels.
 void set_gemm_precision(int bf16);
 // `ws` is split-k scratch of at least the matching *_ws_floats() floats (may be null when that is 0)
-size_t conv_fwd_ws_floats(const ConvGeom& c);
+struct TileRows;
+size_t conv_fwd_ws_floats(const ConvGeom& c, const TileRows* rows = nullptr);
 size_t conv_bwd_data_ws_floats(const ConvGeom& c);
 size_t conv_bwd_weight_ws_floats(const ConvGeom& c);
 // Run mode (unpadded conv over 3-channel pictures, see gemm.h): `wrun` / `dwrun` are padded copies of the
@@ -58,9 +59,16 @@ int launch_conv_run_pack(const ConvGeom& c, const float* wf, float* wrun, hipStr
 // reads those instead of rounding fp32 on the fly.  y16 / dx16: where to leave a bf16 copy of the result for the
 // products that read it next (written by the epilogue, or converted after a split-k pass).
 bool conv_bf16_stored_ok(const ConvGeom& c);
+// Rows that the products of a transformed layer with short tiles run over (winograd.h); share: of the products of all rows
+struct TileRows {
+  int short_y, whole, short_x, tiles;
+  double share;
+};
+// a layer's products (1 x 1, 36 * groups groups) run over rows of their own where both directions are split products
+bool conv_products_split(const ConvGeom& c);
 int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const float* wrun, const float* bias,
                     int relu, float* y, float* ws, hipStream_t st, const uint16_t* x16 = nullptr,
-                    const uint16_t* wf16 = nullptr, uint16_t* y16 = nullptr);
+                    const uint16_t* wf16 = nullptr, uint16_t* y16 = nullptr, const TileRows* rows = nullptr);
 // The first layer with bf16 products over pictures stored as bf16, four channels per pixel (conv_plan.h, run16):
 // x4 from launch_pad4_bf16 (or the preprocessing kernel), wk from launch_run16_pack.  conv_run16_ok(): the
 // geometry allows it.  The weight gradient reads the same pictures where first_weight_ok(), else the fp32 ones in run mode.
@@ -82,7 +90,8 @@ int launch_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, co
                          const float* gate, float* dx, float* ws, hipStream_t st, const uint16_t* dy16 = nullptr,
                          const uint16_t* wb16 = nullptr, uint16_t* dx16 = nullptr, bool small = true);
 int launch_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* dwrun, float* ws,
-                           hipStream_t st, int* defer_ns = nullptr, bool small = true, WgradTail* tail = nullptr);
+                           hipStream_t st, int* defer_ns = nullptr, bool small = true, WgradTail* tail = nullptr,
+                           const TileRows* rows = nullptr);
 
 // ---- 3x3 and 5x5 unit-stride convolutions through F(4x4, 3x3) (winograd.hip) ----
 // All tensors 16-byte aligned, channels per group multiples of 4.  V: wino_v_floats(), U / Ub / dU:

@@ -28,6 +28,7 @@
 #include <stdint.h>
 
 #include "gemm.h"
+#include "wino_rows.h"
 
 namespace ax {
 
@@ -58,6 +59,15 @@ AX_HD Vec2 operator*(float s, Vec2 a) { return {s * a.x, s * a.y}; }
 AX_HD Vec2 vload2(const float* p) {
   const float2 v = *reinterpret_cast<const float2*>(p);
   return {v.x, v.y};
+}
+
+AX_HD Vec2 vload2(const BufView& v, uint32_t off) {
+#ifdef AX_HOST_EMU
+  return {buf_ld1(v, off), off == kOob ? 0.f : buf_ld1(v, off + 4)};
+#else
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(Vec2, __builtin_amdgcn_raw_buffer_load_b64(v, (int)off, 0, 0));
+#endif
 }
 
 // ---- the five 1-D maps (strided in / out so that they serve rows and columns of a register tile) ----
@@ -128,30 +138,79 @@ AX_HD void wino_gt(const Vec4* m, Vec4* o) {
   o[2 * SO] = (1.f / 6.f) * (s34 - s12) + m5;
 }
 
+// The short maps (see WinoGeom): only positions 1, 2 and 5 are written or read
+template <int SI, int SO>
+AX_HD void wino_bt_short(const Vec4* d, Vec4* o) {
+  const Vec4 d0 = d[0], d1 = d[SI], d2 = d[2 * SI];
+  o[SO] = (-3.f) * (d0 + d1);
+  o[2 * SO] = 3.f * (d1 - d0);
+  o[5 * SO] = d2 - d0;
+}
+template <int SI, int SO, class V>
+AX_HD void wino_b_short(const V* m, V* o) {  // three rows of the patch
+  const V m1 = m[SI], m2 = m[2 * SI], m5 = m[5 * SI];
+  o[0] = (-3.f) * (m1 + m2) - m5;
+  o[SO] = 3.f * (m2 - m1);
+  o[2 * SO] = m5;
+}
+
 // ---- geometry of one transformed convolution -----------------------------------------------------
 // `H x W` is the tensor the 6x6 tiles are cut from (pad `pad` on every side), `OH x OW` the tensor
 // of 4x4 tiles (OH = H + 2*pad - 2).  Ctot = groups * Cg channels on the gathered side.
 // k x k taps are handled as nsub x nsub sub-kernels of 3x3 (k = 3: one, k = 5: four).
+// ey, ex: the last row and column of tiles hold one row and one column of outputs (OH, OW = 4n + 1) and take the short
+// transform below in that direction, so that 3 of the 6 positions of such a tile are made and multiplied: 441 products of 576
+// for a 13 x 13 map, every third position of which fell on four times as many outputs as there are.
 struct WinoGeom {
   int B, H, W, pad, OH, OW, th, tw, groups, k, nsub;
+  int ey = 0, ex = 0;
   AX_HD int tiles() const { return B * th * tw; }
   AX_HD int nq() const { return nsub * nsub; }
+  // tiles in the order of their rows in the transformed tensors: short in y only, whole, short in x only, in both
+  AX_HD int short_y() const { return ey ? B * (tw - ex) : 0; }
+  AX_HD int whole() const { return B * (th - ey) * (tw - ex); }
+  AX_HD int short_x() const { return ex ? B * (th - ey) : 0; }
 };
 struct WinoTile {
   int n, ty, tx;
 };
 AX_HD WinoTile wino_tile(const WinoGeom& g, int t) {
   WinoTile r;
-  const int per = g.th * g.tw;
-  r.n = t / per;
-  const int rem = t - r.n * per;
-  r.ty = rem / g.tw;
-  r.tx = rem - r.ty * g.tw;
+  const int nx = g.tw - g.ex, ny = g.th - g.ey, sy = g.short_y(), w = g.whole(), sx = g.short_x();
+  if (t < sy) {
+    r.n = t / nx;
+    r.ty = ny;
+    r.tx = t - r.n * nx;
+  } else if (t < sy + w) {
+    const int per = ny * nx, u = t - sy;
+    r.n = u / per;
+    const int rem = u - r.n * per;
+    r.ty = rem / nx;
+    r.tx = rem - r.ty * nx;
+  } else if (t < sy + w + sx) {
+    const int u = t - sy - w;
+    r.n = u / ny;
+    r.ty = u - r.n * ny;
+    r.tx = nx;
+  } else {
+    r.n = t - sy - w - sx;
+    r.ty = ny;
+    r.tx = nx;
+  }
   return r;
+}
+AX_HD long wino_tile_row(const WinoGeom& g, int n, int ty, int tx) {
+  const int nx = g.tw - g.ex, ny = g.th - g.ey;
+  const bool sy = ty >= ny, sx = tx >= nx;
+  if (sy && !sx) return (long)n * nx + tx;
+  if (!sy && !sx) return g.short_y() + ((long)n * ny + ty) * nx + tx;
+  if (!sy) return (long)g.short_y() + g.whole() + (long)n * ny + ty;
+  return (long)g.short_y() + g.whole() + g.short_x() + n;
 }
 
 // V[t][(p*groups + g)*(nq*Cg) + q*Cg + c] = (Bt d B)[p] of the 6x6 patch of x that sub-kernel q of tile t
 // reads (zero outside x).  idx enumerates (tile, sub-kernel, channel quad); x is [B][H][W][groups*Cg].
+template <bool SHORT = true>
 AX_HD void wino_in_thread(const WinoGeom& g, int Cg, const float* x, float* V, long idx) {
   const int Ctot = g.groups * Cg, quads = Ctot / 4, nq = g.nq();
   const int t = (int)(idx / ((long)nq * quads));
@@ -160,32 +219,46 @@ AX_HD void wino_in_thread(const WinoGeom& g, int Cg, const float* x, float* V, l
   const int qy = q / g.nsub, qx = q - qy * g.nsub;
   const WinoTile tl = wino_tile(g, t);
   const int y0 = 4 * tl.ty - g.pad + 3 * qy, x0 = 4 * tl.tx - g.pad + 3 * qx;
-  Vec4 d[36], u[36];
+  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;  // short: three rows, three columns
+  Vec4 u[36];
 #pragma unroll
-  for (int i = 0; i < 6; ++i)
+  for (int j = 0; j < 6; ++j) {  // columns
+    Vec4 d[6];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
+    for (int i = 0; i < 6; ++i) {
       const int iy = y0 + i, ix = x0 + j;
-      const bool in = (uint32_t)iy < (uint32_t)g.H && (uint32_t)ix < (uint32_t)g.W;
-      d[6 * i + j] = vzero();
-      if (in) d[6 * i + j] = vload(x + (((long)tl.n * g.H + iy) * g.W + ix) * Ctot + c);
+      const bool in = (uint32_t)iy < (uint32_t)g.H && (uint32_t)ix < (uint32_t)g.W && (i < 3 || !sy) && (j < 3 || !sx);
+      d[i] = vzero();
+      if (in) d[i] = vload(x + (((long)tl.n * g.H + iy) * g.W + ix) * Ctot + c);
     }
-#pragma unroll
-  for (int j = 0; j < 6; ++j) wino_bt<6, 6>(d + j, u + j);  // columns
+    if (!sy)
+      wino_bt<1, 6>(d, u + j);
+    else
+      wino_bt_short<1, 6>(d, u + j);
+  }
   const int grp = c / Cg, cl = c - grp * Cg;
   const long pstride = (long)nq * Ctot;
   float* out = V + (long)t * 36 * pstride + (long)grp * nq * Cg + (long)q * Cg + cl;
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
+    if (sy && !in_short(i)) continue;
     Vec4 r[6];
-    wino_bt<1, 1>(u + 6 * i, r);  // row i
+    if (!sx) {
+      wino_bt<1, 1>(u + 6 * i, r);  // row i
 #pragma unroll
-    for (int j = 0; j < 6; ++j) vstore(out + (long)(6 * i + j) * pstride, r[j]);
+      for (int j = 0; j < 6; ++j) vstore(out + (long)(6 * i + j) * pstride, r[j]);
+    } else {
+      wino_bt_short<1, 1>(u + 6 * i, r);
+#pragma unroll
+      for (int j = 0; j < 6; ++j)
+        if (in_short(j)) vstore(out + (long)(6 * i + j) * pstride, r[j]);
+    }
   }
 }
 
 // Y[t][(p*groups + g)*Og + o] = (A e At)[p] of the 4x4 block of dy that tile t owns (zero outside dy).
 // idx enumerates (tile, channel quad); dy is [B][OH][OW][groups*Og].
+template <bool SHORT = true>
 AX_HD void wino_dy_thread(const WinoGeom& g, int Og, const float* dy, float* Y, long idx) {
   const int Ctot = g.groups * Og, quads = Ctot / 4;
   const int t = (int)(idx / quads), c = 4 * (int)(idx - (long)t * quads);
@@ -199,21 +272,36 @@ AX_HD void wino_dy_thread(const WinoGeom& g, int Og, const float* dy, float* Y, 
       e[4 * i + j] = vzero();
       if (oy < g.OH && ox < g.OW) e[4 * i + j] = vload(dy + (((long)tl.n * g.OH + oy) * g.OW + ox) * Ctot + c);
     }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) wino_a<4, 4>(e + j, u + j);  // columns: 4 -> 6 rows of 4
+  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;
   const int grp = c / Og, cl = c - grp * Og;
   float* out = Y + (long)t * 36 * Ctot + (long)grp * Og + cl;
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    Vec4 r[6];
-    wino_a<1, 1>(u + 4 * i, r);
+  for (int j = 0; j < 4; ++j) wino_a<4, 4>(e + j, u + j);  // columns: 4 -> 6 rows of 4; of one row the short positions have that row
 #pragma unroll
-    for (int j = 0; j < 6; ++j) vstore(out + (long)(6 * i + j) * Ctot, r[j]);
+  for (int i = 0; i < 6; ++i) {
+    if (sy && !in_short(i)) continue;
+    Vec4 row[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      row[j] = u[4 * i + j];
+      if (sy) row[j] = e[j];
+    }
+    if (!sx) {
+      Vec4 r[6];
+      wino_a<1, 1>(row, r);
+#pragma unroll
+      for (int j = 0; j < 6; ++j) vstore(out + (long)(6 * i + j) * Ctot, r[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 6; ++j)
+        if (in_short(j)) vstore(out + (long)(6 * i + j) * Ctot, row[0]);
+    }
   }
 }
 
 // y[n][4ty+i][4tx+j][c] = post((At m A)[i][j]) from M[t][(p*groups + g)*Ng + c'], inside OH x OW only.
 // post: + bias[c] and ReLU (relu != 0), or zero where gate[same index] <= 0; bias and gate may be null.
+template <bool SHORT = true>
 AX_HD void wino_out_thread(const WinoGeom& g, int Ng, const float* M, const float* bias, int relu, const float* gate,
                            float* y, long idx) {
   const int Ctot = g.groups * Ng, quads = Ctot / 4;
@@ -221,25 +309,35 @@ AX_HD void wino_out_thread(const WinoGeom& g, int Ng, const float* M, const floa
   const WinoTile tl = wino_tile(g, t);
   const int grp = c / Ng, cl = c - grp * Ng;
   const float* in = M + (long)t * 36 * Ctot + (long)grp * Ng + cl;
+  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;  // short: one row, one column of outputs
   Vec4 u[24];
 #pragma unroll
   for (int j = 0; j < 6; ++j) {
+    if (sx && !in_short(j)) continue;
     Vec4 col[6];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) col[i] = vload(in + (long)(6 * i + j) * Ctot);
-    wino_at<1, 6>(col, u + j);  // u[i][j], 4 rows of 6
+    for (int i = 0; i < 6; ++i)
+      if (!sy || in_short(i)) col[i] = vload(in + (long)(6 * i + j) * Ctot);
+    if (!sy)
+      wino_at<1, 6>(col, u + j);  // u[i][j], 4 rows of 6
+    else
+      u[j] = col[1] + col[2] + col[5];
   }
   Vec4 b = vzero();
   if (bias) b = vload(bias + c);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     Vec4 r[4];
-    wino_at<1, 1>(u + 6 * i, r);
     const int oy = 4 * tl.ty + i;
+    if (oy >= g.OH) continue;
+    if (!sx)
+      wino_at<1, 1>(u + 6 * i, r);
+    else
+      r[0] = u[6 * i + 1] + u[6 * i + 2] + u[6 * i + 5];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int ox = 4 * tl.tx + j;
-      if (oy < g.OH && ox < g.OW) {
+      if (ox < g.OW) {
         const long o = (((long)tl.n * g.OH + oy) * g.OW + ox) * Ctot + c;
         Vec4 v = r[j] + b;
         if (relu) {
@@ -394,6 +492,7 @@ struct WinoDxTask {
 };
 // Round r of a block: every worker loads and transforms one patch (all threads at once: this is where the
 // memory traffic is), ...
+template <bool SHORT = true>
 AX_HD WinoDxTask wino_dx_load(const WinoDx& d, const WinoDxPlan& p, const float* M, int tid, int round, Vec2* z) {
   const WinoGeom& g = d.g;
   const int nq = g.nq(), Ctot = d.Ctot();
@@ -416,18 +515,43 @@ AX_HD WinoDxTask wino_dx_load(const WinoDx& d, const WinoDxPlan& p, const float*
   task.y0 = y0; task.x0 = x0;
   const int grp = c / d.Cg, cl = c - grp * d.Cg;
   const long pstride = (long)nq * Ctot;
-  const long t = ((long)bk.n * g.th + ty) * g.tw + tx;
+  const long t = wino_tile_row(g, bk.n, ty, tx);
+  const bool sy = SHORT && g.ey && ty == g.th - 1, sx = SHORT && g.ex && tx == g.tw - 1;  // short: three rows, three columns of the patch
   const float* in = M + t * 36 * pstride + (long)grp * nq * d.Cg + (long)q * d.Cg + cl;
+  const BufView mv = make_view(M, (uint32_t)((long)g.tiles() * 36 * pstride * 4));
+  const uint32_t at = (uint32_t)((in - M) * 4);
   Vec2 u[36];
 #pragma unroll
   for (int jj = 0; jj < 6; ++jj) {
-    Vec2 col[6];
+    Vec2 col[6], t6[6];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) col[i] = vload2(in + (long)(6 * i + jj) * pstride);
-    wino_b<1, 6>(col, u + jj);  // u[i][jj]
+    for (int i = 0; i < 6; ++i) {
+      col[i] = Vec2{0.f, 0.f};
+      if (!SHORT)
+        col[i] = vload2(in + (long)(6 * i + jj) * pstride);
+      else  // without a branch
+        col[i] = vload2(mv, (!sy || in_short(i)) && (!sx || in_short(jj)) ? at + (uint32_t)(6 * i + jj) * (uint32_t)pstride * 4u : kOob);
+      t6[i] = Vec2{0.f, 0.f};  // what is not there adds zero
+    }
+    if (!sy)
+      wino_b<1, 1>(col, t6);
+    else
+      wino_b_short<1, 1>(col, t6);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) u[6 * i + jj] = t6[i];
   }
 #pragma unroll
-  for (int i = 0; i < 6; ++i) wino_b<1, 1>(u + 6 * i, z + 6 * i);
+  for (int i = 0; i < 6; ++i) {
+    Vec2 t6[6];
+#pragma unroll
+    for (int jj = 0; jj < 6; ++jj) t6[jj] = Vec2{0.f, 0.f};
+    if (!sx)
+      wino_b<1, 1>(u + 6 * i, t6);
+    else
+      wino_b_short<1, 1>(u + 6 * i, t6);
+#pragma unroll
+    for (int jj = 0; jj < 6; ++jj) z[6 * i + jj] = t6[jj];
+  }
   return task;
 }
 // ... then the patches are added to the picture phase by phase (a barrier after each call).

@@ -10,22 +10,25 @@
 
 namespace ax {
 
+template <bool SHORT>
 __global__ void __launch_bounds__(256) wino_in_kernel(WinoGeom g, int Cg, const float* __restrict__ x,
                                                        float* __restrict__ V, long total) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < total) wino_in_thread(g, Cg, x, V, idx);
+  if (idx < total) wino_in_thread<SHORT>(g, Cg, x, V, idx);
 }
+template <bool SHORT>
 __global__ void __launch_bounds__(256) wino_dy_kernel(WinoGeom g, int Og, const float* __restrict__ dy,
                                                        float* __restrict__ Y, long total) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < total) wino_dy_thread(g, Og, dy, Y, idx);
+  if (idx < total) wino_dy_thread<SHORT>(g, Og, dy, Y, idx);
 }
+template <bool SHORT>
 __global__ void __launch_bounds__(256) wino_out_kernel(WinoGeom g, int Ng, const float* __restrict__ M,
                                                         const float* __restrict__ bias, int relu,
                                                         const float* __restrict__ gate, float* __restrict__ y,
                                                         long total) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < total) wino_out_thread(g, Ng, M, bias, relu, gate, y, idx);
+  if (idx < total) wino_out_thread<SHORT>(g, Ng, M, bias, relu, gate, y, idx);
 }
 __global__ void __launch_bounds__(256) wino_filter_kernel(int groups, int Na, int Nb, int k, int nsub, int q_in_cols,
                                                            const float* __restrict__ w, float* __restrict__ U,
@@ -34,6 +37,7 @@ __global__ void __launch_bounds__(256) wino_filter_kernel(int groups, int Na, in
   if (idx < total) wino_filter_thread(groups, Na, Nb, k, nsub, q_in_cols, w, U, idx);
 }
 // one workgroup per (picture, block of CQ channel quads); dynamic LDS: H*W*CQ float4
+template <bool SHORT>
 __global__ void __launch_bounds__(256) wino_dx_kernel(WinoDx d, int rounds, const float* __restrict__ M,
                                                        const float* __restrict__ gate, float* __restrict__ dx) {
   extern __shared__ __attribute__((aligned(16))) float4 wino_dx_lds[];
@@ -44,7 +48,7 @@ __global__ void __launch_bounds__(256) wino_dx_kernel(WinoDx d, int rounds, cons
   __syncthreads();
   for (int r = 0; r < rounds; ++r) {
     Vec2 z[36];
-    const WinoDxTask task = wino_dx_load(d, plan, M, tid, r, z);
+    const WinoDxTask task = wino_dx_load<SHORT>(d, plan, M, tid, r, z);
     int lo, hi;  // the same for every thread of the block
     wino_dx_round_phases(d, plan, r, &lo, &hi);
     for (int ph = lo; ph <= hi; ++ph) {
@@ -79,9 +83,32 @@ __global__ void __launch_bounds__(256) wino_dw_colsum_batch_stage2(ColsumBatch b
 // ---- geometry ----------------------------------------------------------------------------------
 static inline int nsub_of(const ConvGeom& c) { return (c.k + 2) / 3; }
 static inline int nq_of(const ConvGeom& c) { return nsub_of(c) * nsub_of(c); }
+static ConvGeom product_geom(int tiles, int groups, int kin, int nout);
 static WinoGeom fwd_geom(const ConvGeom& c) {
-  return WinoGeom{c.B, c.H, c.W, c.pad, c.Ho, c.Wo, (c.Ho + 3) / 4, (c.Wo + 3) / 4, c.groups, c.k, nsub_of(c)};
+  WinoGeom g{c.B, c.H, c.W, c.pad, c.Ho, c.Wo, (c.Ho + 3) / 4, (c.Wo + 3) / 4, c.groups, c.k, nsub_of(c)};
+  // Short tiles where the last ones hold one row or column each, and the products are split ones in every pass: the small
+  // products of a layer deal with all rows.
+  const bool y = c.Ho % 4 == 1 && c.Ho > 4, x = c.Wo % 4 == 1 && c.Wo > 4;
+  if ((y || x) && conv_products_split(product_geom(g.tiles(), c.groups, nq_of(c) * c.cg(), c.og())) &&
+      conv_products_split(product_geom(g.tiles(), c.groups, c.og(), nq_of(c) * c.cg()))) {
+    g.ey = y;
+    g.ex = x;
+  }
+  return g;
 }
+// null where all tiles are whole
+struct Rows {
+  TileRows r;
+  bool any;
+  explicit Rows(const WinoGeom& g) : any(g.ey || g.ex) {
+    r = TileRows{g.short_y(), g.whole(), g.short_x(), g.tiles(), 0};
+    for (int p = 0; p < 36; ++p) {
+      const RowRange w = wino_rows(p, r.short_y, r.whole, r.short_x, r.tiles);
+      r.share += (double)(w.hi - w.lo) / (36.0 * r.tiles);
+    }
+  }
+  const TileRows* get() const { return any ? &r : nullptr; }
+};
 bool wino_ok(const ConvGeom& c) {
   if ((c.k != 3 && c.k != 5) || c.stride != 1 || c.pad > c.k - 1 || c.cg() % 4 || c.og() % 4) return false;
   // the transformed tensors are 36/16 (tiles cut exactly) to ~4x larger than the activations, times the
@@ -121,10 +148,12 @@ size_t wino_wgrad_ws_floats(const ConvGeom& c) {
   return conv_bwd_weight_ws_floats(product_geom(fwd_geom(c).tiles(), c.groups, nq_of(c) * c.cg(), c.og()));
 }
 size_t wino_gemm_ws_floats(const ConvGeom& c) {
-  const ConvGeom pf = product_geom(fwd_geom(c).tiles(), c.groups, nq_of(c) * c.cg(), c.og());
-  size_t n = std::max(conv_fwd_ws_floats(pf), conv_bwd_weight_ws_floats(pf));
+  const WinoGeom g = fwd_geom(c);
+  const Rows rows(g);
+  const ConvGeom pf = product_geom(g.tiles(), c.groups, nq_of(c) * c.cg(), c.og());
+  size_t n = std::max(conv_fwd_ws_floats(pf, rows.get()), conv_bwd_weight_ws_floats(pf));
   if (wino_bwd_data_ok(c))
-    n = std::max(n, conv_fwd_ws_floats(product_geom(fwd_geom(c).tiles(), c.groups, c.og(), nq_of(c) * c.cg())));
+    n = std::max(n, conv_fwd_ws_floats(product_geom(g.tiles(), c.groups, c.og(), nq_of(c) * c.cg()), rows.get()));
   return n;
 }
 
@@ -154,7 +183,7 @@ int launch_wino_input(const ConvGeom& c, const float* x, float* V, hipStream_t s
   const int T = g.tiles();
   const long total = (long)T * nq_of(c) * (c.Cin / 4);
   KernelScope ks("wino_in", 0, ((double)c.in_elems() + (double)T * 36 * nq_of(c) * c.Cin) * 4.0, st);
-  hipLaunchKernelGGL(wino_in_kernel, blocks_for(total), dim3(256), 0, st, g, c.cg(), x, V, total);
+  hipLaunchKernelGGL(g.ey || g.ex ? wino_in_kernel<true> : wino_in_kernel<false>, blocks_for(total), dim3(256), 0, st, g, c.cg(), x, V, total);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
@@ -166,10 +195,11 @@ int launch_wino_fwd(const ConvGeom& c, const float* x, const float* U, const flo
   const int T = g.tiles();
   AX_TRY(launch_wino_input(c, x, V, st));
   const ConvGeom p = product_geom(T, c.groups, nq_of(c) * c.cg(), c.og());
-  AX_TRY(launch_conv_fwd(p, V, U, nullptr, nullptr, 0, m, ws, st));
+  const Rows rows(g);
+  AX_TRY(launch_conv_fwd(p, V, U, nullptr, nullptr, 0, m, ws, st, nullptr, nullptr, nullptr, rows.get()));
   const long total = (long)T * (c.Cout / 4);
   KernelScope ks("wino_out", 0, ((double)c.out_elems() + (double)T * 36 * c.Cout) * 4.0, st);
-  hipLaunchKernelGGL(wino_out_kernel, blocks_for(total), dim3(256), 0, st, g, c.og(), m, bias, relu,
+  hipLaunchKernelGGL(g.ey || g.ex ? wino_out_kernel<true> : wino_out_kernel<false>, blocks_for(total), dim3(256), 0, st, g, c.og(), m, bias, relu,
                      (const float*)nullptr, y, total);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
@@ -180,7 +210,7 @@ int launch_wino_output_grad(const ConvGeom& c, const float* dy, float* yt, hipSt
   const int T = g.tiles();
   const long total = (long)T * (c.Cout / 4);
   KernelScope ks("wino_dy", 0, ((double)c.out_elems() + (double)T * 36 * c.Cout) * 4.0, st);
-  hipLaunchKernelGGL(wino_dy_kernel, blocks_for(total), dim3(256), 0, st, g, c.og(), dy, yt, total);
+  hipLaunchKernelGGL(g.ey || g.ex ? wino_dy_kernel<true> : wino_dy_kernel<false>, blocks_for(total), dim3(256), 0, st, g, c.og(), dy, yt, total);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
@@ -192,7 +222,8 @@ int launch_wino_bwd_data(const ConvGeom& c, const float* yt, const float* Ut, co
   const WinoGeom g = fwd_geom(c);
   const int T = g.tiles();
   const ConvGeom p = product_geom(T, c.groups, c.og(), nq_of(c) * c.cg());
-  AX_TRY(launch_conv_fwd(p, yt, Ut, nullptr, nullptr, 0, m, ws, st));
+  const Rows rows(g);
+  AX_TRY(launch_conv_fwd(p, yt, Ut, nullptr, nullptr, 0, m, ws, st, nullptr, nullptr, nullptr, rows.get()));
   // eight channel quads (one 128-byte line of m) per workgroup where the channels allow, and as few row bands
   // as make that fit; at most 16 quads when whole pictures fit
   WinoDx d{g, c.cg(), 1, 1};
@@ -201,7 +232,7 @@ int launch_wino_bwd_data(const ConvGeom& c, const float* yt, const float* Ut, co
   while ((size_t)d.lds_vec4() * 16 > kDxLdsBytes && d.bands < c.H) ++d.bands;
   while (d.bands == 1 && d.CQ < 16 && d.CQ * 2 <= c.Cin / 4 && (size_t)d.lds_vec4() * 32 <= kDxLdsBytes) d.CQ *= 2;
   KernelScope ks("wino_dx", 0, ((double)c.in_elems() * (gate ? 2 : 1) + (double)T * 36 * nq_of(c) * c.Cin) * 4.0, st);
-  hipLaunchKernelGGL(wino_dx_kernel, dim3((unsigned)d.blocks()), dim3(256), (size_t)d.lds_vec4() * 16, st, d,
+  hipLaunchKernelGGL(g.ey || g.ex ? wino_dx_kernel<true> : wino_dx_kernel<false>, dim3((unsigned)d.blocks()), dim3(256), (size_t)d.lds_vec4() * 16, st, d,
                      wino_dx_rounds(d), m, gate, dx);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
@@ -217,13 +248,14 @@ int launch_wino_bwd_weight(const ConvGeom& c, const float* V, const float* dy, f
   AX_TRY(launch_wino_output_grad(c, dy, yt, st));
   const ConvGeom p = product_geom(T, c.groups, nq_of(c) * c.cg(), c.og());
   const long total = (long)c.groups * nq_of(c) * c.cg() * (c.og() / 4);
+  const Rows rows(g);
   if (tail) {
     if (tail->n >= kMaxWgradJobs) {
       set_error("weight-gradient tail: more than %d stages", kMaxWgradJobs);
       return ALEXNET_EINVAL;
     }
     int ns = 1;
-    AX_TRY(launch_conv_bwd_weight(p, V, yt, dU, nullptr, ws, st, &ns));
+    AX_TRY(launch_conv_bwd_weight(p, V, yt, dU, nullptr, ws, st, &ns, true, nullptr, rows.get()));
     WgradJob j{};
     j.slices = ws; j.dU = dU; j.dwf = dwf;
     j.slab = (long)p.kf() * p.og(); j.total = total;
@@ -234,7 +266,7 @@ int launch_wino_bwd_weight(const ConvGeom& c, const float* V, const float* dy, f
   }
   // (split over the tiles where that fills the chip; the slices are added by the wide reduction kernel: letting
   // the transform below add them, with its 12 to 25 thousand threads, measured 15-50 us slower)
-  AX_TRY(launch_conv_bwd_weight(p, V, yt, dU, nullptr, ws, st));
+  AX_TRY(launch_conv_bwd_weight(p, V, yt, dU, nullptr, ws, st, nullptr, true, nullptr, rows.get()));
   KernelScope ks("wino_dw", 0, ((double)wino_u_floats(c) + (double)c.w_elems()) * 4.0, st);
   hipLaunchKernelGGL(wino_dw_kernel, blocks_for(total), dim3(256), 0, st, c.groups, c.cg(), c.og(), c.k, nsub_of(c), dU,
                      dwf, total);

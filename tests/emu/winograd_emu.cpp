@@ -93,18 +93,41 @@ static void check_1d() {
   check("1d", "dd_k = sum_i e_i g_{k-i}", got, ref, 1e-5);
 }
 
+// the short form of one output: y = sum_j g_j d_j from three of the six positions, and the adjoint to the patch
+static void check_1d_short() {
+  Vec4 d[3], g[3], gg[6], bd[6], e = {rnd(), rnd(), rnd(), rnd()};
+  for (auto& v : d) v = {rnd(), rnd(), rnd(), rnd()};
+  for (auto& v : g) v = {rnd(), rnd(), rnd(), rnd()};
+  wino_bt_short<1, 1>(d, bd);
+  wino_g<1, 1>(g, gg);
+  double y = 0;
+  Vec4 prod[6], dd[6];
+  for (int p = 0; p < 6; ++p) {
+    if (!in_short(p)) continue;
+    y += (double)gg[p].x * bd[p].x;
+    prod[p] = {gg[p].x * e.x, gg[p].y * e.y, gg[p].z * e.z, gg[p].w * e.w};
+  }
+  check("1d", "short y", {(float)y}, {(double)g[0].x * d[0].x + (double)g[1].x * d[1].x + (double)g[2].x * d[2].x}, 1e-5);
+  wino_b_short<1, 1>(prod, dd);
+  check("1d", "short dd", {dd[0].y, dd[1].y, dd[2].y}, {(double)g[0].y * e.y, (double)g[1].y * e.y, (double)g[2].y * e.y}, 1e-5);
+}
+
 struct Case {
   const char* name;
   int B, H, W, pad, groups, cg, og, k;  // k x k taps: 3, or 5 as four 3x3 sub-kernels
+  int ey = 0, ex = 0;                   // short tiles at the end of columns and rows
 };
 
 // m[t][z*N + o] = sum_c a[t][z*K + c] * u[z][c][o]
+template <class F>
 static void products(int T, int Z, int K, int N, const std::vector<float>& a, const std::vector<float>& u,
-                     std::vector<float>& m) {
+                     std::vector<float>& m, const F& rows_of) {
   for (int t = 0; t < T; ++t)
     for (int z = 0; z < Z; ++z)
       for (int o = 0; o < N; ++o) {
-        float s = 0.f;
+        const RowRange r = rows_of(z);
+        float s = NAN;  // nobody reads it
+        if (t >= r.lo && t < r.hi) s = 0.f;
         for (int c = 0; c < K; ++c) s += a[((size_t)t * Z + z) * K + c] * u[((size_t)z * K + c) * N + o];
         m[((size_t)t * Z + z) * N + o] = s;
       }
@@ -113,8 +136,13 @@ static void products(int T, int Z, int K, int N, const std::vector<float>& a, co
 static void run(const Case& k) {
   const int K = k.k, KK = K * K, nsub = (K + 2) / 3, nq = nsub * nsub;
   const int Ho = k.H + 2 * k.pad - (K - 1), Wo = k.W + 2 * k.pad - (K - 1), G = k.groups, Cin = G * k.cg, Cout = G * k.og;
-  const WinoGeom gf{k.B, k.H, k.W, k.pad, Ho, Wo, (Ho + 3) / 4, (Wo + 3) / 4, G, K, nsub};
+  const WinoGeom gf{k.B, k.H, k.W, k.pad, Ho, Wo, (Ho + 3) / 4, (Wo + 3) / 4, G, K, nsub, k.ey, k.ex};
   const int Tf = gf.tiles();
+  auto rows_of = [&](int z) { return wino_rows(z / G, gf.short_y(), gf.whole(), gf.short_x(), Tf); };
+  for (int t = 0; t < Tf; ++t) {
+    const WinoTile w = wino_tile(gf, t);
+    if (w.n < 0 || w.n >= k.B || wino_tile_row(gf, w.n, w.ty, w.tx) != t) emu_fail("tiles and rows do not agree");
+  }
   std::vector<float> x((size_t)k.B * k.H * k.W * Cin), dy((size_t)k.B * Ho * Wo * Cout), bias(Cout);
   std::vector<float> wf((size_t)G * KK * k.cg * k.og), wb(wf.size());
   for (auto& v : x) v = rnd();
@@ -138,7 +166,7 @@ static void run(const Case& k) {
   for (long i = 0; i < (long)G * nq * k.cg * (k.og / 4); ++i)
     wino_filter_thread(G, k.cg, k.og, K, nsub, 0, wf.data(), U.data(), i);
   for (long i = 0; i < (long)Tf * nq * (Cin / 4); ++i) wino_in_thread(gf, k.cg, x.data(), V.data(), i);
-  products(Tf, 36 * G, nq * k.cg, k.og, V, U, m);
+  products(Tf, 36 * G, nq * k.cg, k.og, V, U, m, rows_of);
   for (long i = 0; i < (long)Tf * (Cout / 4); ++i) wino_out_thread(gf, k.og, m.data(), bias.data(), 1, nullptr, y.data(), i);
   std::vector<double> y_ref(y.size());
   for (int n = 0; n < k.B; ++n)
@@ -173,13 +201,13 @@ static void run(const Case& k) {
     if (!(x[i] > 0.f)) dx_ref[i] = 0;
   // ---- backward weight ----
   const int kc = nq * k.cg;  // rows of one product's result: (sub-kernel, channel)
-  std::vector<float> yt((size_t)Tf * 36 * Cout), dU(U.size()), dw(wf.size(), NAN);
+  std::vector<float> yt((size_t)Tf * 36 * Cout, NAN), dU(U.size()), dw(wf.size(), NAN);
   for (long i = 0; i < (long)Tf * (Cout / 4); ++i) wino_dy_thread(gf, k.og, dy.data(), yt.data(), i);
   for (int z = 0; z < 36 * G; ++z)
     for (int c = 0; c < kc; ++c)
       for (int o = 0; o < k.og; ++o) {
         float s = 0.f;
-        for (int t = 0; t < Tf; ++t) s += V[((size_t)t * 36 * G + z) * kc + c] * yt[((size_t)t * 36 * G + z) * k.og + o];
+        for (int t = rows_of(z).lo; t < rows_of(z).hi; ++t) s += V[((size_t)t * 36 * G + z) * kc + c] * yt[((size_t)t * 36 * G + z) * k.og + o];
         dU[((size_t)z * kc + c) * k.og + o] = s;
       }
   for (long i = 0; i < (long)G * nq * k.cg * (k.og / 4); ++i)
@@ -206,7 +234,7 @@ static void run(const Case& k) {
     std::vector<float> Ut(U.size(), NAN), ma((size_t)Tf * 36 * nq * Cin), dxa(x.size(), NAN);
     for (long i = 0; i < (long)G * nq * k.og * (k.cg / 4); ++i)
       wino_filter_thread(G, k.og, k.cg, K, nsub, 1, wb.data(), Ut.data(), i);
-    products(Tf, 36 * G, k.og, nq * k.cg, yt, Ut, ma);
+    products(Tf, 36 * G, k.og, nq * k.cg, yt, Ut, ma, rows_of);
     std::vector<Vec4> lds(d.lds_vec4());  // exactly what the kernel is given
     for (int block = 0; block < d.blocks(); ++block) {
       for (auto& v : lds) v = {NAN, NAN, NAN, NAN};
@@ -256,7 +284,12 @@ int main() {
       {"4x9 pad2 g1", 1, 4, 9, 2, 1, 4, 8, 3},        {"3x3 pad1 g1", 2, 3, 3, 1, 1, 4, 4, 3},
       {"5x5: 27x27 pad2 g2", 2, 27, 27, 2, 2, 4, 8, 5}, {"5x5: 14x14 pad2 g1", 2, 14, 14, 2, 1, 8, 4, 5},
       {"5x5: 7x9 pad0 g1", 1, 7, 9, 0, 1, 4, 4, 5},     {"5x5: 6x5 pad4 g2", 2, 6, 5, 4, 2, 4, 4, 5},
+      {"13x13 short", 2, 13, 13, 1, 2, 8, 12, 3, 1, 1}, {"9x7 short y", 3, 9, 7, 1, 1, 4, 8, 3, 1, 0},
+      {"6x17 short x", 2, 6, 17, 1, 1, 4, 4, 3, 0, 1},  {"7x7 pad0 short", 2, 7, 7, 0, 1, 8, 4, 3, 1, 1},
+      {"5x3 pad2 short", 1, 5, 3, 2, 1, 4, 4, 3, 0, 1}, {"5x5: 13x17 pad2 short", 2, 13, 17, 2, 2, 4, 4, 5, 1, 1},
+      {"5x5: 9x13 pad0 short", 1, 9, 13, 0, 1, 4, 8, 5, 1, 1},
   };
+  check_1d_short();
   for (const Case& c : cases) run(c);
   if (g_fail) {
     printf("%d FAILED\n", g_fail);
