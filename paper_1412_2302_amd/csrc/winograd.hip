@@ -231,6 +231,10 @@ int launch_wino_bwd_data(const ConvGeom& c, const float* yt, const float* Ut, co
   d.CQ = want;
   while ((size_t)d.lds_vec4() * 16 > kDxLdsBytes && d.bands < c.H) ++d.bands;
   while (d.bands == 1 && d.CQ < 16 && d.CQ * 2 <= c.Cin / 4 && (size_t)d.lds_vec4() * 32 <= kDxLdsBytes) d.CQ *= 2;
+  // A workgroup's rounds are a chain of a load, a transform and two or three barriers each: with fewer than two workgroups per
+  // compute unit there is room for more of them, although patches across a band's edge are transformed in both.  37 pictures,
+  // 222 | 666 workgroups (3 x 3 layers) 37 | 25 us and 28 | 19, 222 | 444 (5 x 5) 78 | 69; 128 pictures, 768 | 1536, 43 | 62.
+  while (d.blocks() < 512 && d.bands < 4 && d.bands < c.H) ++d.bands;
   KernelScope ks("wino_dx", 0, ((double)c.in_elems() * (gate ? 2 : 1) + (double)T * 36 * nq_of(c) * c.Cin) * 4.0, st);
   hipLaunchKernelGGL(g.ey || g.ex ? wino_dx_kernel<true> : wino_dx_kernel<false>, dim3((unsigned)d.blocks()), dim3(256), (size_t)d.lds_vec4() * 16, st, d,
                      wino_dx_rounds(d), m, gate, dx);
