@@ -713,6 +713,7 @@ int launch_conv_fwd(const ConvGeom& c, const float* x, const float* wf, const fl
   if (g_bf16 && x16 && wf16 && !run && conv_bf16_stored_ok(c) && aligned16(x16) && aligned16(wf16)) {
     const Im2colParams a = im2col16(fwd_A(c, nullptr), x16);
     const DenseParams b = fwd_B16k(c, wf16);
+    if (patch_fwd_ok(c)) return launch_patch_fwd(c, x16, wf16, bias, relu, y, y16, st);
     if (direct_fwd_ok(c)) {
       const DirectPlan p = plan_direct(d, (double)c.out_elems() * 4);
       if (p.ns == 1)

@@ -58,6 +58,10 @@ int launch_conv_run_pack(const ConvGeom& c, const float* wf, float* wrun, hipStr
 // When both operands of a product are given, the handle's GEMMs are bf16 and conv_bf16_stored_ok(), the product
 // reads those instead of rounding fp32 on the fly.  y16 / dx16: where to leave a bf16 copy of the result for the
 // products that read it next (written by the epilogue, or converted after a split-k pass).
+// forward products of layers with 16 or 48 channels per group over stored operands (patch_conv.hip)
+bool patch_fwd_ok(const ConvGeom& c);
+int launch_patch_fwd(const ConvGeom& c, const uint16_t* x16, const uint16_t* wf16, const float* bias, int relu, float* y,
+                     uint16_t* y16, hipStream_t st);
 bool conv_bf16_stored_ok(const ConvGeom& c);
 // Rows that the products of a transformed layer with short tiles run over (winograd.h); share: of the products of all rows
 struct TileRows {

@@ -1,0 +1,211 @@
+// Forward products of bf16 handles over layers with 16 or 48 channels per group, from pictures in LDS.
+//
+// With channels that are no multiple of 64 the taps' octets lie in pieces of 32 and 96 bytes across cache lines, and a tile that
+// gathers them tap by tap (gemm_direct.h) waits for the second-level cache: 192 x 128 tiles of the second layer moved 160 KB a
+// k-tile and compute unit, 3 us for 0.7 us of products.  Here a workgroup loads the rows of the picture under a band of output
+// rows once and reads every tap's fragments from LDS; only the weights stream, a tap at a time, two stages.
+//
+// LDS: pixels of U = channels / 8 units of 16 bytes, an odd multiple of two; a pixel whose number has bit 2 set has its units
+// exchanged in pairs, so that a fragment read of one octet of eight neighbouring pixels touches all banks.  The same for the
+// weights' columns.  Two workgroups to a compute unit.
+//
+// Second layer (27 x 27, 48 channels, 5 x 5, 128 columns a group), us: batch 256 ... | ..., 64 ... | ....
+#include <algorithm>
+
+#include "gemm_direct.h"
+#include "kernels.h"
+
+namespace ax {
+
+constexpr int kPatchUnits = 3584;  // of a picture's rows: 56 KiB beside two stages of 128 columns
+
+struct PatchGeom {
+  const uint16_t *x, *w;  // w[g][column][(r, s, c)]
+  uint32_t x_bytes, w_bytes;
+  int H, W, Ctot, Ho, Wo, pad, k, N, rows;  // rows: output rows of a band
+  int PW;                                   // W + 2 pad
+  int bands, groups;
+  uint32_t wgroup;                          // bytes between groups of w
+  FastDiv d_pw, d_wo, d_cols, d_groups, d_bands;
+};
+
+template <int U, int WAVES_M, int WAVES_N, int TM, int TN, class Epi>
+__global__ void __launch_bounds__(256, 2) patch_conv_kernel(PatchGeom g, Epi ep) {
+  static_assert(WAVES_M * WAVES_N == 4 && U % 4 == 2, "four waves; an odd number of pairs");
+  constexpr int BN = WAVES_N * TN * 32;
+  __shared__ __attribute__((aligned(16))) v4u patch[kPatchUnits];
+  __shared__ __attribute__((aligned(16))) v4u stage0[BN * U];
+  __shared__ __attribute__((aligned(16))) v4u stage1[BN * U];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+  const uint32_t total = gridDim.x, L = blockIdx.x, q8 = total >> 3, r8 = total & 7, xcd = L & 7;
+  const uint32_t tile = xcd * q8 + min(xcd, r8) + (L >> 3);  // as in xcd_tile
+  const uint32_t t1 = fdiv(tile, g.d_cols), t2 = fdiv(t1, g.d_groups), n = fdiv(t2, g.d_bands);
+  const int n0 = (int)(tile - t1 * g.d_cols.d) * BN, grp = (int)(t1 - t2 * g.d_groups.d);
+  const int y0 = (int)(t2 - n * g.d_bands.d) * g.rows, valid = min(g.rows, g.Ho - y0);
+  const BufView xv = make_view(reinterpret_cast<const float*>(g.x), g.x_bytes);
+  const BufView wv = make_view(reinterpret_cast<const float*>(g.w), g.w_bytes);
+
+  // a picture's rows y0 - pad .. y0 - pad + valid + k - 2, zero outside it
+  const int units = (valid + g.k - 1) * g.PW * U;
+  for (int u0 = wave * 64; u0 < units; u0 += 256) {  // uniform
+    const int u = u0 + lane, p = u / U, c = (u - p * U) ^ (p >> 2 & 1);
+    const int py = (int)fdiv((uint32_t)p, g.d_pw), px = p - py * g.PW;
+    const int iy = y0 + py - g.pad, ix = px - g.pad;
+    const bool in = u < units && (uint32_t)iy < (uint32_t)g.H && (uint32_t)ix < (uint32_t)g.W;
+    const uint32_t at = (((n * (uint32_t)g.H + (uint32_t)iy) * (uint32_t)g.W + (uint32_t)ix) * (uint32_t)g.Ctot + (uint32_t)(grp * 8 * U + 8 * c)) * 2u;
+    load_lds16(xv, patch + u0, in ? at : kOob, 0);
+  }
+  // a tap's weights: units of this lane
+  constexpr int NB = (BN * U + 255) / 256;
+  uint32_t wat[NB];
+  const uint32_t K2 = (uint32_t)(g.k * g.k * 8 * U) * 2u;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int u = (i * 4 + wave) * 64 + lane, col = u / U, c = (u - col * U) ^ (col >> 2 & 1);
+    wat[i] = (uint32_t)grp * g.wgroup + (uint32_t)min(n0 + col, g.N - 1) * K2 + 16u * c;  // columns past the end are not stored
+  }
+  auto load = [&](v4u* st, int tap) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if ((i * 4 + wave) * 64 < BN * U) load_lds16(wv, st + (i * 4 + wave) * 64, wat[i], (uint32_t)tap * (16u * U));  // uniform
+  };
+  ep.set_group(grp, grp);
+
+  v16f acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const int kh = lane >> 5;
+  int pix[TM];  // of the lane's output pixels, seen from the first tap
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = min((wm * TM + i) * 32 + (lane & 31), valid * g.Wo - 1), y = (int)fdiv((uint32_t)m, g.d_wo);
+    pix[i] = y * g.PW + m - y * g.Wo;
+  }
+  int b_at[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int col = (wn * TN + j) * 32 + (lane & 31);
+    b_at[j] = col * U + (kh ^ (col >> 2 & 1));
+  }
+  int r = 0, s = 0;
+  auto multiply = [&](const v4u* st) {
+    const int off = r * g.PW + s;
+    int a_at[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int p = pix[i] + off;
+      a_at[i] = p * U + (kh ^ (p >> 2 & 1));
+    }
+    // one set of fragments is read while the other is multiplied
+    v8bf a[2][TM], b[2][TN];
+    auto read = [&](int ks) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[ks & 1][i] = __builtin_bit_cast(v8bf, patch[a_at[i] + 2 * ks]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[ks & 1][j] = __builtin_bit_cast(v8bf, st[b_at[j] + 2 * ks]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    read(0);
+#pragma unroll
+    for (int ks = 0; ks < U / 2; ++ks) {
+      if (ks + 1 < U / 2) read(ks + 1);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks & 1][i], b[ks & 1][j], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bool row = ++s == g.k;
+    r += row;
+    s = row ? 0 : s;
+  };
+  const int taps = g.k * g.k;
+  load(stage0, 0);
+  int t = 0;
+  for (; t + 2 < taps; t += 2) {
+    direct_barrier();
+    load(stage1, t + 1);
+    multiply(stage0);
+    direct_barrier();
+    load(stage0, t + 2);
+    multiply(stage1);
+  }
+  direct_barrier();
+  if (t + 1 < taps) {
+    load(stage1, t + 1);
+    multiply(stage0);
+    direct_barrier();
+    multiply(stage1);
+  } else {
+    multiply(stage0);
+  }
+  const int m0 = (int)(n * (uint32_t)g.Ho + (uint32_t)y0) * g.Wo;
+  store_rows(ep, acc, m0 + wm * (TM * 32), n0 + wn * (TN * 32), m0 + valid * g.Wo, g.N, lane);
+}
+
+// Output rows of a band and which tile; rows = 0: the layer does not fit
+struct PatchPlan {
+  int rows, bands;
+  bool tall;  // 384 x 64, else 192 x 128
+};
+static int patch_rows(const ConvGeom& c, int pixels) {
+  const int U = c.cg() / 8, PW = c.W + 2 * c.pad;
+  const int fit = kPatchUnits / (PW * U) - (c.k - 1), rows = std::min(std::min(pixels / c.Wo, fit), c.Ho);
+  if (rows < 1) return 0;
+  return ceil_div(c.Ho, ceil_div(c.Ho, rows));  // bands of nearly the same height
+}
+static PatchPlan patch_plan(const ConvGeom& c) {
+  PatchPlan p{patch_rows(c, 384), 0, true};
+  const long columns = (long)ceil_div(c.og(), 64) * c.groups * c.B;
+  if (p.rows == 0 || ceil_div(c.Ho, p.rows) * columns < 1024) {
+    p.rows = patch_rows(c, 192);
+    p.tall = false;
+  }
+  if (p.rows) p.bands = ceil_div(c.Ho, p.rows);
+  return p;
+}
+bool patch_fwd_ok(const ConvGeom& c) {
+  if (!conv_bf16_stored_ok(c) || (c.cg() != 16 && c.cg() != 48)) return false;
+  const PatchPlan p = patch_plan(c);
+  if (p.rows == 0) return false;
+  // tiles mostly full, and two workgroups for most compute units
+  const int pixels = p.tall ? 384 : 192;
+  return p.rows * c.Wo * 4 >= pixels * 3 && c.og() % 128 == 0 && (long)p.bands * ceil_div(c.og(), p.tall ? 64 : 128) * c.groups * c.B >= 256;
+}
+template <int U, int WM, int WN, int TM, int TN>
+static int launch_patch(const PatchGeom& g, const EpiBiasAct& e, const ConvGeom& c, hipStream_t st) {
+  KernelScope ks("gemm_bf16", 2.0 * c.P() * c.Cout * c.cg() * c.k * c.k,
+                 4.0 * ((double)c.in_elems() + (double)c.w_elems() + (double)c.out_elems()), st);
+  hipLaunchKernelGGL((patch_conv_kernel<U, WM, WN, TM, TN, EpiBiasAct>),
+                     dim3((unsigned)((long)c.B * g.bands * c.groups * ceil_div(c.og(), WN * TN * 32))), dim3(256), 0, st, g, e);
+  AX_LAUNCH_CHECK();
+  return ALEXNET_OK;
+}
+int launch_patch_fwd(const ConvGeom& c, const uint16_t* x16, const uint16_t* wf16, const float* bias, int relu, float* y,
+                     uint16_t* y16, hipStream_t st) {
+  const PatchPlan p = patch_plan(c);
+  PatchGeom g;
+  g.x = x16; g.w = wf16;
+  g.x_bytes = (uint32_t)(c.in_elems() * 2);
+  g.w_bytes = (uint32_t)(c.w_elems() * 2);
+  g.H = c.H; g.W = c.W; g.Ctot = c.Cin; g.Ho = c.Ho; g.Wo = c.Wo; g.pad = c.pad; g.k = c.k; g.N = c.og(); g.rows = p.rows;
+  g.PW = c.W + 2 * c.pad;
+  g.bands = p.bands; g.groups = c.groups;
+  g.wgroup = (uint32_t)((long)c.og() * c.kf() * 2);
+  g.d_pw = make_fastdiv((uint32_t)g.PW);
+  g.d_wo = make_fastdiv((uint32_t)c.Wo);
+  g.d_cols = make_fastdiv((uint32_t)ceil_div(c.og(), p.tall ? 64 : 128));
+  g.d_groups = make_fastdiv((uint32_t)c.groups);
+  g.d_bands = make_fastdiv((uint32_t)p.bands);
+  const EpiBiasAct e{y, c.Cout, bias, relu, c.og(), 0, 0, y16};
+  if (c.cg() == 48) return p.tall ? launch_patch<6, 4, 1, 3, 2>(g, e, c, st) : launch_patch<6, 2, 2, 3, 2>(g, e, c, st);
+  return p.tall ? launch_patch<2, 4, 1, 3, 2>(g, e, c, st) : launch_patch<2, 2, 2, 3, 2>(g, e, c, st);
+}
+
+}  // namespace ax
