@@ -3,13 +3,15 @@
 // With channels that are no multiple of 64 the taps' octets lie in pieces of 32 and 96 bytes across cache lines, and a tile that
 // gathers them tap by tap (gemm_direct.h) waits for the second-level cache: 192 x 128 tiles of the second layer moved 160 KB a
 // k-tile and compute unit, 3 us for 0.7 us of products.  Here a workgroup loads the rows of the picture under a band of output
-// rows once and reads every tap's fragments from LDS; only the weights stream, a tap at a time, two stages.
+// rows once and reads every tap's fragments from LDS; only the weights stream, a tap at a time, three stages.
 //
 // LDS: pixels of U = channels / 8 units of 16 bytes, an odd multiple of two; a pixel whose number has bit 2 set has its units
 // exchanged in pairs, so that a fragment read of one octet of eight neighbouring pixels touches all banks.  The same for the
 // weights' columns.  Two workgroups to a compute unit.
 //
-// Second layer (27 x 27, 48 channels, 5 x 5, 128 columns a group), us: batch 256 ... | ..., 64 ... | ....
+// Second layer (27 x 27, 48 channels, 5 x 5, 128 columns a group), gathered | here: 256 pictures 161 | 111 us (1030 TFLOP/s), 64
+// 60 | 38.  With two stages, whose loads had a tap's products alone to arrive under, 118 and 46.  What bounds it: power at 256
+// pictures; at 64, one round of two workgroups a unit, the picture's way in and the results' way out.
 #include <algorithm>
 
 #include "gemm_direct.h"
@@ -17,7 +19,8 @@
 
 namespace ax {
 
-constexpr int kPatchUnits = 3584;  // of a picture's rows: 56 KiB beside two stages of 128 columns
+// units of a picture's rows beside three stages of the weights, of 64 or 128 columns: 80 KiB together
+constexpr int patch_units(bool tall) { return tall ? 3584 : 2560; }
 
 struct PatchGeom {
   const uint16_t *x, *w;  // w[g][column][(r, s, c)]
@@ -33,9 +36,11 @@ template <int U, int WAVES_M, int WAVES_N, int TM, int TN, class Epi>
 __global__ void __launch_bounds__(256, 2) patch_conv_kernel(PatchGeom g, Epi ep) {
   static_assert(WAVES_M * WAVES_N == 4 && U % 4 == 2, "four waves; an odd number of pairs");
   constexpr int BN = WAVES_N * TN * 32;
-  __shared__ __attribute__((aligned(16))) v4u patch[kPatchUnits];
-  __shared__ __attribute__((aligned(16))) v4u stage0[BN * U];
-  __shared__ __attribute__((aligned(16))) v4u stage1[BN * U];
+  constexpr int NB = (BN * U + 255) / 256;  // loads of a lane and tap; what they bring past the last column is zero
+  __shared__ __attribute__((aligned(16))) v4u patch[patch_units(WAVES_N == 1)];
+  __shared__ __attribute__((aligned(16))) v4u stage0[NB * 256];
+  __shared__ __attribute__((aligned(16))) v4u stage1[NB * 256];
+  __shared__ __attribute__((aligned(16))) v4u stage2[NB * 256];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WAVES_M, wn = wave / WAVES_M;
   const uint32_t total = gridDim.x, L = blockIdx.x, q8 = total >> 3, r8 = total & 7, xcd = L & 7;
@@ -57,18 +62,17 @@ __global__ void __launch_bounds__(256, 2) patch_conv_kernel(PatchGeom g, Epi ep)
     load_lds16(xv, patch + u0, in ? at : kOob, 0);
   }
   // a tap's weights: units of this lane
-  constexpr int NB = (BN * U + 255) / 256;
   uint32_t wat[NB];
   const uint32_t K2 = (uint32_t)(g.k * g.k * 8 * U) * 2u;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const int u = (i * 4 + wave) * 64 + lane, col = u / U, c = (u - col * U) ^ (col >> 2 & 1);
-    wat[i] = (uint32_t)grp * g.wgroup + (uint32_t)min(n0 + col, g.N - 1) * K2 + 16u * c;  // columns past the end are not stored
+    // columns past the end are not stored
+    wat[i] = u < BN * U ? (uint32_t)grp * g.wgroup + (uint32_t)min(n0 + col, g.N - 1) * K2 + 16u * c : kOob;
   }
   auto load = [&](v4u* st, int tap) {
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-      if ((i * 4 + wave) * 64 < BN * U) load_lds16(wv, st + (i * 4 + wave) * 64, wat[i], (uint32_t)tap * (16u * U));  // uniform
+    for (int i = 0; i < NB; ++i) load_lds16(wv, st + (i * 4 + wave) * 64, wat[i] + (uint32_t)tap * (16u * U), 0);
   };
   ep.set_group(grp, grp);
 
@@ -125,26 +129,29 @@ __global__ void __launch_bounds__(256, 2) patch_conv_kernel(PatchGeom g, Epi ep)
     r += row;
     s = row ? 0 : s;
   };
+  // Tap t is multiplied while the next two are on their way.
   const int taps = g.k * g.k;
+  auto step = [&](v4u* cur, v4u* far, int t) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070 | NB);  // all but the next tap's; lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    load(far, t + 2);  // past the last tap: the next column's or outside, and nobody reads it
+    multiply(cur);
+  };
   load(stage0, 0);
+  load(stage1, 1);
   int t = 0;
-  for (; t + 2 < taps; t += 2) {
-    direct_barrier();
-    load(stage1, t + 1);
-    multiply(stage0);
-    direct_barrier();
-    load(stage0, t + 2);
-    multiply(stage1);
+  for (; t + 3 <= taps; t += 3) {
+    step(stage0, stage2, t);
+    step(stage1, stage0, t + 1);
+    step(stage2, stage1, t + 2);
   }
-  direct_barrier();
-  if (t + 1 < taps) {
-    load(stage1, t + 1);
-    multiply(stage0);
-    direct_barrier();
-    multiply(stage1);
-  } else {
-    multiply(stage0);
-  }
+  if (t < taps) step(stage0, stage2, t);
+  if (t + 1 < taps) step(stage1, stage0, t + 1);
+  __builtin_amdgcn_s_waitcnt(0x0070);  // no load is out when the workgroup ends
   const int m0 = (int)(n * (uint32_t)g.Ho + (uint32_t)y0) * g.Wo;
   store_rows(ep, acc, m0 + wm * (TM * 32), n0 + wn * (TN * 32), m0 + valid * g.Wo, g.N, lane);
 }
@@ -154,17 +161,18 @@ struct PatchPlan {
   int rows, bands;
   bool tall;  // 384 x 64, else 192 x 128
 };
-static int patch_rows(const ConvGeom& c, int pixels) {
+static int patch_rows(const ConvGeom& c, bool tall) {
+  const int pixels = tall ? 384 : 192;
   const int U = c.cg() / 8, PW = c.W + 2 * c.pad;
-  const int fit = kPatchUnits / (PW * U) - (c.k - 1), rows = std::min(std::min(pixels / c.Wo, fit), c.Ho);
+  const int fit = patch_units(tall) / (PW * U) - (c.k - 1), rows = std::min(std::min(pixels / c.Wo, fit), c.Ho);
   if (rows < 1) return 0;
   return ceil_div(c.Ho, ceil_div(c.Ho, rows));  // bands of nearly the same height
 }
 static PatchPlan patch_plan(const ConvGeom& c) {
-  PatchPlan p{patch_rows(c, 384), 0, true};
+  PatchPlan p{patch_rows(c, true), 0, true};
   const long columns = (long)ceil_div(c.og(), 64) * c.groups * c.B;
   if (p.rows == 0 || ceil_div(c.Ho, p.rows) * columns < 1024) {
-    p.rows = patch_rows(c, 192);
+    p.rows = patch_rows(c, false);
     p.tall = false;
   }
   if (p.rows) p.bands = ceil_div(c.Ho, p.rows);
