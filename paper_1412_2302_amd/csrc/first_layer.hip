@@ -14,9 +14,9 @@
 //
 // What bounds it: memory -- the result, 4 bytes a value, and what runs on the side stream meanwhile -- and 4 KB of fragments
 // per wave and three products, a third above what LDS gives in the products' time.  256 pictures of 3 x 227 x 227, 96 kernels
-// of 11 x 11, beside the conversion of the dense weights: 284 us as a gather GEMM with 256 x 96 tiles, 191 here (3.9 TB/s with
+// of 11 x 11, beside the conversion of the dense weights: 284 us as a gather GEMM with 256 x 96 tiles, 170 here (4.4 TB/s with
 // the 350 MB of the conversion), the same bits.  It is the faster one wherever it fits: inference of 8, 16, 37 and 100 pictures
-// 266, 315, 411 and 694 us as a gather GEMM, 263, 302, 410 and 656 here.
+// 266, 315, 411 and 694 us as a gather GEMM, 263, 302, 410 and 656 here, with the stores of a tile still in one piece (184 us above).
 #include <algorithm>
 
 #include "gemm_split.h"
@@ -80,6 +80,7 @@ __global__ void __launch_bounds__(kFirstThreads, 2) first_layer_kernel(FirstGeom
   const int row_units = g.plane_units * g.planes;
   const BufView xv = make_view(reinterpret_cast<const float*>(g.x4), g.x_bytes);
   const BufView yv = make_view(g.y, g.y_bytes);
+  const BufView y16v = make_view(Y16 ? reinterpret_cast<const float*>(g.y16) : g.y, g.y_bytes / 2);
   const BufView wv = make_view(reinterpret_cast<const float*>(g.wk), (uint32_t)g.Cout * (uint32_t)g.octets * 16u);
 
   // weights, zero past the last channel and octet
@@ -146,9 +147,24 @@ __global__ void __launch_bounds__(kFirstThreads, 2) first_layer_kernel(FirstGeom
 #pragma unroll
   for (int j = 0; j < NB; ++j) bias[j] = g.bias && j * 32 + (lane & 31) < g.Cout ? g.bias[j * 32 + (lane & 31)] : 0.f;
 
-  // The next tile's loads are issued in front of a tile's products and wait behind them; a tile's results are stored behind
-  // that wait.  Loads and stores are counted together and in order: with the stores in front of it the wait was for them
-  // too, and the kernel took 273 us.
+  // The next tile's loads are issued in front of a tile's products and wait behind them; a tile's results are stored a quarter at
+  // a time between the products of the tile after it.  Loads and stores are counted together and in order: the wait for the
+  // loads, which are the older ones, is not for the stores.  (Stored all at once behind the products, all compute units wrote at
+  // one time and multiplied at another: 13 us a tile of 220 pixels, 5 of products, 3 of arithmetic for the stores and 4 for 84
+  // KB to leave at a compute unit's share of the memory; 256 pictures 184 us.)
+  float out[NB][16];
+  uint32_t out_first = 0;
+  int out_valid = 0;  // pixels of the tile that waits to be stored
+  auto put = [&](int q) {
+    const int pix = wave * 32 + acc_row(lane, q);
+    const uint32_t o = ((out_first + (uint32_t)pix) * (uint32_t)g.Cout + (uint32_t)(lane & 31)) * 4u;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const bool in = pix < out_valid && j * 32 + (lane & 31) < g.Cout;
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(out[j][q]), yv, in ? (int)(o + 128u * j) : (int)kOob, 0, 0);
+      if (Y16) buf_st_bf16(y16v, in ? (o + 128u * j) / 2 : kOob, out[j][q]);
+    }
+  };
   fetch(item);
   first_barrier();
   store();
@@ -175,33 +191,40 @@ __global__ void __launch_bounds__(kFirstThreads, 2) first_layer_kernel(FirstGeom
       __builtin_amdgcn_sched_barrier(0);
     };
     read(0, 0);
-    for (int s = 0; s < steps; s += 2) {
-      read(1, min(s + 1, steps - 1));
-      multiply(0);
-      if (s + 1 == steps) break;
-      read(0, min(s + 2, steps - 1));
-      multiply(1);
+    int s = 0;
+#pragma unroll
+    for (int part = 0; part < 4; ++part) {
+      if (out_valid > 0) {  // uniform
+#pragma unroll
+        for (int q = 4 * part; q < 4 * part + 4; ++q) put(q);
+      }
+      const int end = part == 3 ? steps : (steps * (part + 1) / 4) & ~1;
+      for (; s < end; s += 2) {
+        read(1, min(s + 1, steps - 1));
+        multiply(0);
+        if (s + 1 == steps) break;
+        read(0, min(s + 2, steps - 1));
+        multiply(1);
+      }
     }
 
     first_barrier();  // the waves are done with the picture
     store();
     const int n = (int)fdiv((uint32_t)item, g.d_tiles), y0 = (item - n * g.tiles) * g.rows;
-    const int valid = min(g.rows, g.Ho - y0) * g.Wo;
-    const uint32_t first = (uint32_t)((n * g.Ho + y0) * g.Wo);
+    out_valid = min(g.rows, g.Ho - y0) * g.Wo;
+    out_first = (uint32_t)((n * g.Ho + y0) * g.Wo);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int pix = wave * 32 + acc_row(lane, q);
-      const uint32_t o = ((first + (uint32_t)pix) * (uint32_t)g.Cout + (uint32_t)(lane & 31)) * 4u;
+    for (int q = 0; q < 16; ++q)
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
-        float v = acc[j][q] + bias[j];
-        v = v > 0.f || !g.relu ? v : 0.f;
-        const bool in = pix < valid && j * 32 + (lane & 31) < g.Cout;
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), yv, in ? (int)(o + 128u * j) : (int)kOob, 0, 0);
-        if (Y16 && in) store_bf16(g.y16 + o / 4 + 32 * j, v);
+        const float v = acc[j][q] + bias[j];
+        out[j][q] = v > 0.f || !g.relu ? v : 0.f;
       }
-    }
     first_barrier();
+  }
+  if (out_valid > 0) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) put(q);
   }
 }
 
