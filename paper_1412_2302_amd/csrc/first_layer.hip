@@ -16,7 +16,8 @@
 // per wave and three products, a third above what LDS gives in the products' time.  256 pictures of 3 x 227 x 227, 96 kernels
 // of 11 x 11, beside the conversion of the dense weights: 284 us as a gather GEMM with 256 x 96 tiles, 170 here (4.4 TB/s with
 // the 350 MB of the conversion), the same bits.  It is the faster one wherever it fits: inference of 8, 16, 37 and 100 pictures
-// 266, 315, 411 and 694 us as a gather GEMM, 263, 302, 410 and 656 here, with the stores of a tile still in one piece (184 us above).
+// 266, 315, 411 and 694 us as a gather GEMM, 263, 302, 410 and 656 here, stores still in one
+// piece (184 us above).
 #include <algorithm>
 
 #include "gemm_split.h"

@@ -1,7 +1,7 @@
 // CPU emulation of the small products' workgroup program (csrc/gemm_wave.h): its tables and loaders run lane by lane, the
 // eight values of a lane are multiplied as the matrix core's definition has them, and the sums are compared with plain loops.
 // Built with -fsanitize=address,undefined and operands of exact size, so an access outside one aborts here.  Also the masks
-// of taps inside the tensor (csrc/gemm_direct.h), against their definition.
+// of taps inside the tensor and the walk over the taps (csrc/gemm_direct.h), against their definition.
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -180,6 +180,26 @@ static void masks() {
   printf("masks: %ld, %ld wrong\n", 2 * seen, bad);
 }
 
+// k-tile by k-tile from every first one, against the division of k
+template <bool ONE_TAP>
+static void walk(int Cg, int k, int W) {
+  Im2colParams g{};
+  g.W = W; g.kh = g.kw = k; g.Cg = Cg; g.Ctot = 2 * Cg;
+  g.d_cg = make_fastdiv((uint32_t)Cg); g.d_kw = make_fastdiv((uint32_t)k);
+  const int K = k * k * Cg;
+  long bad = 0, seen = 0;
+  for (int first = 0; first * kBKd < K; ++first)
+    for (int oct = 0; oct < (ONE_TAP ? 1 : 8); ++oct) {
+      int at = first * kBKd + 8 * oct;
+      for (TapWalk<ONE_TAP> w(g, at); at < K; at += kBKd, w.next(g), ++seen) {
+        const TapCoord t = decode_tap(at, g);
+        bad += w.ch != t.c || w.bit != t.r * k + t.s || w.offset(g) != ((uint32_t)t.r * W + t.s) * g.Ctot * 2u;
+      }
+    }
+  failures += bad != 0;
+  printf("walk of %d channels, %dx%d: %ld, %ld wrong\n", Cg, k, k, seen, bad);
+}
+
 int main() {
   srand(5);
   // B, H, W, Cin, Cout, k, stride, pad, groups
@@ -200,6 +220,10 @@ int main() {
   dense<false>(5, 37, 11);
   dense<false>(17, 10, 33);
   masks();
+  for (int k = 1; k <= 5; ++k) {
+    for (int cg = 8; cg <= 136; cg += 8) walk<false>(cg, k, k + 3);
+    for (int cg = 64; cg <= 192; cg += 64) walk<true>(cg, k, k);
+  }
   printf(failures ? "FAILURES: %d\n" : "ALL OK\n", failures);
   return failures != 0;
 }
