@@ -440,7 +440,7 @@ static int stage_fwd(alexnet* n, Stage& s, const float* x, const float* wf, cons
   }
   if (s.r16) {  // x16_ready: s.x16 holds the pictures padded to four channels
     if (!x16_ready) AX_TRY(launch_pad4_bf16(x, s.x16, (size_t)s.g.Q(), s.g.Cin, st));
-    if (!taps_ready) AX_TRY(launch_run16_pack(wf, s.wf16, s.g.k, s.g.Cin, (int)(conv_run16_w_elems(s.g) / ((size_t)s.g.k * s.g.Cout)), s.g.Cout, st));
+    AX_TRY(launch_run16_pack(wf, s.wf16, s.g.k, s.g.Cin, (int)(conv_run16_w_elems(s.g) / ((size_t)s.g.k * s.g.Cout)), s.g.Cout, st));
     return launch_conv_fwd_run16(s.g, s.x16, s.wf16, bias, relu, y, n->gemm_ws, st, y16);
   }
   if (s.wrun && !wave_conv_fwd_ok(s.g, n->cfg.precision == ALEXNET_PRECISION_BF16)) AX_TRY(launch_conv_run_pack(s.g, wf, s.wrun, st));
@@ -540,7 +540,7 @@ static int run_forward(alexnet* n, const float* in, bool train, uint64_t step, h
     uint16_t* next16 = i + 1 == kStages ? n->flat16 : n->st[i + 1].b16 ? n->st[i + 1].x16 : nullptr;
     {
       ProfContext pc(s.lab[1]);
-      if ((s.wino_pass || s.b16 || s.r16) && taps_ready && !waited) {
+      if ((s.wino_pass || s.b16) && taps_ready && !waited) {
         AX_HIP(hipStreamWaitEvent(st, taps_ready, 0));
         waited = true;
       }
@@ -754,19 +754,22 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
 }
 
 // Everything a forward pass derives from the weights -- transformed taps, bf16 copies -- is made on the side stream,
-// under the first layer (which needs its own bf16 weights only); ev_u_done and ev_fcw_done tell when.
+// under the first layer, whose own weights (run16, 70 KB) the caller's stream packs: made over here with the others they
+// held up the first layer by two events and five launches, 50 us of a step of 256 pictures; the others are one launch.  ev_u_done and ev_fcw_done
+// tell when.
 static int fork_forward_weights(alexnet* n, bool train, hipStream_t st) {
   AX_HIP(hipEventRecord(n->ev_step_begin, st));
   AX_HIP(hipStreamWaitEvent(n->upd_stream, n->ev_step_begin, 0));
+  TransposeBatch taps16;
   for (int i = 0; i < kStages; ++i) {  // the convolutions' first: they are needed soonest
     Stage& s = n->st[i];
     ProfContext pc(s.lab[1]);
     if (s.wino_pass) AX_TRY(launch_wino_filter(s.g, n->params + s.w_off, s.wino_u, n->upd_stream));
-    if (s.b16 && !s.wave_fwd)
-      AX_TRY(launch_to_bf16_transposed(n->params + s.w_off, s.wf16, s.g.groups, s.g.kf(), s.g.og(), n->upd_stream));
-    if (s.r16)
-      AX_TRY(launch_run16_pack(n->params + s.w_off, s.wf16, s.g.k, s.g.Cin,
-                               (int)(conv_run16_w_elems(s.g) / ((size_t)s.g.k * s.g.Cout)), s.g.Cout, n->upd_stream));
+    if (s.b16 && !s.wave_fwd) transpose_batch_add(taps16, n->params + s.w_off, s.wf16, s.g.groups, s.g.kf(), s.g.og());
+  }
+  {
+    ProfContext pc("conv.weights16");
+    AX_TRY(launch_to_bf16_transposed_batch(taps16, n->upd_stream));
   }
   AX_HIP(hipEventRecord(n->ev_u_done, n->upd_stream));
   if (fcw16_needed(n, train)) {
@@ -783,7 +786,7 @@ static int fork_forward_weights(alexnet* n, bool train, hipStream_t st) {
 static int run_inference(alexnet* n, const float* in, uint16_t* in16, hipStream_t st) {
   if (!n->fork_inference) return run_forward(n, in, false, 0, st, nullptr, in16);
   bool convs = false;
-  for (int i = 0; i < kStages; ++i) convs = convs || n->st[i].wino_pass || n->st[i].b16 || n->st[i].r16;
+  for (int i = 0; i < kStages; ++i) convs = convs || n->st[i].wino_pass || n->st[i].b16;
   const bool fc = fcw16_needed(n, false);
   if (convs || fc) AX_TRY(fork_forward_weights(n, false, st));
   return run_forward(n, in, false, 0, st, convs ? n->ev_u_done : nullptr, in16, fc ? n->ev_fcw_done : nullptr);
@@ -1014,14 +1017,17 @@ int alexnet_train_step(alexnet_t* n, int32_t slot, const int32_t* d_labels, uint
     // the backward-data packing of the convolution weights depends on the weights only: it runs on the side
     // stream under the forward pass
     AX_TRY(fork_forward_weights(n, true, S(stream)));
+    TransposeBatch taps16;
     for (int i = 1; i < kStages; ++i) {
       Stage& s = n->st[i];
       if (s.wave) continue;
       ProfContext pc(s.lab[3]);
       AX_TRY(launch_conv_weight_wb(n->params + s.w_off, s.wb, s.g.Cout, s.g.cg(), s.g.k, s.g.groups, n->upd_stream));
       if (s.wino_bx && s.wino_pass) AX_TRY(launch_wino_filter_bwd(s.g, s.wb, s.wino_ub, n->upd_stream));
-      if (s.b16) AX_TRY(launch_to_bf16_transposed(s.wb, s.wb16, s.g.groups, s.g.kb(), s.g.cg(), n->upd_stream));
+      if (s.b16) transpose_batch_add(taps16, s.wb, s.wb16, s.g.groups, s.g.kb(), s.g.cg());
     }
+    ProfContext pc("conv.weights16");
+    AX_TRY(launch_to_bf16_transposed_batch(taps16, n->upd_stream));
     AX_HIP(hipEventRecord(n->ev_wb_done, n->upd_stream));
   }
   // all biases, and the weights: of the convolutions, or all where the dense layers' are not updated on the side stream

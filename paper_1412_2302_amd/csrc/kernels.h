@@ -213,6 +213,21 @@ int launch_fill(float* p, size_t n, float v, hipStream_t st);
 int launch_to_bf16(const float* src, uint16_t* dst, size_t n, hipStream_t st, unsigned max_blocks = 4096);
 // dst[g][n][k] = bf16(src[g][k][n]) for G matrices of K x N
 int launch_to_bf16_transposed(const float* src, uint16_t* dst, int G, int K, int N, hipStream_t st);
+// the same for several matrices in one launch
+constexpr int kMaxTransposeJobs = 5;
+struct TransposeJob {
+  const float* src;
+  uint16_t* dst;
+  int K, N, first;  // K a multiple of eight; first workgroup
+};
+struct TransposeBatch {
+  TransposeJob job[kMaxTransposeJobs];
+  int n = 0, blocks = 0;
+  double elems = 0;
+  bool aligned = true;
+};
+void transpose_batch_add(TransposeBatch& t, const float* src, uint16_t* dst, int G, int K, int N);  // t.n < kMaxTransposeJobs
+int launch_to_bf16_transposed_batch(const TransposeBatch& t, hipStream_t st);
 // pictures with C < 4 channels as bf16 with four channels per pixel (the rest zero); the first layer's packed
 // weights as bf16 wk[o][(r, s*4 + c)] for that view
 int launch_pad4_bf16(const float* x, uint16_t* x4, size_t pixels, int C, hipStream_t st);

@@ -69,33 +69,54 @@ int launch_to_bf16(const float* src, uint16_t* dst, size_t n, hipStream_t st, un
   return ALEXNET_OK;
 }
 
-// dst[g][n][k] = bf16(src[g][k][n]): 32 x 32 tiles through LDS, reads and writes both along their rows
-__global__ void __launch_bounds__(256) to_bf16_transposed_kernel(const float* __restrict__ s, uint16_t* __restrict__ d,
-                                                                 int K, int N) {
-  __shared__ float tile[32][33];
-  const size_t g = blockIdx.z;
-  const int k0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  for (int r = ty; r < 32; r += 8) {
-    const int k = k0 + r, n = n0 + tx;
-    tile[r][tx] = (k < K && n < N) ? s[(g * K + k) * N + n] : 0.f;
-  }
-  __syncthreads();
-  for (int r = ty; r < 32; r += 8) {
-    const int n = n0 + r, k = k0 + tx;
-    if (n < N && k < K) {
-      const __bf16 v = (__bf16)tile[tx][r];
-      d[(g * N + n) * K + k] = __builtin_bit_cast(uint16_t, v);
+// dst[g][n][k] = bf16(src[g][k][n]) for up to kMaxTransposeJobs matrices: the jobs' grids laid end to end.  A lane owns one
+// column n and two octets of k: a wave reads 256 bytes of sixteen rows and a workgroup writes the 128 bytes of a line.  No
+// LDS: the bf16 first layer's product, which runs meanwhile, leaves 3 KB of a compute unit's, and with 4 KB tiles these
+// launches waited 130 us for it to end, with 2 KB (one workgroup per unit) the four of a pass took 80 us.
+__global__ void __launch_bounds__(256) to_bf16_transposed_kernel(TransposeBatch t) {
+  int ji = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxTransposeJobs; ++i)
+    if (i < t.n && (int)blockIdx.x >= t.job[i].first) ji = i;
+  const TransposeJob& j = t.job[ji];
+  const int bx = (j.N + 63) / 64, by = (j.K + 63) / 64;
+  const int block = (int)blockIdx.x - j.first, g = block / (bx * by), rest = block - g * bx * by;
+  const int k0 = rest / bx * 64 + (int)(threadIdx.x >> 6) * 16, n = rest % bx * 64 + (int)(threadIdx.x & 63);
+  if (n >= j.N || k0 >= j.K) return;
+  const float* const s = j.src + ((size_t)g * j.K + k0) * j.N + n;
+  uint16_t* const d = j.dst + ((size_t)g * j.N + n) * j.K + k0;
+  float v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = s[(size_t)min(i, j.K - 1 - k0) * j.N];
+#pragma unroll
+  for (int h = 0; h < 16; h += 8)
+    if (k0 + h < j.K) {
+      store_bf16x4(d + h, make_float4(v[h], v[h + 1], v[h + 2], v[h + 3]));
+      store_bf16x4(d + h + 4, make_float4(v[h + 4], v[h + 5], v[h + 6], v[h + 7]));
     }
-  }
 }
-int launch_to_bf16_transposed(const float* src, uint16_t* dst, int G, int K, int N, hipStream_t st) {
-  if (G <= 0 || K <= 0 || N <= 0) return ALEXNET_OK;
-  KernelScope ks("to_bf16", 0, (double)G * K * N * 6.0, st);
-  hipLaunchKernelGGL(to_bf16_transposed_kernel, dim3(ceil_div(N, 32), ceil_div(K, 32), G), dim3(256), 0, st, src, dst, K,
-                     N);
+void transpose_batch_add(TransposeBatch& t, const float* src, uint16_t* dst, int G, int K, int N) {
+  if (G <= 0 || K <= 0 || N <= 0) return;
+  t.job[t.n++] = TransposeJob{src, dst, K, N, t.blocks};
+  t.aligned = t.aligned && K % 8 == 0 && (uintptr_t)dst % 8 == 0;
+  t.blocks += G * ceil_div(K, 64) * ceil_div(N, 64);
+  t.elems += (double)G * K * N;
+}
+int launch_to_bf16_transposed_batch(const TransposeBatch& t, hipStream_t st) {
+  if (!t.n) return ALEXNET_OK;
+  if (!t.aligned) {
+    set_error("transposed bf16 copy: rows that are no octets");
+    return ALEXNET_EALIGN;
+  }
+  KernelScope ks("to_bf16", 0, t.elems * 6.0, st);
+  hipLaunchKernelGGL(to_bf16_transposed_kernel, dim3((unsigned)t.blocks), dim3(256), 0, st, t);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
+}
+int launch_to_bf16_transposed(const float* src, uint16_t* dst, int G, int K, int N, hipStream_t st) {
+  TransposeBatch t;
+  transpose_batch_add(t, src, dst, G, K, N);
+  return launch_to_bf16_transposed_batch(t, st);
 }
 
 // x4[p][0..3] = bf16(x[p][0..C-1]), 0 for the channels past C (C < 4): pictures for the first layer's bf16 products
