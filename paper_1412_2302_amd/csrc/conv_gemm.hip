@@ -307,8 +307,9 @@ static DirectPlan plan_direct(const GemmDims& d, double out_bytes, double* t_out
   return best;
 }
 // Channels per group that are no multiple of 64 cost instructions for every k-tile: there the tiles of gemm_bf16.h have to be
-// a fifth slower by their planner (second layer, 48 channels: at batch 256 six full rounds of 256-row tiles, which stay; at 37,
-// 100 and 128 three rounds, the last one part empty: inference 374 and 610 us, training 1943; here 360, 586, 1917).
+// a fifth slower by their planner (measured on the second layer, 48 channels, whose forward product has a kernel of its own now,
+// patch_conv.hip: at batch 256 six full rounds of 256-row tiles stayed; at 37, 100 and 128 three rounds, the last one part
+// empty, inference 374 and 610 us, training 1943, went to 360, 586, 1917).
 static bool direct_pays(const GemmDims& d, int Cg, int taps, double out_bytes) {
   if (taps > kDirectTaps) return false;
   if (Cg % kBKd == 0) return true;

@@ -663,7 +663,8 @@ AX_HD void store_bf16x4(uint16_t* p, const float4& v) {
 }
 
 // ================================ epilogues ==================================
-// kTransposed selects how a lane's accumulators map to the tile (see Tile::acc_row):
+// kTransposed selects how a lane's accumulators map to the tile in gemm_kernel (see Tile::acc_row; the kernels of the other
+// files store rows of the result, epi_rows.h):
 //  * true: apply4(m, n, v) is called for four consecutive valid columns n .. n+3 (n a multiple of 4) of row m
 //    (apply(m, n, v) for the elements of a ragged last quad): a quarter of the store instructions, each
 //    touching 32 rows.  Measured 3-4 % faster per launch where the tile is written once to its final place.

@@ -19,9 +19,9 @@
 // 82, fourth forward 83 | 82, fifth 62 | 50, second layer's data gradient (48 of 64 columns) 235 | 187; batch 64: 38 | 29,
 // 49 | 36, 38 | 24, 29 | 22.  In a pass with real weights the clock is lower: 113 | 105, 101 | 79, 91 | 95, 66 | 59, 235 |
 // 172, the data gradients of the fourth and fifth layers beside the dense layers' update 422 | 361; so forward products of
-// 192 columns with many tiles stay with gemm16.h (inference of 256 pictures 92 | 100 us).  The second layer's forward product
-// (48 channels, taps by octet) gains where its rounds are better filled: inference of 37 and 100 pictures 374 | 360 and 610 |
-// 586 us, of 256 1079 | 1084; see direct_fwd_ok().  Three stages of 32 k, 256-row tiles of eight waves and 192 x 192
+// 192 columns with many tiles stay with gemm16.h (inference of 256 pictures 92 | 100 us).  Forward products over 16 or 48
+// channels are patch_conv.hip's where they fit.  With the results stored a row of the matrix at a time (epi_rows.h) a pass
+// of 256 pictures has 105 | 87, 78, 95 | 78 and 59 | 46 us.  Three stages of 32 k, 256-row tiles of eight waves and 192 x 192
 // tiles (spills) were slower.  What bounds it: power, and a tile's first and last microseconds, about nine of the 26 of a 192
 // x 128 tile with K = 1728; see plan_direct().
 #pragma once

@@ -58,7 +58,7 @@ def trace_summary(a):
             continue
         lines.append(f"{k:102s} {c:6d} {t / 1e6:9.3f} {float(r['AverageNs']) / 1e3:9.2f} {float(r['MinNs']) / 1e3:8.2f} "
                      f"{float(r['MaxNs']) / 1e3:8.2f} {100 * t / tot:6.2f}")
-        if k.startswith(("gemm", "first_")):
+        if k.startswith(("gemm", "first_", "patch_")):
             g_calls += c
             g_ns += t
     lines += ["", f"total kernel time {tot / 1e6:.3f} ms",
@@ -102,7 +102,7 @@ def main():
         r_mib, w_mib = sum(fr) / len(fr) / 1024, sum(w) / len(w) / 1024
         u = util.get(k)
         lines.append(f"{k:102s} {len(fr):8d} {r_mib:10.2f} {w_mib:10.2f} {('%.1f' % (sum(u) / len(u))) if u else '-':>10s}")
-        if k.startswith(("gemm", "first_")):
+        if k.startswith(("gemm", "first_", "patch_")):
             tot += (sum(fr) + sum(w)) * 1024
             n += len(fr)
     per = tot / max(n, 1)
