@@ -65,7 +65,6 @@ AX_HD Vec2 vload2(const BufView& v, uint32_t off) {
 #ifdef AX_HOST_EMU
   return {buf_ld1(v, off), off == kOob ? 0.f : buf_ld1(v, off + 4)};
 #else
-  typedef unsigned v2u __attribute__((ext_vector_type(2)));
   return __builtin_bit_cast(Vec2, __builtin_amdgcn_raw_buffer_load_b64(v, (int)off, 0, 0));
 #endif
 }

@@ -109,6 +109,8 @@ struct Rows {
   }
   const TileRows* get() const { return any ? &r : nullptr; }
 };
+// values of a channel in the transformed tensor
+static double positions(const WinoGeom& g) { return 36.0 * g.tiles() * Rows(g).r.share; }
 bool wino_ok(const ConvGeom& c) {
   if ((c.k != 3 && c.k != 5) || c.stride != 1 || c.pad > c.k - 1 || c.cg() % 4 || c.og() % 4) return false;
   // the transformed tensors are 36/16 (tiles cut exactly) to ~4x larger than the activations, times the
@@ -182,7 +184,7 @@ int launch_wino_input(const ConvGeom& c, const float* x, float* V, hipStream_t s
   const WinoGeom g = fwd_geom(c);
   const int T = g.tiles();
   const long total = (long)T * nq_of(c) * (c.Cin / 4);
-  KernelScope ks("wino_in", 0, ((double)c.in_elems() + (double)T * 36 * nq_of(c) * c.Cin) * 4.0, st);
+  KernelScope ks("wino_in", 0, ((double)c.in_elems() + positions(g) * nq_of(c) * c.Cin) * 4.0, st);
   hipLaunchKernelGGL(g.ey || g.ex ? wino_in_kernel<true> : wino_in_kernel<false>, blocks_for(total), dim3(256), 0, st, g, c.cg(), x, V, total);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
@@ -198,7 +200,7 @@ int launch_wino_fwd(const ConvGeom& c, const float* x, const float* U, const flo
   const Rows rows(g);
   AX_TRY(launch_conv_fwd(p, V, U, nullptr, nullptr, 0, m, ws, st, nullptr, nullptr, nullptr, rows.get()));
   const long total = (long)T * (c.Cout / 4);
-  KernelScope ks("wino_out", 0, ((double)c.out_elems() + (double)T * 36 * c.Cout) * 4.0, st);
+  KernelScope ks("wino_out", 0, ((double)c.out_elems() + positions(g) * c.Cout) * 4.0, st);
   hipLaunchKernelGGL(g.ey || g.ex ? wino_out_kernel<true> : wino_out_kernel<false>, blocks_for(total), dim3(256), 0, st, g, c.og(), m, bias, relu,
                      (const float*)nullptr, y, total);
   AX_LAUNCH_CHECK();
@@ -209,7 +211,7 @@ int launch_wino_output_grad(const ConvGeom& c, const float* dy, float* yt, hipSt
   const WinoGeom g = fwd_geom(c);
   const int T = g.tiles();
   const long total = (long)T * (c.Cout / 4);
-  KernelScope ks("wino_dy", 0, ((double)c.out_elems() + (double)T * 36 * c.Cout) * 4.0, st);
+  KernelScope ks("wino_dy", 0, ((double)c.out_elems() + positions(g) * c.Cout) * 4.0, st);
   hipLaunchKernelGGL(g.ey || g.ex ? wino_dy_kernel<true> : wino_dy_kernel<false>, blocks_for(total), dim3(256), 0, st, g, c.og(), dy, yt, total);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
@@ -235,7 +237,7 @@ int launch_wino_bwd_data(const ConvGeom& c, const float* yt, const float* Ut, co
   // compute unit there is room for more of them, although patches across a band's edge are transformed in both.  37 pictures,
   // 222 | 666 workgroups (3 x 3 layers) 37 | 25 us and 28 | 19, 222 | 444 (5 x 5) 78 | 69; 128 pictures, 768 | 1536, 43 | 62.
   while (d.blocks() < 512 && d.bands < 4 && d.bands < c.H) ++d.bands;
-  KernelScope ks("wino_dx", 0, ((double)c.in_elems() * (gate ? 2 : 1) + (double)T * 36 * nq_of(c) * c.Cin) * 4.0, st);
+  KernelScope ks("wino_dx", 0, ((double)c.in_elems() * (gate ? 2 : 1) + positions(g) * nq_of(c) * c.Cin) * 4.0, st);
   hipLaunchKernelGGL(g.ey || g.ex ? wino_dx_kernel<true> : wino_dx_kernel<false>, dim3((unsigned)d.blocks()), dim3(256), (size_t)d.lds_vec4() * 16, st, d,
                      wino_dx_rounds(d), m, gate, dx);
   AX_LAUNCH_CHECK();
