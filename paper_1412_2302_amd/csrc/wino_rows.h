@@ -5,10 +5,12 @@
 
 namespace ax {
 
-// The short transform, F(1, 3): of the six points 1, -1 and infinity, with the taps as everybody else has them,
-//     y = m1 + m2 + m5,  m1 = -3 (d0 + d1) g(1),  m2 = -3 (d0 - d1) g(-1),  m5 = (d2 - d0) g(inf).
-constexpr unsigned kShortPoints = 1u << 1 | 1u << 2 | 1u << 5;
-AX_HD bool in_short(int i) { return kShortPoints >> i & 1u; }
+// The short transform, F(1, 3): three of the six points, 0, 1 and -1.  At these x^3 = x, so that a patch goes on as d3 = d1, d4 = d2
+// and the matrices of a whole tile serve it, taps and gradients as everybody else has them:
+//     y = m0 + m1 + m2,  m0 = 4 (d0 - d2) g(0),  m1 = -3 (d1 + d2) g(1),  m2 = 3 (d1 - d2) g(-1).
+// Errors of the products reach y with a variance of sum_p |G[p]|^2 |B[p]|^2 over the inputs that lie in the map: 5, 2.5 and 1 for
+// a padding of 0, 1 and 2, where the first output of a whole tile has 9.0, 4.0 and 1.  (1, -1 and infinity would have 5, 4 and 2.5.)
+AX_HD constexpr bool in_short(int i) { return i < 3; }
 // Rows of the transformed tensors that have position p = 6 * row + column
 struct RowRange {
   int lo, hi;

@@ -61,11 +61,15 @@ AX_HD Vec2 vload2(const float* p) {
   return {v.x, v.y};
 }
 
-AX_HD Vec2 vload2(const BufView& v, uint32_t off) {
+// uni: the same for every lane, added on the vector unit (as the load's scalar offset, 36 of them were spilled: 203 | 240 us for a
+// 5 x 5 layer of 144 channels on 117 maps of 27 x 27, 19 | 21 for the third layer's 3 x 3 on 37 pictures)
+AX_HD Vec2 vload2(const BufView& v, uint32_t off, uint32_t uni) {
 #ifdef AX_HOST_EMU
-  return {buf_ld1(v, off), off == kOob ? 0.f : buf_ld1(v, off + 4)};
+  if (off == kOob) return {0.f, 0.f};
+  if ((uint64_t)off + uni + 8 > v.bytes) emu_fail("a load of the transformed products lies outside them");
+  return {buf_ld1(v, off + uni), buf_ld1(v, off + uni + 4)};
 #else
-  return __builtin_bit_cast(Vec2, __builtin_amdgcn_raw_buffer_load_b64(v, (int)off, 0, 0));
+  return __builtin_bit_cast(Vec2, __builtin_amdgcn_raw_buffer_load_b64(v, (int)(off + uni), 0, 0));
 #endif
 }
 
@@ -137,28 +141,12 @@ AX_HD void wino_gt(const Vec4* m, Vec4* o) {
   o[2 * SO] = (1.f / 6.f) * (s34 - s12) + m5;
 }
 
-// The short maps (see WinoGeom): only positions 1, 2 and 5 are written or read
-template <int SI, int SO>
-AX_HD void wino_bt_short(const Vec4* d, Vec4* o) {
-  const Vec4 d0 = d[0], d1 = d[SI], d2 = d[2 * SI];
-  o[SO] = (-3.f) * (d0 + d1);
-  o[2 * SO] = 3.f * (d1 - d0);
-  o[5 * SO] = d2 - d0;
-}
-template <int SI, int SO, class V>
-AX_HD void wino_b_short(const V* m, V* o) {  // three rows of the patch
-  const V m1 = m[SI], m2 = m[2 * SI], m5 = m[5 * SI];
-  o[0] = (-3.f) * (m1 + m2) - m5;
-  o[SO] = 3.f * (m2 - m1);
-  o[2 * SO] = m5;
-}
-
 // ---- geometry of one transformed convolution -----------------------------------------------------
 // `H x W` is the tensor the 6x6 tiles are cut from (pad `pad` on every side), `OH x OW` the tensor
 // of 4x4 tiles (OH = H + 2*pad - 2).  Ctot = groups * Cg channels on the gathered side.
 // k x k taps are handled as nsub x nsub sub-kernels of 3x3 (k = 3: one, k = 5: four).
 // ey, ex: the last row and column of tiles hold one row and one column of outputs (OH, OW = 4n + 1) and take the short
-// transform below in that direction, so that 3 of the 6 positions of such a tile are made and multiplied: 441 products of 576
+// transform (in_short()) in that direction, so that 3 of the 6 positions of such a tile are made and multiplied: 441 products of 576
 // for a 13 x 13 map, every third position of which fell on four times as many outputs as there are.
 struct WinoGeom {
   int B, H, W, pad, OH, OW, th, tw, groups, k, nsub;
@@ -173,8 +161,17 @@ struct WinoGeom {
 struct WinoTile {
   int n, ty, tx;
 };
+template <bool SHORT>
 AX_HD WinoTile wino_tile(const WinoGeom& g, int t) {
   WinoTile r;
+  if (!SHORT) {
+    const int per = g.th * g.tw;
+    r.n = t / per;
+    const int rem = t - r.n * per;
+    r.ty = rem / g.tw;
+    r.tx = rem - r.ty * g.tw;
+    return r;
+  }
   const int nx = g.tw - g.ex, ny = g.th - g.ey, sy = g.short_y(), w = g.whole(), sx = g.short_x();
   if (t < sy) {
     r.n = t / nx;
@@ -198,7 +195,9 @@ AX_HD WinoTile wino_tile(const WinoGeom& g, int t) {
   }
   return r;
 }
+template <bool SHORT>
 AX_HD long wino_tile_row(const WinoGeom& g, int n, int ty, int tx) {
+  if (!SHORT) return ((long)n * g.th + ty) * g.tw + tx;
   const int nx = g.tw - g.ex, ny = g.th - g.ey;
   const bool sy = ty >= ny, sx = tx >= nx;
   if (sy && !sx) return (long)n * nx + tx;
@@ -209,32 +208,42 @@ AX_HD long wino_tile_row(const WinoGeom& g, int n, int ty, int tx) {
 
 // V[t][(p*groups + g)*(nq*Cg) + q*Cg + c] = (Bt d B)[p] of the 6x6 patch of x that sub-kernel q of tile t
 // reads (zero outside x).  idx enumerates (tile, sub-kernel, channel quad); x is [B][H][W][groups*Cg].
-template <bool SHORT = true>
+template <bool SHORT>
 AX_HD void wino_in_thread(const WinoGeom& g, int Cg, const float* x, float* V, long idx) {
   const int Ctot = g.groups * Cg, quads = Ctot / 4, nq = g.nq();
   const int t = (int)(idx / ((long)nq * quads));
   const int rem = (int)(idx - (long)t * nq * quads);
   const int q = rem / quads, c = 4 * (rem - q * quads);
   const int qy = q / g.nsub, qx = q - qy * g.nsub;
-  const WinoTile tl = wino_tile(g, t);
+  const WinoTile tl = wino_tile<SHORT>(g, t);
   const int y0 = 4 * tl.ty - g.pad + 3 * qy, x0 = 4 * tl.tx - g.pad + 3 * qx;
   const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;  // short: three rows, three columns
-  Vec4 u[36];
+  Vec4 d[36], u[36];
 #pragma unroll
-  for (int j = 0; j < 6; ++j) {  // columns
-    Vec4 d[6];
+  for (int i = 0; i < 6; ++i)
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
+    for (int j = 0; j < 6; ++j) {
       const int iy = y0 + i, ix = x0 + j;
       const bool in = (uint32_t)iy < (uint32_t)g.H && (uint32_t)ix < (uint32_t)g.W && (i < 3 || !sy) && (j < 3 || !sx);
-      d[i] = vzero();
-      if (in) d[i] = vload(x + (((long)tl.n * g.H + iy) * g.W + ix) * Ctot + c);
+      d[6 * i + j] = vzero();
+      if (in) d[6 * i + j] = vload(x + (((long)tl.n * g.H + iy) * g.W + ix) * Ctot + c);
     }
-    if (!sy)
-      wino_bt<1, 6>(d, u + j);
-    else
-      wino_bt_short<1, 6>(d, u + j);
+  if (sy) {  // the patch goes on as rows 1 and 2, see in_short()
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      d[18 + j] = d[6 + j];
+      d[24 + j] = d[12 + j];
+    }
   }
+  if (sx) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      d[6 * i + 3] = d[6 * i + 1];
+      d[6 * i + 4] = d[6 * i + 2];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 6; ++j) wino_bt<6, 6>(d + j, u + j);  // columns
   const int grp = c / Cg, cl = c - grp * Cg;
   const long pstride = (long)nq * Ctot;
   float* out = V + (long)t * 36 * pstride + (long)grp * nq * Cg + (long)q * Cg + cl;
@@ -242,26 +251,20 @@ AX_HD void wino_in_thread(const WinoGeom& g, int Cg, const float* x, float* V, l
   for (int i = 0; i < 6; ++i) {
     if (sy && !in_short(i)) continue;
     Vec4 r[6];
-    if (!sx) {
-      wino_bt<1, 1>(u + 6 * i, r);  // row i
+    wino_bt<1, 1>(u + 6 * i, r);  // row i
 #pragma unroll
-      for (int j = 0; j < 6; ++j) vstore(out + (long)(6 * i + j) * pstride, r[j]);
-    } else {
-      wino_bt_short<1, 1>(u + 6 * i, r);
-#pragma unroll
-      for (int j = 0; j < 6; ++j)
-        if (in_short(j)) vstore(out + (long)(6 * i + j) * pstride, r[j]);
-    }
+    for (int j = 0; j < 6; ++j)
+      if (in_short(j) || !sx) vstore(out + (long)(6 * i + j) * pstride, r[j]);
   }
 }
 
 // Y[t][(p*groups + g)*Og + o] = (A e At)[p] of the 4x4 block of dy that tile t owns (zero outside dy).
 // idx enumerates (tile, channel quad); dy is [B][OH][OW][groups*Og].
-template <bool SHORT = true>
+template <bool SHORT>
 AX_HD void wino_dy_thread(const WinoGeom& g, int Og, const float* dy, float* Y, long idx) {
   const int Ctot = g.groups * Og, quads = Ctot / 4;
   const int t = (int)(idx / quads), c = 4 * (int)(idx - (long)t * quads);
-  const WinoTile tl = wino_tile(g, t);
+  const WinoTile tl = wino_tile<SHORT>(g, t);
   Vec4 e[16], u[24];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -271,72 +274,59 @@ AX_HD void wino_dy_thread(const WinoGeom& g, int Og, const float* dy, float* Y, 
       e[4 * i + j] = vzero();
       if (oy < g.OH && ox < g.OW) e[4 * i + j] = vload(dy + (((long)tl.n * g.OH + oy) * g.OW + ox) * Ctot + c);
     }
-  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) wino_a<4, 4>(e + j, u + j);  // columns: 4 -> 6 rows of 4
+  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;  // short: one row, one column of outputs
   const int grp = c / Og, cl = c - grp * Og;
   float* out = Y + (long)t * 36 * Ctot + (long)grp * Og + cl;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) wino_a<4, 4>(e + j, u + j);  // columns: 4 -> 6 rows of 4; of one row the short positions have that row
-#pragma unroll
   for (int i = 0; i < 6; ++i) {
     if (sy && !in_short(i)) continue;
-    Vec4 row[4];
+    Vec4 r[6];
+    wino_a<1, 1>(u + 4 * i, r);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      row[j] = u[4 * i + j];
-      if (sy) row[j] = e[j];
-    }
-    if (!sx) {
-      Vec4 r[6];
-      wino_a<1, 1>(row, r);
-#pragma unroll
-      for (int j = 0; j < 6; ++j) vstore(out + (long)(6 * i + j) * Ctot, r[j]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 6; ++j)
-        if (in_short(j)) vstore(out + (long)(6 * i + j) * Ctot, row[0]);
-    }
+    for (int j = 0; j < 6; ++j)
+      if (in_short(j) || !sx) vstore(out + (long)(6 * i + j) * Ctot, r[j]);
   }
 }
 
 // y[n][4ty+i][4tx+j][c] = post((At m A)[i][j]) from M[t][(p*groups + g)*Ng + c'], inside OH x OW only.
 // post: + bias[c] and ReLU (relu != 0), or zero where gate[same index] <= 0; bias and gate may be null.
-template <bool SHORT = true>
+template <bool SHORT>
 AX_HD void wino_out_thread(const WinoGeom& g, int Ng, const float* M, const float* bias, int relu, const float* gate,
                            float* y, long idx) {
   const int Ctot = g.groups * Ng, quads = Ctot / 4;
   const int t = (int)(idx / quads), c = 4 * (int)(idx - (long)t * quads);
-  const WinoTile tl = wino_tile(g, t);
+  const WinoTile tl = wino_tile<SHORT>(g, t);
   const int grp = c / Ng, cl = c - grp * Ng;
   const float* in = M + (long)t * 36 * Ctot + (long)grp * Ng + cl;
-  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;  // short: one row, one column of outputs
+  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;  // short: positions past the third add nothing
   Vec4 u[24];
 #pragma unroll
   for (int j = 0; j < 6; ++j) {
-    if (sx && !in_short(j)) continue;
     Vec4 col[6];
 #pragma unroll
-    for (int i = 0; i < 6; ++i)
-      if (!sy || in_short(i)) col[i] = vload(in + (long)(6 * i + j) * Ctot);
-    if (!sy)
-      wino_at<1, 6>(col, u + j);  // u[i][j], 4 rows of 6
-    else
-      u[j] = col[1] + col[2] + col[5];
+    for (int i = 0; i < 6; ++i) {
+      if (!SHORT) {
+        col[i] = vload(in + (long)(6 * i + j) * Ctot);
+        continue;
+      }
+      col[i] = vzero();
+      if ((in_short(i) || !sy) && (in_short(j) || !sx)) col[i] = vload(in + (long)(6 * i + j) * Ctot);
+    }
+    wino_at<1, 6>(col, u + j);  // u[i][j], 4 rows of 6
   }
   Vec4 b = vzero();
   if (bias) b = vload(bias + c);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     Vec4 r[4];
+    wino_at<1, 1>(u + 6 * i, r);
     const int oy = 4 * tl.ty + i;
-    if (oy >= g.OH) continue;
-    if (!sx)
-      wino_at<1, 1>(u + 6 * i, r);
-    else
-      r[0] = u[6 * i + 1] + u[6 * i + 2] + u[6 * i + 5];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int ox = 4 * tl.tx + j;
-      if (ox < g.OW) {
+      if (oy < g.OH && ox < g.OW) {
         const long o = (((long)tl.n * g.OH + oy) * g.OW + ox) * Ctot + c;
         Vec4 v = r[j] + b;
         if (relu) {
@@ -485,13 +475,13 @@ AX_HD void wino_dx_round_phases(const WinoDx& d, const WinoDxPlan& p, int round,
   *lo = wino_dx_phase_of(p, first, &before);
   *hi = wino_dx_phase_of(p, last, &before);
 }
-// One task of a thread: phase < 0 means none.  z = B m Bt of the patch, to be added at (y0 + i, x0 + j).
+// One task of a thread: phase < 0 means none.  z = B m Bt of the patch, to be added at (y0 + i, x0 + j) in front of (y1, x1).
 struct WinoDxTask {
-  int phase, y0, x0;
+  int phase, y0, x0, y1, x1;
 };
 // Round r of a block: every worker loads and transforms one patch (all threads at once: this is where the
 // memory traffic is), ...
-template <bool SHORT = true>
+template <bool SHORT>
 AX_HD WinoDxTask wino_dx_load(const WinoDx& d, const WinoDxPlan& p, const float* M, int tid, int round, Vec2* z) {
   const WinoGeom& g = d.g;
   const int nq = g.nq(), Ctot = d.Ctot();
@@ -499,7 +489,7 @@ AX_HD WinoDxTask wino_dx_load(const WinoDx& d, const WinoDxPlan& p, const float*
   const int cp = tid % d.lanes(), worker = tid / d.lanes(), workers = d.workers();
   const int c = 4 * bk.cblk * d.CQ + 2 * cp;  // Ctot and Cg are multiples of four: the pair lies in one group
   WinoDxTask task;
-  task.phase = -1; task.y0 = 0; task.x0 = 0;
+  task.phase = -1; task.y0 = 0; task.x0 = 0; task.y1 = bk.h1; task.x1 = g.W;
   const int j = round * workers + worker;
   if (c >= Ctot || j >= p.tk.count) return task;
   int before;
@@ -514,46 +504,45 @@ AX_HD WinoDxTask wino_dx_load(const WinoDx& d, const WinoDxPlan& p, const float*
   task.y0 = y0; task.x0 = x0;
   const int grp = c / d.Cg, cl = c - grp * d.Cg;
   const long pstride = (long)nq * Ctot;
-  const long t = wino_tile_row(g, bk.n, ty, tx);
+  const long t = wino_tile_row<SHORT>(g, bk.n, ty, tx);
   const bool sy = SHORT && g.ey && ty == g.th - 1, sx = SHORT && g.ex && tx == g.tw - 1;  // short: three rows, three columns of the patch
   const float* in = M + t * 36 * pstride + (long)grp * nq * d.Cg + (long)q * d.Cg + cl;
+  // where a short tile has no such position the load is outside: no branches, and no arithmetic but the four starts
   const BufView mv = make_view(M, (uint32_t)((long)g.tiles() * 36 * pstride * 4));
-  const uint32_t at = (uint32_t)((in - M) * 4);
+  const uint32_t at = (uint32_t)((in - M) * 4), step = (uint32_t)pstride * 4u;
+  const uint32_t at_y = sy ? kOob : at, at_x = sx ? kOob : at, at_yx = sy || sx ? kOob : at;
   Vec2 u[36];
 #pragma unroll
   for (int jj = 0; jj < 6; ++jj) {
-    Vec2 col[6], t6[6];
+    Vec2 col[6];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      col[i] = Vec2{0.f, 0.f};
-      if (!SHORT)
-        col[i] = vload2(in + (long)(6 * i + jj) * pstride);
-      else  // without a branch
-        col[i] = vload2(mv, (!sy || in_short(i)) && (!sx || in_short(jj)) ? at + (uint32_t)(6 * i + jj) * (uint32_t)pstride * 4u : kOob);
-      t6[i] = Vec2{0.f, 0.f};  // what is not there adds zero
-    }
-    if (!sy)
-      wino_b<1, 1>(col, t6);
-    else
-      wino_b_short<1, 1>(col, t6);
-#pragma unroll
-    for (int i = 0; i < 6; ++i) u[6 * i + jj] = t6[i];
+    for (int i = 0; i < 6; ++i)
+      col[i] = !SHORT ? vload2(in + (long)(6 * i + jj) * pstride)
+                      : vload2(mv, in_short(i) ? (in_short(jj) ? at : at_x) : (in_short(jj) ? at_y : at_yx), (uint32_t)(6 * i + jj) * step);
+    wino_b<1, 6>(col, u + jj);  // u[i][jj]
   }
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    Vec2 t6[6];
+  for (int i = 0; i < 6; ++i) wino_b<1, 1>(u + 6 * i, z + 6 * i);
+  if (sy) {  // rows 3 and 4 are what rows 1 and 2 went on as, see in_short()
+    task.y1 = y0 + 3 < bk.h1 ? y0 + 3 : bk.h1;
 #pragma unroll
-    for (int jj = 0; jj < 6; ++jj) t6[jj] = Vec2{0.f, 0.f};
-    if (!sx)
-      wino_b<1, 1>(u + 6 * i, t6);
-    else
-      wino_b_short<1, 1>(u + 6 * i, t6);
+    for (int jj = 0; jj < 6; ++jj) {
+      z[6 + jj] = z[6 + jj] + z[18 + jj];
+      z[12 + jj] = z[12 + jj] + z[24 + jj];
+    }
+  }
+  if (sx) {
+    task.x1 = x0 + 3 < g.W ? x0 + 3 : g.W;
 #pragma unroll
-    for (int jj = 0; jj < 6; ++jj) z[6 * i + jj] = t6[jj];
+    for (int i = 0; i < 6; ++i) {
+      z[6 * i + 1] = z[6 * i + 1] + z[6 * i + 3];
+      z[6 * i + 2] = z[6 * i + 2] + z[6 * i + 4];
+    }
   }
   return task;
 }
 // ... then the patches are added to the picture phase by phase (a barrier after each call).
+template <bool SHORT>
 AX_HD void wino_dx_add(const WinoDx& d, const WinoDxPlan& p, Vec4* lds, int tid, const WinoDxTask& task, const Vec2* z,
                        int phase) {
   if (task.phase != phase) return;
@@ -566,7 +555,7 @@ AX_HD void wino_dx_add(const WinoDx& d, const WinoDxPlan& p, Vec4* lds, int tid,
 #pragma unroll
     for (int jj = 0; jj < 6; ++jj) {
       const int ix = task.x0 + jj;
-      if (iy >= bk.h0 && iy < bk.h1 && (uint32_t)ix < (uint32_t)d.g.W) {
+      if (iy >= bk.h0 && iy < (SHORT ? task.y1 : bk.h1) && (uint32_t)ix < (uint32_t)(SHORT ? task.x1 : d.g.W)) {
         Vec2* acc = half + ((long)(iy - bk.h0) * d.g.W + ix) * d.lanes() + cp;
         *acc = *acc + z[6 * i + jj];
       }

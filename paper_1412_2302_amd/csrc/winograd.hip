@@ -17,7 +17,7 @@ __global__ void __launch_bounds__(256) wino_in_kernel(WinoGeom g, int Cg, const 
   if (idx < total) wino_in_thread<SHORT>(g, Cg, x, V, idx);
 }
 template <bool SHORT>
-__global__ void __launch_bounds__(256) wino_dy_kernel(WinoGeom g, int Og, const float* __restrict__ dy,
+__global__ void __launch_bounds__(256, 4) wino_dy_kernel(WinoGeom g, int Og, const float* __restrict__ dy,
                                                        float* __restrict__ Y, long total) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < total) wino_dy_thread<SHORT>(g, Og, dy, Y, idx);
@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(256) wino_dx_kernel(WinoDx d, int rounds, cons
     int lo, hi;  // the same for every thread of the block
     wino_dx_round_phases(d, plan, r, &lo, &hi);
     for (int ph = lo; ph <= hi; ++ph) {
-      wino_dx_add(d, plan, lds, tid, task, z, ph);
+      wino_dx_add<SHORT>(d, plan, lds, tid, task, z, ph);
       __syncthreads();
     }
   }
