@@ -691,7 +691,11 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
       for (int j = 0; j < kFc; ++j) {
         Dense& f = n->fc[j];
         if (!late[j]) {
-          AX_TRY(update_range(n, f.w_off, f.w_off + (size_t)f.in * f.out, n->upd_stream));
+          // One launch for neighbours: it starts on a quad, where the first layer does or behind a late one, whose widths are
+          // quads; the layers within it may not.
+          size_t end = f.w_off + (size_t)f.in * f.out;
+          while (j + 1 < kFc && !late[j + 1]) end += (size_t)n->fc[j + 1].in * n->fc[j + 1].out, ++j;
+          AX_TRY(update_range(n, f.w_off, end, n->upd_stream));
           continue;
         }
         ProfContext pc(f.lab[2]);

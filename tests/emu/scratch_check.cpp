@@ -2,7 +2,7 @@
 //
 // The HIP calls that the library makes are defined here, so that a launch only reports its kernel and arguments.  Every
 // kernel that adds slices up reads exactly what the product in front of it wrote: that range has to lie inside one buffer
-// of the handle's workspace (workspace_pieces()).
+// of the handle's workspace (workspace_pieces()).  And every update, which runs over quads, has to start on one.
 //
 //   scratch_check CASES SEED LAYERS: CASES holds a line of numbers per handle (alexnet_config_t from batch to fc, then
 //   precision and flags); LAYERS random layers are checked after them.
@@ -51,6 +51,13 @@ static void range(const std::string& kernel, const void* p, size_t floats) {
   printf("\n");
 }
 
+// kernels that read and write four floats at a time from these pointers on
+static void quads(const std::string& kernel, const void* w, const void* v, const void* g) {
+  if (((uintptr_t)w | (uintptr_t)v | (uintptr_t)g) % 16 == 0) return;
+  if (++g_bad > 20) return;
+  printf("%s: %s takes quads from %p, %p, %p on\n", g_what.c_str(), kernel.c_str(), w, v, g);
+}
+
 template <class T>
 static T arg(void** args, int i) {
   return *static_cast<T*>(args[i]);
@@ -68,11 +75,18 @@ static void launched(const std::string& k, void** a) {
     range(k, arg<float*>(a, 0), (size_t)arg<int>(a, 1) * arg<size_t>(a, 2) * arg<int>(a, 3));
   else if (is("ax::reduce_slabs_unpack_kernel("))  // ws, slices, slab
     range(k, arg<float*>(a, 0), (size_t)arg<int>(a, 1) * arg<size_t>(a, 2));
+  else if (is("ax::sgd_update_kernel("))
+    quads(k, arg<float*>(a, 0), arg<float*>(a, 1), arg<float*>(a, 2));
   else if (is("ax::reduce_slabs_batch_kernel(")) {
     const WgradTail& t = *static_cast<WgradTail*>(a[0]);
     for (int i = 0; i < t.n; ++i)
       if (t.job[i].nsplit > 1) range(k, t.job[i].slices, (size_t)t.job[i].groups36 * t.job[i].nsplit * t.job[i].slab);
-  } else if (k.find("colsum_batch_stage2(") != std::string::npos) {
+  }
+  if (is("ax::sgd_colsum_batch_stage2(")) {
+    const SgdArgs& u = *static_cast<SgdArgs*>(a[1]);
+    quads(k, u.w, u.v, u.g);
+  }
+  if (k.find("colsum_batch_stage2(") != std::string::npos) {
     const ColsumBatch& b = *static_cast<ColsumBatch*>(a[0]);
     for (int i = 0; i < b.n; ++i) range(k, b.job[i].part, (size_t)b.job[i].nparts * b.job[i].cols);
   }

@@ -30,7 +30,12 @@ def test_slices_stay_inside_their_buffers(tmp_path):
     # every batch up to 64 and from there on every 13th to 2048: the lines between kernels and slice counts lie anywhere
     batches = [*range(1, 65), *range(65, 2049, 13)]
     cases.write_text("\n".join(line(wl, b, precision, flags) for wl in S.WORKLOADS.values() for b in batches
-                               for precision, flags in ((0, 0), (1, 0), (0, 1))))
+                               for precision, flags in ((0, 0), (1, 0), (0, 1))) + "\n")
+    # dense layers that start between quads behind one another, in vectors whose ends do not
+    with cases.open("a") as f:
+        for wl, fc in ((wl, fc) for wl in S.WORKLOADS.values() for fc in ((3, 5, 1), (201, 135, 35), (5, 512, 4), (64, 7, 12))):
+            for b in (1, 2, 4, 7, 8, 16, 37, 64, 200):
+                f.write("\n".join(line(dict(wl, fc=fc), b, precision) for precision in (0, 1)) + "\n")
     r = subprocess.run([exe, str(cases), "7", "6000"], capture_output=True, text=True, timeout=1500)
     assert r.returncode == 0, r.stdout[-4000:] + r.stderr[-2000:]
     assert r.stdout.rstrip().endswith(" 0 outside")
