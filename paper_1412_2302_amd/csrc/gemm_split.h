@@ -437,6 +437,43 @@ __device__ __forceinline__ void store_rows(const EpiSlabSwapped& e, const v16f (
 }
 #endif
 
+// The one-dimensional grid of gx * gy * (groups * nsplit) workgroups (see xcd_tile).  The divisors are constants of the
+// launch, so that a workgroup's place is worked out on the scalar unit and the buffer descriptors that depend on it
+// stay in scalar registers.
+// of: rows (1) or the reduction (2) of the product run over the rows that a group's position has in a transformed layer with short
+// tiles (wino_rows(), group = position * positions.d + group of channels); the sizes of the launch are those of all rows.  Tiles of
+// rows that a group does not have are nobody's, and slices share what there is.
+struct SplitGrid {
+  FastDiv gx, gy, nsplit;
+  int of;
+  FastDiv positions;
+  int short_y, whole, short_x, tiles;
+};
+// A workgroup's first row and k, and the ends of both; m0 >= M: nobody's tile
+struct SplitPlace {
+  int m0, M, kbeg, kend;
+};
+template <class T>
+AX_HD SplitPlace split_place(const SplitGrid& grid, uint32_t g, int split, int m0, int M, int K, int kchunk) {
+  SplitPlace p{m0, M, split * kchunk, 0};
+  p.kend = K < p.kbeg + kchunk ? K : p.kbeg + kchunk;
+  if (grid.of == 0) return p;  // uniform
+  const RowRange r = wino_rows((int)fdiv(g, grid.positions), grid.short_y, grid.whole, grid.short_x, grid.tiles);
+  if (grid.of == 1) {
+    p.m0 += r.lo;
+    p.M = r.hi;
+  } else {
+    const uint32_t steps = (uint32_t)(r.hi - r.lo + T::BK - 1) / T::BK;
+    const int per = (int)fdiv(steps + grid.nsplit.d - 1, grid.nsplit) * T::BK;
+    p.kbeg = r.lo + split * per;
+    p.kend = r.hi < p.kbeg + per ? r.hi : p.kbeg + per;
+  }
+  return p;
+}
+AX_HD void split_row_limit(DenseParams& a, int rows) { a.R = rows; }
+template <class P>
+AX_HD void split_row_limit(P&, int) {}
+
 // ================================= kernel ====================================
 #ifndef AX_HOST_EMU
 template <class L, int TT>
@@ -543,21 +580,6 @@ struct SplitMinBlocks {
   static constexpr int value = T::BM * T::BN < 128 * 128 ? 3 : 2;
 };
 
-// The one-dimensional grid of gx * gy * (groups * nsplit) workgroups (see xcd_tile).  The divisors are constants of the
-// launch, so that a workgroup's place is worked out on the scalar unit and the buffer descriptors that depend on it
-// stay in scalar registers.
-// of: rows (1) or the reduction (2) of the product run over the rows that a group's position has in a transformed layer with short
-// tiles (wino_rows(), group = position * positions.d + group of channels); the sizes of the launch are those of all rows.  Tiles of
-// rows that a group does not have are nobody's, and slices share what there is.
-struct SplitGrid {
-  FastDiv gx, gy, nsplit;
-  int of;
-  FastDiv positions;
-  int short_y, whole, short_x, tiles;
-};
-__device__ __forceinline__ void split_row_limit(DenseParams& a, int rows) { a.R = rows; }
-template <class P>
-__device__ __forceinline__ void split_row_limit(P&, int) {}
 template <class T, class AL, class BL, class Epi>
 __global__ void __launch_bounds__(kThreads, (SplitMinBlocks<T>::value))
 gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int N, int K, int kchunk,
@@ -571,23 +593,12 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
   const uint32_t tile = xcd * q8 + min(xcd, r8) + (L >> 3);  // as in xcd_tile
   const uint32_t rest = fdiv(tile, grid.gy), z = fdiv(rest, grid.gx), g = fdiv(z, grid.nsplit);
   const int split = (int)(z - g * grid.nsplit.d);
-  int m0 = (int)(rest - z * grid.gx.d) * T::BM;
   const int n0 = (int)(tile - rest * grid.gy.d) * T::BN;
-  int kbeg = split * kchunk;
-  int kend = min(K, kbeg + kchunk);
-  if (grid.of != 0) {  // uniform
-    const RowRange r = wino_rows((int)fdiv(g, grid.positions), grid.short_y, grid.whole, grid.short_x, grid.tiles);
-    if (grid.of == 1) {
-      m0 += r.lo;
-      M = r.hi;
-      if (m0 >= M) return;
-      split_row_limit(ap, M);
-    } else {
-      const uint32_t steps = (uint32_t)(r.hi - r.lo + T::BK - 1) / T::BK;
-      const int per = (int)fdiv(steps + grid.nsplit.d - 1, grid.nsplit) * T::BK;
-      kbeg = r.lo + split * per;
-      kend = min(r.hi, kbeg + per);
-    }
+  const SplitPlace at = split_place<T>(grid, g, split, (int)(rest - z * grid.gx.d) * T::BM, M, K, kchunk);
+  const int m0 = at.m0, kbeg = at.kbeg, kend = at.kend;
+  if (grid.of == 1) {
+    if (m0 >= at.M) return;
+    split_row_limit(ap, at.M);
   }
   const int nt = kend > kbeg ? (kend - kbeg + T::BK - 1) / T::BK : 0;
 
@@ -648,7 +659,7 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
                                               reinterpret_cast<float*>(Bs[0]), acc);
   }
 
-  store_rows(ep, acc, m0 + wm * (T::TM * 32), n0 + wn * (T::TN * 32), M, N, lane);
+  store_rows(ep, acc, m0 + wm * (T::TM * 32), n0 + wn * (T::TN * 32), at.M, N, lane);
 }
 #endif  // AX_HOST_EMU
 

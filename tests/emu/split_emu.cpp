@@ -33,7 +33,8 @@ static float frand() { return (float)rand() / RAND_MAX * 2.f - 1.f; }
 
 template <class T, class AL, class BL, class Epi>
 static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, int M, int N, int K, int kchunk,
-                      int nsplit, int groups) {
+                      int nsplit, int groups, SplitGrid grid = {}, const std::vector<int>& only = {}) {
+  grid.nsplit = make_fastdiv((uint32_t)nsplit);
   const int gx = (M + T::BM - 1) / T::BM, gy = (N + T::BN - 1) / T::BN, gz = groups * nsplit;
   std::vector<uint32_t> As(AL::UNITS * 4), Bs(BL::UNITS * 4);
   std::vector<float> acc((size_t)T::BM * T::BN), lo(acc.size());
@@ -41,8 +42,15 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
     for (int by = 0; by < gy; ++by)
       for (int bx = 0; bx < gx; ++bx) {
         const int g = bz / nsplit, split = bz - g * nsplit;
-        const int m0 = bx * T::BM, n0 = by * T::BN;
-        const int kbeg = split * kchunk, kend = std::min(K, kbeg + kchunk);
+        if (!only.empty() && std::find(only.begin(), only.end(), g) == only.end()) continue;
+        const int n0 = by * T::BN;
+        const SplitPlace at = split_place<T>(grid, (uint32_t)g, split, bx * T::BM, M, K, kchunk);
+        const int m0 = at.m0, kbeg = at.kbeg, kend = at.kend;
+        typename AL::Params mine = ap;
+        if (grid.of == 1) {
+          if (m0 >= at.M) continue;
+          split_row_limit(mine, at.M);
+        }
         const int nt = kend > kbeg ? (kend - kbeg + T::BK - 1) / T::BK : 0;
         std::fill(acc.begin(), acc.end(), 0.f);
         std::fill(lo.begin(), lo.end(), 0.f);
@@ -52,7 +60,7 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
           std::fill(As.begin(), As.end(), 0x7fc07fc0u);  // two bf16 NaNs: an unwritten slot shows up
           std::fill(Bs.begin(), Bs.end(), 0x7fc07fc0u);
           for (int tid = 0; tid < kThreads; ++tid) {
-            AL al(ap, g, tid, m0, kbeg);
+            AL al(mine, g, tid, m0, kbeg);
             BL bl(bp, g, tid, n0, kbeg);
             float4 ra[AL::NL], rb[BL::NL];
             for (int u = 0; u <= t; ++u) {  // offsets run along with k
@@ -93,7 +101,7 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
           std::fill(Bs.begin(), Bs.end(), 0x7fc00000u);
           float *ar = reinterpret_cast<float*>(As.data()), *br = reinterpret_cast<float*>(Bs.data());
           for (int tid = 0; tid < kThreads; ++tid) {
-            AL al(ap, g, tid, m0, kbeg);
+            AL al(mine, g, tid, m0, kbeg);
             BL bl(bp, g, tid, n0, kbeg);
             float4 ra[AL::NL], rb[BL::NL];
             for (int u = 0; u <= t; ++u) {
@@ -108,7 +116,7 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
               for (int k = 0; k < T::BK; k += 2)
                 acc[(size_t)i * T::BN + j] += ar[i * kRawLd + k] * br[j * kRawLd + k] + ar[i * kRawLd + k + 1] * br[j * kRawLd + k + 1];
         }
-        for (int i = 0; i < T::BM && m0 + i < M; ++i)
+        for (int i = 0; i < T::BM && m0 + i < at.M; ++i)
           for (int j = 0; j < T::BN && n0 + j < N; ++j) e.apply(m0 + i, n0 + j, acc[(size_t)i * T::BN + j]);
       }
 }
@@ -194,6 +202,70 @@ static void dense_case(int M, int N, int K, int ns, int ng) {
   run("rows,rows", false, false);
   delete[] a;
   delete[] b;
+}
+
+// Products of a transformed layer with short tiles: rows (of 1) or the reduction (of 2) run over the rows of a group's position only.
+// What lies outside those is NaN, in operands and results, and stays so.
+template <class T>
+static void short_case(int of, int short_y, int whole, int short_x, int both, int G, int K, int N, int ns) {
+  const int tiles = short_y + whole + short_x + both, Z = 36 * G;
+  const std::vector<int> groups = {0, 2 * G, 3 * G + G - 1, 18 * G, 35 * G + G - 1};  // both in, once more, row only, column only, neither
+  SplitGrid grid{};
+  grid.of = of;
+  grid.positions = make_fastdiv((uint32_t)G);
+  grid.short_y = short_y; grid.whole = whole; grid.short_x = short_x; grid.tiles = tiles;
+  std::vector<float> a((size_t)tiles * Z * K, NAN), b(of == 1 ? (size_t)Z * K * N : (size_t)tiles * Z * N, NAN);
+  for (int g : groups) {
+    const RowRange r = wino_rows(g / G, short_y, whole, short_x, tiles);
+    for (int t = r.lo; t < r.hi; ++t)
+      for (int k = 0; k < K; ++k) a[((size_t)t * Z + g) * K + k] = frand();
+    if (of == 1)
+      for (size_t i = 0; i < (size_t)K * N; ++i) b[(size_t)g * K * N + i] = frand();
+    else
+      for (int t = r.lo; t < r.hi; ++t)
+        for (int n = 0; n < N; ++n) b[((size_t)t * Z + g) * N + n] = frand();
+  }
+  std::vector<float> got;
+  std::vector<double> want;
+  if (of == 1) {  // c[t][g][n] = sum_k a[t][g][k] b[g][k][n]
+    std::vector<float> c((size_t)tiles * Z * N, NAN);
+    const DenseParams pa{a.data(), (long)Z * K, K, tiles, (uint32_t)(a.size() * 4)}, pb{b.data(), N, (long)K * N, N, (uint32_t)(b.size() * 4)};
+    emu_split<T, SplitKInner<T::BM>, SplitRowInner<T::BN>, EpiBiasAct>(pa, pb, EpiBiasAct{c.data(), (long)Z * N, nullptr, 0, N, 0, 0, nullptr},
+                                                                       tiles, N, K, (K + 15) / 16 * 16, 1, Z, grid, groups);
+    for (int g : groups) {
+      const RowRange r = wino_rows(g / G, short_y, whole, short_x, tiles);
+      for (int t = 0; t < tiles; ++t)
+        for (int n = 0; n < N; ++n) {
+          const float v = c[((size_t)t * Z + g) * N + n];
+          if (t < r.lo || t >= r.hi) {
+            if (!std::isnan(v)) ++failures, printf("short rows FAIL: row %d of group %d was written\n", t, g);
+            continue;
+          }
+          double s = 0;
+          for (int k = 0; k < K; ++k) s += (double)a[((size_t)t * Z + g) * K + k] * b[((size_t)g * K + k) * N + n];
+          got.push_back(v);
+          want.push_back(s);
+        }
+    }
+  } else {  // c[g][k][n] = sum_t a[t][g][k] b[t][g][n], in slices
+    const long slab = (long)K * N;
+    std::vector<float> c((size_t)Z * ns * slab, NAN);
+    const DenseParams pa{a.data(), (long)Z * K, K, K, (uint32_t)(a.size() * 4)}, pb{b.data(), (long)Z * N, N, N, (uint32_t)(b.size() * 4)};
+    emu_split<T, SplitRowInner<T::BM>, SplitRowInner<T::BN>, EpiSlab>(pa, pb, EpiSlab{c.data(), slab, N, nullptr}, K, N, tiles,
+                                                                      (tiles + 16 * ns - 1) / (16 * ns) * 16, ns, Z, grid, groups);
+    for (int g : groups) {
+      const RowRange r = wino_rows(g / G, short_y, whole, short_x, tiles);
+      for (long i = 0; i < slab; ++i) {
+        float v = 0.f;
+        for (int z = 0; z < ns; ++z) v += c[((size_t)g * ns + z) * slab + i];
+        double s = 0;
+        for (int t = r.lo; t < r.hi; ++t) s += (double)a[((size_t)t * Z + g) * K + i / N] * b[((size_t)t * Z + g) * N + i % N];
+        got.push_back(v);
+        want.push_back(s);
+      }
+    }
+  }
+  check(of == 1 ? "short rows" : "short sums", tiles, N, K, got, want);
 }
 
 // first-layer shapes in run mode: forward and weight gradient of an unpadded convolution over three-channel pictures
@@ -335,6 +407,12 @@ int main() {
     dense_case<S96>(128, 96, 16, 1, 3);
     dense_case<S64>(60, 68, 36, 2, 2);
     dense_case<Tile<64, 128, 16, 2, 2>>(50, 132, 40, 2, 1);
+    short_case<S128>(1, 27, 81, 27, 9, 1, 20, 36, 1);  // a row tile that ends inside a range, and one that starts inside
+    short_case<S64>(1, 5, 128, 7, 3, 2, 12, 8, 1);
+    short_case<S64>(1, 0, 30, 10, 0, 1, 8, 4, 1);      // one direction only
+    short_case<S64>(2, 27, 81, 27, 9, 1, 20, 12, 1);   // sums that start and end between k-tiles
+    short_case<S64>(2, 3, 9, 3, 1, 2, 8, 8, 3);        // a slice without a k-tile
+    short_case<S64>(2, 10, 50, 0, 0, 1, 8, 8, 4);
     run_case<S96>(2, 75, 76, 96, 11, 4, 1);   // 17 pixels a row: a k-tile crosses a row's end, and a picture's
     run_case<S96>(3, 41, 45, 20, 7, 2, 3);    // runs of 24, slices that start inside a run and inside a row
     run_case<S128>(1, 22, 36, 132, 5, 1, 2);  // runs of 16, 32 pixels a row
