@@ -449,6 +449,12 @@ struct SplitGrid {
   FastDiv positions;
   int short_y, whole, short_x, tiles;
 };
+// the launch's `turn`-th group
+AX_HD uint32_t split_group(const SplitGrid& grid, uint32_t turn) {
+  if (grid.of == 0) return turn;
+  const uint32_t s = fdiv(turn, grid.positions);
+  return (uint32_t)wino_spread((int)s) * grid.positions.d + (turn - s * grid.positions.d);
+}
 // A workgroup's first row and k, and the ends of both; m0 >= M: nobody's tile
 struct SplitPlace {
   int m0, M, kbeg, kend;
@@ -591,10 +597,11 @@ gemm_split_kernel(typename AL::Params ap, typename BL::Params bp, Epi ep, int M,
   const int wm = wave % T::WAVES_M, wn = wave / T::WAVES_M;
   const uint32_t total = gridDim.x, L = blockIdx.x, q8 = total >> 3, r8 = total & 7, xcd = L & 7;
   const uint32_t tile = xcd * q8 + min(xcd, r8) + (L >> 3);  // as in xcd_tile
-  const uint32_t rest = fdiv(tile, grid.gy), z = fdiv(rest, grid.gx), g = fdiv(z, grid.nsplit);
-  const int split = (int)(z - g * grid.nsplit.d);
+  const uint32_t rest = fdiv(tile, grid.gy), place = fdiv(rest, grid.gx), turn = fdiv(place, grid.nsplit);
+  const int split = (int)(place - turn * grid.nsplit.d);
+  const uint32_t g = split_group(grid, turn), z = g * grid.nsplit.d + (uint32_t)split;
   const int n0 = (int)(tile - rest * grid.gy.d) * T::BN;
-  const SplitPlace at = split_place<T>(grid, g, split, (int)(rest - z * grid.gx.d) * T::BM, M, K, kchunk);
+  const SplitPlace at = split_place<T>(grid, g, split, (int)(rest - place * grid.gx.d) * T::BM, M, K, kchunk);
   const int m0 = at.m0, kbeg = at.kbeg, kend = at.kend;
   if (grid.of == 1) {
     if (m0 >= at.M) return;

@@ -11,6 +11,13 @@ namespace ax {
 // Errors of the products reach y with a variance of sum_p |G[p]|^2 |B[p]|^2 over the inputs that lie in the map: 5, 2.5 and 1 for
 // a padding of 0, 1 and 2, where the first output of a whole tile has 9.0, 4.0 and 1.  (1, -1 and infinity would have 5, 4 and 2.5.)
 AX_HD constexpr bool in_short(int i) { return i < 3; }
+// The s-th position of a launch over all 36: one that short tiles have in both directions, in one, in neither, in the other, and so on.
+// Compute units that share a second-level cache take neighbouring positions; in their own order the first half of them had a seventh
+// more to do (third to fifth layer of 128 pictures, forward 78.7, 66.6 and 47.8 us).
+AX_HD int wino_spread(int s) {
+  const int b = s >> 2, r = s & 3, i = b / 3, j = b - 3 * i;
+  return 6 * (i + (r >= 2 ? 3 : 0)) + j + (r == 1 || r == 2 ? 3 : 0);
+}
 // Rows of the transformed tensors that have position p = 6 * row + column
 struct RowRange {
   int lo, hi;

@@ -41,7 +41,7 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
   for (int bz = 0; bz < gz; ++bz)
     for (int by = 0; by < gy; ++by)
       for (int bx = 0; bx < gx; ++bx) {
-        const int g = bz / nsplit, split = bz - g * nsplit;
+        const int turn = bz / nsplit, split = bz - turn * nsplit, g = (int)split_group(grid, (uint32_t)turn);
         if (!only.empty() && std::find(only.begin(), only.end(), g) == only.end()) continue;
         const int n0 = by * T::BN;
         const SplitPlace at = split_place<T>(grid, (uint32_t)g, split, bx * T::BM, M, K, kchunk);
@@ -55,7 +55,7 @@ static void emu_split(typename AL::Params ap, typename BL::Params bp, Epi ep, in
         std::fill(acc.begin(), acc.end(), 0.f);
         std::fill(lo.begin(), lo.end(), 0.f);
         Epi e = ep;
-        e.set_group(g, bz);
+        e.set_group(g, g * nsplit + split);
         for (int t = 0; t < nt; ++t) {
           std::fill(As.begin(), As.end(), 0x7fc07fc0u);  // two bf16 NaNs: an unwritten slot shows up
           std::fill(Bs.begin(), Bs.end(), 0x7fc07fc0u);
@@ -390,6 +390,12 @@ static void conv16_case(int B, int H, int Cin, int Cout, int groups) {
 
 int main() {
   srand(4321);
+  SplitGrid spread{};
+  spread.of = 1;
+  spread.positions = make_fastdiv(3);
+  std::vector<int> turns(108, 0);
+  for (uint32_t t = 0; t < 108; ++t) ++turns.at(split_group(spread, t));
+  if (std::count(turns.begin(), turns.end(), 1) != 108) ++failures, printf("FAIL: a group has no turn of its own\n");
   split_is_exact();
   typedef Tile<128, 128, 16, 2, 2> S128;
   typedef Tile<128, 192, 16, 2, 2> S192;
