@@ -654,7 +654,7 @@ static int run_backward(alexnet* n, const float* in, hipStream_t st, bool early_
     if (s.fused()) {  // pool adjoint, normalisation adjoint, ReLU gate and the bias gradient's partial sums in one pass
       // the kernel leaves one row of sums per workgroup; those rows are one more matrix for the batch at the end
       float* part = n->colsum_ws + bias_ws_used;
-      const size_t part_rows = lrn_part_rows(s.g.B, s.g.Ho, s.g.Wo, s.g.Cout);
+      const size_t part_rows = lrn_part_rows(s.g.B, s.g.Ho, s.g.Wo, s.g.Cout, c.lrn_n, c.lrn_beta);
       bias_ws_used += (part_rows * s.g.Cout + 3) / 4 * 4;
       if (bias_ws_used > n->colsum_ws_floats_) {
         set_error("bias gradients: partial sums do not fit their workspace");

@@ -268,7 +268,7 @@ int launch_pool_lrn_bwd(const float* a, const float* dy, const uint8_t* slot, fl
                         int Ho, int Wo, int n, float k, float alpha, float beta, int relu_gate, float* colsum_out,
                         float* part, hipStream_t st, bool partials_only = false, uint16_t* da16 = nullptr);
 // partials_only: leave the lrn_part_rows() rows of per-workgroup sums in `part` for the caller to add up
-size_t lrn_part_rows(int N, int H, int W, int C);
+size_t lrn_part_rows(int N, int H, int W, int C, int n, float beta);
 int launch_pool_fwd(const float* x, float* y, uint8_t* slot, int N, int H, int W, int C, int Ho, int Wo,
                     hipStream_t st, uint16_t* y16 = nullptr);
 // dx[n][y][x][c] = sum of dy over the windows whose winning tap is (y,x); gated by gate > 0 when gate != null

@@ -556,10 +556,60 @@ __device__ __forceinline__ float4 lrn_window_sum_net(const float* row, int c, in
   return lrn_window_sum_regs(v, 2);
 }
 
-template <bool BWD>
+// Where the gradient of the normalised activations comes from: a tensor, or (dy != null) the adjoint of the
+// 3x3 stride-2 max-pool that follows, gathered on the fly from the pooled gradient and the winning taps.
+struct PoolGather {
+  const float* dy;       // [N][Ho][Wo][C]
+  const uint8_t* slot;   // winning tap 0..8 of each pooled element
+  int H, W, Ho, Wo;
+  FastDiv d_w, d_h;
+};
+// The (at most four) pooled windows over an input pixel, as loaded: the reduction is a separate step so
+// that the loads can be issued a trip ahead of their use.
+struct PoolTaps {
+  uint32_t s4[4];    // winning taps of four channels
+  float4 d[4];       // pooled gradient of four channels
+  uint32_t want[4];  // this pixel's tap number in that window; 9 (never a winner) for a window that does not exist
+};
+__device__ __forceinline__ void pool_taps_fetch(const PoolGather& pg, long pix, int c, int C, PoolTaps& t) {
+  const uint32_t q = fdiv((uint32_t)pix, pg.d_w);  // pix < 2^31: a tensor is smaller than 2 GiB
+  const int x = (int)((uint32_t)pix - q * (uint32_t)pg.W);
+  const uint32_t n = fdiv(q, pg.d_h);
+  const int y = (int)(q - n * (uint32_t)pg.H);
+  const int yo_lo = y >= 2 ? (y - 1) / 2 : 0, yo_hi = min(y / 2, pg.Ho - 1);
+  const int xo_lo = x >= 2 ? (x - 1) / 2 : 0, xo_hi = min(x / 2, pg.Wo - 1);
+#pragma unroll
+  for (int wy = 0; wy < 2; ++wy)
+#pragma unroll
+    for (int wx = 0; wx < 2; ++wx) {
+      const int yo = min(yo_lo + wy, yo_hi), xo = min(xo_lo + wx, xo_hi);
+      // a pixel in a last row or column that no window covers has lo > hi: the clamped address is still inside
+      const bool valid = yo_lo + wy <= yo_hi && xo_lo + wx <= xo_hi;
+      const uint32_t o = ((n * (uint32_t)pg.Ho + (uint32_t)yo) * (uint32_t)pg.Wo + (uint32_t)xo) * (uint32_t)C + c;
+      t.want[wy * 2 + wx] = valid ? (uint32_t)((y - 2 * yo) * 3 + (x - 2 * xo)) : 9u;
+      t.s4[wy * 2 + wx] = *reinterpret_cast<const uint32_t*>(pg.slot + o);
+      t.d[wy * 2 + wx] = *reinterpret_cast<const float4*>(pg.dy + o);
+    }
+}
+__device__ __forceinline__ float4 pool_taps_reduce(const PoolTaps& t) {
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const uint32_t s4 = t.s4[w], want = t.want[w];
+    acc.x += (s4 & 0xffu) == want ? t.d[w].x : 0.f;
+    acc.y += ((s4 >> 8) & 0xffu) == want ? t.d[w].y : 0.f;
+    acc.z += ((s4 >> 16) & 0xffu) == want ? t.d[w].z : 0.f;
+    acc.w += (s4 >> 24) == want ? t.d[w].w : 0.f;
+  }
+  return acc;
+}
+
+template <bool BWD, bool GATHER, bool NET>
 __global__ void __launch_bounds__(256)
 lrn_vec_kernel(const float* __restrict__ a, const float* __restrict__ db, float* __restrict__ out, long pixels, int C,
-               int half, int PB, float k, float alpha, float beta, int relu_gate) {
+               int half, int PB, float k, float alpha, float beta_, int relu_gate, PoolGather pg,
+               float* __restrict__ part, uint16_t* __restrict__ out16) {
+  const float beta = lrn_beta<NET>(beta_);
   extern __shared__ __attribute__((aligned(16))) float sh[];  // [2][PB][kLrnPad + C + kLrnPad]
   const int q = C >> 2;                                        // lanes per pixel
   const int ld = C + 2 * kLrnPad;
@@ -572,35 +622,40 @@ lrn_vec_kernel(const float* __restrict__ a, const float* __restrict__ db, float*
     *reinterpret_cast<float4*>(sh + (size_t)r * ld + kLrnPad + C) = zero;
   }
   const int c = cq * 4;
+  float4 colsum = make_float4(0.f, 0.f, 0.f, 0.f);  // of this lane's outputs over all its pixels
   // every workgroup makes the same number of trips, so the barriers inside are uniform; the loads of a
   // trip are issued during the trip before
   const long stride = (long)gridDim.x * PB;
   float4 nav = make_float4(0.f, 0.f, 0.f, 0.f), ndv = nav;
+  PoolTaps taps;
   {
     const long pix = (long)blockIdx.x * PB + pl;
     if (pl < PB && pix < pixels) {
       nav = *reinterpret_cast<const float4*>(a + pix * C + c);
-      if (BWD) ndv = *reinterpret_cast<const float4*>(db + pix * C + c);
+      if (BWD && GATHER) pool_taps_fetch(pg, pix, c, C, taps);
+      if (BWD && !GATHER) ndv = *reinterpret_cast<const float4*>(db + pix * C + c);
     }
   }
   for (long first = (long)blockIdx.x * PB; first < pixels; first += stride) {
     const long pix = first + pl;
     const bool on = pl < PB && pix < pixels;
     const float4 av = nav;
-    const float4 dv = ndv;
+    float4 dv = ndv;
+    if (BWD && GATHER && on) dv = pool_taps_reduce(taps);
     if (on) *reinterpret_cast<float4*>(sq + c) = make_float4(av.x * av.x, av.y * av.y, av.z * av.z, av.w * av.w);
     {
       const long npix = pix + stride;
       if (pl < PB && npix < pixels) {
         nav = *reinterpret_cast<const float4*>(a + npix * C + c);
-        if (BWD) ndv = *reinterpret_cast<const float4*>(db + npix * C + c);
+        if (BWD && GATHER) pool_taps_fetch(pg, npix, c, C, taps);
+        if (BWD && !GATHER) ndv = *reinterpret_cast<const float4*>(db + npix * C + c);
       }
     }
     __syncthreads();
     float4 p = av;  // s^-beta per channel
     float4 sv = av;
     if (on) {
-      const float4 w = lrn_window_sum(sq, c, half);
+      const float4 w = lrn_window_sum_net<NET>(sq, c, half);
       sv = make_float4(k + alpha * w.x, k + alpha * w.y, k + alpha * w.z, k + alpha * w.w);
       p = make_float4(neg_pow(sv.x, beta), neg_pow(sv.y, beta), neg_pow(sv.z, beta), neg_pow(sv.w, beta));
     }
@@ -616,7 +671,7 @@ lrn_vec_kernel(const float* __restrict__ a, const float* __restrict__ db, float*
                       dv.z * av.z * neg_pow_over_s(sv.z, p.z, beta), dv.w * av.w * neg_pow_over_s(sv.w, p.w, beta));
     __syncthreads();
     if (on) {
-      const float4 acc = lrn_window_sum(tt, c, half);
+      const float4 acc = lrn_window_sum_net<NET>(tt, c, half);
       const float f = 2.f * alpha * beta;
       float4 r = make_float4(dv.x * p.x - f * av.x * acc.x, dv.y * p.y - f * av.y * acc.y,
                              dv.z * p.z - f * av.z * acc.z, dv.w * p.w - f * av.w * acc.w);
@@ -627,9 +682,29 @@ lrn_vec_kernel(const float* __restrict__ a, const float* __restrict__ db, float*
         r.w = av.w > 0.f ? r.w : 0.f;
       }
       *reinterpret_cast<float4*>(out + pix * C + c) = r;
+      if (out16) store_bf16x4(out16 + pix * C + c, r);  // bf16 copy for the products that read the gradient next
+      colsum.x += r.x;
+      colsum.y += r.y;
+      colsum.z += r.z;
+      colsum.w += r.w;
     }
     // the next trip writes the squares, which were last read before the barrier above, and writes the
     // products only after its own first barrier, when every lane is done with this trip's
+  }  if (BWD && part) {  // part[workgroup][channel] = sum of this workgroup's outputs, in a fixed order
+    __syncthreads();
+    if (pl < PB) *reinterpret_cast<float4*>(sh + (size_t)pl * C + c) = colsum;
+    __syncthreads();
+    if (pl == 0) {
+      float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int r = 0; r < PB; ++r) {
+        const float4 v = *reinterpret_cast<const float4*>(sh + (size_t)r * C + c);
+        t.x += v.x;
+        t.y += v.y;
+        t.z += v.z;
+        t.w += v.w;
+      }
+      *reinterpret_cast<float4*>(part + (size_t)blockIdx.x * C + c) = t;
+    }
   }
 }
 
@@ -733,7 +808,8 @@ lrn_pool_fwd_kernel(const float* __restrict__ a, float* __restrict__ y, uint8_t*
   }
 }
 
-// The adjoint of the two, gated by the ReLU, with the bias gradient's partial sums (C % 4 == 0).  A lane owns four channels of a
+// The adjoint of the two with the network's own window, gated by the ReLU, with the bias gradient's partial sums (C % 4 == 0), on
+// tensors that are large enough (pool_lrn_by_pixel()).  A lane owns four channels of a
 // block of 2 x 2 pixels: those lie under the same four pooled windows at most, with taps that are known, so that a window is
 // loaded once for four pixels and nine comparisons serve them, where pixel by pixel there were sixteen loads and comparisons.
 // A workgroup walks over neighbouring blocks, workgroups of one XCD over neighbouring runs of them; the loads of a trip are
@@ -746,12 +822,11 @@ struct PoolLrnBwd {
   uint16_t* out16;       // may be null: a bf16 copy of out
   float* part;           // may be null: part[workgroup][channel], the sums of the workgroup's outputs
   uint32_t blocks;       // N * by * bx
-  int H, W, C, Ho, Wo, half, PB, relu_gate;
-  float k, alpha, beta;
+  int H, W, C, Ho, Wo, PB, relu_gate;
+  float k, alpha;
   uint32_t bytes, pooled;  // of a; elements of dy
   FastDiv bx, by;
 };
-template <bool NET>
 __global__ void __launch_bounds__(256, 3) pool_lrn_bwd_kernel(PoolLrnBwd g) {
   extern __shared__ __attribute__((aligned(16))) float sh[];  // [2][4 * PB][kLrnPad + C + kLrnPad]: squares, products
   const int C = g.C, q = C >> 2, ld = C + 2 * kLrnPad, pl = threadIdx.x / q, c = (threadIdx.x - pl * q) * 4;
@@ -826,9 +901,9 @@ __global__ void __launch_bounds__(256, 3) pool_lrn_bwd_kernel(PoolLrnBwd g) {
     if (lane_on) {
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        const float4 w = lrn_window_sum_net<NET>(sq + p * ld, c, g.half);
+        const float4 w = lrn_window_sum_net<true>(sq + p * ld, c, 2);
         const float4 u = make_float4(g.k + g.alpha * w.x, g.k + g.alpha * w.y, g.k + g.alpha * w.z, g.k + g.alpha * w.w);
-        const float beta = lrn_beta<NET>(g.beta);
+        constexpr float beta = 0.75f;
         f[p] = make_float4(neg_pow(u.x, beta), neg_pow(u.y, beta), neg_pow(u.z, beta), neg_pow(u.w, beta));
         *reinterpret_cast<float4*>(tt + p * ld + c) =
             make_float4(d[p].x * x[p].x * neg_pow_over_s(u.x, f[p].x, beta), d[p].y * x[p].y * neg_pow_over_s(u.y, f[p].y, beta),
@@ -837,10 +912,10 @@ __global__ void __launch_bounds__(256, 3) pool_lrn_bwd_kernel(PoolLrnBwd g) {
     }
     __syncthreads();
     if (lane_on) {
-      const float h = 2.f * g.alpha * lrn_beta<NET>(g.beta);
+      const float h = 2.f * g.alpha * 0.75f;
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        const float4 acc = lrn_window_sum_net<NET>(tt + p * ld, c, g.half);
+        const float4 acc = lrn_window_sum_net<true>(tt + p * ld, c, 2);
         float4 r = make_float4(d[p].x * f[p].x - h * x[p].x * acc.x, d[p].y * f[p].y - h * x[p].y * acc.y,
                                d[p].z * f[p].z - h * x[p].z * acc.z, d[p].w * f[p].w - h * x[p].w * acc.w);
         if (g.relu_gate) {
@@ -881,6 +956,7 @@ __global__ void __launch_bounds__(256, 3) pool_lrn_bwd_kernel(PoolLrnBwd g) {
 
 constexpr int kLrnMaxBlocks = 2048;  // workgroups of the vector kernels (= rows of their column-sum partials)
 static int lrn_grid(long pixels, int PB) { return (int)std::min<long>(ceil_div(pixels, PB), kLrnMaxBlocks); }
+static bool lrn_is_net(int n, float beta) { return n == 5 && beta == 0.75f; }
 static bool lrn_vec_ok(const void* p0, const void* p1, const void* p2, int C, int half) {
   return C % 4 == 0 && C <= 1024 && half <= kLrnMaxHalf && aligned16(p0) && aligned16(p1) && aligned16(p2);
 }
@@ -894,8 +970,8 @@ int launch_lrn_fwd(const float* a, float* b, long pixels, int C, int n, float k,
   if (lrn_vec_ok(a, b, b, C, half)) {
     const int PB = 256 / (C / 4);
     const size_t lds = (size_t)2 * PB * (C + 2 * kLrnPad) * sizeof(float);
-    hipLaunchKernelGGL((lrn_vec_kernel<false>), dim3(lrn_grid(pixels, PB)), dim3(256), lds, st, a, nullptr, b,
-                       pixels, C, half, PB, k, alpha, beta, 0);
+    hipLaunchKernelGGL((lrn_vec_kernel<false, false, false>), dim3(lrn_grid(pixels, PB)), dim3(256), lds, st, a, nullptr, b,
+                       pixels, C, half, PB, k, alpha, beta, 0, PoolGather{}, nullptr, nullptr);
   } else {
     hipLaunchKernelGGL(lrn_fwd_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, a, b, total, C, half, k, alpha,
                        beta);
@@ -912,8 +988,8 @@ int launch_lrn_bwd(const float* a, const float* db, float* da, long pixels, int 
   if (lrn_vec_ok(a, db, da, C, half)) {
     const int PB = 256 / (C / 4);
     const size_t lds = (size_t)2 * PB * (C + 2 * kLrnPad) * sizeof(float);
-    hipLaunchKernelGGL((lrn_vec_kernel<true>), dim3(lrn_grid(pixels, PB)), dim3(256), lds, st, a, db, da,
-                       pixels, C, half, PB, k, alpha, beta, relu_gate);
+    hipLaunchKernelGGL((lrn_vec_kernel<true, false, false>), dim3(lrn_grid(pixels, PB)), dim3(256), lds, st, a, db, da,
+                       pixels, C, half, PB, k, alpha, beta, relu_gate, PoolGather{}, nullptr, nullptr);
   } else {
     hipLaunchKernelGGL(lrn_bwd_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, a, db, da, total, C, half, k,
                        alpha, beta, relu_gate);
@@ -973,7 +1049,7 @@ int launch_lrn_pool_fwd(const float* a, float* y, uint8_t* slot, int N, int H, i
   const int tiles_y = ceil_div(Ho, PH), tiles_x = ceil_div(Wo, PW);
   const size_t lds = (size_t)(2 * PH + 1) * (2 * PW + 1) * C * sizeof(float);
   KernelScope ks("lrn_pool_fwd", 0, (double)N * H * W * C * 4.0 + (double)total * 5.0, st);
-  const auto kernel = n == 5 && beta == 0.75f ? lrn_pool_fwd_kernel<true> : lrn_pool_fwd_kernel<false>;
+  const auto kernel = lrn_is_net(n, beta) ? lrn_pool_fwd_kernel<true> : lrn_pool_fwd_kernel<false>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)(N * tiles_y * tiles_x)), dim3(256), lds, st, a, y, slot, H, W,
                      C, Ho, Wo, PH, PW, tiles_y, tiles_x, n / 2, k, alpha, beta, y16);
   AX_LAUNCH_CHECK();
@@ -983,7 +1059,19 @@ int launch_lrn_pool_fwd(const float* a, float* y, uint8_t* slot, int N, int H, i
 // Blocks of 2 x 2 pixels that a workgroup of the adjoint takes at a time: a lane for each of their channel quads, and at most 36
 // KiB of LDS, which leaves four workgroups to a compute unit
 static int pool_lrn_blocks(int C) { return std::max(1, std::min(256 / (C / 4), 36 * 1024 / (32 * (C + 2 * kLrnPad)))); }
-size_t lrn_part_rows(int N, int H, int W, int C) {
+// Pixel by pixel (lrn_vec_kernel) instead: other windows and exponents, whose powers leave nothing to gain from fewer loads and are
+// better off with five waves a SIMD than with three (96 channels, 64 maps of 55 x 55, exponent 1/2: 103 us, 124 in blocks; 100
+// channels, seven of them, 64 of 28 x 28: 32.6 | 35.5), and tensors under 24 MB, whose repeated reads the second-level caches
+// serve while four times the workgroups take a quarter of the chain (one map of 27 x 27, 256 channels 6.7 | 8.1; 96 channels
+// of 55 x 55, 1, 4, 8, 16, 24, 64 maps 7.3 | 8.5, 8.2 | 9.2, 11.2 both, 15.5 | 15.0, 19.5 | 18.7, 41.6 | 37.0).  Under 28 channels
+// blocks leave lanes idle, and it takes 64 MB (24, 16 channels of 56 x 56, 12.5 million values: 29.9 | 32.8, 29.8 | 33.6; of 112 x
+// 112, 30 and 26 million: 75.8 | 69.3, 57.2 | 55.6; 12 channels, 19 million: 48.8 | 43.6); under 12 it does not pay (8, 26 million: 62 | 80).
+static bool pool_lrn_by_pixel(int N, int H, int W, int C, bool net) {
+  const double values = (double)N * H * W * C;
+  return !net || C < 12 || values < (C < 28 ? 16e6 : 6e6);
+}
+size_t lrn_part_rows(int N, int H, int W, int C, int n, float beta) {
+  if (pool_lrn_by_pixel(N, H, W, C, lrn_is_net(n, beta))) return (size_t)lrn_grid((long)N * H * W, 256 / (C / 4));
   return (size_t)std::min<long>(ceil_div((long)N * ((H + 1) / 2) * ((W + 1) / 2), pool_lrn_blocks(C)), kLrnMaxBlocks);
 }
 int launch_pool_lrn_bwd(const float* a, const float* dy, const uint8_t* slot, float* da, int N, int H, int W, int C,
@@ -991,23 +1079,31 @@ int launch_pool_lrn_bwd(const float* a, const float* dy, const uint8_t* slot, fl
                         float* part, hipStream_t st, bool partials_only, uint16_t* da16) {
   const long pixels = (long)N * H * W;
   if (!pixels) return ALEXNET_OK;
-  const int blocks = (int)lrn_part_rows(N, H, W, C);
-  const bool sums = colsum_out || partials_only;
-  {
+  const int blocks = (int)lrn_part_rows(N, H, W, C, n, beta);
+  const bool sums = colsum_out || partials_only, net = lrn_is_net(n, beta);
+  if (pool_lrn_by_pixel(N, H, W, C, net)) {
+    KernelScope ks("pool_lrn_bwd", 0, (double)pixels * C * 8.0 + (double)N * Ho * Wo * C * 5.0, st);
+    const int PB = 256 / (C / 4);
+    const size_t lds = (size_t)2 * PB * (C + 2 * kLrnPad) * sizeof(float);
+    const PoolGather pg{dy, slot, H, W, Ho, Wo, make_fastdiv((uint32_t)W), make_fastdiv((uint32_t)H)};
+    const auto kernel = net && C >= 16 ? lrn_vec_kernel<true, true, true> : lrn_vec_kernel<true, true, false>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), lds, st, a, nullptr, da, pixels, C, n / 2, PB, k, alpha, beta, relu_gate, pg,
+                       sums ? part : nullptr, da16);
+    AX_LAUNCH_CHECK();
+  } else {
     KernelScope ks("pool_lrn_bwd", 0, (double)pixels * C * 8.0 + (double)N * Ho * Wo * C * 5.0, st);
     PoolLrnBwd g;
     g.a = a; g.dy = dy; g.slot = slot; g.out = da; g.out16 = da16; g.part = sums ? part : nullptr;
     const int bx = (W + 1) / 2, by = (H + 1) / 2;
     g.blocks = (uint32_t)N * by * bx;
-    g.H = H; g.W = W; g.C = C; g.Ho = Ho; g.Wo = Wo; g.half = n / 2; g.PB = pool_lrn_blocks(C); g.relu_gate = relu_gate;
-    g.k = k; g.alpha = alpha; g.beta = beta;
+    g.H = H; g.W = W; g.C = C; g.Ho = Ho; g.Wo = Wo; g.PB = pool_lrn_blocks(C); g.relu_gate = relu_gate;
+    g.k = k; g.alpha = alpha;
     g.bytes = (uint32_t)(pixels * C * 4);
     g.pooled = (uint32_t)((long)N * Ho * Wo * C);
     g.bx = make_fastdiv((uint32_t)bx);
     g.by = make_fastdiv((uint32_t)by);
     const size_t lds = (size_t)8 * g.PB * (C + 2 * kLrnPad) * sizeof(float);
-    const auto kernel = n == 5 && beta == 0.75f ? pool_lrn_bwd_kernel<true> : pool_lrn_bwd_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), lds, st, g);
+    hipLaunchKernelGGL(pool_lrn_bwd_kernel, dim3(blocks), dim3(256), lds, st, g);
     AX_LAUNCH_CHECK();
   }
   if (colsum_out && !partials_only) {

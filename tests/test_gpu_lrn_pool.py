@@ -1,5 +1,6 @@
 """Fused normalisation + pool and its adjoint where their blocks are cut: odd and even maps (last row and column under no window),
-one channel quad to 128, windows and exponents other than the network's own."""
+one channel quad to 128, windows and exponents other than the network's own, tensors on either side of the line between the
+adjoint's two kernels."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,9 @@ OP_RTOL = 2e-5  # as in test_gpu_ops.py: one fp32 operator against float64 on id
 
 @pytest.mark.parametrize("c,size,n,beta,batch", [
     (4, 6, 5, 0.75, 2), (12, 7, 3, 0.75, 3), (24, 3, 5, 0.75, 1), (96, 9, 5, 0.5, 2), (100, 10, 5, 0.75, 3), (256, 8, 9, 1.0, 2),
-    (512, 5, 5, 0.75, 2)])
+    (512, 5, 5, 0.75, 2),
+    # large enough for the adjoint on blocks of 2 x 2 pixels; workgroups of unequal shares, lanes without a block
+    (96, 9, 5, 0.75, 790), (28, 10, 5, 0.75, 2200), (512, 5, 5, 0.75, 480), (16, 13, 5, 0.75, 6000), (12, 7, 5, 0.75, 28000)])
 def test_fused_kernels_at_their_edges(lib, c, size, n, beta, batch):
     wl = dict(S.TINY, crop=size, raw=size, lrn=(n, 2.0, 1e-4, beta),
               conv=[(c, 3, 1, 1, 1, 1, 1)] + [(8, 1, 1, 0, 1, 0, 0)] * 4)
