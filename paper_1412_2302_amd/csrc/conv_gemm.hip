@@ -1343,8 +1343,11 @@ int launch_fc_bwd_weight(int B, int in, int out, const float* x, const float* dy
   if (g_bf16 && vec)
     return launch_tile_bf<B128, BfDenseR, BfDenseR, EpiSlab>(a, b, ep, out, in, B, round_up(B, kBKbf), 1, 1, st);
   const GemmPlan p = fc_split_ok(vec, B) ? plan_split(out, in, B, 1, 0, 1) : GemmPlan{128, 128, 1, round_up(B, kBK)};
-  if (u)
+  if (u) {
+    // weights and momentum are read and written beside the gradient
+    const AlgoFlops af(2.0 * B * in * (double)out, 4.0 * ((double)B * (in + out) + 5.0 * in * (double)out));
     return by_tile_split<SplitRowInner, SplitRowInner>(p, a, b, EpiSgd{dw, u->w, u->v, in, u->lr, u->mu, u->wd}, out, in, B, 1, st);
+  }
   return launch_dense<SplitRowInner, SplitRowInner, DenseRowInner, DenseRowInner>(vec, p, a, b, ep, out, in, B, st);
 }
 
