@@ -9,8 +9,8 @@
 // exchanged in pairs, so that a fragment read of one octet of eight neighbouring pixels touches all banks.  The same for the
 // weights' columns.  Two workgroups to a compute unit.
 //
-// Second layer (27 x 27, 48 channels, 5 x 5, 128 columns a group), gathered | here: 256 pictures 161 | 111 us (1030 TFLOP/s), 64
-// 60 | 38.  With two stages, whose loads had a tap's products alone to arrive under, 118 and 46.  What bounds it: power at 256
+// Second layer (27 x 27, 48 channels, 5 x 5, 128 columns a group), gathered | here: 256 pictures 161 | 104 us (1100 TFLOP/s), 64
+// 55 | 33.  With two stages, whose loads had a tap's products alone to arrive under, 118 and 46.  What bounds it: power at 256
 // pictures; at 64, one round of two workgroups a unit, the picture's way in and the results' way out.
 #include <algorithm>
 
@@ -67,8 +67,7 @@ __global__ void __launch_bounds__(256, 2) patch_conv_kernel(PatchGeom g, Epi ep)
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const int u = (i * 4 + wave) * 64 + lane, col = u / U, c = (u - col * U) ^ (col >> 2 & 1);
-    // columns past the end are not stored
-    wat[i] = u < BN * U ? (uint32_t)grp * g.wgroup + (uint32_t)min(n0 + col, g.N - 1) * K2 + 16u * c : kOob;
+    wat[i] = u < BN * U ? (uint32_t)grp * g.wgroup + (uint32_t)(n0 + col) * K2 + 16u * c : kOob;
   }
   auto load = [&](v4u* st, int tap) {
 #pragma unroll
@@ -168,30 +167,35 @@ static int patch_rows(const ConvGeom& c, bool tall) {
   if (rows < 1) return 0;
   return ceil_div(c.Ho, ceil_div(c.Ho, rows));  // bands of nearly the same height
 }
+static bool patch_full(const ConvGeom& c, int rows, int pixels) { return rows > 0 && rows * c.Wo * 4 >= pixels * 3; }
+// 384 x 64 tiles, which read half the weights for a product, from two of them to a compute unit on (second layer, 192 x 128 | 384 x 64: 24
+// pictures 21.8 | 22.2 us, 40 29.5 | 29.4, 64 33.9 | 32.6, 256 110 | 104; 48 channels of 50 x 50, 3 x 3, 32: 24.7 | 18.5), if they are
+// mostly full (13 x 13, 512 maps: 19.5 | 26.4).  Not with 16 channels, where a tap is one product long (27 x 27, 256 maps: 22.9 | 24.3).
 static PatchPlan patch_plan(const ConvGeom& c) {
-  PatchPlan p{patch_rows(c, true), 0, true};
-  const long columns = (long)ceil_div(c.og(), 64) * c.groups * c.B;
-  if (p.rows == 0 || ceil_div(c.Ho, p.rows) * columns < 1024) {
+  PatchPlan p{c.cg() == 48 ? patch_rows(c, true) : 0, 0, true};
+  if (!patch_full(c, p.rows, 384) || (long)ceil_div(c.Ho, p.rows) * (c.og() / 64) * c.groups * c.B < 512) {
     p.rows = patch_rows(c, false);
     p.tall = false;
   }
   if (p.rows) p.bands = ceil_div(c.Ho, p.rows);
   return p;
 }
+// An odd number of pairs of octets is what the kernel can do, and whole columns of tiles; 16 and 48 channels have an instance.  us,
+// gathered (and stored in the order of the accumulators, as it was then) | here: 16 channels, 3 x 3 on 27 x 27, 64, 128, 256 maps 33.7 | 12.6, 25.4 | 15.5,
+// 63.2 | 22.9; 1 x 1 on 28 x 28, 256: 60.9 | 20.8; 5 x 5, two groups, 14 x 14, 128: 37.4 | 17.9; 48 channels, 3 x 3 on 13 x 13, 300: 38.3 | 17.0,
+// on 28 x 28, 128: 46.9 | 25.1; gathered and stored by rows 13 x 13, 512: 22.4 | 19.7, 28 x 28, 256: 47.1 | 39.1.  Tiles mostly full, and a workgroup to
+// every compute unit.
 bool patch_fwd_ok(const ConvGeom& c) {
-  if (!conv_bf16_stored_ok(c) || (c.cg() != 16 && c.cg() != 48)) return false;
+  if (!conv_bf16_stored_ok(c) || (c.cg() != 16 && c.cg() != 48) || c.og() % 128 != 0) return false;
   const PatchPlan p = patch_plan(c);
-  if (p.rows == 0) return false;
-  // tiles mostly full, and two workgroups for most compute units
-  const int pixels = p.tall ? 384 : 192;
-  return p.rows * c.Wo * 4 >= pixels * 3 && c.og() % 128 == 0 && (long)p.bands * ceil_div(c.og(), p.tall ? 64 : 128) * c.groups * c.B >= 256;
+  return patch_full(c, p.rows, p.tall ? 384 : 192) && (long)p.bands * (c.og() / (p.tall ? 64 : 128)) * c.groups * c.B >= 256;
 }
 template <int U, int WM, int WN, int TM, int TN>
 static int launch_patch(const PatchGeom& g, const EpiBiasAct& e, const ConvGeom& c, hipStream_t st) {
   KernelScope ks("gemm_bf16", 2.0 * c.P() * c.Cout * c.cg() * c.k * c.k,
                  4.0 * ((double)c.in_elems() + (double)c.w_elems() + (double)c.out_elems()), st);
   hipLaunchKernelGGL((patch_conv_kernel<U, WM, WN, TM, TN, EpiBiasAct>),
-                     dim3((unsigned)((long)c.B * g.bands * c.groups * ceil_div(c.og(), WN * TN * 32))), dim3(256), 0, st, g, e);
+                     dim3((unsigned)((long)c.B * g.bands * c.groups * (c.og() / (WN * TN * 32)))), dim3(256), 0, st, g, e);
   AX_LAUNCH_CHECK();
   return ALEXNET_OK;
 }
@@ -208,12 +212,12 @@ int launch_patch_fwd(const ConvGeom& c, const uint16_t* x16, const uint16_t* wf1
   g.wgroup = (uint32_t)((long)c.og() * c.kf() * 2);
   g.d_pw = make_fastdiv((uint32_t)g.PW);
   g.d_wo = make_fastdiv((uint32_t)c.Wo);
-  g.d_cols = make_fastdiv((uint32_t)ceil_div(c.og(), p.tall ? 64 : 128));
+  g.d_cols = make_fastdiv((uint32_t)(c.og() / (p.tall ? 64 : 128)));
   g.d_groups = make_fastdiv((uint32_t)c.groups);
   g.d_bands = make_fastdiv((uint32_t)p.bands);
   const EpiBiasAct e{y, c.Cout, bias, relu, c.og(), 0, 0, y16};
   if (c.cg() == 48) return p.tall ? launch_patch<6, 4, 1, 3, 2>(g, e, c, st) : launch_patch<6, 2, 2, 3, 2>(g, e, c, st);
-  return p.tall ? launch_patch<2, 4, 1, 3, 2>(g, e, c, st) : launch_patch<2, 2, 2, 3, 2>(g, e, c, st);
+  return launch_patch<2, 2, 2, 3, 2>(g, e, c, st);
 }
 
 }  // namespace ax

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("side,cin,cout,k,pad,groups,batch", [
     (27, 96, 256, 5, 2, 2, 32), (27, 96, 256, 5, 2, 2, 128), (13, 48, 128, 3, 1, 1, 300), (13, 48, 256, 3, 0, 1, 257),
     (30, 32, 256, 3, 1, 2, 40), (30, 16, 128, 4, 3, 1, 300), (20, 96, 768, 6, 1, 2, 40), (60, 48, 128, 2, 1, 1, 30),
-    (14, 16, 128, 1, 0, 1, 260), (11, 48, 128, 7, 6, 1, 140)])
+    (14, 16, 128, 1, 0, 1, 260), (11, 48, 128, 7, 6, 1, 140),
+    (27, 96, 256, 5, 2, 2, 64), (13, 48, 128, 3, 1, 1, 512), (50, 48, 256, 3, 1, 1, 17)])
 def test_forward_against_fp64(lib, side, cin, cout, k, pad, groups, batch):
     """Operands are bf16 numbers already: only fp32 sums of at most 2352 products are rounded, 3e-6 of the result."""
     net = lib.AlexNet(net_of(side, cin, cout, k, pad, groups), batch, precision=1)
