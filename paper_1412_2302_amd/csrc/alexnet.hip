@@ -177,13 +177,13 @@ static bool use_winograd(const alexnet_config_t& c, const ConvGeom& g) {
 }
 // In a training or inference pass the layer also has to be large enough for the multiplies to matter: the transformed
 // form takes two or three launches more, each as long as a small direct product.  Whole passes on the full net, all
-// layers transformed | those direct that the line leaves so: one picture 232 | 147 us, 4 pictures (0.6 to 1.8 GFLOP a
-// layer) 263 | 205, 8 (1.2 to 3.6) 310 | 300; with the line at 4 GFLOP 16 pictures (2.4 to 7.2) 351 | 372 and training
-// on 24 (3.6 to 11) 1391 | 1420.  Training the small nets of the tests, batch 256: 682 | 603 and 590 | 513.
+// layers transformed | those direct that the line leaves so: one picture 230 | 111 us, 4 pictures (0.6 to 1.8 GFLOP a
+// layer) 260 | 177, 8 (1.2 to 3.6) 284 | 276; with the line at 4 GFLOP 8 pictures 253, 16 (2.4 to 7.2) 337 | 330 and training
+// on 24 (3.6 to 11) 1138 | 1151.  Training the small nets of the tests, batch 256: 542 | 298 and 411 | 195.
 constexpr double kWinoMinFlops = 2e9;
-// Forward flops of the convolutions from which a bf16 handle's inference pass makes its weight copies on the side stream:
-// its first layer needs one of them, and with little to hide them under the two streams' meeting costs more (batch 16 341
-// against 320 us, the small nets 147 and 166 against 109 and 134; batch 100, 133 GFLOP, 694 against 713).
+// Forward flops of the convolutions from which a bf16 handle's inference pass makes its weight copies on the side stream: its
+// first layer needs none of them.  On the side stream | on the caller's: batch 16 237 | 244 us, 64 364 | 361, 100 (133 GFLOP) 467
+// | 471, the small nets, 64 pictures, 59.0 | 58.5 and 50.8 | 50.5.
 constexpr double kForkFlops = 100e9;
 static bool winograd_in_pass(const ConvGeom& g) { return 2.0 * g.P() * g.Cout * g.cg() * g.k * g.k >= kWinoMinFlops; }
 
@@ -452,7 +452,7 @@ static int stage_fwd(alexnet* n, Stage& s, const float* x, const float* wf, cons
 static bool small_ok(const alexnet* n, const Stage& s, bool in_pass) { return !in_pass || !n->beside || &s == &n->st[0]; }
 // have_v: the forward pass of the same minibatch left its form of x in place (s.wino_v, the transform of x; s.x16,
 // its bf16 copy)
-// tail: put the end of a transformed stage's weight gradient off to launch_wgrad_tail() (see WgradTail)
+// tail: put the end of a transformed stage's weight gradient off to launch_grad_tail() (see WgradTail)
 // dy16_ready: s.dy16 already holds the bf16 copy of dy (the kernel that made dy wrote it)
 static int stage_bwd_weight(alexnet* n, Stage& s, const float* x, const float* dy, float* dwf, bool have_v,
                             hipStream_t st, bool in_pass = false, WgradTail* tail = nullptr, bool dy16_ready = false) {

@@ -1273,9 +1273,11 @@ int launch_fc_fwd(int B, int in, int out, const float* x, const float* w, const 
     if (bf) return launch_tile_bf<B128, BfDenseK, BfDenseK, Epi>(a, b, ep, B, out, in, kchunk, ns, 1, st);
     return launch_dense<SplitKInner, SplitKInner, DenseKInner, DenseKInner>(vec, p, a, b, ep, B, out, in, st);
   };
-  // A full tile that finishes itself works through 32 to 64 values per lane, one after the other: the mask's hash costs
-  // more there than a second launch (128 rows 256 wide: 456 against 434 us per small training step), and so do mask and
-  // gate in the bf16 kernels, whose blocks are not transposed (438 against 434; 30 rows 200 wide 363 against 357).
+  // A full tile that finishes itself works through 32 to 64 values per lane, one after the other: the mask's hash costs more
+  // there than a second launch (128 rows 256 wide: 456 against 434 us per small training step), and so do mask and gate in the
+  // bf16 kernels (438 against 434; 30 rows 200 wide 363 against 357).  (Measured when fp32 tiles were stored four columns of 32
+  // rows at a time; a row at a time, as they are now, a product of 1000 x 1000 over 512 takes 22.9 us, 22.8 then, of 64 x 4096
+  // 17.0 and 17.8.)
   if (ns == 1 && !bf && (B <= 32 || !act.dropout)) return product(EpiFcAct{y, out, act, y16});
   const EpiSlab slabs{ws, (long)B * out, out, nullptr};
   if (s16)

@@ -149,8 +149,9 @@ __global__ void __launch_bounds__(kFirstThreads, 2) first_layer_kernel(FirstGeom
   for (int j = 0; j < NB; ++j) bias[j] = g.bias && j * 32 + (lane & 31) < g.Cout ? g.bias[j * 32 + (lane & 31)] : 0.f;
 
   // The next tile's loads are issued in front of a tile's products and wait behind them; a tile's results are stored a quarter at
-  // a time between the products of the tile after it.  Loads and stores are counted together and in order: the wait for the
-  // loads, which are the older ones, is not for the stores.  (Stored all at once behind the products, all compute units wrote at
+  // a time between the products of the tile after it.  The wait for the loads takes the stores too, although they are the younger
+  // ones: the first tile has none, and the compiler counts for the way without them.  By then they have had up to a tile's
+  // products to leave.  (Stored all at once behind the products, all compute units wrote at
   // one time and multiplied at another: 13 us a tile of 220 pixels, 5 of products, 3 of arithmetic for the stores and 4 for 84
   // KB to leave at a compute unit's share of the memory; 256 pictures 184 us.)
   float out[NB][16];

@@ -802,16 +802,10 @@ AX_HD void sgd_one(float& w, float& v, float g, float d, float lr, float mu) {
 }
 // A weight gradient and the update of the weights it is for, all of them decayed: g[m][n] = value, then sgd_one() on w and v.
 struct EpiSgd {
-  static constexpr bool kTransposed = false;
   float *g, *w, *v;
   long ldc;
   float lr, mu, wd;
   AX_HD void set_group(int /*g*/, int /*z*/) {}
-  AX_HD void apply(int m, int n, float x) const {
-    const long o = (long)m * ldc + n;
-    g[o] = x;
-    sgd_one(w[o], v[o], x, wd, lr, mu);
-  }
 };
 
 // Hands one accumulator block of a lane to the epilogue: row m, register quads at columns nb + acc_row(lane, 4q).

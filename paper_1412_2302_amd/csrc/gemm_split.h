@@ -407,13 +407,11 @@ constexpr int kSplitProducts = 6;
 // A weight gradient with its operands exchanged (rows of the product = columns of the result): ws[z][n][m] = v.  The
 // lanes of a store run along m, the result's contiguous direction.
 struct EpiSlabSwapped {
-  static constexpr bool kTransposed = true;
   float* ws;
   long slab;  // M*N
   long ldc;   // M
   float* base;
   AX_HD void set_group(int /*g*/, int z) { base = ws + (long)z * slab; }
-  AX_HD void apply(int m, int n, float v) const { base[(long)n * ldc + m] = v; }
 };
 // Whether the lanes of a block run along the product's rows (the MFMA's operands exchanged) and not along its columns.  Only here
 // are the rows what lies side by side in memory.  Everything else is stored 32 columns at a time; 16-byte stores of four columns

@@ -195,7 +195,7 @@ int launch_wave_conv_fwd(const ConvGeom& c, const float* x, const float* wf, con
 int launch_wave_conv_bwd_data(const ConvGeom& c, const float* dy, const float* wf, const float* gate, float* dx,
                               uint16_t* dx16, float* ws, bool bf, hipStream_t st);
 // slices: the weight gradient's scratch, wave_conv_bwd_weight_ws_floats() floats; tail: they are added up by
-// launch_wgrad_tail() and are this stage's own until then
+// launch_grad_tail() and are this stage's own until then
 int launch_wave_conv_bwd_weight(const ConvGeom& c, const float* x, const float* dy, float* dwf, float* slices, bool bf,
                                 hipStream_t st, WgradTail* tail = nullptr);
 int launch_wave_conv_bwd(const ConvGeom& c, const float* x, const float* dy, const float* wf, const float* gate, float* dx,

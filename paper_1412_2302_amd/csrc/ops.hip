@@ -1059,13 +1059,14 @@ int launch_lrn_pool_fwd(const float* a, float* y, uint8_t* slot, int N, int H, i
 // Blocks of 2 x 2 pixels that a workgroup of the adjoint takes at a time: a lane for each of their channel quads, and at most 36
 // KiB of LDS, which leaves four workgroups to a compute unit
 static int pool_lrn_blocks(int C) { return std::max(1, std::min(256 / (C / 4), 36 * 1024 / (32 * (C + 2 * kLrnPad)))); }
-// Pixel by pixel (lrn_vec_kernel) instead: other windows and exponents, whose powers leave nothing to gain from fewer loads and are
-// better off with five waves a SIMD than with three (96 channels, 64 maps of 55 x 55, exponent 1/2: 103 us, 124 in blocks; 100
-// channels, seven of them, 64 of 28 x 28: 32.6 | 35.5), and tensors under 24 MB, whose repeated reads the second-level caches
-// serve while four times the workgroups take a quarter of the chain (one map of 27 x 27, 256 channels 6.7 | 8.1; 96 channels
-// of 55 x 55, 1, 4, 8, 16, 24, 64 maps 7.3 | 8.5, 8.2 | 9.2, 11.2 both, 15.5 | 15.0, 19.5 | 18.7, 41.6 | 37.0).  Under 28 channels
-// blocks leave lanes idle, and it takes 64 MB (24, 16 channels of 56 x 56, 12.5 million values: 29.9 | 32.8, 29.8 | 33.6; of 112 x
-// 112, 30 and 26 million: 75.8 | 69.3, 57.2 | 55.6; 12 channels, 19 million: 48.8 | 43.6); under 12 it does not pay (8, 26 million: 62 | 80).
+// Pixel by pixel (lrn_vec_kernel) instead: other windows and exponents, whose powers leave nothing to gain from fewer loads and
+// are better off with five waves a SIMD than with three (96 channels, 64 maps of 55 x 55, exponent 1/2: 103 us, 124 in blocks;
+// 100 channels, seven of them, 64 of 28 x 28: 32.6 | 35.5), and tensors under 24 MB, whose repeated reads the second-level caches
+// serve while four times the workgroups take a quarter of the chain (one map of 27 x 27, 256 channels 6.7 | 8.1; 96 channels of
+// 55 x 55, 1, 4, 8, 16, 24, 64 maps 7.3 | 8.5, 8.2 | 9.2, 11.2 both, 15.5 | 15.0, 19.5 | 18.7, 41.6 | 37.0).  Under 28 channels
+// blocks leave lanes idle, and it takes 64 MB (24, 16 channels of 56 x 56, 12.5 million values: 29.9 | 32.8, 29.8 | 33.6; of 112
+// x 112, 30 and 26 million: 75.8 | 69.3, 57.2 | 55.6; 12 channels, 19 million: 48.8 | 43.6); under 12 it does not pay (8, 26
+// million: 62 | 80).
 static bool pool_lrn_by_pixel(int N, int H, int W, int C, bool net) {
   const double values = (double)N * H * W * C;
   return !net || C < 12 || values < (C < 28 ? 16e6 : 6e6);

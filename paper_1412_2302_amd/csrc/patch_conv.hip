@@ -168,9 +168,10 @@ static int patch_rows(const ConvGeom& c, bool tall) {
   return ceil_div(c.Ho, ceil_div(c.Ho, rows));  // bands of nearly the same height
 }
 static bool patch_full(const ConvGeom& c, int rows, int pixels) { return rows > 0 && rows * c.Wo * 4 >= pixels * 3; }
-// 384 x 64 tiles, which read half the weights for a product, from two of them to a compute unit on (second layer, 192 x 128 | 384 x 64: 24
-// pictures 21.8 | 22.2 us, 40 29.5 | 29.4, 64 33.9 | 32.6, 256 110 | 104; 48 channels of 50 x 50, 3 x 3, 32: 24.7 | 18.5), if they are
-// mostly full (13 x 13, 512 maps: 19.5 | 26.4).  Not with 16 channels, where a tap is one product long (27 x 27, 256 maps: 22.9 | 24.3).
+// 384 x 64 tiles, which read half the weights for a product, from two of them to a compute unit on (second layer, 192 x 128 | 384
+// x 64: 24 pictures 21.8 | 22.2 us, 40 29.5 | 29.4, 64 33.9 | 32.6, 256 110 | 104; 48 channels of 50 x 50, 3 x 3, 32: 24.7 |
+// 18.5), if they are mostly full (13 x 13, 512 maps: 19.5 | 26.4).  Not with 16 channels, where a tap is one product long (27 x
+// 27, 256 maps: 22.9 | 24.3).
 static PatchPlan patch_plan(const ConvGeom& c) {
   PatchPlan p{c.cg() == 48 ? patch_rows(c, true) : 0, 0, true};
   if (!patch_full(c, p.rows, 384) || (long)ceil_div(c.Ho, p.rows) * (c.og() / 64) * c.groups * c.B < 512) {
@@ -180,11 +181,11 @@ static PatchPlan patch_plan(const ConvGeom& c) {
   if (p.rows) p.bands = ceil_div(c.Ho, p.rows);
   return p;
 }
-// An odd number of pairs of octets is what the kernel can do, and whole columns of tiles; 16 and 48 channels have an instance.  us,
-// gathered (and stored in the order of the accumulators, as it was then) | here: 16 channels, 3 x 3 on 27 x 27, 64, 128, 256 maps 33.7 | 12.6, 25.4 | 15.5,
-// 63.2 | 22.9; 1 x 1 on 28 x 28, 256: 60.9 | 20.8; 5 x 5, two groups, 14 x 14, 128: 37.4 | 17.9; 48 channels, 3 x 3 on 13 x 13, 300: 38.3 | 17.0,
-// on 28 x 28, 128: 46.9 | 25.1; gathered and stored by rows 13 x 13, 512: 22.4 | 19.7, 28 x 28, 256: 47.1 | 39.1.  Tiles mostly full, and a workgroup to
-// every compute unit.
+// An odd number of pairs of octets is what the kernel can do, and whole columns of tiles; 16 and 48 channels have an instance.
+// us, gathered (and stored in the order of the accumulators, as it was then) | here: 16 channels, 3 x 3 on 27 x 27, 64, 128, 256
+// maps 33.7 | 12.6, 25.4 | 15.5, 63.2 | 22.9; 1 x 1 on 28 x 28, 256: 60.9 | 20.8; 5 x 5, two groups, 14 x 14, 128: 37.4 | 17.9;
+// 48 channels, 3 x 3 on 13 x 13, 300: 38.3 | 17.0, on 28 x 28, 128: 46.9 | 25.1; gathered and stored by rows 13 x 13, 512: 22.4 |
+// 19.7, 28 x 28, 256: 47.1 | 39.1.  Tiles mostly full, and a workgroup to every compute unit.
 bool patch_fwd_ok(const ConvGeom& c) {
   if (!conv_bf16_stored_ok(c) || (c.cg() != 16 && c.cg() != 48) || c.og() % 128 != 0) return false;
   const PatchPlan p = patch_plan(c);

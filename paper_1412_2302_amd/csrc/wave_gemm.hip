@@ -23,9 +23,9 @@ static double wave_seconds(double blocks, double steps, bool bf) {
 // from the kernels over stored operands, but weight gradients and dense layers from those of gemm_bf16.h, which fp32 operands
 // would run on; the direct ones take half of that.  By products alone stages would leave much earlier (mini net, second layer,
 // 128 pictures, both gradients: 24 us here, 14 there), but the first to leave brings the side stream, its events and three
-// conversions with it: a step of 128 pictures takes 193 us with small products only, 255 with the gradients in tiles, 296
-// without any; of 200 230, 267, 329.  From 214 pictures on, where this line ends it (midi net: 380), up to 450 small products
-// only would still be 20 to 6 % faster; at 512 they are level.
+// conversions with it: a step of 128 pictures takes 176 us with small products only, 289 with the gradients in tiles, 270
+// without any; of 200 210, 329, 332.  From 214 pictures on, where this line ends it (midi net: 380), small products only would
+// still be faster for a while: 256 282 | 253, 400 338 | 330, 450 361 | 356, 512 383 | 406, midi net 450 270 | 229.
 static double tile_floor(double seconds, bool bf, double below = 18e-6, double extra = 5e-6) {
   return bf && seconds < below ? seconds + extra : seconds;
 }
@@ -141,10 +141,11 @@ bool wave_conv_bwd_weight_ok(const ConvGeom& c, bool bf) {
   return bwd_weight_fits(c) && bwd_weight_plan(c, bf).seconds < tile_floor(tile_seconds_bwd_weight(c, bf), bf, kWeightBelow);
 }
 // Both gradients in one launch, where the data gradient is not sliced.  beside: large dense layers are updated meanwhile, which
-// slows these kernels more than tiles.  Full net, fp32, tiles against small products by the profiler, us, and what the work
-// alone comes to: fourth layer, 2, 4, 6 and 8 pictures 46 | 53 (17), 58 | 75 (30), 67 | 98 (42), 82 | 131 (55); fifth, 4, 8 and 12
-// 50 | 39 (21), 70 | 57 (38), 79 | 97 (55); chains of 50 and 54 steps, second and third layer, 2 pictures 40 | 77 (33) and 51 | 91
-// (19); bf16 alike.  With the work alone compared, whole steps at 2 to 12 pictures took 1 to 4 % more than with tiles.
+// slows these kernels more than tiles.  Full net, fp32, tiles against small products by the profiler, us, and what the work alone
+// comes to: fourth layer, 2, 4, 6 and 8 pictures 46 | 53 (17), 58 | 75 (30), 67 | 98 (42), 82 | 131 (55); fifth, 4, 8 and 12 50 |
+// 39 (21), 70 | 57 (38), 79 | 97 (55); chains of 50 and 54 steps, second and third layer, 2 pictures 40 | 77 (33) and 51 | 91
+// (19); bf16 alike.  Whole steps of 2, 4, 6, 8 and 12 pictures by the work alone | by this 695 | 696, 697 | 700, 904 | 839, 876 |
+// 898, 944 | 966 us, bf16 4 and 8 689 and 692 either way.
 constexpr double kWaveBeside = 1.6;
 bool wave_conv_bwd_ok(const ConvGeom& c, bool bf, bool beside) {
   if (!bwd_data_fits(c) || !bwd_weight_fits(c) || c.kb() > kWaveMaxK) return false;

@@ -146,8 +146,8 @@ AX_HD void wino_gt(const Vec4* m, Vec4* o) {
 // of 4x4 tiles (OH = H + 2*pad - 2).  Ctot = groups * Cg channels on the gathered side.
 // k x k taps are handled as nsub x nsub sub-kernels of 3x3 (k = 3: one, k = 5: four).
 // ey, ex: the last row and column of tiles hold one row and one column of outputs (OH, OW = 4n + 1) and take the short
-// transform (in_short()) in that direction, so that 3 of the 6 positions of such a tile are made and multiplied: 441 products of 576
-// for a 13 x 13 map, every third position of which fell on four times as many outputs as there are.
+// transform (in_short()) in that direction, so that 3 of the 6 positions of such a tile are made and multiplied: 441
+// products of 576 for a 13 x 13 map, every third position of which fell on four times as many outputs as there are.
 struct WinoGeom {
   int B, H, W, pad, OH, OW, th, tw, groups, k, nsub;
   int ey = 0, ex = 0;
@@ -276,7 +276,8 @@ AX_HD void wino_dy_thread(const WinoGeom& g, int Og, const float* dy, float* Y, 
     }
 #pragma unroll
   for (int j = 0; j < 4; ++j) wino_a<4, 4>(e + j, u + j);  // columns: 4 -> 6 rows of 4
-  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;  // short: one row, one column of outputs
+  // short: one row, one column of outputs
+  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;
   const int grp = c / Og, cl = c - grp * Og;
   float* out = Y + (long)t * 36 * Ctot + (long)grp * Og + cl;
 #pragma unroll
@@ -300,7 +301,8 @@ AX_HD void wino_out_thread(const WinoGeom& g, int Ng, const float* M, const floa
   const WinoTile tl = wino_tile<SHORT>(g, t);
   const int grp = c / Ng, cl = c - grp * Ng;
   const float* in = M + (long)t * 36 * Ctot + (long)grp * Ng + cl;
-  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;  // short: positions past the third add nothing
+  // short: positions past the third add nothing
+  const bool sy = SHORT && g.ey && tl.ty == g.th - 1, sx = SHORT && g.ex && tl.tx == g.tw - 1;
   Vec4 u[24];
 #pragma unroll
   for (int j = 0; j < 6; ++j) {
@@ -505,7 +507,8 @@ AX_HD WinoDxTask wino_dx_load(const WinoDx& d, const WinoDxPlan& p, const float*
   const int grp = c / d.Cg, cl = c - grp * d.Cg;
   const long pstride = (long)nq * Ctot;
   const long t = wino_tile_row<SHORT>(g, bk.n, ty, tx);
-  const bool sy = SHORT && g.ey && ty == g.th - 1, sx = SHORT && g.ex && tx == g.tw - 1;  // short: three rows, three columns of the patch
+  // short: three rows, three columns of the patch
+  const bool sy = SHORT && g.ey && ty == g.th - 1, sx = SHORT && g.ex && tx == g.tw - 1;
   const float* in = M + t * 36 * pstride + (long)grp * nq * d.Cg + (long)q * d.Cg + cl;
   // where a short tile has no such position the load is outside: no branches, and no arithmetic but the four starts
   const BufView mv = make_view(M, (uint32_t)((long)g.tiles() * 36 * pstride * 4));
@@ -517,8 +520,9 @@ AX_HD WinoDxTask wino_dx_load(const WinoDx& d, const WinoDxPlan& p, const float*
     Vec2 col[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i)
-      col[i] = !SHORT ? vload2(in + (long)(6 * i + jj) * pstride)
-                      : vload2(mv, in_short(i) ? (in_short(jj) ? at : at_x) : (in_short(jj) ? at_y : at_yx), (uint32_t)(6 * i + jj) * step);
+      col[i] = !SHORT         ? vload2(in + (long)(6 * i + jj) * pstride)
+               : in_short(i) ? vload2(mv, in_short(jj) ? at : at_x, (uint32_t)(6 * i + jj) * step)
+                             : vload2(mv, in_short(jj) ? at_y : at_yx, (uint32_t)(6 * i + jj) * step);
     wino_b<1, 6>(col, u + jj);  // u[i][jj]
   }
 #pragma unroll

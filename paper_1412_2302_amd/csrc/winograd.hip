@@ -234,9 +234,10 @@ int launch_wino_bwd_data(const ConvGeom& c, const float* yt, const float* Ut, co
   while ((size_t)d.lds_vec4() * 16 > kDxLdsBytes && d.bands < c.H) ++d.bands;
   while (d.bands == 1 && d.CQ < 16 && d.CQ * 2 <= c.Cin / 4 && (size_t)d.lds_vec4() * 32 <= kDxLdsBytes) d.CQ *= 2;
   // A workgroup's rounds are a chain of a load, a transform and two or three barriers each: with fewer than two workgroups per
-  // compute unit there is room for more of them, although patches across a band's edge are transformed in both.  37 pictures,
-  // 222 | 666 workgroups (fifth layer) 21 | 19 us, 222 | 444 (second, 5 x 5) 73 | 65, eight 68 | 53; 128 pictures, 768 | 1536, 43 | 62.
-  // Not where one row of tiles reaches all rows of the map, so that every band would transform them all (5 x 5 maps, 52 of them, 10.6 | 12.0).
+  // compute unit there is room for more of them, although patches across a band's edge are transformed in both.  37 pictures, 222
+  // | 666 workgroups (fifth layer) 21 | 19 us, 222 | 444 (second, 5 x 5) 73 | 65, eight 68 | 53; 128 pictures, 768 | 1536, 43 |
+  // 62. Not where one row of tiles reaches all rows of the map, so that every band would transform them all (5 x 5 maps, 52 of
+  // them, 10.6 | 12.0).
   while (d.blocks() < 512 && d.bands < 4 && d.bands < c.H && g.th > 1) ++d.bands;
   KernelScope ks("wino_dx", 0, ((double)c.in_elems() * (gate ? 2 : 1) + positions(g) * nq_of(c) * c.Cin) * 4.0, st);
   hipLaunchKernelGGL(g.ey || g.ex ? wino_dx_kernel<true> : wino_dx_kernel<false>, dim3((unsigned)d.blocks()), dim3(256), (size_t)d.lds_vec4() * 16, st, d,
@@ -247,7 +248,7 @@ int launch_wino_bwd_data(const ConvGeom& c, const float* yt, const float* Ut, co
 
 // dy -> yt, V^T x yt -> dU (36 products over the tiles), dU -> dwf.  V is the forward pass's.
 // With `tail`, the slices of the products stay in ws and their sum and the transform back are left to
-// launch_wgrad_tail(): ws and dU must then be this stage's own until that has run.
+// launch_grad_tail(): ws and dU must then be this stage's own until that has run.
 int launch_wino_bwd_weight(const ConvGeom& c, const float* V, const float* dy, float* dwf, float* yt, float* dU,
                            float* ws, hipStream_t st, WgradTail* tail) {
   const WinoGeom g = fwd_geom(c);
