@@ -329,6 +329,13 @@ __device__ __forceinline__ void wave_put(const EpiGate& e, int m, int n, float v
   if (e.dx16) store_bf16(e.dx16 + o, v);
 }
 
+// Whether an operand without a table is asked for while the other's table is made.  In front of a weight gradient's table it was in
+// the way (us without | with: 16 channels, 5 x 5 on 14 x 14, 128 maps 14.4 | 14.9; 24, 3 x 3 on 13 x 13, 64 maps 9.2 | 9.6; 224, 5 x 5
+// on 9 x 9, 40 maps 43.3 | 45.2; steps of the small nets 1 % longer); in front of a forward product's, with the bias, it saves a
+// trip (32 channels, 14 x 14, 60 maps 15.4 | 15.2; 64, 9 x 9, 50 maps 11.8 | 11.5; steps of the small nets 1 to 3 % shorter).
+template <class J>
+constexpr bool kOtherFirst = J::BL::kWords == 0 && !std::is_same<typename J::AL, WaveIm2colT>::value;
+
 template <int W, int WORDS>
 struct WaveLds {
   float part[W][kWaveTile * kWaveTile];
@@ -381,10 +388,10 @@ __device__ __forceinline__ void wave_tile(const J& j, uint32_t block, Lds& lds) 
   uint32_t* const tb = lds.table + J::AL::kWords;
   const int kh = 8 * (lane >> 5), kfirst = 16 * wave;
   constexpr int kStep = 16 * W;
-  // an operand that needs no table is on its way while the other's is made
+  // see kOtherFirst
   const typename J::BL bl(j.b, (int)g, n0 + (lane & 31), kbeg, kend, tb);
   float4 rb[2];
-  if (J::BL::kWords == 0 && kfirst < len) bl.load(rb, kfirst + kh);
+  if (kOtherFirst<J> && kfirst < len) bl.load(rb, kfirst + kh);
   typename J::Epi ep = j.ep;
   ep.set_group((int)g, (int)z);
   constexpr int kMine = kWaveTile * kWaveTile / (64 * W);  // of the tile's elements, tid + i * 64 * W
@@ -409,7 +416,7 @@ __device__ __forceinline__ void wave_tile(const J& j, uint32_t block, Lds& lds) 
       else al.load(ra, k);
     };
     load_a(kfirst + kh);
-    if (J::BL::kWords > 0) bl.load(rb, kfirst + kh);
+    if (!kOtherFirst<J>) bl.load(rb, kfirst + kh);
     for (int k = kfirst; k < len; k += kStep) {
       // the registers are free once their values are split: the next step's loads run under this step's products
       const bool more = k + kStep < len;
